@@ -1,0 +1,581 @@
+"""Timed cases of the acquisition library.
+
+Each case is one call that a base station's program makes, through the Python
+face of the library: a search of one receiver block, a batch of blocks, a batch
+of tracking tasks, the FSK chain's search and tracking calls, and the proposal
+network's calls (power map, gradients, proposal search).  `prepare` makes what
+such a program holds before the call (samples on the GPU, the plan with its
+replica bank, network weights), `run` makes the call and hands back every field
+of its records, `exact` computes the same records in 64 bits with plain torch.
+
+Signals are synthetic: BPSK or continuous-phase FSK packets with random codes,
+delays (a fraction of a sample included), carrier phases, carrier offsets on the
+bin grid and signal-to-noise ratios, in complex white noise of unit power (int16
+noise of rms 1000 for FSK).
+"""
+from __future__ import annotations
+
+import math
+import os
+
+import numpy as np
+import torch
+
+import paper_2005_10445_amd as acq
+from paper_2005_10445_amd import fsk, proposals
+
+FS = 8e6                        # samples per second of every receiver here
+BIN_STEP_HZ = 1000.0
+LO_HZ, F1_HZ, F0_HZ, CUTOFF_HZ = 1.0e6, 250e3, -250e3, 600e3
+NOISE_RMS = 1000.0
+POS_WEIGHT = 4.0
+
+
+# ------------------------------------------------------------------ the cases
+def listed():
+    return [
+        # the smallest search: one known tag, one block, no frequency search; launches and latency
+        dict(name="plain", kind="detect", tags=1, chips=1024, spc=4, bins=1, n=1 << 17, precision="fp32"),
+        # a small station: a few tags with short codes, a block of odd length
+        dict(name="small_bank", kind="detect", tags=13, chips=1023, spc=4, bins=5, n=100003, precision="fp32"),
+        # the ordinary search: 64 tags over 131 ms of samples, eleven carrier offsets
+        dict(name="tagbank", kind="detect", tags=64, chips=8192, spc=2, bins=11, n=1 << 20, precision="fp32"),
+        # the same search with 16-bit storage of spectra and replicas
+        dict(name="tagbank_bf16", kind="detect", tags=64, chips=8192, spc=2, bins=11, n=1 << 20, precision="bf16"),
+        # the largest search: uneven blocks from several receivers, 256 tags, 21 offsets, one launch sequence
+        dict(name="stream", kind="batch", tags=256, chips=8192, spc=2, bins=21, blocks=6, len_seed=4, precision="fp32"),
+        # tracking: one tag per 3 ms block around its predicted arrival, a full batch
+        dict(name="track_256", kind="track", tags=256, chips=8192, spc=2, bins=21, tasks=256, n=24576, precision="fp32"),
+        # tracking: the few tasks of a small station
+        dict(name="track_9", kind="track", tags=64, chips=8192, spc=2, bins=21, tasks=9, n=24577, precision="fp32"),
+        # the FSK search: a 100 ms window of int16 samples against 128 codes of 8192 bits
+        dict(name="fsk_search", kind="fsk", tags=128, bits=8192, sps=8, taps=200, n=800000),
+        # FSK tracking: 64 windows of 12 ms, one code each
+        dict(name="fsk_track", kind="fsk_track", tags=128, bits=8192, sps=8, taps=200, tasks=64, n=96000),
+        # what every proposal search starts with: the log-power map of a block and its median
+        dict(name="power_map", kind="map", n=1 << 20, precision="bf16"),
+        # training: loss and gradient of the proposal network, the batch of eight blocks that training uses
+        dict(name="gradients", kind="grad", blocks=8, n=1 << 20),
+        # the proposal search of an ordinary block: map, network, then only the proposed segments
+        dict(name="learned", kind="learned", tags=64, chips=8192, spc=2, bins=11, n=1 << 20, precision="fp32"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case: the same calls, sizes spread over what the listed ones span."""
+    kind = rng.choice(["detect", "detect", "detect", "batch", "track", "track", "fsk", "fsk_track", "map", "grad",
+                       "learned"])
+    if kind == "detect":
+        spc = rng.choice([1, 2, 2, 4, 8])
+        chips = _log_int(rng, 1024 // spc + 1, 8192)
+        c = dict(kind=kind, tags=_log_int(rng, 1, 64), chips=chips, spc=spc, bins=rng.choice([1, 3, 5, 7, 9, 11]),
+                 n=max(_log_int(rng, 1 << 16, 1 << 20), int(1.3 * chips * spc)),
+                 precision=rng.choice(["fp32", "fp32", "fp16", "bf16"]))
+        if rng.random() < 0.2:
+            c["exact_bins"] = True
+        return c
+    if kind == "batch":
+        return dict(kind=kind, tags=rng.randint(32, 200), chips=8192, spc=2, bins=rng.choice([5, 11, 21]),
+                    blocks=rng.randint(2, 5), len_seed=rng.randint(0, 1 << 20),
+                    precision=rng.choice(["fp32", "fp32", "bf16"]))
+    if kind == "track":
+        return dict(kind=kind, tags=rng.randint(16, 256), chips=8192, spc=2, bins=rng.choice([5, 11, 21]),
+                    tasks=_log_int(rng, 1, 256), n=rng.randint(17000, 32000), precision=rng.choice(["fp32", "fp32", "fp16"]))
+    if kind in ("fsk", "fsk_track"):
+        bits, sps, taps = _log_int(rng, 512, 8192), rng.randint(5, 8), rng.randint(60, 200)
+        nt = bits * sps + taps + sps - 2
+        c = dict(kind=kind, tags=_log_int(rng, 8, 128), bits=bits, sps=sps, taps=taps)
+        if kind == "fsk":
+            c["n"] = min(800000, int(nt * rng.uniform(1.5, 12.0)))
+        else:
+            c["tasks"], c["n"] = _log_int(rng, 1, 64), int(nt * rng.uniform(1.1, 1.46))
+        return c
+    if kind == "map":
+        return dict(kind=kind, n=_log_int(rng, 1 << 15, 1 << 21), precision=rng.choice(["bf16", "bf16", "fp32"]))
+    if kind == "grad":
+        return dict(kind=kind, blocks=rng.randint(1, 8), n=_log_int(rng, 1 << 16, 1 << 20))
+    return dict(kind=kind, tags=rng.randint(16, 64), chips=8192, spc=2, bins=rng.choice([5, 11]),
+                n=_log_int(rng, 1 << 18, 1 << 20), precision="fp32")
+
+
+# ------------------------------------------------------------------ signals
+def _np_rng(seed, *stream):
+    return np.random.default_rng([seed, *stream])
+
+
+def _codes(case, seed):
+    return (2 * _np_rng(seed, 1).integers(0, 2, size=(case["tags"], case["chips"])) - 1).astype(np.int8)
+
+
+def _noise(n, seed, sub):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed * 1000003 + sub)
+    return torch.randn(n, 2, generator=g, device="cuda")
+
+
+def _bpsk_block(n, rng, seed, sub, codes, spc, freqs, tags):
+    """Unit-power complex noise with one packet of each of `tags`; returns (complex64 samples, packet starts)."""
+    x = torch.view_as_complex(_noise(n, seed, sub) * math.sqrt(0.5))
+    L = codes.shape[1] * spc
+    starts = []
+    # 16384-sample packets at -15 .. -5 dB per sample, shorter ones as much stronger as they are shorter
+    gain_db = 10.0 * math.log10(16384.0 / L)
+    for t in tags:
+        delay, frac = int(rng.integers(0, n - L)), float(rng.random())
+        amp = 10.0 ** ((rng.uniform(-15.0, -5.0) + gain_db) / 20.0)
+        wave = codes[t].repeat_interleave(spc).float()
+        w = torch.zeros(L + 1, device="cuda")
+        w[:L] += (1.0 - frac) * wave
+        w[1:] += frac * wave
+        i = torch.arange(delay, delay + L + 1, device="cuda", dtype=torch.float64)
+        cyc = (i * (float(freqs[int(rng.integers(0, len(freqs)))]) / FS) + float(rng.random())).remainder(1.0)
+        x[delay:delay + L + 1] += torch.polar(amp * w, (2.0 * math.pi * cyc).float())
+        starts.append(delay)
+    return x.contiguous(), starts
+
+
+def _batch_lengths(case):
+    r = _np_rng(case["len_seed"], 2)
+    return [int(2.0 ** r.uniform(18.0, 21.0)) for _ in range(case["blocks"])]
+
+
+def _plan_kw(case):
+    fft_len = 1 << 15 if case["chips"] == 8192 and case["spc"] == 2 else 0
+    return dict(spc=case["spc"], fs_hz=FS, num_bins=case["bins"], bin_step_hz=BIN_STEP_HZ if case["bins"] > 1 else 0.0,
+                fft_len=fft_len, precision=case["precision"], refine_radius=1 if case["precision"] == "fp32" else 8,
+                exact_bins=bool(case.get("exact_bins", False)))
+
+
+def _blocks(case, seed):
+    """(codes, bin frequencies, blocks, packet starts, tag of each block or None) of an acquisition case."""
+    codes = _codes(case, seed)
+    kind = case["kind"]
+    lens = _batch_lengths(case) if kind == "batch" else [case["n"]] * case.get("tasks", 1)
+    freqs = acq.bin_frequencies(chips=codes, max_block_len=max(lens), **_plan_kw(case))
+    dev = torch.from_numpy(codes).cuda()
+    rng = _np_rng(seed, 3)
+    out, starts, tags = [], [], []
+    for b, n in enumerate(lens):
+        if kind == "track":                       # the task's packet nine times out of ten, sometimes another's
+            tag = int(rng.integers(0, case["tags"]))
+            tx = [tag] if rng.random() < 0.9 else []
+            tx += [int(rng.integers(0, case["tags"]))] if rng.random() < 0.5 else []
+        else:
+            tag = None
+            most = 20 if kind == "batch" else 10
+            count = int(rng.integers(0, most + 1)) if kind == "batch" else most
+            tx = [int(t) for t in rng.permutation(case["tags"])[:count]]
+        x, at = _bpsk_block(n, rng, seed, b, dev, case["spc"], freqs, tx)
+        out.append(x)
+        starts.append(at)
+        tags.append(tag)
+    return codes, freqs, out, starts, tags
+
+
+def _taps(case):
+    k = np.arange(case["taps"]) - (case["taps"] - 1) / 2.0
+    h = np.sinc(2.0 * CUTOFF_HZ / FS * k) * np.hanning(case["taps"] + 2)[1:-1]
+    return (h / h.sum()).astype(np.complex128)
+
+
+def _fsk_wave(bits, sps):
+    """Continuous-phase FSK packet, complex128 on the GPU."""
+    f = torch.from_numpy(np.where(np.repeat(bits, sps) == 1, F1_HZ, F0_HZ) / FS).cuda()
+    cyc = torch.cat([torch.zeros(1, dtype=torch.float64, device="cuda"), torch.cumsum(f, 0)[:-1]]).remainder(1.0)
+    return torch.polar(torch.ones_like(cyc), 2.0 * math.pi * cyc)
+
+
+def _fsk_threshold(case):
+    """Noise alone peaks at z of about 25 / bits over a window of ten packets."""
+    return 80.0 / case["bits"]
+
+
+def _fsk_bits(case, seed):
+    return _np_rng(seed, 4).integers(0, 2, size=(case["tags"], case["bits"])).astype(np.uint8)
+
+
+def _fsk_block(case, n, rng, seed, sub, bits, tags):
+    x = torch.zeros(n, dtype=torch.complex128, device="cuda")
+    plen = case["bits"] * case["sps"]
+    for t in tags:
+        delay = int(rng.integers(0, n - plen))
+        amp = NOISE_RMS * 10.0 ** (rng.uniform(-10.0, 0.0) / 20.0)
+        x[delay:delay + plen] += _fsk_wave(bits[t], case["sps"]) * complex(amp * np.exp(2j * np.pi * rng.random()))
+    i = torch.arange(n, device="cuda", dtype=torch.float64)
+    x *= torch.polar(torch.ones_like(i), 2.0 * math.pi * (i * (LO_HZ / FS)).remainder(1.0))
+    iq = torch.view_as_real(x) + _noise(n, seed, sub).double() * (NOISE_RMS / math.sqrt(2.0))
+    return iq.round().clamp(-32768, 32767).to(torch.int16).contiguous()
+
+
+def _fsk_blocks(case, seed):
+    bits = _fsk_bits(case, seed)
+    rng = _np_rng(seed, 5)
+    if case["kind"] == "fsk":
+        tags = [int(t) for t in rng.permutation(case["tags"])[:6]]
+        return bits, [_fsk_block(case, case["n"], rng, seed, 0, bits, tags)], [None]
+    blocks, tags = [], []
+    for i in range(case["tasks"]):
+        t = int(rng.integers(0, case["tags"]))
+        blocks.append(_fsk_block(case, case["n"], rng, seed, i, bits, [t] if rng.random() < 0.9 else []))
+        tags.append(t)
+    return bits, blocks, tags
+
+
+def _training_blocks(case, seed):
+    """Blocks as the proposal network is trained on, and the label of every frame."""
+    shape = dict(case, kind="detect", tags=64, chips=min(8192, case["n"] // 3), spc=2, bins=11, precision="fp32")
+    xs, labels = [], []
+    L = shape["chips"] * 2
+    for b in range(case["blocks"]):
+        _, _, out, starts, _ = _blocks(shape, seed * 64 + b)
+        xs.append(out[0])
+        cover = torch.zeros(case["n"] + 1, dtype=torch.int64)
+        for d in starts[0]:
+            cover[d] += 1
+            cover[d + L] -= 1
+        inside = torch.cat([torch.zeros(1, dtype=torch.int64), (torch.cumsum(cover, 0)[:-1] > 0).long().cumsum(0)])
+        at = torch.arange(proposals.num_frames(case["n"])) * 128
+        labels.append((inside[at + 256] - inside[at] >= 128).float())
+    return xs, torch.cat(labels).cuda()
+
+
+def _init_params(seed):
+    """He-normal weights, zero biases, as training starts from."""
+    g = _np_rng(seed, 6)
+    parts, cin = [], 256
+    for _ in range(4):
+        parts += [g.normal(0.0, math.sqrt(2.0 / (5 * cin)), size=5 * cin * 64), np.zeros(64)]
+        cin = 64
+    parts += [g.normal(0.0, math.sqrt(1.0 / 64), size=64), np.zeros(1)]
+    return np.concatenate(parts).astype(np.float32)
+
+
+def _trained():
+    from paper_2005_10445_amd.train_proposals import load_model
+    params, meta = load_model()
+    return params, float(meta["kappa"])
+
+
+# ------------------------------------------------------------------ the calls
+def _per(case):
+    """Records per block at most: one a tag, or the task's."""
+    return 1 if case["kind"] in ("track", "fsk_track") else case["tags"]
+
+
+def _rows(case):
+    return _per(case) * case.get("blocks", case.get("tasks", 1))
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind in ("detect", "batch", "track", "learned"):
+        codes, _, xs, _, tags = _blocks(case, seed)
+        kw = _plan_kw(case)
+        if kind in ("batch", "track"):
+            kw.update(max_batch_blocks=len(xs), max_batch_samples=sum(x.numel() for x in xs))
+        s = dict(kind=kind, rows=_rows(case), tags=_per(case), plan=acq.Plan(codes, max_block_len=max(x.numel() for x in xs), **kw))
+        if kind == "batch":
+            s["blocks"] = xs
+        elif kind == "track":
+            s["tasks"] = list(zip(xs, tags))
+        else:
+            s["block"] = xs[0]
+        if kind == "learned":
+            params, kappa = _trained()
+            rows = proposals.num_frames(case["n"])
+            s["net"] = proposals.Network("bf16", 256, max_rows=rows, max_block_len=case["n"])
+            s["net"].set_params(params)
+            s["params"] = proposals.LearnedParams(kappa=kappa)
+        return s
+    if kind in ("fsk", "fsk_track"):
+        bits, xs, tags = _fsk_blocks(case, seed)
+        total = sum(x.shape[0] for x in xs)
+        kw = dict(max_track_tasks=len(xs)) if kind == "fsk_track" else {}
+        s = dict(kind=kind, rows=_rows(case), tags=_per(case),
+                 plan=fsk.FskPlan(bits, FS, LO_HZ, F1_HZ, F0_HZ, _taps(case), case["sps"], total,
+                                  threshold=_fsk_threshold(case), **kw))
+        if kind == "fsk":
+            s["block"] = xs[0]
+        else:
+            s["tasks"] = list(zip(xs, tags))
+        return s
+    rows = proposals.num_frames(case["n"]) * case.get("blocks", 1)
+    net = proposals.Network(case.get("precision", "bf16"), 256, max_rows=rows, max_block_len=case["n"])
+    if kind == "map":
+        x = _blocks(dict(case, kind="detect", tags=16, chips=min(8192, case["n"] // 3), spc=2, bins=11,
+                         precision="fp32"), seed)[2][0]
+        return dict(kind=kind, net=net, block=x)
+    net.set_params(_init_params(seed))
+    xs, labels = _training_blocks(case, seed)
+    return dict(kind=kind, net=net, labels=labels, blocks=case["blocks"],
+                maps=torch.cat([net.power_map(x)[0] for x in xs]))
+
+
+INTS = ("tag", "bin", "lag", "block", "flags", "crossings")
+FLOATS = ("toa", "freq_hz", "peak_power", "z", "energy", "block_power", "power", "snr")
+FSK_INTS = ("tag", "lag", "block", "flags")
+FSK_FLOATS = ("toa", "xcorr", "q", "p", "z")
+
+
+def _columns(state, dets, ints=INTS, floats=FLOATS):
+    """Every field of every record, a column each, in the row of its (block, tag) or task (0 where there is none)."""
+    per = state["tags"]
+    at = [d.block * per + (d.tag if per > 1 else 0) for d in dets]
+    i = np.zeros((state["rows"], len(ints)), dtype=np.int64)
+    v = np.zeros((state["rows"], len(floats)))
+    if at:
+        i[at] = [[getattr(d, f) for f in ints] for d in dets]
+        v[at] = [[getattr(d, f) for f in floats] for d in dets]
+    return {**{f: i[:, k] for k, f in enumerate(ints)}, **{f: v[:, k] for k, f in enumerate(floats)}}
+
+
+def run(state):
+    kind = state["kind"]
+    if kind == "detect":
+        return _columns(state, state["plan"].detect(state["block"]))
+    if kind == "batch":
+        return _columns(state, state["plan"].detect_batch(state["blocks"]))
+    if kind == "track":
+        return _columns(state, state["plan"].track(state["tasks"]))
+    if kind == "learned":
+        dets, report = state["net"].detect(state["plan"], state["block"], state["params"])
+        return dict(_columns(state, dets), proposals=report.proposals, segments=report.segments, fallback=report.fallback,
+                    median=report.median)
+    if kind == "fsk":
+        return _columns(state, state["plan"].detect(state["block"]), FSK_INTS, FSK_FLOATS)
+    if kind == "fsk_track":
+        return _columns(state, state["plan"].track(state["tasks"]), FSK_INTS, FSK_FLOATS)
+    if kind == "map":
+        m, median = state["net"].power_map(state["block"])
+        return dict(map=m, median=median)
+    loss, grad = state["net"].gradients(state["maps"], state["labels"], POS_WEIGHT, state["blocks"])
+    return dict(loss=loss, grad=grad)
+
+
+# ------------------------------------------------------------------ work
+def work(case):
+    kind = case["kind"]
+    if kind in ("detect", "batch", "track", "learned"):
+        L = case["chips"] * case["spc"]
+        M = 1 << max(math.ceil(math.log2(2 * L)), 10)
+        lens = _batch_lengths(case) if kind == "batch" else [case["n"]] * case.get("tasks", 1)
+        V = M - L + 1
+        segs = sum(-(-(n - L + 1) // V) for n in lens)
+        pairs = case["bins"] * (1 if kind == "track" else case["tags"])
+        return {"bytes": 8.0 * sum(lens) + 8.0 * case["tags"] * M // case["spc"] / 2,
+                "flops": float(pairs * segs) * (5.0 * M * math.log2(M) + 6.0 * M + 4.0 * V)}
+    if kind in ("fsk", "fsk_track"):
+        nt = case["bits"] * case["sps"] + case["taps"] + case["sps"] - 2
+        tasks = case.get("tasks", 1)
+        n = case["n"] * tasks
+        M = 1 << math.ceil(math.log2(2 * nt))
+        # two real segments share a complex transform
+        segs = -(-(case["n"] - nt + 1) // (M - nt + 1)) * tasks / 2
+        codes = 1 if kind == "fsk_track" else case["tags"]
+        front = 3 * (n / 3890) * 5.0 * 4096 * 12
+        # samples, and each code's template spectrum (half of it, for a real template)
+        return {"bytes": 4.0 * n + min(case["tags"], codes * tasks) * 4.0 * M,
+                "flops": front + codes * segs * (5.0 * M * math.log2(M) + 6.0 * M)}
+    rows = proposals.num_frames(case["n"]) * case.get("blocks", 1)
+    if kind == "map":
+        out = 2 if case["precision"] == "bf16" else 4
+        return {"bytes": 8.0 * case["n"] + out * 256.0 * rows, "flops": rows * (5.0 * 256 * 8 + 256 * 8)}
+    macs = rows * 5.0 * 64 * (256 + 3 * 64)
+    # forward, weight gradients, and the input gradients of all layers but the first
+    return {"bytes": rows * (512.0 + 4.0), "flops": 2.0 * (2 * macs + rows * 5.0 * 64 * 3 * 64)}
+
+
+# ------------------------------------------------------------------ 64-bit values
+def _parabola(pm, p0, pp):
+    den = pm - 2.0 * p0 + pp
+    return min(0.5, max(-0.5, 0.5 * (pm - pp) / den)) if den < 0.0 else 0.0
+
+
+def _search64(x, codes, spc, freqs, tags, theta, block, keep=None):
+    """The search of one block by its definition, through full-length FFTs in 64 bits: a record for each of `tags`
+    whose peak reaches theta.  keep: lags that are searched (all of them by default)."""
+    x = x.to(torch.complex128)
+    n, L = x.numel(), codes.shape[1] * spc
+    lags, F, K = n - L + 1, 1 << math.ceil(math.log2(n)), len(freqs)
+    px = float((x.real.square() + x.imag.square()).sum()) / n
+    i = torch.arange(n, device="cuda", dtype=torch.float64)
+    spectra = torch.stack([torch.fft.fft(x * torch.polar(torch.ones_like(i), -2.0 * math.pi * (i * (float(f) / FS)).remainder(1.0)), F)
+                           for f in freqs])
+    energy = torch.cat([torch.zeros(1, dtype=torch.float64, device="cuda"),
+                        torch.cumsum(x.real.square() + x.imag.square(), 0)])
+    out = []
+    for t in tags:
+        s = torch.from_numpy(codes[t]).cuda().double().repeat_interleave(spc)
+        S = torch.fft.fft(s, F).conj()
+        P = torch.empty(K, lags, dtype=torch.float64, device="cuda")
+        for k in range(K):
+            c = torch.fft.ifft(spectra[k] * S)[:lags]
+            P[k] = c.real.square() + c.imag.square()
+        if keep is not None:
+            P = torch.where(keep[None, :], P, torch.full_like(P, -1.0))
+        best, at = P.max(1)
+        k = int(best.argmax())
+        lag, p0 = int(at[k]), float(best[k])
+        if p0 / (L * px) < theta:
+            continue
+        edge = lag in (0, lags - 1)
+        if keep is not None and not edge:          # neighbours outside the searched segments count too
+            c = torch.fft.ifft(spectra[k] * S)[lag - 1:lag + 2]
+            tri = (c.real.square() + c.imag.square()).tolist()
+        else:
+            tri = P[k, max(lag - 1, 0):lag + 2].tolist()
+        e = float(energy[lag + L] - energy[lag])
+        s2 = (e - p0 / L) / L
+        out.append(dict(tag=t, bin=k, lag=lag, block=block, flags=1 if edge else 0,
+                        crossings=int((P >= theta * L * px).sum()),
+                        toa=lag + (0.0 if edge else _parabola(*tri)), freq_hz=float(freqs[k]), peak_power=p0,
+                        z=p0 / (L * px), energy=e, block_power=px, power=p0 / (L * L),
+                        snr=p0 / (L * L) / s2 if s2 > 0 else math.inf))
+    return out
+
+
+def _table(case, rows, ints=INTS, floats=FLOATS):
+    per = _per(case)
+    at = [r["block"] * per + (r["tag"] if per > 1 else 0) for r in rows]
+    out = {**{f: np.zeros(_rows(case), dtype=np.int64) for f in ints}, **{f: np.zeros(_rows(case)) for f in floats}}
+    for f in out:
+        out[f][at] = [r[f] for r in rows]
+    return out
+
+
+def _map64(x):
+    fr = x.to(torch.complex128).unfold(0, 256, 128)
+    w = 0.5 * (1.0 - torch.cos(2.0 * math.pi * torch.arange(256, device="cuda", dtype=torch.float64) / 256))
+    X = torch.fft.fft(fr * w)
+    P = X.real.square() + X.imag.square()
+    med = P.reshape(-1).kthvalue((P.numel() - 1) // 2 + 1).values
+    return torch.log(P / med), float(med)
+
+
+class _Bf16(torch.autograd.Function):
+    """Rounding to bfloat16 whose gradient is the identity (layer outputs are stored so)."""
+
+    @staticmethod
+    def forward(ctx, a):
+        return a.to(torch.bfloat16).to(a.dtype)
+
+    @staticmethod
+    def backward(ctx, g):
+        return g
+
+
+def _network64(params, m, blocks):
+    """Logits [rows] of the network on maps [rows][256], in 64 bits with weights and layer outputs in bfloat16."""
+    F = m.shape[0] // blocks
+    h, off, cin = m.reshape(blocks, F, 256), 0, 256
+    for d in (1, 2, 4, 8):
+        W = _Bf16.apply(params[off:off + 5 * cin * 64]).reshape(5, cin, 64)
+        off += 5 * cin * 64
+        b = params[off:off + 64]
+        off += 64
+        pad = torch.nn.functional.pad(h, (0, 0, 2 * d, 2 * d))
+        a = b + sum((pad[:, i * d:i * d + F].reshape(-1, cin) @ W[i]).reshape(blocks, F, 64) for i in range(5))
+        h, cin = _Bf16.apply(torch.relu(a)), 64
+    return (h.reshape(-1, 64) @ params[off:off + 64] + params[off + 64])
+
+
+def _threshold(tags, bins, lags):
+    return math.log(tags * bins * lags / 1e-3)
+
+
+def _demod64(x, case):
+    """(d, u) of the composed filters and the demodulator, 64 bits."""
+    bp = torch.from_numpy(_taps(case).astype(np.complex64).astype(np.complex128)).cuda()
+    k = torch.arange(case["sps"], dtype=torch.float64, device="cuda")
+    F = 1 << math.ceil(math.log2(x.numel() + case["taps"] + case["sps"]))
+    X, B = torch.fft.fft(x, F), torch.fft.fft(bp, F)
+    a = []
+    for f in (F1_HZ, F0_HZ):
+        ph = -2.0 * math.pi * f * (case["sps"] - 1 - k) / FS
+        H = torch.fft.fft(torch.polar(torch.ones_like(ph), ph), F)
+        a.append(torch.fft.ifft(X * B * H)[:x.numel()].abs())
+    s = a[0] + a[1]
+    return torch.where(s > 0, (a[0] - a[1]) / s, torch.zeros_like(s)), a[0] - a[1]
+
+
+def _fsk64(case, seed):
+    bits, blocks, tags = _fsk_blocks(case, seed)
+    nt = case["bits"] * case["sps"] + case["taps"] + case["sps"] - 2
+    rows, tmpl = [], {}
+    for b, iq in enumerate(blocks):
+        n = iq.shape[0]
+        i = torch.arange(n, device="cuda", dtype=torch.float64)
+        x = torch.view_as_complex(iq.double()) * torch.polar(torch.ones_like(i), -2.0 * math.pi * (i * (LO_HZ / FS)).remainder(1.0))
+        d, u = _demod64(x, case)
+        F = 1 << math.ceil(math.log2(n))
+        D = torch.fft.rfft(d, F)
+        for t in range(case["tags"]) if tags[b] is None else [tags[b]]:
+            if t not in tmpl:
+                wave = _fsk_wave(bits[t], case["sps"])
+                r = torch.zeros(nt, dtype=torch.complex128, device="cuda")
+                r[:wave.numel()] = wave
+                tmpl[t] = _demod64(r, case)[0]
+            c = torch.fft.irfft(D * torch.fft.rfft(tmpl[t], F).conj(), F)[:n - nt + 1]
+            lag = int(c.abs().argmax())
+            edge = lag in (0, n - nt)
+            w, q = float(c[lag]), float(d[lag:lag + nt].square().sum())
+            ec = float(tmpl[t].square().sum())
+            rows.append(dict(tag=t, lag=lag, block=b, flags=1 if edge else 0, xcorr=w, q=q,
+                             toa=lag + (0.0 if edge else _parabola(*c[lag - 1:lag + 2].abs().tolist())),
+                             p=float(tmpl[t] @ u[lag:lag + nt]), z=w * w / (q * ec)))
+    rows = [r for r in rows if r["z"] >= _fsk_threshold(case)]
+    return _table(case, rows, FSK_INTS, FSK_FLOATS)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind in ("detect", "batch", "track"):
+        codes, freqs, xs, _, tags = _blocks(case, seed)
+        L, K = codes.shape[1] * case["spc"], len(freqs)
+        rows = []
+        for b, x in enumerate(xs):
+            one = tags[b] is not None
+            theta = _threshold(1 if one else case["tags"], K, x.numel() - L + 1)
+            rows += _search64(x, codes, case["spc"], freqs, [tags[b]] if one else range(case["tags"]), theta, b)
+        return _table(case, rows)
+    if kind == "learned":
+        codes, freqs, xs, _, _ = _blocks(case, seed)
+        params, kappa = _trained()
+        n, L = case["n"], codes.shape[1] * case["spc"]
+        lags, V = n - L + 1, (1 << 15) - L + 1
+        m, med = _map64(xs[0])
+        y = _network64(torch.from_numpy(np.asarray(params)).cuda().double(), m.to(torch.bfloat16).double(), 1)
+        score = torch.nn.functional.pad(y, (63, 64)).unfold(0, 128, 1).sum(1)
+        frames = torch.nonzero(score >= kappa).flatten().tolist()
+        segs = -(-lags // V)
+        hit = np.zeros(segs, dtype=bool)
+        for f in frames:
+            lo, hi = max(128 * f + 256 - L, 0), min(128 * f, lags - 1)
+            if lo <= hi:
+                hit[lo // V:hi // V + 1] = True
+        full = hit.sum() > 0.5 * segs
+        keep = None if full else torch.from_numpy(np.repeat(hit, V)[:lags]).cuda()
+        rows = _search64(xs[0], codes, case["spc"], freqs, range(case["tags"]),
+                         _threshold(case["tags"], len(freqs), lags), 0, keep) if hit.any() or full else []
+        return dict(_table(case, rows), proposals=len(frames), segments=int(segs if full else hit.sum()),
+                    fallback=1 if full else 0, median=med)
+    if kind in ("fsk", "fsk_track"):
+        return _fsk64(case, seed)
+    if kind == "map":
+        x = _blocks(dict(case, kind="detect", tags=16, chips=min(8192, case["n"] // 3), spc=2, bins=11,
+                         precision="fp32"), seed)[2][0]
+        m, med = _map64(x)
+        return dict(map=m, median=np.float64(med))
+    xs, labels = _training_blocks(case, seed)
+    params = torch.from_numpy(_init_params(seed)).cuda().double().requires_grad_(True)
+    maps = torch.cat([_map64(x)[0].to(torch.bfloat16).double() for x in xs])
+    y = _network64(params, maps, case["blocks"])
+    lab = labels.double()
+    soft = torch.nn.functional.softplus
+    loss = (POS_WEIGHT * lab * soft(-y) + (1.0 - lab) * soft(y)).mean()
+    loss.backward()
+    return dict(loss=np.float64(loss.item()), grad=params.grad.detach())
