@@ -16,7 +16,7 @@ noise of rms 1000 for FSK).
 from __future__ import annotations
 
 import math
-import os
+import operator
 
 import numpy as np
 import torch
@@ -328,8 +328,8 @@ def _columns(state, dets, ints=INTS, floats=FLOATS):
     i = np.zeros((state["rows"], len(ints)), dtype=np.int64)
     v = np.zeros((state["rows"], len(floats)))
     if at:
-        i[at] = [[getattr(d, f) for f in ints] for d in dets]
-        v[at] = [[getattr(d, f) for f in floats] for d in dets]
+        i[at] = list(map(operator.attrgetter(*ints), dets))
+        v[at] = list(map(operator.attrgetter(*floats), dets))
     return {**{f: i[:, k] for k, f in enumerate(ints)}, **{f: v[:, k] for k, f in enumerate(floats)}}
 
 
