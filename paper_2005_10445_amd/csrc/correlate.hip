@@ -28,9 +28,11 @@
 // power with ties going to the smaller lag and then the smaller bin (the
 // argmax of Section 3, step 8).  P >= 0, so its bit pattern orders like its
 // value.  Each tag also counts its threshold crossings, the (bin, lag) with
-// P >= theta * L * Pxhat: each lane counts its own (invalid lags carry
-// P = -1), and the wave adds the lanes' counts only when some lane has one.
+// P >= theta * L * Pxhat.  Both are formed only for transforms that reach the
+// tag's best power so far or the threshold (invalid lags carry P = -1).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "host_logic.h"
@@ -123,22 +125,94 @@ __device__ __forceinline__ unsigned wave_sum_u32(unsigned v) {
     return v;
 }
 
-// Powers of this lane's valid outputs (ob + out_off < ulim) that reach the
-// threshold pth.  Only a lane whose largest power bp reaches it has any, so
-// the others skip the count; the powers are formed again exactly as in the
-// maximum, and the per-lane test alone decides validity (no wave-uniform
-// branches, which would hold a scalar mask per register).
-template <class E>
-__device__ __forceinline__ unsigned lane_crossings(const float2 (&v)[16], float bp, float pth, int ob, int ulim) {
-    unsigned lc = 0;
-    if (bp >= pth) {
+__device__ __forceinline__ float power(float2 c) { return fmaf(c.x, c.x, c.y * c.y); }
+
+// Powers of this lane's outputs (-1 where the output is not a valid lag) and the
+// largest of them.  LOWER: exactly the outputs below E::HI_OFF are valid, in
+// every lane of the wave -- the usual transform of a segment with about half
+// valid lags -- so no register needs a test, and the other powers stay unset.
+template <class E, bool LOWER>
+__device__ __forceinline__ float lane_powers(const float2 (&v)[16], float (&p)[16], int ob, int omin, int ulim) {
+    float bp = -1.0f;
+    if constexpr (LOWER) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (E::out_off(r) < E::HI_OFF) {
+                p[r] = power(v[r]);
+                bp = fmaxf(bp, p[r]);
+            }
+    } else {
+        int lim = ulim - ob;                       // this lane's outputs below this offset are valid
+        asm volatile("" : "+v"(lim));
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float p = fmaf(v[r].x, v[r].x, v[r].y * v[r].y);
-            lc += (ob + E::out_off(r) < ulim && p >= pth) ? 1u : 0u;
+            const int off = E::out_off(r);
+            p[r] = -1.0f;
+            if (omin + off < ulim) {               // wave-uniform: some lane of this register is valid
+                p[r] = off < lim ? power(v[r]) : -1.0f;
+                bp = fmaxf(bp, p[r]);
+            }
         }
     }
-    return lc;
+    return bp;
+}
+
+// Largest value over the wave (uniform).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_fmax_step(float v) {
+    const int b = int(__float_as_uint(v));
+    return fmaxf(v, __uint_as_float(unsigned(__builtin_amdgcn_update_dpp(b, b, CTRL, ROW_MASK, 0xf, false))));
+}
+
+__device__ __forceinline__ float wave_fmax(float v) {
+    v = dpp_fmax_step<0x111, 0xf>(v);
+    v = dpp_fmax_step<0x112, 0xf>(v);
+    v = dpp_fmax_step<0x114, 0xf>(v);
+    v = dpp_fmax_step<0x118, 0xf>(v);
+    v = dpp_fmax_step<0x142, 0xa>(v);
+    v = dpp_fmax_step<0x143, 0xc>(v);
+    return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(__float_as_uint(v)), 63)));
+}
+
+// The wave's peak key and its count of threshold crossings, for a transform
+// with some power >= 0 (bp: each lane's largest, of the powers p).  The output
+// that holds the peak is looked for here and not tracked in the scan of every
+// transform: few transforms reach their tag's best so far or the threshold
+// (searching 2^20 samples for 64 tags in 11 bins: 2.56 ms a call with the
+// output tracked and a key formed for every transform, 2.35 ms so).
+template <class E, bool LOWER>
+__device__ __forceinline__ unsigned long long wave_peak(const float (&p)[16], float bp, float pth, unsigned idx0,
+                                                        unsigned kstep, unsigned* count) {
+    const float wm = wave_fmax(bp);
+    int boff = 0;                            // smallest offset of a lane that holds wm
+#pragma unroll
+    for (int rr = 15; rr >= 0; --rr) {
+        const int off = E::out_off(E::visit(rr));
+        if (!LOWER || off < E::HI_OFF) boff = p[E::visit(rr)] == wm ? off : boff;
+    }
+    const unsigned idx = idx0 + unsigned(boff) * kstep;
+    unsigned long long m = __builtin_amdgcn_ballot_w64(bp == wm);
+    unsigned best = ~0u;
+    while (m) {                              // ties go to the smaller index (uniform loop, nearly always one lane)
+        const unsigned i = unsigned(__builtin_amdgcn_readlane(int(idx), __builtin_ctzll(m)));
+        best = i < best ? i : best;
+        m &= m - 1;
+    }
+    unsigned lc = 0;
+    if (wm >= pth) {                         // uniform
+#pragma unroll
+        for (int r = 0; r < 16; ++r) lc += (!LOWER || E::out_off(r) < E::HI_OFF) && p[r] >= pth ? 1u : 0u;
+        lc = wave_sum_u32(lc);
+    }
+    *count = lc;
+    return (static_cast<unsigned long long>(__float_as_uint(wm)) << 32) | static_cast<unsigned long long>(~best);
+}
+
+// The power below which a transform changes nothing: the smaller of the best
+// one recorded so far under `key` and the threshold.
+__device__ __forceinline__ float gate_power(const unsigned long long* key, float pth) {
+    const unsigned long long k = __hip_atomic_load(key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return fminf(__uint_as_float(unsigned(k >> 32)), pth);
 }
 
 // One work item: (tile of tags, global segment g, bin k, phase rho), item index
@@ -191,6 +265,14 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
     const unsigned idx00 = kbase + unsigned(ob0) * kstep;
     const int omin = eng.out_min(), omax = eng.out_max();   // wave-uniform
     const bool hi = omin + E::HI_OFF < ulim;               // any output of the upper half needed
+    const bool lower = !hi && omax + E::LOW_MAX < ulim;    // exactly the lower outputs, in every lane
+    // lane t: the power that tag t's transform has to reach to matter.  The keys
+    // only grow during a launch, so a value read early is a lower bound
+    const float gates = lane < ntag ? gate_power(&keys[tag0 + lane], pth) : 0.0f;
+    for (int i = int(threadIdx.x); i < ntag * NW; i += E::NT) {   // (the transform's barriers order these)
+        red[i] = 0ull;
+        cred[i] = 0u;
+    }
 
     // bank element of register m: i = in_index(0) + m*NT, stored for i <= N/2;
     // registers m >= 8 read the mirror N - i = (NT - in_index(0)) + (15-m)*NT
@@ -200,49 +282,48 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
     for (int tt = 0; tt < ntag; ++tt) {
         float2 v[16];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v[m] = cmul(G[m], St::bload(bank, voff, (tt * NB + m * E::NT) * St::BYTES));
+        for (int m = 0; m < 8; ++m) v[m] = St::bload(bank, voff, (tt * NB + m * E::NT) * St::BYTES);
 #pragma unroll
-        for (int m = 8; m < 16; ++m)
-            v[m] = cmulc(G[m], St::bload(bank, voffm, (tt * NB + (15 - m) * E::NT) * St::BYTES));
-        eng.template transform<+1>(v, lds, b1, extra, hi);
+        for (int m = 8; m < 16; ++m) v[m] = St::bload(bank, voffm, (tt * NB + (15 - m) * E::NT) * St::BYTES);
+        // products with the replica in the transform's first butterflies
+#pragma unroll
+        for (int m = 0; m < 8; ++m) bflyc(cmul(G[m], v[m]), G[m + 8], v[m + 8], v[m], v[m + 8]);
+        eng.template transform_rest<+1>(v, lds, b1, extra, hi);
         // per-register indices and masks are the same for every tag: keep the
         // optimiser from holding all of them across the loop (recomputing is cheap)
         int ob = ob0;
         unsigned idx0 = idx00;
         asm volatile("" : "+v"(ob), "+v"(idx0));
-        // this lane's largest valid power; registers are visited in increasing
-        // output index, so the strict comparison keeps the smallest lag of a tie
-        float bp = -1.0f;
-        int boff = 0;
+        if constexpr (DUMP) {
 #pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            const int r = E::visit(rr);
-            const int off = E::out_off(r);
-            if (omin + off < ulim) {               // wave-uniform: some lane of this register is valid
-                float p = fmaf(v[r].x, v[r].x, v[r].y * v[r].y);
-                if constexpr (DUMP) {
-                    if (ob + off < ulim) {
-                        const int64_t tau = seg0 + int64_t(a.spc) * (ob + off) + rho;
-                        a.dump[(size_t(tag0 + tt) * a.K + k) * size_t(d.lags) + size_t(tau)] = p;
-                    }
+            for (int r = 0; r < 16; ++r) {
+                const int off = E::out_off(r);
+                if (ob + off < ulim) {
+                    const int64_t tau = seg0 + int64_t(a.spc) * (ob + off) + rho;
+                    a.dump[(size_t(tag0 + tt) * a.K + k) * size_t(d.lags) + size_t(tau)] = power(v[r]);
                 }
-                if (omax + off >= ulim && ob + off >= ulim) p = -1.0f;
-                boff = p > bp ? off : boff;
-                bp = p > bp ? p : bp;
             }
         }
-        const unsigned lc = lane_crossings<E>(v, bp, pth, ob, ulim);
-        unsigned cross = 0;
-        if (__builtin_amdgcn_ballot_w64(lc != 0)) cross = wave_sum_u32(lc);
-        unsigned long long best = bp >= 0.0f
-            ? (static_cast<unsigned long long>(__float_as_uint(bp)) << 32) |
-                  static_cast<unsigned long long>(~(idx0 + unsigned(boff) * kstep))
-            : 0ull;
-        best = wave_max(best);
-        if (lane == 0) {
-            red[tt * NW + wave] = best;
-            cred[tt * NW + wave] = cross;
-        }
+        // most transforms hold neither a power that reaches the tag's best so
+        // far nor one that reaches the threshold: no key, no count
+        const float gate = __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(__float_as_uint(gates)), tt)));
+        auto scan = [&](auto low) {
+            constexpr bool LOW = decltype(low)::value;
+            float p[16];
+            const float bp = lane_powers<E, LOW>(v, p, ob, omin, ulim);
+            if (__builtin_amdgcn_ballot_w64(bp >= gate)) {
+                unsigned cross;
+                const unsigned long long best = wave_peak<E, LOW>(p, bp, pth, idx0, kstep, &cross);
+                if (lane == 0) {
+                    red[tt * NW + wave] = best;
+                    cred[tt * NW + wave] = cross;
+                }
+            }
+        };
+        if (E::HAS_UPPER && lower)
+            scan(std::bool_constant<E::HAS_UPPER>{});
+        else
+            scan(std::false_type{});
     }
     __syncthreads();
     for (int i = int(threadIdx.x); i < ntag; i += E::NT) {
@@ -261,8 +342,9 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
 // One tracking work item: (global segment g, tile of bins, phase rho) for the
 // block's own tag, item index wi = (g * bin_tiles + tile) * spc + rho, with
 // a.tile bins per tile.  Every bin forms its G_rho and runs one inverse
-// transform; each lane keeps its largest key over all the item's bins, so one
-// wave reduction and one atomic per item remain.
+// transform; each wave keeps its largest key over all the item's bins (formed
+// only for the bins that reach what it has, or the threshold), so one atomic
+// per item remains.
 template <class E, int PREC>
 __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int wi, float2* lds,
                                            const float2* extra, unsigned long long* red, unsigned* cred) {
@@ -297,11 +379,13 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
     const int ob0 = eng.out_base();
     const int omin = eng.out_min(), omax = eng.out_max();
     const bool hi = omin + E::HI_OFF < ulim;
+    const bool lower = !hi && omax + E::LOW_MAX < ulim;        // as in correlate_item
     const int voff = eng.in_index(0) * St::BYTES;              // half bank, as in correlate_item
     const int voffm = (E::NT - eng.in_index(0)) * St::BYTES;
 
-    unsigned long long best = 0ull;
-    unsigned lc = 0;                               // this lane's crossings over the item's bins
+    unsigned long long best = 0ull;                // the wave's largest key over the item's bins
+    unsigned cross = 0;                            // the wave's crossings over the item's bins
+    float gate = gate_power(&a.keys[size_t(bi) * a.T + tag], pth);
     // the task's replica spectrum is the same for every bin: read it once
     float2 bk[16];
 #pragma unroll
@@ -312,36 +396,28 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
         float2 v[16];
         first_step<E, PREC>(a, eng, g, k, rho, gscale, v);
 #pragma unroll
-        for (int m = 0; m < 8; ++m) v[m] = cmul(v[m], bk[m]);
-#pragma unroll
-        for (int m = 8; m < 16; ++m) v[m] = cmulc(v[m], bk[m]);
-        eng.template transform<+1>(v, lds, b1, extra, hi);
+        for (int m = 0; m < 8; ++m) bflyc(cmul(v[m], bk[m]), v[m + 8], bk[m + 8], v[m], v[m + 8]);
+        eng.template transform_rest<+1>(v, lds, b1, extra, hi);
         int ob = ob0;
         unsigned idx0 = unsigned((seg0 + rho) * a.K + k) + unsigned(ob0) * kstep;
         asm volatile("" : "+v"(ob), "+v"(idx0));
-        float bp = -1.0f;
-        int boff = 0;
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            const int r = E::visit(rr);
-            const int off = E::out_off(r);
-            if (omin + off < ulim) {
-                float p = fmaf(v[r].x, v[r].x, v[r].y * v[r].y);
-                if (omax + off >= ulim && ob + off >= ulim) p = -1.0f;
-                lc += p >= pth ? 1u : 0u;
-                boff = p > bp ? off : boff;
-                bp = p > bp ? p : bp;
+        auto scan = [&](auto low) {
+            constexpr bool LOW = decltype(low)::value;
+            float p[16];
+            const float bp = lane_powers<E, LOW>(v, p, ob, omin, ulim);
+            if (__builtin_amdgcn_ballot_w64(bp >= gate)) {
+                unsigned count;
+                const unsigned long long key = wave_peak<E, LOW>(p, bp, pth, idx0, kstep, &count);
+                cross += count;
+                best = key > best ? key : best;
+                gate = fminf(pth, fmaxf(gate, __uint_as_float(unsigned(best >> 32))));
             }
-        }
-        const unsigned long long key = bp >= 0.0f
-            ? (static_cast<unsigned long long>(__float_as_uint(bp)) << 32) |
-                  static_cast<unsigned long long>(~(idx0 + unsigned(boff) * kstep))
-            : 0ull;
-        best = key > best ? key : best;
+        };
+        if (E::HAS_UPPER && lower)
+            scan(std::bool_constant<E::HAS_UPPER>{});
+        else
+            scan(std::false_type{});
     }
-    best = wave_max(best);
-    unsigned cross = 0;
-    if (__builtin_amdgcn_ballot_w64(lc != 0)) cross = wave_sum_u32(lc);
     if (lane == 0) {
         red[wave] = best;
         cred[wave] = cross;

@@ -11,6 +11,7 @@
 namespace acq {
 namespace kdev {
 
+using dev::bflyc;
 using dev::cadd;
 using dev::cmul;
 using dev::cmulc;
@@ -73,10 +74,14 @@ __device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
 
 // ------------------------------------------------------------------ transform engines
 // Both engines take v[m] = a[in_index(m)] and leave output index
-// out_base() + out_off(r) in v[r].
+// out_base() + out_off(r) in v[r].  transform_rest takes the first butterflies
+// as done: v[n] and v[n + 8], n < 8, hold the sum and the difference of inputs
+// n and n + 8.
 
-// Stockham passes (2^10 .. 2^13 points), see device_fft.h.
-template <int LOGN_>
+// Stockham passes (2^10 .. 2^13 points), see device_fft.h.  IN: twiddles taken
+// into the butterflies (the FSK front end keeps products before the DFTs: its
+// outputs are reported, and their roundings stay as they were).
+template <int LOGN_, bool IN = true>
 struct StockhamEngine {
     using F = Fft<LOGN_>;
     static constexpr int LOGN = LOGN_;
@@ -97,7 +102,9 @@ struct StockhamEngine {
     __device__ __forceinline__ int out_min() const { return __builtin_amdgcn_readfirstlane(t & ~63); }
     __device__ __forceinline__ int out_max() const { return out_min() + 63; }
     static constexpr int out_off(int r) { return r * NT; }
-    static constexpr int HI_OFF = 1 << 30;      // no output is ever pruned
+    static constexpr bool HAS_UPPER = false;    // no output is ever left out
+    static constexpr int HI_OFF = 1 << 30;
+    static constexpr int LOW_MAX = 15 * NT;     // largest out_off below HI_OFF
     // register holding the rr-th smallest output offset
     static constexpr int visit(int rr) { return rr; }
     template <int S>
@@ -105,7 +112,18 @@ struct StockhamEngine {
                                               const float2*, bool = true) const {
         int tq = t;
         asm volatile("" : "+v"(tq));            // recompute addressing per call, no hoisting
-        F::template transform<S>(v, lds, roots, tq);
+        if constexpr (IN)
+            F::template transform_in<S, false>(v, lds, roots, tq);
+        else
+            F::template transform<S>(v, lds, roots, tq);
+    }
+    template <int S>
+    __device__ __forceinline__ void transform_rest(float2 (&v)[16], float2* lds, __amdgpu_buffer_rsrc_t, const float2*,
+                                                   bool = true) const {
+        static_assert(IN, "the products before the DFTs have no separate first butterflies");
+        int tq = t;
+        asm volatile("" : "+v"(tq));
+        F::template transform_in<S, true>(v, lds, roots, tq);
     }
 };
 

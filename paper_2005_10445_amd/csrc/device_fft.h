@@ -134,6 +134,150 @@ __device__ __forceinline__ void dft16(float2 (&u)[16]) {
     for (int i = 0; i < 16; ++i) u[i] = r[i];
 }
 
+// ---------------------------------------------------------------- butterflies that take their twiddles in
+// s = a + w b, d = a - w b in six instructions (the product and the sum in four
+// fused ones, then d = 2 a - s) instead of a product and two additions in eight.
+__device__ __forceinline__ void bfly(float2 a, float2 b, float2 w, float2& s, float2& d) {
+    s.x = fmaf(b.x, w.x, fmaf(-b.y, w.y, a.x));
+    s.y = fmaf(b.x, w.y, fmaf(b.y, w.x, a.y));
+    d.x = fmaf(2.0f, a.x, -s.x);
+    d.y = fmaf(2.0f, a.y, -s.y);
+}
+// the same with conj(w)
+__device__ __forceinline__ void bflyc(float2 a, float2 b, float2 w, float2& s, float2& d) {
+    s.x = fmaf(b.x, w.x, fmaf(b.y, w.y, a.x));
+    s.y = fmaf(-b.x, w.y, fmaf(b.y, w.x, a.y));
+    d.x = fmaf(2.0f, a.x, -s.x);
+    d.y = fmaf(2.0f, a.y, -s.y);
+}
+// S = +1: w, S = -1: conj(w)
+template <int S>
+__device__ __forceinline__ void bfly_s(float2 a, float2 b, float2 w, float2& s, float2& d) {
+    if constexpr (S > 0)
+        bfly(a, b, w, s, d);
+    else
+        bflyc(a, b, w, s, d);
+}
+
+// (1 + S j t) a and (t + S j) a
+template <int S>
+__device__ __forceinline__ float2 mul_1t(float2 a, float t) {
+    return S > 0 ? make_float2(fmaf(-t, a.y, a.x), fmaf(t, a.x, a.y)) : make_float2(fmaf(t, a.y, a.x), fmaf(-t, a.x, a.y));
+}
+template <int S>
+__device__ __forceinline__ float2 mul_t1(float2 a, float t) {
+    return S > 0 ? make_float2(fmaf(t, a.x, -a.y), fmaf(t, a.y, a.x)) : make_float2(fmaf(t, a.x, a.y), fmaf(t, a.y, -a.x));
+}
+// (1 + S j) a and (-1 + S j) a
+template <int S>
+__device__ __forceinline__ float2 mul_1j(float2 a) {
+    return S > 0 ? make_float2(a.x - a.y, a.x + a.y) : make_float2(a.x + a.y, a.y - a.x);
+}
+template <int S>
+__device__ __forceinline__ float2 mul_m1j(float2 a) {
+    return S > 0 ? make_float2(-a.x - a.y, a.x - a.y) : make_float2(a.y - a.x, -a.x - a.y);
+}
+// a + c b and a - c b for a real c
+__device__ __forceinline__ float2 axpy(float2 a, float c, float2 b) { return make_float2(fmaf(c, b.x, a.x), fmaf(c, b.y, a.y)); }
+
+constexpr float kTan8 = 0.41421356237309504880f;   // tan(pi/8)
+
+// 16-point DFT (the 4 x 4 form of dft16) whose first butterflies are done:
+// u[n] and u[n + 8], n < 8, hold the sum and the difference of inputs n and
+// n + 8.  The inner rotations are factored so that they cost two instructions
+// each: exp(j pi/8) = c (1 + j t), exp(j 3 pi/8) = c (t + j) and exp(j pi/4) =
+// h (1 + j) with c = cos(pi/8), t = tan(pi/8), h = sqrt(1/2), the real factor
+// (the same for both operands of a pair) going into the fused additions that
+// follow: 112 instructions, where dft16's form takes 128.
+template <int S>
+__device__ __forceinline__ void dft16_rest(float2 (&u)[16]) {
+    // first stage, second half: A[n2][k1] into u[n2 + 4 k1]
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+        const float2 a0 = u[n2], a1 = u[n2 + 8], b0 = u[n2 + 4], b1 = mul_sj<S>(u[n2 + 12]);
+        u[n2] = cadd(a0, b0);
+        u[n2 + 8] = csub(a0, b0);
+        u[n2 + 4] = cadd(a1, b1);
+        u[n2 + 12] = csub(a1, b1);
+    }
+    float2 r[16];
+    // second stage over n2; outputs k1 + 4 k2.  finish: a0, a1 the sum and
+    // difference of inputs 0 and 2, b0, b1 those of inputs 1 and 3 over c
+    auto finish = [&](int k1, float2 a0, float2 a1, float2 b0, float2 b1, float c) {
+        const float2 jb = mul_sj<S>(b1);
+        r[k1] = axpy(a0, c, b0);
+        r[k1 + 8] = axpy(a0, -c, b0);
+        r[k1 + 4] = axpy(a1, c, jb);
+        r[k1 + 12] = axpy(a1, -c, jb);
+    };
+    {
+        float2 x0 = u[0], x1 = u[1], x2 = u[2], x3 = u[3];
+        dft4<S>(x0, x1, x2, x3);
+        r[0] = x0;
+        r[4] = x1;
+        r[8] = x2;
+        r[12] = x3;
+    }
+    {                                                          // rotations by 1, 2, 3 sixteenths
+        const float2 q = mul_1j<S>(u[6]);
+        const float2 y1 = mul_1t<S>(u[5], kTan8), y3 = mul_t1<S>(u[7], kTan8);
+        finish(1, axpy(u[4], kRsqrt2, q), axpy(u[4], -kRsqrt2, q), cadd(y1, y3), csub(y1, y3), kCos8);
+    }
+    {                                                          // 2, 4, 6
+        const float2 q = mul_sj<S>(u[10]);
+        const float2 y1 = mul_1j<S>(u[9]), y3 = mul_m1j<S>(u[11]);
+        finish(2, cadd(u[8], q), csub(u[8], q), cadd(y1, y3), csub(y1, y3), kRsqrt2);
+    }
+    {                                                          // 3, 6, 9
+        const float2 q = mul_m1j<S>(u[14]);
+        const float2 y1 = mul_t1<S>(u[13], kTan8), y3 = mul_1t<S>(u[15], kTan8);
+        finish(3, axpy(u[12], kRsqrt2, q), axpy(u[12], -kRsqrt2, q), csub(y1, y3), cadd(y1, y3), kCos8);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) u[i] = r[i];
+}
+
+// the first butterflies of dft16_rest without and with twiddles w[0..15] on the inputs
+__device__ __forceinline__ void dft16_first(float2 (&u)[16]) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+        const float2 a = u[n], b = u[n + 8];
+        u[n] = cadd(a, b);
+        u[n + 8] = csub(a, b);
+    }
+}
+
+// dft_r after its first butterflies: u[r] and u[r + R/2] hold the sum and the
+// difference of inputs r and r + R/2 (twiddled).
+template <int R, int S>
+__device__ __forceinline__ void dft_rest(float2 (&u)[R]) {
+    if constexpr (R == 4) {
+        const float2 a0 = u[0], a1 = u[2], b0 = u[1], b1 = mul_sj<S>(u[3]);
+        u[0] = cadd(a0, b0);
+        u[2] = csub(a0, b0);
+        u[1] = cadd(a1, b1);
+        u[3] = csub(a1, b1);
+    } else if constexpr (R == 8) {
+        float2 e0 = u[0], e1 = u[1], e2 = u[2], e3 = u[3];
+        dft4<S>(e0, e1, e2, e3);
+        const float2 q = mul_sj<S>(u[6]);
+        const float2 y1 = mul_1j<S>(u[5]), y3 = mul_m1j<S>(u[7]);
+        const float2 a0 = cadd(u[4], q), a1 = csub(u[4], q), b0 = cadd(y1, y3), b1 = mul_sj<S>(csub(y1, y3));
+        u[0] = e0;
+        u[2] = e1;
+        u[4] = e2;
+        u[6] = e3;
+        u[1] = axpy(a0, kRsqrt2, b0);
+        u[5] = axpy(a0, -kRsqrt2, b0);
+        u[3] = axpy(a1, kRsqrt2, b1);
+        u[7] = axpy(a1, -kRsqrt2, b1);
+    } else if constexpr (R == 16) {
+        dft16_rest<S>(u);
+    } else {
+        static_assert(R == 2, "radix");
+    }
+}
+
 template <int R, int S>
 __device__ __forceinline__ void dft_r(float2 (&u)[R]) {
     if constexpr (R == 2) {
@@ -184,6 +328,35 @@ struct Fft {
         }
     }
 
+    // The same pass with the twiddles taken into the first butterflies of the
+    // DFT (inputs r and r + R/2).  FIRST_DONE (NS = 1): those are done already.
+    template <int NS, int R, int S, bool FIRST_DONE>
+    __device__ __forceinline__ static void pass_in(float2 (&v)[16], const float2* __restrict__ tw, int t) {
+        constexpr int NB = 16 / R;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            float2 u[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) u[r] = v[q + r * NB];
+            if constexpr (NS > 1) {
+                const int j = (t + q * NT) & (NS - 1);
+                auto w = [&](int r) { return tw[j * r * (N / (NS * R))]; };
+#pragma unroll
+                for (int r = 0; r < R / 2; ++r) {
+                    float2 a = u[r];
+                    if (r) a = S > 0 ? cmul(a, w(r)) : cmulc(a, w(r));
+                    bfly_s<S>(a, u[r + R / 2], w(r + R / 2), u[r], u[r + R / 2]);
+                }
+            } else if constexpr (!FIRST_DONE) {
+#pragma unroll
+                for (int r = 0; r < R / 2; ++r) dft2<S>(u[r], u[r + R / 2]);
+            }
+            dft_rest<R, S>(u);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[q + r * NB] = u[r];
+        }
+    }
+
     template <int NS, int R>
     __device__ __forceinline__ static void store(const float2 (&v)[16], float2* lds, int t) {
         constexpr int NB = 16 / R;
@@ -209,17 +382,20 @@ struct Fft {
         static constexpr bool LAST = (P == P16 - 1 && RLAST == 1) || (P == P16);
     };
 
-    template <int P, int S>
+    template <int P, int S, bool IN = false, bool FIRST_DONE = false>
     __device__ __forceinline__ static void run_from(float2 (&v)[16], float2* lds,
                                                     const float2* __restrict__ tw, int t) {
         using St = Step<P>;
-        pass<St::NS, St::R, S>(v, tw, t);
+        if constexpr (IN)
+            pass_in<St::NS, St::R, S, FIRST_DONE>(v, tw, t);
+        else
+            pass<St::NS, St::R, S>(v, tw, t);
         if constexpr (!St::LAST) {
             store<St::NS, St::R>(v, lds, t);
             __syncthreads();
             load(v, lds, t);
             __syncthreads();
-            run_from<P + 1, S>(v, lds, tw, t);
+            run_from<P + 1, S, IN>(v, lds, tw, t);
         }
     }
 
@@ -229,6 +405,15 @@ struct Fft {
     __device__ __forceinline__ static void transform(float2 (&v)[16], float2* lds,
                                                      const float2* __restrict__ tw, int t) {
         run_from<0, S>(v, lds, tw, t);
+    }
+
+    // The same with the twiddles taken into the butterflies (fewer instructions,
+    // other roundings); FIRST_DONE: v[n] and v[n + 8], n < 8, already hold the
+    // sum and the difference of inputs n and n + 8.
+    template <int S, bool FIRST_DONE>
+    __device__ __forceinline__ static void transform_in(float2 (&v)[16], float2* lds,
+                                                        const float2* __restrict__ tw, int t) {
+        run_from<0, S, true, FIRST_DONE>(v, lds, tw, t);
     }
 };
 

@@ -113,7 +113,7 @@ struct FrontArgs {
 // (at most 168 VGPRs: the forward spectrum stays in registers through the
 // first inverse transform; at 128 it spills and runs slower).
 __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
-    using E = StockhamEngine<kFrontLog>;
+    using E = StockhamEngine<kFrontLog, false>;
     __shared__ float2 lds[E::LDS];
     E eng;
     eng.init(a.roots, nullptr);
@@ -982,7 +982,7 @@ hipError_t launch_front(acq_fsk_plan_s* p, const acq::FskTasks& tasks, int fsegs
     a.out_stride = p->g.M;
     a.lo_cyc = c.lo_hz / c.sample_rate_hz;
     {
-        using E = acq::kdev::StockhamEngine<acq::kFrontLog>;
+        using E = acq::kdev::StockhamEngine<acq::kFrontLog, false>;
         for (int m = 0; m < 16; ++m) {
             double cyc = -a.lo_cyc * double(int64_t(E::NT) * m);
             cyc -= std::floor(cyc);

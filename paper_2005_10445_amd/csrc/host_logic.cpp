@@ -241,8 +241,9 @@ std::vector<float> fft14_b1_table() {
     std::vector<float> out(size_t(2 * 16 * 16 * 64));
     size_t o = 0;
     for (int64_t w = 0; w < 16; ++w)
-        for (int64_t k2a = 0; k2a < 16; ++k2a)
-            for (int64_t l = 0; l < 64; ++l) {
+        for (int64_t m = 0; m < 16; ++m)
+            for (int64_t lane = 0; lane < 64; ++lane) {
+                const int64_t k2a = lane / 4, l = lane % 4 + 4 * m;
                 const int64_t e = (l * (w + 16 * k2a)) % n;
                 out[o++] = roots[size_t(2 * e)];
                 out[o++] = roots[size_t(2 * e + 1)];

@@ -67,8 +67,8 @@ std::vector<float> unit_roots(int64_t n);
 // The same roots in FP64: [2n] = (cos, sin)(2 pi m / n).
 std::vector<double> unit_roots64(int64_t n);
 
-// Twiddles of the 2^14-point workgroup transform, laid out [w][k2a][l] with
-// entry exp(+j 2 pi l (w + 16 k2a) / 2^14), w, k2a < 16, l < 64.
+// Twiddles of the 2^14-point workgroup transform, laid out [w][m][4 k2a + q]
+// with entry exp(+j 2 pi l (w + 16 k2a) / 2^14), l = q + 4 m; w, m, k2a < 16, q < 4.
 std::vector<float> fft14_b1_table();
 
 // Weights of the tag-independent first step of the split inverse transform:
