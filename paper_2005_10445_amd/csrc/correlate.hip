@@ -440,8 +440,10 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
 // persistent loop's live state does not weigh on the one-item-per-workgroup forms.
 enum CorrMode { kCorrGrid = 0, kCorrGridDump = 1, kCorrPersistent = 2, kCorrTrack = 3 };
 
+// Four waves per SIMD (at most 128 registers): with more, the 2^13-point engine's
+// second workgroup no longer fits a compute unit.
 template <class E, int PREC, int MODE>
-__global__ __launch_bounds__(E::NT) void k_correlate(CorrArgs a) {
+__global__ __launch_bounds__(E::NT, 4) void k_correlate(CorrArgs a) {
     constexpr int NW = E::NT / 64;
     constexpr bool DUMP = MODE == kCorrGridDump;
     __shared__ float2 lds[E::LDS];

@@ -91,10 +91,11 @@ struct StockhamEngine {
     static constexpr int EXTRA = 1;
     static constexpr int B1_TABLE = 1;
     int t;
-    const float2* roots;
+    __amdgpu_buffer_rsrc_t tw;
+    // r: the N unit roots (unused here) and the pass twiddles after them
     __device__ __forceinline__ void init(const float2* __restrict__ r, float2*) {
         t = int(threadIdx.x);
-        roots = r;
+        tw = dev::make_rsrc(r + N, F::TW * 8);
     }
     __device__ __forceinline__ int in_index(int m) const { return t + m * NT; }
     __device__ __forceinline__ int out_base() const { return t; }
@@ -113,9 +114,9 @@ struct StockhamEngine {
         int tq = t;
         asm volatile("" : "+v"(tq));            // recompute addressing per call, no hoisting
         if constexpr (IN)
-            F::template transform_in<S, false>(v, lds, roots, tq);
+            F::template transform_in<S, false>(v, lds, tw, tq);
         else
-            F::template transform<S>(v, lds, roots, tq);
+            F::template transform<S>(v, lds, tw, tq);
     }
     template <int S>
     __device__ __forceinline__ void transform_rest(float2 (&v)[16], float2* lds, __amdgpu_buffer_rsrc_t, const float2*,
@@ -123,7 +124,7 @@ struct StockhamEngine {
         static_assert(IN, "the products before the DFTs have no separate first butterflies");
         int tq = t;
         asm volatile("" : "+v"(tq));
-        F::template transform_in<S, true>(v, lds, roots, tq);
+        F::template transform_in<S, true>(v, lds, tw, tq);
     }
 };
 

@@ -46,15 +46,6 @@
 namespace acq {
 namespace dev {
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-    // raw buffer, stride 0, num_records in bytes; loads past the end return 0
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-__device__ __forceinline__ float2 bload(__amdgpu_buffer_rsrc_t r, int voff_bytes, int soff_bytes) {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff_bytes, soff_bytes, 0));
-}
-
 // Order LDS accesses of one wave (LDS executes a wave's instructions in order;
 // this only keeps the compiler from moving them across).
 __device__ __forceinline__ void wave_lds_order() {

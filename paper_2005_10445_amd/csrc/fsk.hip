@@ -96,7 +96,7 @@ struct FrontArgs {
     const double* bit_cyc;      // replica: [T][nbits] carrier phase (cycles, in [0,1)) at each bit start
     const float2* G1;           // [kFrontN] DFT(h_BP * h_1) / kFrontN
     const float2* G0;
-    const float2* roots;        // [kFrontN] exp(+j 2 pi m / kFrontN)
+    const float2* roots;        // [kFrontN] exp(+j 2 pi m / kFrontN), then the pass twiddles
     float2* out;                // replica: [T][out_stride] (d, 0)
     float* out_d;               // block: d at the block's zoff
     float* out_u;               // block: u at the block's zoff
@@ -247,7 +247,7 @@ struct FskCorrArgs {
     const float2* X;            // [slots][M] spectra of the packed segment pairs
     const float2* bank;         // [T][M] conj(DFT_M(d^(c))) / M
     const float2* rootsM;       // [M]
-    const float2* rootsSub;     // [Msub]
+    const float2* rootsSub;     // [Msub], then the pass twiddles
     const float2* b1tab;
     float2* scratch;            // [gridDim.x][M]: the P first-step outputs of the workgroup's item
     unsigned long long* keys;   // [T] (searching) or [tasks] (tracking)
@@ -834,7 +834,7 @@ int fsk_geometry(const acq_fsk_config* c, FskGeometry* g) {
     const int64_t slots = g->slots;
     g->bytes = c->max_block_len * 8 + 2 * slots * M * 8 + std::min<int64_t>(T * slots, kFskMaxGrid) * M * 8 +
                2 * T * M * 8 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
-               kFrontN * 8 * 3 + M * 8 + g->Msub * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
+               kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
     return ACQ_OK;
 }
 
@@ -888,7 +888,7 @@ struct acq_fsk_plan_s {
     hipStream_t stream = nullptr;
     float2* d_G1 = nullptr;             // [kFrontN]
     float2* d_G0 = nullptr;
-    float2* d_rootsF = nullptr;         // [kFrontN]
+    float2* d_rootsF = nullptr;         // unit roots and pass twiddles of the front end's transform
     uint8_t* d_bits = nullptr;          // [T][nbits]
     double* d_bitcyc = nullptr;         // [T][nbits]
     float2* d_tmpl = nullptr;           // [T][M] (d^(c), 0), zero beyond n_t
@@ -1030,7 +1030,7 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     hipStream_t st = p->stream;
     FSK_HIP(dalloc(&p->d_G1, size_t(acq::kFrontN)));
     FSK_HIP(dalloc(&p->d_G0, size_t(acq::kFrontN)));
-    FSK_HIP(dalloc(&p->d_rootsF, size_t(acq::kFrontN)));
+    FSK_HIP(dalloc(&p->d_rootsF, size_t(acq::transform_roots_len(acq::kFrontN))));
     FSK_HIP(dalloc(&p->d_bits, T * NB));
     FSK_HIP(dalloc(&p->d_bitcyc, T * NB));
     FSK_HIP(dalloc(&p->d_tmpl, T * M));
@@ -1046,7 +1046,7 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_tasks), sizeof(acq::FskTask) * size_t(g.max_tasks)));
     FSK_HIP(dalloc(&p->d_scratch, size_t(p->corr_grid) * M));
     FSK_HIP(dalloc(&p->d_rootsM, M));
-    FSK_HIP(dalloc(&p->d_rootsSub, size_t(g.Msub)));
+    FSK_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
     FSK_HIP(dalloc(&p->d_b1tab, b1.size() / 2));
     FSK_HIP(dalloc(&p->d_zero, 1));
@@ -1064,9 +1064,9 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     // tables: composed filter spectra, unit roots, replica bit phases (FP64 on the host)
     const std::vector<float> G1 = acq::filter_spectrum(acq::composed(&c, c.f1_hz));
     const std::vector<float> G0 = acq::filter_spectrum(acq::composed(&c, c.f0_hz));
-    const std::vector<float> rootsF = acq::unit_roots(acq::kFrontN);
+    const std::vector<float> rootsF = acq::transform_roots(acq::kFrontN);
     const std::vector<float> rootsM = acq::unit_roots(g.M);
-    const std::vector<float> rootsSub = acq::unit_roots(g.Msub);
+    const std::vector<float> rootsSub = acq::transform_roots(g.Msub);
     std::vector<double> bitcyc(T * NB);
     std::vector<uint8_t> bits(T * NB);
     for (size_t t = 0; t < T; ++t) {

@@ -235,6 +235,28 @@ std::vector<float> unit_roots(int64_t n) {
     return std::vector<float>(r.begin(), r.end());
 }
 
+int64_t transform_roots_len(int64_t n) {
+    int64_t len = n;
+    for (int64_t ns = 16; ns < n; ns *= 16) len += (std::min<int64_t>(16, n / ns) - 1) * ns;
+    return len;
+}
+
+std::vector<float> transform_roots(int64_t n) {
+    std::vector<float> out = unit_roots(n);
+    out.reserve(size_t(2 * transform_roots_len(n)));
+    for (int64_t ns = 16; ns < n; ns *= 16) {
+        const int64_t r = std::min<int64_t>(16, n / ns), step = n / (ns * r);
+        for (int64_t q = 1; q < r; ++q)
+            for (int64_t j = 0; j < ns; ++j) {
+                const size_t e = size_t(2 * (j * q * step));     // j q step < n
+                const float re = out[e], im = out[e + 1];
+                out.push_back(re);
+                out.push_back(im);
+            }
+    }
+    return out;
+}
+
 std::vector<float> fft14_b1_table() {
     const int64_t n = 16384;
     const std::vector<float> roots = unit_roots(n);

@@ -64,7 +64,14 @@ double default_threshold(int64_t num_tags, int64_t num_bins, int64_t n, int64_t 
 // exp(+j 2 pi m / n) for m in [0, n), computed in FP64 with exact quadrant
 // symmetry and rounded to FP32; interleaved (re, im).
 std::vector<float> unit_roots(int64_t n);
-// The same roots in FP64: [2n] = (cos, sin)(2 pi m / n).
+// unit_roots(n) followed by the pass twiddles of the n-point Stockham transform
+// (radix 16, the last pass 2, 4 or 8 where log2(n) is no multiple of 4): for
+// every pass after the first, with span ns and radix r, exp(+j 2 pi j q / (ns r))
+// as [q - 1][j], 1 <= q < r, j < ns.  n a power of two in [2^8, 2^14].
+std::vector<float> transform_roots(int64_t n);
+// complex entries of transform_roots(n)
+int64_t transform_roots_len(int64_t n);
+// The n unit roots in FP64: [2n] = (cos, sin)(2 pi m / n).
 std::vector<double> unit_roots64(int64_t n);
 
 // Twiddles of the 2^14-point workgroup transform, laid out [w][m][4 k2a + q]

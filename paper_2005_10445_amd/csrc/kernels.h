@@ -66,7 +66,7 @@ struct CorrArgs {
     const float2* wts;          // [spc][M] W_rho[i] = sum_{r<spc} exp(+j 2 pi i (r + rho) / M)
                                 // (read for spc != 2; spc = 2 forms them in closed form)
     const float2* rootsM;       // [M] exp(+j 2 pi m / M)
-    const float2* rootsSub;     // [Msub] exp(+j 2 pi m / Msub)
+    const float2* rootsSub;     // [Msub] exp(+j 2 pi m / Msub), then the Stockham engine's pass twiddles
     const float2* b1tab;        // 2^14-point engine twiddle table (else unused)
     const int32_t* rot;         // [K] rotation of bin k, in [0, M)
     const int32_t* cls;         // [K] residual class of bin k (spectra slot g * ncls + cls[k])

@@ -72,7 +72,7 @@ struct acq_plan_s {
     int bank_exp = 0;                   // power-of-two prescale of the stored bank
     float2* d_wts = nullptr;            // [spc][M] first-step weights of the split inverse transform
     float2* d_rootsM = nullptr;         // [M]
-    float2* d_rootsSub = nullptr;       // [Msub]
+    float2* d_rootsSub = nullptr;       // [Msub] and the pass twiddles of the Stockham engine
     double2* d_roots64 = nullptr;       // [M] FP64 unit roots (refinement mix)
     float2* d_b1tab = nullptr;          // 2^14-point engine table (or a 1-entry stub)
     int8_t* d_chips = nullptr;          // [T][C]
@@ -230,7 +230,8 @@ size_t own_bytes(const Geometry& g, const acq_config& c) {
     const size_t T = size_t(c.num_tags), K = size_t(c.num_bins);
     const size_t half = c.precision != ACQ_FP32 ? 4 : 8;
     size_t b = T * size_t(acq::bank_stride(int(g.Msub))) * half;
-    b += size_t(g.M) * size_t(c.samples_per_chip) * 8 + size_t(g.M) * 8 + size_t(g.Msub) * 8 + size_t(g.M) * 16;
+    b += size_t(g.M) * size_t(c.samples_per_chip) * 8 + size_t(g.M) * 8 + size_t(acq::transform_roots_len(g.Msub)) * 8 +
+         size_t(g.M) * 16;
     b += (g.log2_sub == 14 ? size_t(16 * 16 * 64) : 1) * 8;
     b += T * size_t(c.num_chips) + K * (4 + 8 + 8 + 8 + 4) + size_t(g.ncls) * 8;
     return b;
@@ -261,7 +262,7 @@ int build_plan(acq_plan_s* p, void* workspace, size_t ws_bytes) {
     p->bank_exp = half ? int(std::lrint(std::log2(double(g.M) / std::sqrt(double(C))))) : 0;
     ACQ_HIP(dalloc(&p->d_wts, size_t(g.M) * size_t(c.samples_per_chip)));
     ACQ_HIP(dalloc(&p->d_rootsM, size_t(g.M)));
-    ACQ_HIP(dalloc(&p->d_rootsSub, size_t(g.Msub)));
+    ACQ_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     ACQ_HIP(dalloc(&p->d_roots64, size_t(g.M)));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
     ACQ_HIP(dalloc(&p->d_b1tab, b1.size() / 2));
@@ -278,7 +279,7 @@ int build_plan(acq_plan_s* p, void* workspace, size_t ws_bytes) {
     ACQ_HIP(hipEventCreateWithFlags(&p->desc_ev, hipEventDisableTiming));
 
     const std::vector<float> rootsM = acq::unit_roots(g.M);
-    const std::vector<float> rootsSub = acq::unit_roots(g.Msub);
+    const std::vector<float> rootsSub = acq::transform_roots(g.Msub);
     const std::vector<double> roots64 = acq::unit_roots64(g.M);
     const std::vector<float> wts = acq::phase_weights(g.M, c.samples_per_chip);
     hipStream_t st = p->stream;
