@@ -159,15 +159,20 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
         float sn0, cs0;
         sincospif(2.0f * float(cyc), &sn0, &cs0);
         const float2 e0 = make_float2(cs0, sn0);
+        // samples outside the block are zero: buffer loads bounded by the
+        // block's samples (a position before its start is a large unsigned
+        // offset), so that all 16 are in flight together
+        const int64_t first = base > 0 ? base : 0;
+        const int64_t left = n_in - first < kFrontN ? n_in - first : kFrontN;
+        const __amdgpu_buffer_rsrc_t ir = make_rsrc(iq + 2 * first, left > 0 ? uint32_t(left) * 4u : 0u);
+        uint32_t raw[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+            raw[m] = __builtin_amdgcn_raw_buffer_load_b32(ir, int(base - first + eng.in_index(m)) * 4, 0, 0);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
-            const int64_t p = base + eng.in_index(m);
-            float2 v = make_float2(0.f, 0.f);
-            if (p >= 0 && p < n_in) {
-                const float2 e = m ? cmul(e0, a.lo_step[m]) : e0;
-                v = cmul(make_float2(float(iq[2 * p]), float(iq[2 * p + 1])), e);
-            }
-            x[m] = v;
+            const float2 e = m ? cmul(e0, a.lo_step[m]) : e0;
+            x[m] = cmul(make_float2(float(int16_t(raw[m] & 0xffffu)), float(int16_t(raw[m] >> 16))), e);
         }
     }
     const __amdgpu_buffer_rsrc_t dummy = make_rsrc(a.roots, 8);   // unused by the Stockham engine
@@ -903,7 +908,6 @@ struct acq_fsk_plan_s {
     float2* d_rootsM = nullptr;
     float2* d_rootsSub = nullptr;
     float2* d_b1tab = nullptr;
-    double* d_zero = nullptr;           // [1] residual offset 0 for the forward transform
     BlockDesc* d_tdescs = nullptr;      // [T] templates as blocks of the forward transform
     int32_t* d_tcounts = nullptr;       // [2]
     unsigned long long* d_keys = nullptr;
@@ -952,7 +956,7 @@ void free_fsk(acq_fsk_plan_s* p) {
         for (hipEvent_t e : pair)
             if (e) (void)hipEventDestroy(e);
     void* dev[] = {p->d_G1, p->d_G0, p->d_rootsF, p->d_bits, p->d_bitcyc, p->d_tmpl, p->d_bank, p->d_d, p->d_u, p->d_zp, p->d_X, p->d_scratch, p->d_partial,
-                   p->d_rootsM, p->d_rootsSub, p->d_b1tab, p->d_zero, p->d_tdescs, p->d_tcounts, p->d_keys,
+                   p->d_rootsM, p->d_rootsSub, p->d_b1tab, p->d_tdescs, p->d_tcounts, p->d_keys,
                    p->d_dets, p->d_out, p->d_found, p->d_count};
     for (void* d : dev)
         if (d) (void)hipFree(d);
@@ -1009,7 +1013,7 @@ acq::FwdArgs fwd_args(acq_fsk_plan_s* p, const BlockTable& bt, float2* X, int64_
     fa.X = X;
     fa.Xh = nullptr;
     fa.exps = nullptr;
-    fa.cls_cyc = p->d_zero;
+    fa.cls_cyc = nullptr;            // no residual offsets
     fa.ncls = 1;
     fa.rootsM = p->d_rootsM;
     fa.rootsSub = p->d_rootsSub;
@@ -1049,7 +1053,6 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
     FSK_HIP(dalloc(&p->d_b1tab, b1.size() / 2));
-    FSK_HIP(dalloc(&p->d_zero, 1));
     FSK_HIP(dalloc(&p->d_tdescs, T));
     FSK_HIP(dalloc(&p->d_tcounts, 2));
     FSK_HIP(dalloc(&p->d_keys, items));
@@ -1079,7 +1082,6 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
             acc -= std::floor(acc);
         }
     }
-    const double zero = 0.0;
     FSK_HIP(hipMemcpyAsync(p->d_G1, G1.data(), G1.size() * sizeof(float), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_G0, G0.data(), G0.size() * sizeof(float), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_rootsF, rootsF.data(), rootsF.size() * sizeof(float), hipMemcpyHostToDevice, st));
@@ -1089,7 +1091,6 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(hipMemcpyAsync(p->d_b1tab, b1.data(), b1.size() * sizeof(float), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_bits, bits.data(), bits.size(), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_bitcyc, bitcyc.data(), bitcyc.size() * sizeof(double), hipMemcpyHostToDevice, st));
-    FSK_HIP(hipMemcpyAsync(p->d_zero, &zero, sizeof(double), hipMemcpyHostToDevice, st));
 
     // replica templates d^(c) (zero beyond n_t), then their spectra
     const int64_t tcount = int64_t(T * M);

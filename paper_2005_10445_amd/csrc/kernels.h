@@ -92,11 +92,12 @@ struct FwdArgs {
     const float2* rootsM;
     const float2* rootsSub;
     const float2* b1tab;
-    const double* cls_cyc;      // [ncls] residual offset of each class, cycles per sample
+    const double* cls_cyc;      // [ncls] residual offset of each class, cycles per sample (premix only)
     int64_t V;
     int64_t xstride;            // elements per slot (M when unpadded)
     int32_t xpad;               // wrap-around copies before and after each spectrum (0: none)
     int32_t spc, M, Msub, ncls;
+    int32_t premix;             // 1: some class has a residual offset (exact bins)
 };
 
 struct RefineArgs {

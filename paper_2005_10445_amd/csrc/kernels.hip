@@ -160,7 +160,9 @@ __global__ __launch_bounds__(kStatsThreads) void k_block_stats(BlockTable bt, co
 // 16 lanes (a permutation of [0, N)).
 __device__ __forceinline__ int out_swizzle(int i) { return i ^ (((i >> 4) + 4 * (i >> 10)) & 15); }
 
-template <class E>
+// PREMIX: exact bins, whose classes have residual offsets (a kernel of its own:
+// its phase reductions cost the other one registers).
+template <class E, bool PREMIX>
 __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
     __shared__ float2 lds[E::LDS];
     __shared__ float2 extra[E::EXTRA];
@@ -186,13 +188,19 @@ __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
         const int bi = a.blocks.block_of_segment(g);
         const BlockDesc d = a.blocks.get(bi);
         const int64_t base = int64_t(a.blocks.segment(g, d)) * a.V;
-        const double cyc = a.cls_cyc[c];          // residual offset of the class (exact bins)
+        const double cyc = PREMIX ? a.cls_cyc[c] : 0.0;          // residual offset of the class
+        // the segment's samples, zero past the block's end: buffer loads bounded
+        // by the samples left, so that all 16 are in flight together (a branch
+        // around each load waits for them one by one)
+        const int64_t left = d.n - base < a.M ? d.n - base : a.M;
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(d.x + base, uint32_t(left) * 8u);
         float2 v[16];
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const int64_t idx = base + int64_t(a.spc) * eng.in_index(m) + r;
-            v[m] = idx < d.n ? d.x[idx] : make_float2(0.f, 0.f);
-            if (cyc != 0.0) {                      // x * exp(-j 2 pi cyc idx), phase reduced in FP64
+        for (int m = 0; m < 16; ++m) v[m] = bload(xr, (a.spc * eng.in_index(m) + r) * 8, 0);
+        if (PREMIX && cyc != 0.0) {                // x * exp(-j 2 pi cyc idx), phase reduced in FP64
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                const int64_t idx = base + int64_t(a.spc) * eng.in_index(m) + r;
                 double ph = cyc * double(idx);
                 ph -= floor(ph);
                 float sn, cs;
@@ -594,7 +602,10 @@ hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st) {
 
 template <class E>
 static hipError_t fwd_e(const FwdArgs& a, int grid, hipStream_t st) {
-    hipLaunchKernelGGL((k_forward_sub<E>), dim3(grid), dim3(E::NT), 0, st, a);
+    if (a.premix)
+        hipLaunchKernelGGL((k_forward_sub<E, true>), dim3(grid), dim3(E::NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_forward_sub<E, false>), dim3(grid), dim3(E::NT), 0, st, a);
     return hipGetLastError();
 }
 

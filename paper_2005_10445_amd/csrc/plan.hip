@@ -370,6 +370,7 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     fa.exps = w.exps;
     fa.cls_cyc = p->d_cls_cyc;
     fa.ncls = g.ncls;
+    fa.premix = g.exact ? 1 : 0;
     fa.rootsM = p->d_rootsM;
     fa.rootsSub = p->d_rootsSub;
     fa.b1tab = p->d_b1tab;
