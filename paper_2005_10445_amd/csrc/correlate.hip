@@ -157,23 +157,6 @@ __device__ __forceinline__ float lane_powers(const float2 (&v)[16], float (&p)[1
     return bp;
 }
 
-// Largest value over the wave (uniform).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_fmax_step(float v) {
-    const int b = int(__float_as_uint(v));
-    return fmaxf(v, __uint_as_float(unsigned(__builtin_amdgcn_update_dpp(b, b, CTRL, ROW_MASK, 0xf, false))));
-}
-
-__device__ __forceinline__ float wave_fmax(float v) {
-    v = dpp_fmax_step<0x111, 0xf>(v);
-    v = dpp_fmax_step<0x112, 0xf>(v);
-    v = dpp_fmax_step<0x114, 0xf>(v);
-    v = dpp_fmax_step<0x118, 0xf>(v);
-    v = dpp_fmax_step<0x142, 0xa>(v);
-    v = dpp_fmax_step<0x143, 0xc>(v);
-    return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(__float_as_uint(v)), 63)));
-}
-
 // The wave's peak key and its count of threshold crossings, for a transform
 // with some power >= 0 (bp: each lane's largest, of the powers p).  The output
 // that holds the peak is looked for here and not tracked in the scan of every
@@ -190,14 +173,6 @@ __device__ __forceinline__ unsigned long long wave_peak(const float (&p)[16], fl
         const int off = E::out_off(E::visit(rr));
         if (!LOWER || off < E::HI_OFF) boff = p[E::visit(rr)] == wm ? off : boff;
     }
-    const unsigned idx = idx0 + unsigned(boff) * kstep;
-    unsigned long long m = __builtin_amdgcn_ballot_w64(bp == wm);
-    unsigned best = ~0u;
-    while (m) {                              // ties go to the smaller index (uniform loop, nearly always one lane)
-        const unsigned i = unsigned(__builtin_amdgcn_readlane(int(idx), __builtin_ctzll(m)));
-        best = i < best ? i : best;
-        m &= m - 1;
-    }
     unsigned lc = 0;
     if (wm >= pth) {                         // uniform
 #pragma unroll
@@ -205,14 +180,13 @@ __device__ __forceinline__ unsigned long long wave_peak(const float (&p)[16], fl
         lc = wave_sum_u32(lc);
     }
     *count = lc;
-    return (static_cast<unsigned long long>(__float_as_uint(wm)) << 32) | static_cast<unsigned long long>(~best);
+    return wave_key(bp, wm, idx0 + unsigned(boff) * kstep);
 }
 
 // The power below which a transform changes nothing: the smaller of the best
 // one recorded so far under `key` and the threshold.
 __device__ __forceinline__ float gate_power(const unsigned long long* key, float pth) {
-    const unsigned long long k = __hip_atomic_load(key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return fminf(__uint_as_float(unsigned(k >> 32)), pth);
+    return fminf(key_value(key), pth);
 }
 
 // One work item: (tile of tags, global segment g, bin k, phase rho), item index
@@ -288,7 +262,7 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
         // products with the replica in the transform's first butterflies
 #pragma unroll
         for (int m = 0; m < 8; ++m) bflyc(cmul(G[m], v[m]), G[m + 8], v[m + 8], v[m], v[m + 8]);
-        eng.template transform_rest<+1>(v, lds, b1, extra, hi);
+        eng.template transform_rest<+1>(v, lds, b1, extra, hi, [] {});
         // per-register indices and masks are the same for every tag: keep the
         // optimiser from holding all of them across the loop (recomputing is cheap)
         int ob = ob0;
@@ -397,7 +371,7 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
         first_step<E, PREC>(a, eng, g, k, rho, gscale, v);
 #pragma unroll
         for (int m = 0; m < 8; ++m) bflyc(cmul(v[m], bk[m]), v[m + 8], bk[m + 8], v[m], v[m + 8]);
-        eng.template transform_rest<+1>(v, lds, b1, extra, hi);
+        eng.template transform_rest<+1>(v, lds, b1, extra, hi, [] {});
         int ob = ob0;
         unsigned idx0 = unsigned((seg0 + rho) * a.K + k) + unsigned(ob0) * kstep;
         asm volatile("" : "+v"(ob), "+v"(idx0));

@@ -46,30 +46,41 @@ __device__ __forceinline__ double wave_sum(double v) {
     return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
 }
 
-// One step of a wave maximum: each lane takes the larger of its value and the
-// value DPP control CTRL routes to it (lanes with no source, or in rows outside
-// ROW_MASK, see 0).
+// Largest value over the wave (uniform, no LDS): the steps of wave_sum.
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ unsigned long long dpp_max_step(unsigned long long v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, int(unsigned(v)), CTRL, ROW_MASK, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, int(unsigned(v >> 32)), CTRL, ROW_MASK, 0xf, true);
-    const unsigned long long t = (static_cast<unsigned long long>(unsigned(hi)) << 32) | unsigned(lo);
-    return t > v ? t : v;
+__device__ __forceinline__ float dpp_fmax_step(float v) {
+    const int b = int(__float_as_uint(v));
+    return fmaxf(v, __uint_as_float(unsigned(__builtin_amdgcn_update_dpp(b, b, CTRL, ROW_MASK, 0xf, false))));
 }
 
-// Maximum over the wave (uniform result, no LDS): row_shr 1, 2, 4, 8 leave each
-// 16-lane row's maximum in its lane 15; row_bcast 15 (into rows 1 and 3) and
-// row_bcast 31 (into rows 2 and 3) carry the total to lane 63.
-__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
-    v = dpp_max_step<0x111, 0xf>(v);
-    v = dpp_max_step<0x112, 0xf>(v);
-    v = dpp_max_step<0x114, 0xf>(v);
-    v = dpp_max_step<0x118, 0xf>(v);
-    v = dpp_max_step<0x142, 0xa>(v);
-    v = dpp_max_step<0x143, 0xc>(v);
-    const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(unsigned(v)), 63));
-    const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(unsigned(v >> 32)), 63));
-    return (static_cast<unsigned long long>(hi) << 32) | lo;
+__device__ __forceinline__ float wave_fmax(float v) {
+    v = dpp_fmax_step<0x111, 0xf>(v);
+    v = dpp_fmax_step<0x112, 0xf>(v);
+    v = dpp_fmax_step<0x114, 0xf>(v);
+    v = dpp_fmax_step<0x118, 0xf>(v);
+    v = dpp_fmax_step<0x142, 0xa>(v);
+    v = dpp_fmax_step<0x143, 0xc>(v);
+    return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(__float_as_uint(v)), 63)));
+}
+
+// Peak key of the lanes whose largest value bp is the wave's, wm >= 0: the
+// smallest index idx among them (a uniform loop, nearly always over one lane).
+__device__ __forceinline__ unsigned long long wave_key(float bp, float wm, unsigned idx) {
+    unsigned long long m = __builtin_amdgcn_ballot_w64(bp == wm);
+    unsigned best = ~0u;
+    while (m) {
+        const unsigned i = unsigned(__builtin_amdgcn_readlane(int(idx), __builtin_ctzll(m)));
+        best = i < best ? i : best;
+        m &= m - 1;
+    }
+    return (static_cast<unsigned long long>(__float_as_uint(wm)) << 32) | static_cast<unsigned long long>(~best);
+}
+
+// The value held by a peak key.  Keys only grow during a launch, so one read
+// early (past the L1 and this XCD's view) is a lower bound.
+__device__ __forceinline__ float key_value(const unsigned long long* key) {
+    const unsigned long long k = __hip_atomic_load(key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __uint_as_float(unsigned(k >> 32));
 }
 
 // ------------------------------------------------------------------ transform engines
@@ -118,19 +129,45 @@ struct StockhamEngine {
         else
             F::template transform<S>(v, lds, tw, tq);
     }
-    template <int S>
+    template <int S, class Mid>
     __device__ __forceinline__ void transform_rest(float2 (&v)[16], float2* lds, __amdgpu_buffer_rsrc_t, const float2*,
-                                                   bool = true) const {
+                                                   bool, Mid mid) const {
         static_assert(IN, "the products before the DFTs have no separate first butterflies");
         int tq = t;
         asm volatile("" : "+v"(tq));
+        mid();
         F::template transform_in<S, true>(v, lds, tw, tq);
     }
 };
 
 using dev::bload;
+using dev::dft16_first;
 using dev::Fft14;
 using dev::make_rsrc;
+
+// LDS position of transform output i for the natural-order staging: bits 0-3
+// XOR-ed with a function of bits 4-7 and 10-11, so that both the engine-order
+// writes and the lane-consecutive reads hit 16 distinct 8-byte banks per
+// 16 lanes (a permutation of [0, N)).
+__device__ __forceinline__ int out_swizzle(int i) { return i ^ (((i >> 4) + 4 * (i >> 10)) & 15); }
+
+// Store a transform's outputs in natural order to F[0 .. N): they leave in the
+// engine's order, so they are put in order in LDS and whole lines stored.  Ends
+// with a barrier (LDS is free again).
+template <class E>
+__device__ __forceinline__ void store_natural(const E& eng, const float2 (&v)[16], float2* lds, float2* F) {
+    const int ob = eng.out_base();
+    __syncthreads();                 // every wave is done with the transform's LDS
+#pragma unroll
+    for (int m = 0; m < 16; ++m) lds[out_swizzle(ob + E::out_off(m))] = v[m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+        const int i = eng.in_index(m);
+        F[i] = lds[out_swizzle(i)];
+    }
+    __syncthreads();
+}
 
 }  // namespace kdev
 }  // namespace acq

@@ -109,14 +109,16 @@ struct Fft14 {
     __device__ __forceinline__ void transform(float2 (&v)[16], float2* lds, __amdgpu_buffer_rsrc_t b1tab,
                                               const float2* extra, bool hi = true) const {
         dft16_first(v);
-        transform_rest<S>(v, lds, b1tab, extra, hi);
+        transform_rest<S>(v, lds, b1tab, extra, hi, [] {});
     }
 
     // The transform after its first butterflies: v[n] and v[n + 8], n < 8, hold
-    // the sum and the difference of inputs n and n + 8.
-    template <int S>
+    // the sum and the difference of inputs n and n + 8.  mid() runs after the
+    // transform's last global load is issued: loads it issues (the next input)
+    // are not waited for by the transform.
+    template <int S, class Mid>
     __device__ __forceinline__ void transform_rest(float2 (&v)[16], float2* lds, __amdgpu_buffer_rsrc_t b1tab,
-                                                   const float2* extra, bool hi = true) const {
+                                                   const float2* extra, bool hi, Mid mid) const {
         int ln = l;
         asm volatile("" : "+v"(ln));            // recompute lane addressing per call
         // A
@@ -166,6 +168,7 @@ struct Fft14 {
         }
 #pragma unroll
         for (int m = PRE; m < 16; ++m) tb[m] = bload(b1tab, tboff, m * 512);
+        mid();
         wave_lds_order();
         const int k2 = ln >> 2, q = ln & 3;
         float2* row = sl + k2 * ROW;

@@ -8,28 +8,31 @@
 //                     with the spectra of h_BP * h_1 and h_BP * h_0, two inverse
 //                     transforms, demodulation d = (|f1|-|f0|)/(|f1|+|f0|),
 //                     u = |f1|-|f0|.  Output d and u (block) or d (replica).
-//   k_fsk_pack      : overlap-save segments 2s and 2s+1 of the call (numbered
+//   k_fsk_forward   : overlap-save segments 2s and 2s+1 of the call (numbered
 //                     over its blocks) as the real and imaginary parts of one
-//                     complex M-point input (slot s)
-//   (forward spectra of the slots and of the templates: launch_forward, the
+//                     complex M-point input (slot s), its P = M / Msub decimated
+//                     Msub-point transforms, one a workgroup
+//   (their combination, and the forward spectra of the templates: the
 //    decimation-in-time transform of the acquisition path)
-//   k_fsk_correlate : the real cross-correlation of d with each template by
-//                     overlap-save.  The template d^(c) is real, so the inverse
-//                     transform of Z_g conj(D^(c)) / M holds the correlation of
-//                     segment 2g in its real part and of segment 2g+1 in its
-//                     imaginary part: one complex transform per two segments.
-//                     Two tracking segments with different templates share
-//                     a slot too: with Z the slot's spectrum, X_A = (Z[i] +
-//                     conj Z[-i]) / 2 and j X_B = (Z[i] - conj Z[-i]) / 2,
-//                     so the product is (Z[i] (B_a + B_b) + conj Z[-i]
-//                     (B_a - B_b)) / 2 for the conjugate spectra B of the two
-//                     templates.  The peak search uses |c|.  An M-point inverse
-//                     transform (M up to 2^18) runs as P = M / Msub phases of
-//                     an Msub-point transform: for output lag tau = P u + rho,
+//   k_fsk_first, k_fsk_first_track, k_fsk_phase : the real cross-correlation of
+//                     d with each template by overlap-save.  The template d^(c)
+//                     is real, so the inverse transform of Z_g conj(D^(c)) / M
+//                     holds the correlation of segment 2g in its real part and of
+//                     segment 2g+1 in its imaginary part: one complex transform
+//                     per two segments.  Two tracking segments with different
+//                     templates share a slot too: with Z the slot's spectrum,
+//                     X_A = (Z[i] + conj Z[-i]) / 2 and j X_B = (Z[i] -
+//                     conj Z[-i]) / 2, so the product is (Z[i] (B_a + B_b) +
+//                     conj Z[-i] (B_a - B_b)) / 2 for the conjugate spectra B of
+//                     the two templates.  The peak search uses |c|.  An M-point
+//                     inverse transform (M up to 2^18) runs as P = M / Msub
+//                     phases of an Msub-point transform: for output lag tau =
+//                     P u + rho,
 //                       G_rho[i'] = exp(+j 2 pi i' rho / M)
 //                                   sum_a Y[i' + Msub a] exp(+j 2 pi a rho / P),
-//                     Y the spectrum product, then an Msub-point inverse
-//                     transform of G_rho.  Keys: bits(|Re c|) << 32 | ~tau.
+//                     Y the spectrum product (first step, k_fsk_first*), then an
+//                     Msub-point inverse transform of G_rho (k_fsk_phase).
+//                     Keys: bits(|Re c|) << 32 | ~tau.
 //   k_fsk_refine_*  : FP64 sums over +/-3 lags of the peak from the stored d,
 //                     u and template (in parts, added in order), re-maximisation,
 //                     parabola, w_c, q, p_c, z.
@@ -55,8 +58,14 @@ namespace {
 
 constexpr int kFrontLog = 12;                 // composed filters applied on 4096-point segments
 constexpr int kFrontN = 1 << kFrontLog;
-constexpr int kFskMaxGrid = 256;              // workgroups (and scratch slots) of the correlation: one per CU
-constexpr int kFskSplitMaxGrid = 2048;        // workgroups of the one-phase-per-workgroup form (no scratch)
+constexpr int kFskPhaseGrid = 256;            // workgroups of the phase transforms: one per CU
+// First-step outputs held at a time (complex values, 512 MiB): a search of more
+// (template, slot) items runs through them in groups.  Groups small enough for
+// the 256 MiB memory-side cache did not pay: a launch of the phase transforms
+// costs 15 us before its first transform ends (128 MiB groups: 315 us for the
+// 100 ms window's 256 items, 512 MiB: 305 us).
+constexpr int64_t kFskGroup = int64_t(1) << 26;
+constexpr int kFskPerBlock = 4;               // templates per workgroup of the first step
 
 // One block of an FSK call: the searching window (tag -1: every template) or
 // one tracking task (its tag only).  Front-end segments and correlation
@@ -73,19 +82,29 @@ struct FskTask {
     int32_t nseg;               // overlap-save segments of the correlation
 };
 
+// One correlation segment of a call: slot s holds units 2s and 2s+1.
+struct FskUnit {
+    int64_t z0;                 // first sample of the segment in the plan's d
+    int32_t left;               // samples from there to the end of its block (at most M)
+    int32_t vlim;               // valid lags (0: an absent second unit)
+    uint32_t lag0;              // lag of its first output
+    int32_t tag;                // tracking: the template
+    int32_t key;                // tracking: result index
+    int32_t reserved;
+};
+
 struct FskTasks {
     const FskTask* t;           // device [count]
     int32_t count;
     int32_t track;              // 1: tracking tasks (one template each)
 };
 
-// block holding global index g of the field (fseg0 or unit0), by binary search
-template <int32_t FskTask::*FIRST>
+// block holding global front-end segment g, by binary search
 __device__ __forceinline__ int fsk_task_of(const FskTasks& tt, int g) {
     int lo = 0, hi = tt.count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (tt.t[mid].*FIRST <= g) lo = mid; else hi = mid - 1;
+        if (tt.t[mid].fseg0 <= g) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -124,7 +143,7 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
         s = int(blockIdx.x) % a.nseg;
         tag = int(blockIdx.x) / a.nseg;
     } else {
-        const int b = fsk_task_of<&FskTask::fseg0>(a.tasks, int(blockIdx.x));
+        const int b = fsk_task_of(a.tasks, int(blockIdx.x));
         const FskTask tk = a.tasks.t[b];
         s = int(blockIdx.x) - tk.fseg0;
         iq = tk.iq;
@@ -205,33 +224,41 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
     }
 }
 
-// zp[s][i] = (d_A[jA V + i], d_B[jB V + i]) for the correlation segments 2s
-// (segment jA of block A) and 2s+1 (segment jB of block B; zero if the call
-// has no such segment), zero past the end of a block.  256 threads per
-// workgroup, each workgroup CHUNK (or M) consecutive i of one slot: the slot,
-// and so the block lookups, are uniform over the workgroup and done once.
-// Chunks of 4096 when that still gives 512 workgroups, else 1024 (a
-// searching window's two slots in 512 workgroups: 7.9 -> 5.6 us; the 32
-// slots of 64 tracking tasks keep 4096: with 1024, 23 us against 16).
-template <int CHUNK>
-__global__ __launch_bounds__(256) void k_fsk_pack(FskTasks tt, const float* __restrict__ d, int64_t V, int64_t M,
-                                                  int units, float2* __restrict__ zp) {
-    const int64_t chunk = M < CHUNK ? M : CHUNK;
-    const int64_t per_slot = M / chunk;
-    const int64_t s = int64_t(blockIdx.x) / per_slot;
-    const int ua = int(2 * s), ub = int(2 * s + 1);
-    const FskTask ta = tt.t[fsk_task_of<&FskTask::unit0>(tt, ua)];
-    const bool second = ub < units;
-    const FskTask tb = second ? tt.t[fsk_task_of<&FskTask::unit0>(tt, ub)] : ta;
-    const float* da = d + ta.zoff;
-    const float* dbb = d + tb.zoff;
-    const int64_t sa = int64_t(ua - ta.unit0) * V, sb = int64_t(ub - tb.unit0) * V;
-    const int64_t i0 = (int64_t(blockIdx.x) - s * per_slot) * chunk;
-    for (int64_t i = i0 + threadIdx.x; i < i0 + chunk; i += 256) {
-        const float re = sa + i < ta.n ? da[sa + i] : 0.f;
-        const float im = (second && sb + i < tb.n) ? dbb[sb + i] : 0.f;
-        zp[s * M + i] = make_float2(re, im);
+// Decimated transforms of the call's slots: work item (slot s, phase r) is the
+// Msub-point DFT of the values at i = P n + r of the slot's input, the two
+// segments' samples of d as real and imaginary parts (zero past their blocks),
+// written to X[s][r Msub + .].  The P items of a slot read interleaved samples
+// of one range and are placed on one XCD, as in the acquisition path's forward
+// transform.  The samples come straight from d: a packed copy in between cost
+// 17 us of its own for 64 blocks of 96,000 samples.
+template <class E>
+__global__ __launch_bounds__(E::NT, 4) void k_fsk_forward(const FskUnit* __restrict__ units, const float* __restrict__ d,
+                                                          int P, int M, int items, const float2* __restrict__ rootsSub,
+                                                          const float2* __restrict__ b1tab, float2* __restrict__ X) {
+    __shared__ float2 lds[E::LDS];
+    __shared__ float2 extra[E::EXTRA];
+    E eng;
+    eng.init(rootsSub, extra);
+    const __amdgpu_buffer_rsrc_t b1 = make_rsrc(b1tab, E::B1_TABLE * 8);
+    const int grp = kXcds * P, b = int(blockIdx.x);
+    int it = b;
+    if (b < items / grp * grp) {
+        const int q = b / grp, j = b - q * grp;
+        it = (q * kXcds + j % kXcds) * P + j / kXcds;
     }
+    const int s = it / P, r = it - s * P;
+    const FskUnit ua = units[2 * s], ub = units[2 * s + 1];
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(d + ua.z0, uint32_t(ua.left) * 4u);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(d + ub.z0, uint32_t(ub.left) * 4u);
+    float2 v[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+        const int off = (P * eng.in_index(m) + r) * 4;
+        v[m].x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, off, 0, 0));
+        v[m].y = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, off, 0, 0));
+    }
+    eng.template transform<-1>(v, lds, b1, extra);
+    store_natural(eng, v, lds, X + size_t(s) * size_t(M) + size_t(r) * size_t(E::N));
 }
 
 // bank[t][i] = conj(X_t[i]) / M in place
@@ -249,278 +276,269 @@ __global__ void k_fsk_fill(float2* p, int64_t count) {
 }
 
 struct FskCorrArgs {
-    const float2* X;            // [slots][M] spectra of the packed segment pairs
+    float2* X;                  // [slots][M] spectra of the packed segment pairs (tracking with P > 1: the
+                                // decimated transforms, not yet combined)
     const float2* bank;         // [T][M] conj(DFT_M(d^(c))) / M
     const float2* rootsM;       // [M]
     const float2* rootsSub;     // [Msub], then the pass twiddles
     const float2* b1tab;
-    float2* scratch;            // [gridDim.x][M]: the P first-step outputs of the workgroup's item
+    float2* G;                  // [items of the launch][P][Msub] first-step outputs (P > 1)
     unsigned long long* keys;   // [T] (searching) or [tasks] (tracking)
     float* dump;                // optional [T][lags]: c at every lag (test hook, searching)
-    FskTasks tasks;
-    int64_t V;
-    int32_t M, Msub, P, T, nslots;      // nslots: slots of the call
-    int32_t units;                      // correlation segments of the call
-    int32_t split;                      // 1: one phase per work item (set by the launcher)
+    const FskUnit* units;       // device [2 slots]
+    int64_t lags;               // lags of the searched block (dump)
+    int32_t M, Msub, P, track;
+    int32_t t0, nt, s0, ns;     // the launch's templates (searching) and slots; item i: template t0 + i / ns,
+                                // slot s0 + i % ns; tracking: slot s0 + i
 };
 
-// Work item (template t, slot s), taken with a stride of the grid: searching,
-// items t * nslots + s for every template; tracking, item s with the
-// templates of its segments' tasks.  Slot s holds correlation segments 2s
-// (real part) and 2s+1 (imaginary part).
-//   first step, once per item: for each i' < Msub, the spectrum products
-//     Y_a = Z_s[i' + Msub a] B_t[i' + Msub a], a < P, B_t = conj(D_t) / M (or
-//     the two-template product when the segments' templates differ), and
-//     G_rho[i'] = exp(+j 2 pi i' rho / M) sum_a Y_a exp(+j 2 pi a rho / P),
-//     written to the workgroup's scratch (each input read once);
-//   then, per phase rho, the Msub-point inverse transform of G_rho (lag
-//   P u + rho) and each segment's lane maximum of |c| over all phases.
-// SPLIT (calls with fewer items than CUs, e.g. a few tracking tasks): work
-// item (item, rho) forms its G_rho in registers from the P products, reading
-// the spectra once per phase instead of going through the scratch.
-// exp(+j 2 pi k / 8), k < 8 (the values FP64 rounds to in FP32)
-__device__ __forceinline__ float2 root8(int k) {
-    constexpr float h = 0.70710678118654752f;
-    switch (k) {
-        case 0: return make_float2(1.f, 0.f);
-        case 1: return make_float2(h, h);
-        case 2: return make_float2(0.f, 1.f);
-        case 3: return make_float2(-h, h);
-        case 4: return make_float2(-1.f, 0.f);
-        case 5: return make_float2(-h, -h);
-        case 6: return make_float2(0.f, -1.f);
-        default: return make_float2(h, -h);
+// w[r] = w1^r, r < P (w[0] unset)
+template <int P>
+__device__ __forceinline__ void phase_powers(float2 w1, float2 (&w)[P]) {
+    w[1] = w1;
+#pragma unroll
+    for (int r = 2; r < P; ++r) w[r] = cmul(w[r - 1], w1);
+}
+
+// P-point DFT, P a power of two
+template <int P, int S>
+__device__ __forceinline__ void dft_p(float2 (&y)[P]) {
+#pragma unroll
+    for (int r = 0; r < P / 2; ++r) dev::dft2<S>(y[r], y[r + P / 2]);
+    dev::dft_rest<P, S>(y);
+}
+
+// First step of a search, P > 1: for input index i' of a pair of slots, with
+// every template of the workgroup, the P products Y_a = Z[i' + Msub a]
+// B[i' + Msub a] and G_rho[i'] = exp(+j 2 pi i' rho / M) sum_a Y_a
+// exp(+j 2 pi a rho / P).  It streams the bank in (once for the two slots) and
+// G out and is bound by that, so it is a kernel of its own with many more loads
+// in flight than the one workgroup of a 2^14-point transform that a CU holds.
+// 128 templates, 800,000 samples, M = 2^18: 386 us for both steps in one kernel,
+// 305 us so (this one 145 us at 5.6 TB/s).
+// (Reading half the bank, each thread taking i' and Msub - i', needs 256
+// registers and was slower.)
+template <int P>
+__global__ __launch_bounds__(256, 2) void k_fsk_first(FskCorrArgs a) {
+    const int nib = a.Msub / 256, npair = (a.ns + 1) / 2;
+    int rem = int(blockIdx.x);
+    const int ip = (rem % nib) * 256 + int(threadIdx.x);
+    rem /= nib;
+    const int sl = 2 * (rem % npair), ta = (rem / npair) * kFskPerBlock, tb = min(a.nt, ta + kFskPerBlock);
+    const bool two = sl + 1 < a.ns;                     // uniform
+    const float2* X = a.X + size_t(a.s0 + sl) * size_t(a.M) + ip;
+    const size_t second = two ? size_t(a.M) : 0;
+    float2 z[2][P], w[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        z[0][q] = X[q * a.Msub];
+        z[1][q] = X[second + q * a.Msub];
+    }
+    phase_powers<P>(a.rootsM[ip], w);
+    for (int t = ta; t < tb; ++t) {
+        const float2* B = a.bank + size_t(a.t0 + t) * size_t(a.M) + ip;
+        float2* G = a.G + (size_t(t) * size_t(a.ns) + size_t(sl)) * size_t(a.M) + ip;
+        float2 b[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) b[q] = B[q * a.Msub];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (h && !two) break;
+            float2 y[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) y[q] = cmul(z[h][q], b[q]);
+            dft_p<P, +1>(y);
+            G[h * a.M] = y[0];
+#pragma unroll
+            for (int r = 1; r < P; ++r) G[h * a.M + r * a.Msub] = cmul(y[r], w[r]);
+        }
     }
 }
 
-// exp(+j 2 pi k / 8) for a run-time k (selects, no table)
-__device__ __forceinline__ float2 root8_rt(int k) {
-    constexpr float h = 0.70710678118654752f;
-    auto c = [](int kk) {                    // cos(pi kk / 4), kk < 8
-        const float mag = (kk & 1) ? h : ((kk & 2) ? 0.0f : 1.0f);
-        return (kk >= 3 && kk <= 5) ? -mag : mag;
+// First step of tracking slots, P > 1: combines the slot's decimated transforms
+// at i' (and at -i' for two templates) in the same pass, as each slot has one
+// item only.
+template <int P>
+__global__ __launch_bounds__(256, 2) void k_fsk_first_track(FskCorrArgs a) {
+    const int nib = a.Msub / 256;
+    const int ip = (int(blockIdx.x) % nib) * 256 + int(threadIdx.x);
+    const int sl = int(blockIdx.x) / nib;
+    const int tga = a.units[2 * (a.s0 + sl)].tag, tgb = a.units[2 * (a.s0 + sl) + 1].tag;
+    const float2* F = a.X + size_t(a.s0 + sl) * size_t(a.M);
+    const float2* Ba = a.bank + size_t(tga) * size_t(a.M) + ip;
+    const float2* Bb = a.bank + size_t(tgb) * size_t(a.M) + ip;
+    // Z[i + Msub q], q < P, from the decimated transforms F_r[i]
+    auto combine = [&](int i, const float2 (&w)[P], float2 (&z)[P]) {
+#pragma unroll
+        for (int r = 0; r < P; ++r) z[r] = F[r * a.Msub + i];
+#pragma unroll
+        for (int r = 1; r < P; ++r) z[r] = cmulc(z[r], w[r]);
+        dft_p<P, -1>(z);
     };
-    return make_float2(c(k & 7), c((k + 6) & 7));
+    float2 w[P], z[P], y[P];
+    phase_powers<P>(a.rootsM[ip], w);
+    combine(ip, w, z);
+    if (tga == tgb) {                                   // uniform
+#pragma unroll
+        for (int q = 0; q < P; ++q) y[q] = cmul(z[q], Ba[q * a.Msub]);
+    } else {
+        // conj Z[-i] for i = i' + Msub q: element P - 1 - q of Msub - i' (element -q of 0 for i' = 0)
+        const int im = (a.Msub - ip) & (a.Msub - 1);
+        float2 wm[P], zm[P];
+        phase_powers<P>(a.rootsM[im], wm);
+        combine(im, wm, zm);
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const float2 ba = Ba[q * a.Msub], bb = Bb[q * a.Msub];
+            const float2 m0 = zm[(P - q) % P], m1 = zm[P - 1 - q];
+            const float2 m = make_float2(ip ? m1.x : m0.x, ip ? -m1.y : -m0.y);
+            const float2 r = cadd(cmul(z[q], cadd(ba, bb)), cmul(m, dev::csub(ba, bb)));
+            y[q] = make_float2(0.5f * r.x, 0.5f * r.y);
+        }
+    }
+    dft_p<P, +1>(y);
+    float2* G = a.G + size_t(sl) * size_t(a.M) + ip;
+    G[0] = y[0];
+#pragma unroll
+    for (int r = 1; r < P; ++r) G[r * a.Msub] = cmul(y[r], w[r]);
 }
 
-// TRACK: tracking calls, whose slots may hold segments of two templates.
-template <class E, int PP, bool DUMP, bool SPLIT, bool TRACK>
-__global__ __launch_bounds__(E::NT) void k_fsk_correlate(FskCorrArgs a) {
-    constexpr int NW = E::NT / 64;
+// Largest |c| of a segment over the wave's outputs against the workgroup's key
+// so far (LDS): c = the real (H = 0) or imaginary part of v.  A wave that stays
+// below the key forms none, and most do: those that come late see what the
+// earlier ones reached.
+template <class E, int H>
+__device__ __forceinline__ void fsk_segment_peak(const float2 (&v)[16], int omin, int omax, int ob, int ulim, unsigned lag0,
+                                                 unsigned step, unsigned long long* best) {
+    int lim = ulim - ob;                              // this lane's outputs below this offset are valid lags
+    asm volatile("" : "+v"(lim));
+    float bp = -1.0f;
+    auto mag = [&](int r) { return fabsf(H ? v[r].y : v[r].x); };
+    // four registers at a time, in increasing offset: wave-uniform branches for
+    // groups without a valid output and for groups without an invalid one
+#pragma unroll
+    for (int g = 0; g < 16; g += 4) {
+        if (omin + E::out_off(E::visit(g)) >= ulim) break;
+        if (omax + E::out_off(E::visit(g + 3)) < ulim) {
+            asm volatile("" : "+v"(bp));              // (kept a branch: three instructions)
+            bp = fmaxf(fmaxf(bp, mag(E::visit(g))), mag(E::visit(g + 1)));
+            bp = fmaxf(fmaxf(bp, mag(E::visit(g + 2))), mag(E::visit(g + 3)));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int r = E::visit(g + k);
+                bp = fmaxf(bp, E::out_off(r) < lim ? mag(r) : -1.0f);
+            }
+        }
+    }
+    const unsigned long long sofar = __hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_amdgcn_ballot_w64(bp >= __uint_as_float(unsigned(sofar >> 32)))) {
+        const float wm = wave_fmax(bp);
+        int boff = 0;                                 // smallest offset that holds wm
+#pragma unroll
+        for (int rr = 15; rr >= 0; --rr) {
+            const int r = E::visit(rr), off = E::out_off(r);
+            boff = off < lim && fabsf(H ? v[r].y : v[r].x) == wm ? off : boff;
+        }
+        const unsigned long long k = wave_key(bp, wm, lag0 + unsigned(ob + boff) * step);
+        if ((threadIdx.x & 63) == 0) atomicMax(best, k);
+    }
+}
+
+// Phase transforms: work item (item, rho), the Msub-point inverse transform of
+// G_rho of the item (P = 1: of the spectrum product, formed here), whose output
+// u is lag P u + rho of the slot's two segments.  One workgroup per CU (the
+// transform's LDS) runs through a contiguous range of work items, loading the
+// next one's input during the transform and keeping the largest key in LDS
+// until the result it belongs to changes: an atomic of every work item on its
+// template's key was waited for, 14.5 us a work item against 8.
+template <class E, int P, bool DUMP>
+__global__ __launch_bounds__(E::NT, 4) void k_fsk_phase(FskCorrArgs a) {
     __shared__ float2 lds[E::LDS];
     __shared__ float2 extra[E::EXTRA];
-    __shared__ unsigned long long red[2 * NW];
+    __shared__ unsigned long long best[2][2];         // [buffer][segment, when they have different results]
     E eng;
     eng.init(a.rootsSub, extra);
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
     const __amdgpu_buffer_rsrc_t b1 = make_rsrc(a.b1tab, E::B1_TABLE * 8);
-    const int mmask = a.M - 1;
-    float2* G = a.scratch + size_t(blockIdx.x) * size_t(a.M);
-    const int items = (a.tasks.track ? a.nslots : a.T * a.nslots) * (SPLIT ? PP : 1);
-    // SPLIT with one work item per workgroup: the PP phases of an item read
-    // the same spectra, so they run on one XCD (workgroups go to the XCDs in
-    // turn) and share its L2.  Within each group of kXcds * PP workgroups,
-    // workgroup j takes phase j / kXcds of item j % kXcds of the group.
-    constexpr int grp = kXcds * PP;
-    const bool xcd_map = SPLIT && int(gridDim.x) >= items;
-    // Searching without SPLIT (a grid of whole-XCD multiples): XCD x takes the
-    // templates x, x + kXcds, ..., and its workgroups take the slots of one
-    // template side by side, so that template's spectrum is read once into
-    // the XCD's L2 instead of once per slot on different XCDs.
-    const bool tmap = !SPLIT && !TRACK && int(gridDim.x) % kXcds == 0;
-    const int xg = int(blockIdx.x) % kXcds, nw = int(gridDim.x) / kXcds;
-    const int nloop = tmap ? ((a.T - xg + kXcds - 1) / kXcds) * a.nslots : items;
-    for (int ci = tmap ? int(blockIdx.x) / kXcds : int(blockIdx.x); ci < nloop;
-         ci += tmap ? nw : int(gridDim.x)) {
-        const int wi = tmap ? (xg + kXcds * (ci / a.nslots)) * a.nslots + ci % a.nslots : ci;
-        int it = SPLIT ? wi / PP : wi;
-        int rho0 = SPLIT ? wi % PP : 0;
-        if (xcd_map && wi < items / grp * grp) {
-            const int q = wi / grp, j = wi - q * grp;
-            it = q * kXcds + j % kXcds;
-            rho0 = j / kXcds;
-        }
-        const int rho1 = SPLIT ? rho0 + 1 : PP;
-        const int slot = a.tasks.track ? it : it % a.nslots;
-        // the slot's two correlation segments: block, segment within it, template, key
-        int bk[2], jseg[2], tg[2], kidx[2];
+    const int64_t items = int64_t(a.track ? a.ns : a.nt * a.ns) * P;
+    const int w0 = int(items * blockIdx.x / gridDim.x), w1 = int(items * (blockIdx.x + 1) / gridDim.x);
+    if (threadIdx.x < 4) best[threadIdx.x >> 1][threadIdx.x & 1] = 0ull;
+    const int voff = eng.in_index(0) * 8;
+    // input of work item wi, P > 1
+    auto fetch = [&](int wi, float2 (&x)[16]) {
+        const __amdgpu_buffer_rsrc_t gr = make_rsrc(a.G + size_t(wi) * size_t(E::N), uint32_t(E::N) * 8u);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int u = 2 * slot + h < a.units ? 2 * slot + h : 2 * slot;     // absent: as the first
-            bk[h] = fsk_task_of<&FskTask::unit0>(a.tasks, u);
-            jseg[h] = 2 * slot + h < a.units ? u - a.tasks.t[bk[h]].unit0 : -1;
-            tg[h] = a.tasks.track ? a.tasks.t[bk[h]].tag : it / a.nslots;
-            kidx[h] = a.tasks.track ? bk[h] : tg[h];
+        for (int m = 0; m < 16; ++m) x[m] = bload(gr, voff, m * E::NT * 8);
+    };
+    // write a buffer's keys and clear it (every wave is past its last update)
+    auto flush = [&](unsigned long long (&b)[2], int ka, int kb) {
+        if (threadIdx.x == 0) {
+            if (b[0]) atomicMax(&a.keys[ka], b[0]);
+            if (b[1]) atomicMax(&a.keys[kb], b[1]);
+            b[0] = b[1] = 0ull;
         }
-        const float2* Xj = a.X + size_t(slot) * size_t(a.M);
-        const float2* B = a.bank + size_t(tg[0]) * size_t(a.M);
-        const float2* Bb = a.bank + size_t(tg[1]) * size_t(a.M);
-        const bool two = TRACK && tg[1] != tg[0];              // uniform: tracking segments of two templates
-        // first step: P outputs per i' from P products; the P-point DFT uses
-        // constant eighth roots of unity, so each i' issues its 2P product
-        // loads and P-1 twiddle loads together (one i' at a time keeps them in
-        // registers without holding all 16)
-        // the P spectrum products of input index ip
-        auto products = [&](int ip, float2 (&y)[PP]) {
-            if (!two) {
+    };
+    float2 v[16];
+    if constexpr (P > 1) fetch(w0, v);                // the grid is at most the work items: w0 < w1
+    int ka = -1, kb = -1, par = 0;                    // results of the keys in best[par]
+    for (int wi = w0; wi < w1; ++wi) {
+        const int it = wi / P, rho = wi % P;
+        const int slot = a.s0 + (a.track ? it : it % a.ns);
+        const int t = a.track ? 0 : a.t0 + it / a.ns;
+        const FskUnit ua = a.units[2 * slot], ub = a.units[2 * slot + 1];
+        const int na = a.track ? ua.key : t, nb = a.track ? ub.key : t;
+        const int oa = ka, ob_ = kb;
+        const bool change = na != ka || nb != kb;     // uniform
+        if (change) {
+            ka = na;
+            kb = nb;
+            par ^= 1;
+        }
+        if constexpr (P == 1) {
+            const float2* Z = a.X + size_t(slot) * size_t(E::N);
+            const float2* Ba = a.bank + size_t(a.track ? ua.tag : t) * size_t(E::N);
+            const float2* Bb = a.bank + size_t(a.track ? ub.tag : t) * size_t(E::N);
+            if (Ba == Bb) {                           // uniform
 #pragma unroll
-                for (int q = 0; q < PP; ++q) y[q] = cmul(Xj[ip + q * a.Msub], B[ip + q * a.Msub]);
+                for (int m = 0; m < 16; ++m) v[m] = cmul(Z[eng.in_index(m)], Ba[eng.in_index(m)]);
             } else {
 #pragma unroll
-                for (int q = 0; q < PP; ++q) {
-                    const int i = ip + q * a.Msub;
-                    const float2 z = Xj[i], zm = Xj[(a.M - i) & mmask];
-                    const float2 ba = B[i], bb = Bb[i];
-                    const float2 s = cadd(ba, bb), d = make_float2(ba.x - bb.x, ba.y - bb.y);
-                    const float2 r = cadd(cmul(z, s), cmul(make_float2(zm.x, -zm.y), d));
-                    y[q] = make_float2(0.5f * r.x, 0.5f * r.y);
-                }
-            }
-        };
-        float2 gs[16];                            // SPLIT: G_rho0 of this thread's inputs
-        if constexpr (SPLIT) {
-            float2 w[PP];                         // exp(+j 2 pi q rho0 / P)
-#pragma unroll
-            for (int q = 0; q < PP; ++q) w[q] = root8_rt(q * rho0 * (8 / PP));
-#pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                // opaque index: its address arithmetic is not hoisted out of
-                // the item loop for all 16 registers at once
-                int ip = eng.in_index(m);
-                asm volatile("" : "+v"(ip));
-                float2 y[PP];
-                products(ip, y);
-                float2 acc = y[0];
-#pragma unroll
-                for (int q = 1; q < PP; ++q) acc = cadd(acc, cmul(y[q], w[q]));
-                gs[m] = rho0 ? cmul(acc, a.rootsM[(ip * rho0) & mmask]) : acc;
-                asm volatile("" ::: "memory");    // one input index at a time: no hoisting of later loads
-            }
-        } else {
-            // two input indices per pass (one for P = 16), so that their 4P
-            // loads are in flight together; the P-point DFT over q is a
-            // radix-P butterfly, and the twiddle of phase rho is the rho-th
-            // power of exp(+j 2 pi i' / M)
-            constexpr int IPP = PP > 8 ? 1 : 2;
-#pragma unroll 1
-            for (int m = 0; m < 16; m += IPP) {
-                float2 y[IPP][PP];
-                int ipv[IPP];
-#pragma unroll
-                for (int h = 0; h < IPP; ++h) {
-                    ipv[h] = eng.in_index(m + h);
-                    products(ipv[h], y[h]);
-                }
-#pragma unroll
-                for (int h = 0; h < IPP; ++h) {
-                    const int ip = ipv[h];
-                    if constexpr (PP > 1) dev::dft_r<PP, +1>(y[h]);
-                    G[ip] = y[h][0];
-                    if constexpr (PP > 1) {
-                        const float2 w1 = a.rootsM[ip];
-                        float2 tw = w1;
-#pragma unroll
-                        for (int rho = 1; rho < PP; ++rho) {
-                            G[rho * a.Msub + ip] = cmul(y[h][rho], tw);
-                            if (rho + 1 < PP) tw = cmul(tw, w1);
-                        }
-                    }
+                for (int m = 0; m < 16; ++m) {
+                    const int i = eng.in_index(m);
+                    const float2 zm = Z[(E::N - i) & (E::N - 1)], ba = Ba[i], bb = Bb[i];
+                    const float2 r = cadd(cmul(Z[i], cadd(ba, bb)), cmul(make_float2(zm.x, -zm.y), dev::csub(ba, bb)));
+                    v[m] = make_float2(0.5f * r.x, 0.5f * r.y);
                 }
             }
         }
-        if constexpr (!SPLIT) {
-            __threadfence_block();
-            __syncthreads();
-        }
-        int ulim[2];
-        int64_t sbeg[2];
-        unsigned long long best[2] = {0ull, 0ull};
-        int vlim[2];                                  // valid lags of each segment
+        const int ula = ua.vlim > rho ? (ua.vlim - rho + P - 1) / P : 0;
+        const int ulb = ub.vlim > rho ? (ub.vlim - rho + P - 1) / P : 0;
+        const int omin = eng.out_min();
+        const bool hi = omin + E::HI_OFF < max(ula, ulb);
+        float2 next[16];
+        dft16_first(v);
+        eng.template transform_rest<+1>(v, lds, b1, extra, hi, [&] {
+            if constexpr (P > 1) fetch(wi + 1 < w1 ? wi + 1 : wi, next);
+        });
+        if (change && oa >= 0) flush(best[par ^ 1], oa, ob_);
+        const int ob = eng.out_base();
+        if constexpr (DUMP) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t lags = a.tasks.t[bk[h]].lags;
-            sbeg[h] = int64_t(jseg[h]) * a.V;
-            vlim[h] = jseg[h] >= 0 ? int(lags - sbeg[h] < a.V ? lags - sbeg[h] : a.V) : 0;
-        }
-        for (int rho = rho0; rho < rho1; ++rho) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) ulim[h] = vlim[h] > rho ? (vlim[h] - rho + PP - 1) / PP : 0;
-            const int ob0 = eng.out_base();
-            const int omin = eng.out_min();
-            const bool hi = omin + E::HI_OFF < max(ulim[0], ulim[1]);
-            float2 v[16];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                if constexpr (SPLIT) v[m] = gs[m];
-                else v[m] = G[rho * a.Msub + eng.in_index(m)];
-            }
-            eng.template transform<+1>(v, lds, b1, extra, hi);
-            // output off of this lane is a valid lag of segment h when off < lim[h]
-            int lim[2] = {ulim[0] - ob0, ulim[1] - ob0};
-            asm volatile("" : "+v"(lim[0]), "+v"(lim[1]));
-            // this lane's largest |c| of the phase, in increasing lag (strict
-            // comparison: the smallest lag of a tie within the phase); one
-            // maximum per segment when tracking, else one over both segments
-            // (the first segment's lags come first)
-            constexpr int NR = TRACK ? 2 : 1;
-            float bp[NR];
-            int boff[NR], bh[NR];
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                bp[k] = -1.0f;
-                boff[k] = bh[k] = 0;
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int k = TRACK ? h : 0;
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    const int r = E::visit(rr);
-                    const int off = E::out_off(r);
-                    if (omin + off < ulim[h]) {
-                        const float cv = h ? v[r].y : v[r].x;
-                        const float pv = fabsf(cv);
-                        if constexpr (DUMP) {
-                            if (off < lim[h]) {
-                                const int64_t tau = sbeg[h] + int64_t(PP) * (ob0 + off) + rho;
-                                a.dump[size_t(tg[h]) * size_t(a.tasks.t[bk[h]].lags) + size_t(tau)] = cv;
-                            }
-                        }
-                        const bool take = pv > bp[k] && off < lim[h];
-                        boff[k] = take ? off : boff[k];
-                        bh[k] = take ? h : bh[k];
-                        bp[k] = take ? pv : bp[k];
-                    }
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                const unsigned lag = unsigned(sbeg[bh[k]] + rho) + unsigned(ob0 + boff[k]) * unsigned(PP);
-                const unsigned long long key = bp[k] >= 0.0f
-                    ? (static_cast<unsigned long long>(__float_as_uint(bp[k])) << 32) | static_cast<unsigned long long>(~lag)
-                    : 0ull;
-                best[k] = key > best[k] ? key : best[k];    // across phases the key order decides ties
+            for (int r = 0; r < 16; ++r) {
+                const int u = ob + E::out_off(r);
+                if (u < ula) a.dump[size_t(t) * size_t(a.lags) + size_t(ua.lag0) + size_t(P) * u + rho] = v[r].x;
+                if (u < ulb) a.dump[size_t(t) * size_t(a.lags) + size_t(ub.lag0) + size_t(P) * u + rho] = v[r].y;
             }
         }
-        // one key per result: the two segments' maxima combine when they
-        // belong to the same result (searching, or one tracking task)
-        const bool same = kidx[1] == kidx[0];
-        if (same) best[0] = best[1] > best[0] ? best[1] : best[0];
-        best[0] = wave_max(best[0]);
-        if (!same) best[1] = wave_max(best[1]);
-        if (lane == 0) {
-            red[wave] = best[0];
-            red[NW + wave] = best[1];
+        fsk_segment_peak<E, 0>(v, omin, eng.out_max(), ob, ula, ua.lag0 + unsigned(rho), unsigned(P), &best[par][0]);
+        fsk_segment_peak<E, 1>(v, omin, eng.out_max(), ob, ulb, ub.lag0 + unsigned(rho), unsigned(P), &best[par][na == nb ? 0 : 1]);
+        if constexpr (P > 1) {
+#pragma unroll
+            for (int m = 0; m < 16; ++m) v[m] = next[m];
         }
-        __syncthreads();
-        if (threadIdx.x < (same ? 1 : 2)) {
-            const int h = int(threadIdx.x);
-            unsigned long long m = 0ull;
-            for (int q = 0; q < NW; ++q) m = red[h * NW + q] > m ? red[h * NW + q] : m;
-            if (m) atomicMax(&a.keys[kidx[h]], m);
-        }
-        __syncthreads();                     // red[], scratch and LDS are reused by the next item
     }
+    __syncthreads();
+    flush(best[par], ka, kb);
 }
 
 // Results: searching, one item per template of the window; tracking, one item
@@ -731,43 +749,68 @@ __global__ __launch_bounds__(1024) void k_fsk_compact(const acq_fsk_detection* _
     if (t == 1023) *count = scan[t];
 }
 
-template <class E, int PP>
-void launch_fsk_corr_ep(const FskCorrArgs& a, int grid, hipStream_t st) {
-    const bool track = a.tasks.track != 0;
-    // one phase per work item (split) is built for P <= 8 (eighth roots of unity)
-    constexpr bool can_split = PP > 1 && PP <= 8;
-    if (a.dump)                                          // searching only
-        hipLaunchKernelGGL((k_fsk_correlate<E, PP, true, false, false>), dim3(grid), dim3(E::NT), 0, st, a);
-    else if (can_split && a.split && track)
-        hipLaunchKernelGGL((k_fsk_correlate<E, PP, false, can_split, true>), dim3(grid), dim3(E::NT), 0, st, a);
-    else if (can_split && a.split)
-        hipLaunchKernelGGL((k_fsk_correlate<E, PP, false, can_split, false>), dim3(grid), dim3(E::NT), 0, st, a);
-    else if (track)
-        hipLaunchKernelGGL((k_fsk_correlate<E, PP, false, false, true>), dim3(grid), dim3(E::NT), 0, st, a);
+template <class E, int P>
+void launch_fsk_ep(const FskCorrArgs& a, hipStream_t st) {
+    const int items = a.track ? a.ns : a.nt * a.ns;
+    if constexpr (P > 1) {
+        const unsigned nib = unsigned(a.Msub / 256);
+        if (a.track)
+            hipLaunchKernelGGL((k_fsk_first_track<P>), dim3(nib * unsigned(a.ns)), dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_fsk_first<P>),
+                               dim3(nib * unsigned((a.ns + 1) / 2) * unsigned((a.nt + kFskPerBlock - 1) / kFskPerBlock)), dim3(256),
+                               0, st, a);
+    }
+    // P = 1: as many workgroups as items (nothing to load ahead)
+    const dim3 grid(unsigned(P > 1 ? std::min(items * P, kFskPhaseGrid) : items));
+    if (a.dump)
+        hipLaunchKernelGGL((k_fsk_phase<E, P, true>), grid, dim3(E::NT), 0, st, a);
     else
-        hipLaunchKernelGGL((k_fsk_correlate<E, PP, false, false, false>), dim3(grid), dim3(E::NT), 0, st, a);
+        hipLaunchKernelGGL((k_fsk_phase<E, P, false>), grid, dim3(E::NT), 0, st, a);
 }
 
-// M <= 2^14 runs as one phase (P = 1) on the Stockham engine of that size;
-// larger M as P = M / 2^14 phases on the 2^14-point engine.
-hipError_t launch_fsk_correlate(const FskCorrArgs& a, int grid, int log2_sub, hipStream_t st) {
-    if (grid <= 0) return hipSuccess;
-    if ((log2_sub < 14 && a.P != 1) || (1 << log2_sub) != a.Msub) return hipErrorInvalidValue;
+// M <= 2^14 runs as one phase (P = 1) on the engine of that size; larger M as
+// P = M / 2^14 phases on the 2^14-point engine.
+hipError_t launch_fsk_correlate(const FskCorrArgs& a, int log2_sub, hipStream_t st) {
+    if (a.ns <= 0 || (!a.track && a.nt <= 0)) return hipSuccess;
+    if ((log2_sub < 14 && a.P != 1) || (1 << log2_sub) != a.Msub || a.M != a.P * a.Msub) return hipErrorInvalidValue;
     switch (log2_sub) {
-        case 10: launch_fsk_corr_ep<StockhamEngine<10>, 1>(a, grid, st); break;
-        case 11: launch_fsk_corr_ep<StockhamEngine<11>, 1>(a, grid, st); break;
-        case 12: launch_fsk_corr_ep<StockhamEngine<12>, 1>(a, grid, st); break;
-        case 13: launch_fsk_corr_ep<StockhamEngine<13>, 1>(a, grid, st); break;
+        case 10: launch_fsk_ep<StockhamEngine<10>, 1>(a, st); break;
+        case 11: launch_fsk_ep<StockhamEngine<11>, 1>(a, st); break;
+        case 12: launch_fsk_ep<StockhamEngine<12>, 1>(a, st); break;
+        case 13: launch_fsk_ep<StockhamEngine<13>, 1>(a, st); break;
         case 14:
             switch (a.P) {
-                case 1: launch_fsk_corr_ep<Fft14, 1>(a, grid, st); break;
-                case 2: launch_fsk_corr_ep<Fft14, 2>(a, grid, st); break;
-                case 4: launch_fsk_corr_ep<Fft14, 4>(a, grid, st); break;
-                case 8: launch_fsk_corr_ep<Fft14, 8>(a, grid, st); break;
-                case 16: launch_fsk_corr_ep<Fft14, 16>(a, grid, st); break;
+                case 1: launch_fsk_ep<Fft14, 1>(a, st); break;
+                case 2: launch_fsk_ep<Fft14, 2>(a, st); break;
+                case 4: launch_fsk_ep<Fft14, 4>(a, st); break;
+                case 8: launch_fsk_ep<Fft14, 8>(a, st); break;
+                case 16: launch_fsk_ep<Fft14, 16>(a, st); break;
                 default: return hipErrorInvalidValue;
             }
             break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <class E>
+void launch_fsk_forward_e(const FskUnit* units, const float* d, int P, int M, int slots, const float2* rootsSub,
+                          const float2* b1tab, float2* X, hipStream_t st) {
+    hipLaunchKernelGGL((k_fsk_forward<E>), dim3(unsigned(slots * P)), dim3(E::NT), 0, st, units, d, P, M, slots * P,
+                       rootsSub, b1tab, X);
+}
+
+hipError_t launch_fsk_forward(const FskUnit* units, const float* d, int P, int M, int log2_sub, int slots,
+                              const float2* rootsSub, const float2* b1tab, float2* X, hipStream_t st) {
+    if (slots <= 0) return hipSuccess;
+    if (M != P << log2_sub) return hipErrorInvalidValue;
+    switch (log2_sub) {
+        case 10: launch_fsk_forward_e<StockhamEngine<10>>(units, d, P, M, slots, rootsSub, b1tab, X, st); break;
+        case 11: launch_fsk_forward_e<StockhamEngine<11>>(units, d, P, M, slots, rootsSub, b1tab, X, st); break;
+        case 12: launch_fsk_forward_e<StockhamEngine<12>>(units, d, P, M, slots, rootsSub, b1tab, X, st); break;
+        case 13: launch_fsk_forward_e<StockhamEngine<13>>(units, d, P, M, slots, rootsSub, b1tab, X, st); break;
+        case 14: launch_fsk_forward_e<Fft14>(units, d, P, M, slots, rootsSub, b1tab, X, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -777,6 +820,7 @@ hipError_t launch_fsk_correlate(const FskCorrArgs& a, int grid, int log2_sub, hi
 struct FskGeometry {
     int64_t lg = 0, nt = 0, M = 0, Msub = 0, V = 0, vf = 0, max_seg = 0, max_front_seg = 0, bytes = 0;
     int64_t slots = 0;          // packed segment pairs a call may use
+    int64_t group = 0;          // first-step outputs held at a time (complex values, a multiple of M; 0: P = 1)
     int P = 1, log2_sub = 0;
     int max_tasks = 16;         // tracking tasks per call
     int items = 0;              // results per call: max(templates, tasks)
@@ -837,7 +881,10 @@ int fsk_geometry(const acq_fsk_config* c, FskGeometry* g) {
     g->items = std::max<int>(c->num_tags, g->max_tasks);
     const int64_t T = c->num_tags;
     const int64_t slots = g->slots;
-    g->bytes = c->max_block_len * 8 + 2 * slots * M * 8 + std::min<int64_t>(T * slots, kFskMaxGrid) * M * 8 +
+    // every item of a call, (template, slot) or tracking slot, or a group of them
+    g->group = g->P > 1 ? std::min<int64_t>(std::max<int64_t>(T * ((g->max_seg + 1) / 2), slots),
+                                            std::max<int64_t>(1, kFskGroup / M)) * M : 0;
+    g->bytes = c->max_block_len * 8 + slots * M * 8 + g->group * 8 + slots * 2 * int64_t(sizeof(FskUnit)) +
                2 * T * M * 8 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
                kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
     return ACQ_OK;
@@ -900,11 +947,9 @@ struct acq_fsk_plan_s {
     float2* d_bank = nullptr;           // [T][M] conj(DFT_M(d^(c))) / M
     float* d_d = nullptr;               // [max_block_len] demodulated d
     float* d_u = nullptr;               // [max_block_len] u
-    float2* d_zp = nullptr;             // [slots][M] packed segment pairs of d
-    float2* d_X = nullptr;              // [slots][M] their spectra
-    float2* d_scratch = nullptr;        // [correlation workgroups][M]
+    float2* d_X = nullptr;              // [slots][M] spectra of the packed segment pairs of d
+    float2* d_G = nullptr;              // [group] first-step outputs of the correlation
     double* d_partial = nullptr;        // [T][parts][sums] refinement partial sums
-    int corr_grid = 0;
     float2* d_rootsM = nullptr;
     float2* d_rootsSub = nullptr;
     float2* d_b1tab = nullptr;
@@ -915,8 +960,9 @@ struct acq_fsk_plan_s {
     acq_fsk_detection* d_out = nullptr;
     int32_t* d_found = nullptr;
     int32_t* d_count = nullptr;
-    acq::FskTask* d_tasks = nullptr;        // [max_tasks] blocks of a call
-    acq::FskTask* h_tasks = nullptr;        // pinned [max_tasks]
+    acq::FskTask* d_tasks = nullptr;        // [max_tasks] blocks of a call, then (right after the call's
+                                            // blocks) [2 slots] its correlation segments
+    acq::FskTask* h_tasks = nullptr;        // pinned, the same
     acq_fsk_detection* h_out = nullptr;     // pinned [items]
     int32_t* h_count = nullptr;             // pinned [1]
     bool profiling = false;
@@ -955,7 +1001,7 @@ void free_fsk(acq_fsk_plan_s* p) {
     for (auto& pair : p->ev)
         for (hipEvent_t e : pair)
             if (e) (void)hipEventDestroy(e);
-    void* dev[] = {p->d_G1, p->d_G0, p->d_rootsF, p->d_bits, p->d_bitcyc, p->d_tmpl, p->d_bank, p->d_d, p->d_u, p->d_zp, p->d_X, p->d_scratch, p->d_partial,
+    void* dev[] = {p->d_G1, p->d_G0, p->d_rootsF, p->d_bits, p->d_bitcyc, p->d_tmpl, p->d_bank, p->d_d, p->d_u, p->d_X, p->d_G, p->d_partial,
                    p->d_rootsM, p->d_rootsSub, p->d_b1tab, p->d_tdescs, p->d_tcounts, p->d_keys,
                    p->d_dets, p->d_out, p->d_found, p->d_count};
     for (void* d : dev)
@@ -1043,12 +1089,11 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     const size_t items = size_t(g.items);
     FSK_HIP(dalloc(&p->d_d, size_t(c.max_block_len)));
     FSK_HIP(dalloc(&p->d_u, size_t(c.max_block_len)));
-    FSK_HIP(dalloc(&p->d_zp, slots * M));
     FSK_HIP(dalloc(&p->d_X, slots * M));
-    p->corr_grid = int(std::min<size_t>(T * slots, size_t(acq::kFskMaxGrid)));
-    FSK_HIP(dalloc(&p->d_tasks, size_t(g.max_tasks)));
-    FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_tasks), sizeof(acq::FskTask) * size_t(g.max_tasks)));
-    FSK_HIP(dalloc(&p->d_scratch, size_t(p->corr_grid) * M));
+    FSK_HIP(dalloc(&p->d_G, size_t(g.group)));
+    const size_t table_bytes = sizeof(acq::FskTask) * size_t(g.max_tasks) + sizeof(acq::FskUnit) * 2 * slots;
+    FSK_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_tasks), table_bytes));
+    FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_tasks), table_bytes));
     FSK_HIP(dalloc(&p->d_rootsM, M));
     FSK_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
@@ -1243,7 +1288,29 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
     if (zoff > p->cfg.max_block_len) return acq::fail(ACQ_ERR_BLOCK_TOO_LONG, "blocks longer than max_block_len in all");
     if (slots > g.slots) return acq::fail(ACQ_ERR_BLOCK_TOO_LONG, "blocks need more segments than the plan holds");
     *items = track ? nblocks : T;
-    FSK_HIP(hipMemcpyAsync(p->d_tasks, p->h_tasks, sizeof(acq::FskTask) * size_t(nblocks), hipMemcpyHostToDevice, st));
+    // the correlation segments follow the blocks in the table
+    acq::FskUnit* hu = reinterpret_cast<acq::FskUnit*>(p->h_tasks + nblocks);
+    for (int b = 0; b < nblocks; ++b) {
+        const acq::FskTask& tk = p->h_tasks[b];
+        for (int64_t s = 0; s < tk.nseg; ++s) {
+            acq::FskUnit& u = hu[tk.unit0 + s];
+            u = acq::FskUnit{};
+            u.z0 = tk.zoff + s * g.V;
+            u.left = int32_t(std::min<int64_t>(tk.n - s * g.V, g.M));
+            u.vlim = int32_t(std::min<int64_t>(tk.lags - s * g.V, g.V));
+            u.lag0 = uint32_t(s * g.V);
+            u.tag = tk.tag;
+            u.key = b;
+        }
+    }
+    if (units & 1) {                                // the last slot's absent second segment
+        hu[units] = hu[units - 1];
+        hu[units].left = hu[units].vlim = 0;
+    }
+    FSK_HIP(hipMemcpyAsync(p->d_tasks, p->h_tasks,
+                           sizeof(acq::FskTask) * size_t(nblocks) + sizeof(acq::FskUnit) * 2 * size_t(slots),
+                           hipMemcpyHostToDevice, st));
+    const acq::FskUnit* du = reinterpret_cast<const acq::FskUnit*>(p->d_tasks + nblocks);
     acq::FskTasks tt{p->d_tasks, nblocks, track ? 1 : 0};
     FSK_HIP(acq::launch_fill_u64(p->d_keys, *items, st));
     if (slots == 0) return ACQ_OK;
@@ -1251,25 +1318,15 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
         FskTimer kt(p, ACQ_FSK_KERNEL_FRONT);
         FSK_HIP(launch_front(p, tt, fsegs, false, nullptr));
     }
-    const int64_t packed = int64_t(slots) * g.M;      // M is a power of two >= 2^10
-    if (packed / 4096 >= 512)
-        hipLaunchKernelGGL(acq::k_fsk_pack<4096>, dim3(unsigned(packed / std::min<int64_t>(g.M, 4096))), dim3(256), 0,
-                           st, tt, p->d_d, g.V, g.M, units, p->d_zp);
-    else
-        hipLaunchKernelGGL(acq::k_fsk_pack<1024>, dim3(unsigned(packed / std::min<int64_t>(g.M, 1024))), dim3(256), 0,
-                           st, tt, p->d_d, g.V, g.M, units, p->d_zp);
-    FSK_HIP(hipGetLastError());
-    BlockTable bt{};
-    bt.one.x = p->d_zp;
-    bt.one.n = packed;
-    bt.one.lags = packed;
-    bt.one.seg0 = 0;
-    bt.one.nseg = slots;
-    bt.one.tag = -1;
-    const acq::FwdArgs fa = fwd_args(p, bt, p->d_X, g.M);
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_FORWARD);
-        FSK_HIP(acq::launch_forward(fa, slots * g.P, slots, g.log2_sub, ACQ_FP32, st));
+        FSK_HIP(acq::launch_fsk_forward(du, p->d_d, g.P, int(g.M), g.log2_sub, slots, p->d_rootsSub, p->d_b1tab,
+                                        p->d_X, st));
+        if (!track && g.P > 1) {                    // tracking combines in its first step
+            BlockTable bt{};
+            bt.one.nseg = slots;
+            FSK_HIP(acq::launch_forward_combine(fwd_args(p, bt, p->d_X, g.M), slots, ACQ_FP32, st));
+        }
     }
     acq::FskCorrArgs ca{};
     ca.X = p->d_X;
@@ -1277,27 +1334,31 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
     ca.rootsM = p->d_rootsM;
     ca.rootsSub = p->d_rootsSub;
     ca.b1tab = p->d_b1tab;
+    ca.G = p->d_G;
     ca.keys = p->d_keys;
     ca.dump = dump;
-    ca.tasks = tt;
-    ca.V = g.V;
+    ca.units = du;
+    ca.lags = p->h_tasks[0].lags;
     ca.M = int(g.M);
     ca.Msub = int(g.Msub);
     ca.P = g.P;
-    ca.T = T;
-    ca.scratch = p->d_scratch;
-    ca.nslots = slots;
-    ca.units = units;
-    int64_t work = track ? int64_t(slots) : int64_t(T) * slots;
-    int grid = int(std::min<int64_t>(work, p->corr_grid));
-    if (!dump && g.P > 1 && g.P <= 8 && work < acq::kFskMaxGrid) {   // fewer items than CUs: one phase per workgroup
-        ca.split = 1;
-        work *= g.P;
-        grid = int(std::min<int64_t>(work, acq::kFskSplitMaxGrid));
-    }
+    ca.track = track ? 1 : 0;
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_CORRELATE);
-        FSK_HIP(acq::launch_fsk_correlate(ca, grid, g.log2_sub, st));
+        // groups of items whose first-step outputs fit the plan's buffer: all
+        // slots with some of the templates, or some of the slots
+        const int most = g.P > 1 ? int(g.group / g.M) : INT32_MAX;
+        const int ns = std::min(slots, most);
+        int nt = track ? 1 : std::min(T, std::max(1, most / ns));
+        if (!track) nt = (T + (T + nt - 1) / nt - 1) / ((T + nt - 1) / nt);       // even groups
+        for (int s0 = 0; s0 < slots; s0 += ns)
+            for (int t0 = 0; t0 < (track ? 1 : T); t0 += nt) {
+                ca.s0 = s0;
+                ca.ns = std::min(ns, slots - s0);
+                ca.t0 = t0;
+                ca.nt = track ? 1 : std::min(nt, T - t0);
+                FSK_HIP(acq::launch_fsk_correlate(ca, g.log2_sub, st));
+            }
     }
     return ACQ_OK;
 }

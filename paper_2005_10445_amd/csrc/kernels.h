@@ -143,6 +143,8 @@ hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st);
 // grid: workgroups of the sub-transforms (items = segments * spc); combine_slots:
 // segment slots the combine step covers (>= the segments in use)
 hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int log2_sub, int prec, hipStream_t st);
+// the combine step alone, of sub-transforms already in a.X
+hipError_t launch_forward_combine(const FwdArgs& a, int slots, int prec, hipStream_t st);
 hipError_t launch_bank(const int8_t* chips, int T, int C, void* bank, const float2* rootsSub,
                        const float2* b1tab, int Msub, int M, int bank_exp, int log2_sub, int prec,
                        hipStream_t st);

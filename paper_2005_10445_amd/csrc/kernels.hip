@@ -154,12 +154,6 @@ __global__ __launch_bounds__(kStatsThreads) void k_block_stats(BlockTable bt, co
 //   and packed in the 16-bit copy instead.  Each spectrum sits at offset xpad
 //   of its slot, with its last xpad entries copied before it and its first
 //   xpad after it (rotated reads need no wrap-around).
-// LDS position of transform output i for the natural-order staging: bits 0-3
-// XOR-ed with a function of bits 4-7 and 10-11, so that both the engine-order
-// writes and the lane-consecutive reads hit 16 distinct 8-byte banks per
-// 16 lanes (a permutation of [0, N)).
-__device__ __forceinline__ int out_swizzle(int i) { return i ^ (((i >> 4) + 4 * (i >> 10)) & 15); }
-
 // PREMIX: exact bins, whose classes have residual offsets (a kernel of its own:
 // its phase reductions cost the other one registers).
 template <class E, bool PREMIX>
@@ -211,19 +205,7 @@ __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
         eng.template transform<-1>(v, lds, b1, extra);
         float2* F = a.X + (size_t(g) * size_t(a.ncls) + size_t(c)) * size_t(a.xstride) + size_t(a.xpad) +
                     size_t(r) * size_t(a.Msub);
-        // outputs leave in the engine's order: put them in natural order in LDS
-        // (XOR-swizzled, conflict-free both ways), then store whole lines
-        const int ob = eng.out_base();
-        __syncthreads();                 // every wave is done with the transform's LDS
-#pragma unroll
-        for (int m = 0; m < 16; ++m) lds[out_swizzle(ob + E::out_off(m))] = v[m];
-        __syncthreads();
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const int i = eng.in_index(m);
-            F[i] = lds[out_swizzle(i)];
-        }
-        __syncthreads();                 // LDS is reused by the next item
+        store_natural(eng, v, lds, F);
     }
 }
 
@@ -631,6 +613,20 @@ static hipError_t combine_p(const FwdArgs& a, dim3 grid, hipStream_t st) {
     return hipSuccess;
 }
 
+hipError_t launch_forward_combine(const FwdArgs& a, int slots, int prec, hipStream_t st) {
+    if (slots <= 0) return hipSuccess;
+    if (a.Msub % 256 || a.spc < 1 || (a.spc > 8 && !(a.spc == 16 && prec == ACQ_FP32))) return hipErrorInvalidValue;
+    const dim3 cgrid(unsigned(slots) * unsigned(a.Msub / 256));
+    hipError_t e;
+    switch (prec) {
+        case ACQ_FP32: e = combine_p<ACQ_FP32>(a, cgrid, st); break;
+        case ACQ_FP16: e = combine_p<ACQ_FP16>(a, cgrid, st); break;
+        case ACQ_BF16: e = combine_p<ACQ_BF16>(a, cgrid, st); break;
+        default: return hipErrorInvalidValue;
+    }
+    return e == hipSuccess ? hipGetLastError() : e;
+}
+
 hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int log2_sub, int prec, hipStream_t st) {
     if (grid <= 0 || combine_slots <= 0) return hipSuccess;
     if ((1 << log2_sub) != a.Msub || a.Msub % 256 || a.spc < 1 || (a.spc > 8 && !(a.spc == 16 && prec == ACQ_FP32)))
@@ -646,15 +642,7 @@ hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int log
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    const dim3 cgrid(unsigned(combine_slots) * unsigned(a.Msub / 256));
-    switch (prec) {
-        case ACQ_FP32: e = combine_p<ACQ_FP32>(a, cgrid, st); break;
-        case ACQ_FP16: e = combine_p<ACQ_FP16>(a, cgrid, st); break;
-        case ACQ_BF16: e = combine_p<ACQ_BF16>(a, cgrid, st); break;
-        default: return hipErrorInvalidValue;
-    }
-    if (e != hipSuccess) return e;
-    return hipGetLastError();
+    return launch_forward_combine(a, combine_slots, prec, st);
 }
 
 template <class E>
