@@ -46,6 +46,39 @@ def _det(d) -> Detection:
                      d.block, d.flags, d.power, d.snr, d.crossings)
 
 
+_DET_DTYPE = np.dtype(AcqDetection)
+_TASK_DTYPE = np.dtype(_capi.AcqTrackTask)
+# the library's names of Detection's fields, in their order
+_DET_COLUMNS = ("tag", "bin", "lag", "toa_samples", "freq_hz", "peak_power", "z", "energy", "block_power", "block",
+                "flags", "power", "snr", "crossings")
+
+
+def _dets(buf, n: int, make=Detection, dtype=_DET_DTYPE, columns=_DET_COLUMNS, one=_det) -> list:
+    """The first n records of a ctypes array.  A few are read field by field; many (a batch of tracking tasks)
+    column by column."""
+    if n <= 16:
+        return [one(d) for d in buf[:n]]
+    a = np.frombuffer(buf, dtype=dtype, count=n)
+    return list(map(make, *(a[c].tolist() for c in columns)))
+
+
+def _task_array(struct, dtype, field, tasks, device_ptrs):
+    """ctypes array of `struct` (dtype its numpy type; field `field` the device pointer, n, tag) from (tensor, tag)
+    pairs."""
+    n = len(tasks)
+    ptrs = device_ptrs([b for b, _ in tasks])
+    if n <= 16:
+        arr = (struct * n)()
+        for i, ((ptr, m), (_, tag)) in enumerate(zip(ptrs, tasks)):
+            arr[i] = struct(ptr, m, int(tag), 0)
+        return arr
+    rec = np.zeros(n, dtype=dtype)               # a column at a time
+    rec[field] = np.array([p for p, _ in ptrs], dtype=np.uint64)
+    rec["n"] = [m for _, m in ptrs]
+    rec["tag"] = np.array([int(tag) for _, tag in tasks], dtype=np.int64)
+    return (struct * n).from_buffer(rec)
+
+
 def make_config(chips: np.ndarray, spc: int, fs_hz: float, num_bins: int = 1,
                 bin_center_hz: float = 0.0, bin_step_hz: float = 0.0, max_block_len: int = 1 << 20,
                 fft_len: int = 0, threshold: float = 0.0, precision: str = "fp32",
@@ -120,13 +153,22 @@ def tune_fft_len(block, reps: int = 2, stream=None, **kw):
                          "batch_launch": e.tuning.batch_launch, "ms": e.ms} for e in out[:cnt.value]]
 
 
-def _device_ptr(block):
+def _device_ptrs(blocks):
+    """(device address, samples) of every block."""
     import torch
-    if not isinstance(block, torch.Tensor) or not block.is_cuda:
-        raise TypeError("block must be a CUDA (HIP) torch tensor")
-    if block.dtype != torch.complex64 or not block.is_contiguous() or block.dim() != 1:
-        raise TypeError("block must be a contiguous 1-D complex64 tensor")
-    return block.data_ptr(), block.numel()
+    tensor, c64 = torch.Tensor, torch.complex64
+    out = []
+    for block in blocks:
+        if not isinstance(block, tensor) or not block.is_cuda:
+            raise TypeError("block must be a CUDA (HIP) torch tensor")
+        if block.dtype != c64 or not block.is_contiguous() or block.dim() != 1:
+            raise TypeError("block must be a contiguous 1-D complex64 tensor")
+        out.append((block.data_ptr(), block.numel()))
+    return out
+
+
+def _device_ptr(block):
+    return _device_ptrs((block,))[0]
 
 
 class Plan:
@@ -185,7 +227,7 @@ class Plan:
                                    ctypes.byref(nf)), "acq_detect")
         if self.asynchronous:
             return self.collect()
-        return [_det(d) for d in self._out[:nf.value]]
+        return _dets(self._out, nf.value)
 
     def enqueue(self, block):
         """acq_detect on an asynchronous plan: enqueue the search and return at once
@@ -201,7 +243,7 @@ class Plan:
         out = (AcqDetection * max(cap, 1))()
         nf = ctypes.c_int32(0)
         check(self._lib.acq_collect(self._h, out, cap, ctypes.byref(nf)), "acq_collect")
-        return [_det(d) for d in out[:min(nf.value, cap)]]
+        return _dets(out, min(nf.value, cap))
 
     def device_results(self):
         """acq_device_results: (device address of the records, device address of the int32[2] counts)."""
@@ -212,11 +254,9 @@ class Plan:
     def detect_batch(self, blocks) -> List[Detection]:
         """acq_detect_batch over a list of 1-D complex64 device tensors of any lengths."""
         n = len(blocks)
-        ptrs = (ctypes.c_void_p * n)()
-        lens = (ctypes.c_int64 * n)()
-        for i, b in enumerate(blocks):
-            ptr, m = _device_ptr(b)
-            ptrs[i], lens[i] = ptr, m
+        at = _device_ptrs(blocks)
+        ptrs = (ctypes.c_void_p * n)(*(p for p, _ in at))
+        lens = (ctypes.c_int64 * n)(*(m for _, m in at))
         cap = n * self.num_tags
         out = (AcqDetection * cap)()
         nf = ctypes.c_int32(0)
@@ -224,7 +264,7 @@ class Plan:
               "acq_detect_batch")
         if self.asynchronous:
             return self.collect(cap)
-        return [_det(d) for d in out[:nf.value]]
+        return _dets(out, nf.value)
 
     def track(self, tasks) -> List[Detection]:
         """acq_track_batch over (1-D complex64 device tensor, tag) pairs: at most one
@@ -236,16 +276,12 @@ class Plan:
         check(self._lib.acq_track_batch(self._h, arr, n, out, n, ctypes.byref(nf)), "acq_track_batch")
         if self.asynchronous:
             return self.collect(n)
-        return [_det(d) for d in out[:nf.value]]
+        return _dets(out, nf.value)
 
     @staticmethod
     def task_array(tasks):
         """acq_track_task array of (device tensor, tag) pairs (the tensors must stay alive)."""
-        arr = (_capi.AcqTrackTask * len(tasks))()
-        for i, (b, tag) in enumerate(tasks):
-            ptr, m = _device_ptr(b)
-            arr[i] = _capi.AcqTrackTask(ptr, m, int(tag), 0)
-        return arr
+        return _task_array(_capi.AcqTrackTask, _TASK_DTYPE, "block", tasks, _device_ptrs)
 
     def track_raw(self, arr) -> int:
         """acq_track_batch on a prebuilt task_array, without building Python records (for

@@ -9,7 +9,7 @@ from typing import List
 
 import numpy as np
 
-from . import _capi
+from . import _capi, _dets, _task_array
 from ._capi import check
 
 __all__ = ["FskPlan", "FskDetection", "fsk_geometry"]
@@ -60,13 +60,35 @@ def fsk_geometry(**kw) -> dict:
     return {name: getattr(g, name) for name, _ in _capi.AcqFskGeometry._fields_}
 
 
-def _iq_ptr(iq):
+def _iq_ptrs(blocks):
+    """(device address, samples) of every int16 block."""
     import torch
-    if not isinstance(iq, torch.Tensor) or not iq.is_cuda or iq.dtype != torch.int16 or not iq.is_contiguous():
-        raise TypeError("iq must be a contiguous int16 CUDA (HIP) tensor of shape [n, 2]")
-    if iq.dim() != 2 or iq.shape[1] != 2:
-        raise TypeError("iq must have shape [n, 2]")
-    return iq.data_ptr(), iq.shape[0]
+    tensor, i16 = torch.Tensor, torch.int16
+    out = []
+    for iq in blocks:
+        if not isinstance(iq, tensor) or not iq.is_cuda or iq.dtype != i16 or not iq.is_contiguous():
+            raise TypeError("iq must be a contiguous int16 CUDA (HIP) tensor of shape [n, 2]")
+        if iq.dim() != 2 or iq.shape[1] != 2:
+            raise TypeError("iq must have shape [n, 2]")
+        out.append((iq.data_ptr(), iq.shape[0]))
+    return out
+
+
+def _iq_ptr(iq):
+    return _iq_ptrs((iq,))[0]
+
+
+def _record(d):
+    return FskDetection(d.tag, d.lag, d.toa_samples, d.xcorr, d.q, d.p, d.z, d.flags, d.block)
+
+
+_TASK_DTYPE = np.dtype(_capi.AcqFskTask)
+_RECORD_DTYPE = np.dtype(_capi.AcqFskDetection)
+_RECORD_COLUMNS = ("tag", "lag", "toa_samples", "xcorr", "q", "p", "z", "flags", "block")
+
+
+def _records(buf, n: int):
+    return _dets(buf, n, FskDetection, _RECORD_DTYPE, _RECORD_COLUMNS, _record)
 
 
 class FskPlan:
@@ -123,17 +145,12 @@ class FskPlan:
         nf = ctypes.c_int32(0)
         check(self._lib.acq_fsk_detect(self._h, ctypes.c_void_p(ptr), n, self._out, self.num_tags,
                                        ctypes.byref(nf)), "acq_fsk_detect")
-        return [FskDetection(d.tag, d.lag, d.toa_samples, d.xcorr, d.q, d.p, d.z, d.flags, d.block)
-                for d in self._out[:nf.value]]
+        return _records(self._out, nf.value)
 
     @staticmethod
     def task_array(tasks):
         """acq_fsk_task array of (int16 [n, 2] device tensor, tag) pairs (the tensors must stay alive)."""
-        arr = (_capi.AcqFskTask * len(tasks))()
-        for i, (iq, tag) in enumerate(tasks):
-            ptr, n = _iq_ptr(iq)
-            arr[i] = _capi.AcqFskTask(ptr, n, int(tag), 0)
-        return arr
+        return _task_array(_capi.AcqFskTask, _TASK_DTYPE, "iq", tasks, _iq_ptrs)
 
     def track_raw(self, arr) -> int:
         """acq_fsk_track on a prebuilt task_array, without building Python records (for
@@ -151,8 +168,7 @@ class FskPlan:
         out = (_capi.AcqFskDetection * len(tasks))()
         nf = ctypes.c_int32(0)
         check(self._lib.acq_fsk_track(self._h, arr, len(tasks), out, len(tasks), ctypes.byref(nf)), "acq_fsk_track")
-        return [FskDetection(d.tag, d.lag, d.toa_samples, d.xcorr, d.q, d.p, d.z, d.flags, d.block)
-                for d in out[:nf.value]]
+        return _records(out, nf.value)
 
     def detect_raw(self, iq) -> int:
         ptr, n = _iq_ptr(iq)
