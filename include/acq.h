@@ -122,7 +122,7 @@ typedef struct acq_config {
     int32_t       fft_len;           /* M: power of two >= M_min; 0 = library's choice   */
     int32_t       precision;         /* acq_precision                                    */
     int32_t       refine_radius;     /* FP64 re-maximisation radius in lags, 0 -> 1, <= 8 */
-    int32_t       tag_tile;          /* tags per correlation work item; 0 = default      */
+    int32_t       tag_tile;          /* tags per correlation work item; 0 = by its work  */
     uint32_t      flags;             /* ACQ_FLAG_*                                       */
     int32_t       max_batch_blocks;  /* blocks per acq_detect_batch call; 0 -> 1         */
     int64_t       max_batch_samples; /* samples per acq_detect_batch call; 0 -> blocks * max_block_len */
@@ -306,7 +306,9 @@ int acq_detect_noalloc(acq_plan_t plan, const void* block, int64_t n, acq_detect
  * Launch configuration of the correlation kernel.  engine: 0 = the default
  * transform engine for the plan's inverse-transform length, 1 = Stockham
  * passes through padded LDS (available for every length).  tag_tile: tags per
- * work item, 1..64.  Results do not depend on the tuning.
+ * work item, 1..64; a plan made with tag_tile 0 and not tuned since reports 16
+ * and chooses the tile of each launch from its work items (batches captured
+ * into the plan's graph keep 16).  Results do not depend on the tuning.
  */
 typedef struct acq_tuning {
     int32_t engine;

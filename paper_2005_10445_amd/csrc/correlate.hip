@@ -66,7 +66,9 @@ __device__ __forceinline__ float2 root32(int m) {
 //   W_0 = 1 + e, 1 - e   ->  G_0 = S + e D
 //   W_1 = e + e^2, e^2 - e  ->  G_1 = e (D + e S)
 // and e = exp(+j 2 pi in_index(0) / M) exp(+j pi m / 16) (in_index(m) =
-// in_index(0) + m Msub / 16); other spc read W from the table.
+// in_index(0) + m Msub / 16); spc = 1 has W = 1, the others read W from the table
+// (the same closed form over an spc-point transform needs no table but adds
+// roundings: 2 to 17 % more error in a power at spc = 4 and 8).
 template <class E, int PREC>
 __device__ __forceinline__ void first_step(const CorrArgs& a, const E& eng, int g, int k, int rho, float gscale,
                                            float2 (&G)[16]) {
@@ -98,6 +100,9 @@ __device__ __forceinline__ void first_step(const CorrArgs& a, const E& eng, int 
                 G[m] = cmul(e, cadd(D, cmul(e, S)));
             }
         }
+    } else if (a.spc == 1) {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) G[m] = St::bload(xr, xoff, m * NT * St::BYTES);
     } else {
         const __amdgpu_buffer_rsrc_t wr =
             make_rsrc(a.wts + size_t(rho) * size_t(a.M), uint32_t(a.M) * 8u);
@@ -193,11 +198,10 @@ __device__ __forceinline__ float gate_power(const unsigned long long* key, float
 // wi = ((tile * segments + g) * K + k) * spc + rho.
 template <class E, int PREC, bool DUMP>
 __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, int wi, int total_seg,
-                                               float2* lds, const float2* extra, unsigned long long* red,
-                                               unsigned* cred) {
+                                               float2* lds, const float2* extra, unsigned long long* best,
+                                               unsigned* count) {
     using St = dev::Storage<PREC>;
     constexpr int N = E::N;
-    constexpr int NW = E::NT / 64;
     int rem = wi;
     const int rho = rem % a.spc;
     rem /= a.spc;
@@ -205,7 +209,7 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
     rem /= a.K;
     const int g = rem % total_seg;
     const int tile = rem / total_seg;
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int lane = int(threadIdx.x) & 63;
     const int bi = a.blocks.block_of_segment(g);
     const BlockDesc d = a.blocks.get(bi);
     // a tracking task searches its own tag only (launched with one tile)
@@ -243,9 +247,9 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
     // lane t: the power that tag t's transform has to reach to matter.  The keys
     // only grow during a launch, so a value read early is a lower bound
     const float gates = lane < ntag ? gate_power(&keys[tag0 + lane], pth) : 0.0f;
-    for (int i = int(threadIdx.x); i < ntag * NW; i += E::NT) {   // (the transform's barriers order these)
-        red[i] = 0ull;
-        cred[i] = 0u;
+    for (int i = int(threadIdx.x); i < ntag; i += E::NT) {   // (the transform's barriers order these)
+        best[i] = 0ull;
+        count[i] = 0u;
     }
 
     // bank element of register m: i = in_index(0) + m*NT, stored for i <= N/2;
@@ -287,10 +291,10 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
             const float bp = lane_powers<E, LOW>(v, p, ob, omin, ulim);
             if (__builtin_amdgcn_ballot_w64(bp >= gate)) {
                 unsigned cross;
-                const unsigned long long best = wave_peak<E, LOW>(p, bp, pth, idx0, kstep, &cross);
+                const unsigned long long key = wave_peak<E, LOW>(p, bp, pth, idx0, kstep, &cross);
                 if (lane == 0) {
-                    red[tt * NW + wave] = best;
-                    cred[tt * NW + wave] = cross;
+                    atomicMax(&best[tt], key);
+                    if (cross) atomicAdd(&count[tt], cross);
                 }
             }
         };
@@ -301,16 +305,9 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
     }
     __syncthreads();
     for (int i = int(threadIdx.x); i < ntag; i += E::NT) {
-        unsigned long long m = 0ull;
-        unsigned c = 0;
-        for (int q = 0; q < NW; ++q) {
-            m = red[i * NW + q] > m ? red[i * NW + q] : m;
-            c += cred[i * NW + q];
-        }
-        if (m) atomicMax(&keys[tag0 + i], m);
-        if (c) atomicAdd(&a.cross[size_t(bi) * a.T + tag0 + i], c);
+        if (best[i]) atomicMax(&keys[tag0 + i], best[i]);
+        if (count[i]) atomicAdd(&a.cross[size_t(bi) * a.T + tag0 + i], count[i]);
     }
-    __syncthreads();                             // red[] is rewritten by the next item
 }
 
 // One tracking work item: (global segment g, tile of bins, phase rho) for the
@@ -321,9 +318,8 @@ __device__ __forceinline__ void correlate_item(const CorrArgs& a, const E& eng, 
 // per item remains.
 template <class E, int PREC>
 __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int wi, float2* lds,
-                                           const float2* extra, unsigned long long* red, unsigned* cred) {
+                                           const float2* extra, unsigned long long* wg_best, unsigned* wg_count) {
     using St = dev::Storage<PREC>;
-    constexpr int NW = E::NT / 64;
     const int ntl = (a.K + a.tile - 1) / a.tile;
     int rem = wi;
     const int rho = rem % a.spc;
@@ -331,7 +327,7 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
     const int btile = rem % ntl;
     const int g = rem / ntl;
     const int k0 = btile * a.tile, k1 = min(a.K, k0 + a.tile);
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int lane = int(threadIdx.x) & 63;
     const int bi = a.blocks.block_of_segment(g);
     const BlockDesc d = a.blocks.get(bi);
     const int j = a.blocks.segment(g, d);
@@ -359,6 +355,10 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
 
     unsigned long long best = 0ull;                // the wave's largest key over the item's bins
     unsigned cross = 0;                            // the wave's crossings over the item's bins
+    if (threadIdx.x == 0) {                        // (the transform's barriers order these)
+        *wg_best = 0ull;
+        *wg_count = 0u;
+    }
     float gate = gate_power(&a.keys[size_t(bi) * a.T + tag], pth);
     // the task's replica spectrum is the same for every bin: read it once
     float2 bk[16];
@@ -393,21 +393,14 @@ __device__ __forceinline__ void track_item(const CorrArgs& a, const E& eng, int 
             scan(std::false_type{});
     }
     if (lane == 0) {
-        red[wave] = best;
-        cred[wave] = cross;
+        if (best) atomicMax(wg_best, best);
+        if (cross) atomicAdd(wg_count, cross);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long m = 0ull;
-        unsigned c = 0;
-        for (int q = 0; q < NW; ++q) {
-            m = red[q] > m ? red[q] : m;
-            c += cred[q];
-        }
-        if (m) atomicMax(&a.keys[size_t(bi) * a.T + tag], m);
-        if (c) atomicAdd(&a.cross[size_t(bi) * a.T + tag], c);
+        if (*wg_best) atomicMax(&a.keys[size_t(bi) * a.T + tag], *wg_best);
+        if (*wg_count) atomicAdd(&a.cross[size_t(bi) * a.T + tag], *wg_count);
     }
-    __syncthreads();
 }
 
 // Launch forms of the correlation kernel.  Each is its own instantiation so the
@@ -418,12 +411,11 @@ enum CorrMode { kCorrGrid = 0, kCorrGridDump = 1, kCorrPersistent = 2, kCorrTrac
 // second workgroup no longer fits a compute unit.
 template <class E, int PREC, int MODE>
 __global__ __launch_bounds__(E::NT, 4) void k_correlate(CorrArgs a) {
-    constexpr int NW = E::NT / 64;
     constexpr bool DUMP = MODE == kCorrGridDump;
     __shared__ float2 lds[E::LDS];
     __shared__ float2 extra[E::EXTRA];
-    __shared__ unsigned long long red[kMaxTagTile * NW];
-    __shared__ unsigned cred[kMaxTagTile * NW];
+    __shared__ unsigned long long best[kMaxTagTile];    // the item's keys and crossing counts
+    __shared__ unsigned count[kMaxTagTile];
     __shared__ int s_item;
     const int total_seg = a.blocks.total_seg();
     const int total = MODE == kCorrTrack ? total_seg * ((a.K + a.tile - 1) / a.tile) * a.spc
@@ -445,7 +437,8 @@ __global__ __launch_bounds__(E::NT, 4) void k_correlate(CorrArgs a) {
             const int it = begin + __builtin_amdgcn_readfirstlane(s_item);
             __syncthreads();
             if (it >= end) break;
-            correlate_item<E, PREC, false>(a, eng, it, total_seg, lds, extra, red, cred);
+            correlate_item<E, PREC, false>(a, eng, it, total_seg, lds, extra, best, count);
+            __syncthreads();                     // best[] is cleared by the next item
         }
     } else {
         // one item per workgroup; the grid may exceed the work (a batch captured
@@ -457,9 +450,9 @@ __global__ __launch_bounds__(E::NT, 4) void k_correlate(CorrArgs a) {
         if (q >= per || wi >= total) return;
         eng.init(a.rootsSub, extra);
         if constexpr (MODE == kCorrTrack)
-            track_item<E, PREC>(a, eng, wi, lds, extra, red, cred);
+            track_item<E, PREC>(a, eng, wi, lds, extra, best, count);
         else
-            correlate_item<E, PREC, DUMP>(a, eng, wi, total_seg, lds, extra, red, cred);
+            correlate_item<E, PREC, DUMP>(a, eng, wi, total_seg, lds, extra, best, count);
     }
 }
 

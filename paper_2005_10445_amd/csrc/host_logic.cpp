@@ -292,4 +292,39 @@ std::vector<float> phase_weights(int64_t M, int spc) {
     return out;
 }
 
+// An item costs its tags' transforms and about one more (its first step and
+// its workgroup's start), so long tiles waste least; but the launch lasts as
+// long as the compute unit with the most items, so few items leave units idle
+// or a last round nearly empty.  A unit holds R workgroups of a transform
+// length (16 of 2^10 points .. 1 of 2^14), which run at its full rate together
+// and at 1 / (0.6 R) of it alone.  The rule takes the tile of least
+//   (tile + 1) x (full rounds of R items + the last round), the last round of
+//   r items counted as max(r, 0.6 R),
+// the larger at a tie.  Against the best tile of a sweep over 20 shapes (2^10 to 2^14
+// points, 100 to 89,000 items at one tag each) it is 3 % slower on average, 21 %
+// at the worst; a fixed 16 tags was 54 % slower on average and at worst 4.5
+// times as slow (k_correlate, us, 16 tags -> rule: 13 tags x 5 bins x 4 phases
+// x 8 segments of 2^12 points 57.7 -> 37.3; 30 tags x 7 x 2 x 11 of 2^14
+// points 200.8 -> 141.3; 7 tags x 3 x 2 x 6 of 2^14 points 53.8 -> 20.1; 64
+// tags x 11 x 2 x 63 of 2^14 points 2065 -> 2019).  More than 32 tags were
+// never better.
+int choose_tag_tile(int64_t T, int64_t per_tile, int log2_sub, int cus) {
+    const int64_t r = int64_t(1) << (14 - log2_sub);
+    const int top = int(std::min<int64_t>(T, 32));
+    int best = top;
+    int64_t best_cost = INT64_MAX;
+    for (int t = top; t >= 1; --t) {
+        const int64_t items = (T + t - 1) / t * per_tile;
+        if (items >= (int64_t(1) << 31) - 8) break;
+        const int64_t w = (items + cus - 1) / cus;            // items of the fullest unit
+        const int64_t rest = w % r;
+        const int64_t rounds5 = 5 * (w - rest) + (rest ? std::max<int64_t>({5, 5 * rest, 3 * r}) : 0);
+        if (rounds5 * (t + 1) < best_cost) {
+            best_cost = rounds5 * (t + 1);
+            best = t;
+        }
+    }
+    return best;
+}
+
 }  // namespace acq

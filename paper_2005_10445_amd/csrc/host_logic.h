@@ -78,6 +78,11 @@ std::vector<double> unit_roots64(int64_t n);
 // with entry exp(+j 2 pi l (w + 16 k2a) / 2^14), l = q + 4 m; w, m, k2a < 16, q < 4.
 std::vector<float> fft14_b1_table();
 
+// Tags per correlation work item where the caller names none, for T tags whose
+// every tile is `per_tile` items (segments x bins x phases) of transforms of
+// 2^log2_sub points on `cus` compute units.
+int choose_tag_tile(int64_t T, int64_t per_tile, int log2_sub, int cus);
+
 // Weights of the tag-independent first step of the split inverse transform:
 // W_rho[i] = conj(Rect[i]) exp(+j 2 pi i rho / M) = sum_{r<spc} exp(+j 2 pi i (r + rho) / M)
 // for rho in [0, spc), i in [0, M), with Rect the M-point spectrum of a run of

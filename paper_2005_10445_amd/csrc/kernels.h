@@ -64,7 +64,7 @@ struct CorrArgs {
     const void* bank;           // [T][Msub] 2^bank_exp conj(DFT_Msub(chips)) / M (storage format)
     const int* exps;            // [block] 16-bit storage prescale exponents (16-bit plans)
     const float2* wts;          // [spc][M] W_rho[i] = sum_{r<spc} exp(+j 2 pi i (r + rho) / M)
-                                // (read for spc != 2; spc = 2 forms them in closed form)
+                                // (read for spc >= 4: spc = 2 forms them in closed form)
     const float2* rootsM;       // [M] exp(+j 2 pi m / M)
     const float2* rootsSub;     // [Msub] exp(+j 2 pi m / Msub), then the Stockham engine's pass twiddles
     const float2* b1tab;        // 2^14-point engine twiddle table (else unused)

@@ -60,6 +60,7 @@ struct acq_plan_s {
     int cus = 256;                      // compute units (persistent grid size)
     int engine = 0;                     // acq_tuning.engine
     int tile = 16;                      // acq_tuning.tag_tile
+    bool auto_tile = false;             // no tile asked for: searches choose one per launch
     int batch_launch = ACQ_BATCH_GRID;  // acq_tuning.batch_launch
     int track_bins = 0;                 // acq_tuning.track_bins (0: chosen per launch)
 
@@ -415,8 +416,14 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     ca.M = int(g.M);
     ca.Msub = int(g.Msub);
     ca.T = c.num_tags;
-    ca.tile = p->tile;
-    ca.ntiles = (c.num_tags + p->tile - 1) / p->tile;
+    // a captured batch sizes its grid for the plan's capacity and keeps one tile
+    // for every batch it will replay
+    const bool replayed = batch && p->capturing;
+    const int64_t segs = replayed ? int64_t(g.max_total_segments) : int64_t(total_seg_host);
+    ca.tile = p->auto_tile && !track && !replayed
+                  ? acq::choose_tag_tile(c.num_tags, segs * c.num_bins * c.samples_per_chip, g.log2_sub, p->cus)
+                  : p->tile;
+    ca.ntiles = (c.num_tags + ca.tile - 1) / ca.tile;
     ca.bank_exp = p->bank_exp;
     ca.persistent = batch && !track && p->batch_launch == ACQ_BATCH_PERSISTENT ? 1 : 0;
     ca.track = track ? 1 : 0;
@@ -429,7 +436,6 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
         // per item and 0.430 ms, 11 bins 0.437 ms).  The choice follows this batch's
         // segments (for a captured graph, those of the batch it was captured
         // on), while a captured graph sizes its grid for the plan's capacity.
-        const int64_t segs = p->capturing ? int64_t(g.max_total_segments) : int64_t(total_seg_host);
         int bins = p->track_bins;
         if (bins <= 0) {
             const int64_t per_bin = int64_t(total_seg_host) * c.samples_per_chip;
@@ -448,9 +454,7 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
         ACQ_HIP(acq::launch_fill_i32(w.counters, acq::kXcds, st));
         grid = p->cus;
     } else {
-        // batches captured into a graph size the grid for the plan's capacity;
-        // the kernel reads the real item count from the block table
-        const int64_t segs = batch && p->capturing ? int64_t(g.max_total_segments) : int64_t(total_seg_host);
+        // the kernel reads a batch's real item count from the block table
         const int64_t nwork = int64_t(ca.ntiles) * segs * c.num_bins * c.samples_per_chip;
         if (nwork >= (int64_t(1) << 31) - 8) return acq::fail(ACQ_ERR_UNSUPPORTED, "too many work items");
         grid = int((nwork + acq::kXcds - 1) / acq::kXcds) * acq::kXcds;
@@ -704,6 +708,7 @@ int acq_plan(const acq_config* cfg, void* workspace, size_t workspace_bytes_, vo
     p->cfg = *cfg;                   // chips are read by build_plan only
     p->g = std::move(g);
     p->tile = p->g.tag_tile;
+    p->auto_tile = cfg->tag_tile == 0;
     p->stream = static_cast<hipStream_t>(stream);
     if (hipGetDevice(&p->device) != hipSuccess) {
         delete p;
@@ -1050,11 +1055,12 @@ int acq_set_tuning(acq_plan_t p, const acq_tuning* t) {
         return acq::fail(ACQ_ERR_INVALID_ARG,
                          "engine must be 0 or 1, tag_tile in [1, 64], batch_launch 0 or 1, track_bins in [0, 64]");
     const int tile = t->tag_tile < p->cfg.num_tags ? t->tag_tile : p->cfg.num_tags;
-    if (t->engine != p->engine || tile != p->tile || t->batch_launch != p->batch_launch ||
+    if (t->engine != p->engine || tile != p->tile || p->auto_tile || t->batch_launch != p->batch_launch ||
         t->track_bins != p->track_bins)
         drop_graph(p);   // the captured kernels change
     p->engine = t->engine;
     p->tile = tile;
+    p->auto_tile = false;
     p->batch_launch = t->batch_launch;
     p->track_bins = t->track_bins;
     return ACQ_OK;
@@ -1081,6 +1087,7 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
             c.fft_len = int32_t(p->g.M);
             cand.push_back(c);
         }
+    const bool was_auto = p->auto_tile;
     const acq_tuning before{p->engine, p->tile, p->batch_launch, p->track_bins};
     BlockTable bt{};
     bt.one = single_desc(p, block, n);
@@ -1150,6 +1157,7 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
     }
     if (rc != ACQ_OK) {
         acq_set_tuning(p, &before);
+        p->auto_tile = was_auto;
         acq_set_profiling(p, was_profiling);
         return rc;
     }
