@@ -1160,7 +1160,7 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     bt.descs = p->d_tdescs;
     bt.counts = p->d_tcounts;
     const acq::FwdArgs fa = fwd_args(p, bt, p->d_bank, g.M);
-    FSK_HIP(acq::launch_forward(fa, int(T) * g.P, int(T), g.log2_sub, ACQ_FP32, st));
+    FSK_HIP(acq::launch_forward(fa, int(T) * g.P, int(T), 0, 0, g.log2_sub, ACQ_FP32, st));
     hipLaunchKernelGGL(acq::k_fsk_conj_scale, dim3(unsigned((tcount + 255) / 256)), dim3(256), 0, st, p->d_bank, tcount,
                        float(1.0 / double(g.M)));
     FSK_HIP(hipGetLastError());

@@ -83,7 +83,29 @@ struct CorrArgs {
     int32_t track;              // 1: tracking tasks; `tile` then counts bins per work item
 };
 
+// Block power and what follows from it, formed by the forward launch's first
+// `groups` workgroups: exps[b] = round(log2(sqrt(M * Pxhat_b))) (the 16-bit storage
+// prescale), pthr[b] = theta_b * L * Pxhat_b (+inf when Pxhat_b is 0 or not
+// finite), bad[b] = 1 when Pxhat_b is not finite (some sample is NaN or
+// infinite), nbad[0] the number of such blocks.  The same workgroups clear the
+// search's peak keys, crossing counts and refinement tickets, nclear of each
+// (one ticket more).
+struct PowerArgs {
+    double* parts;              // [block][kPowerParts] partial sums of |x|^2
+    int* exps;
+    float* pthr;
+    int32_t* bad;
+    int32_t* nbad;
+    unsigned long long* keys;
+    unsigned* cross;
+    unsigned* tickets;
+    unsigned* ticket;           // arrivals of the power workgroups: zero before and after each launch
+    int64_t nclear, L;
+    int32_t M, groups, max_parts;   // groups, max_parts: set by launch_forward
+};
+
 struct FwdArgs {
+    PowerArgs power;
     BlockTable blocks;
     float2* X;                  // [segments][ncls][xstride] FP32 spectra (sub-transforms, then the
                                 // result), at offset xpad of each slot with wrap-around copies
@@ -118,31 +140,30 @@ struct RefineArgs {
     int32_t track;              // 1: one candidate per block, the block's own tag
     int32_t check_finite;       // 1: no detection in a block with a non-finite sample
     double* partial;            // [items][kRefineParts][3 * window] FP64 partial sums
-    int64_t* center;            // [items] window centre of the second round (-1: none)
+    unsigned* tickets;          // [1 + items] arrivals, zero at the launch: of the items, of each item's parts
+    // tail = 1 (at most kTailItems items): the launch writes the detections too
+    int32_t tail, capacity;
+    acq_detection* out;         // [capacity]
+    int32_t* count;             // [1]
+    const int32_t* nbad;        // [1]
+    acq_detection* h_out;       // the same in host memory, or nullptr
+    int32_t* h_count;           // [2] {detections, blocks with a non-finite sample}
 };
 
 // Refinement work: items = blocks * (tracking ? 1 : T); each item's sums run in
 // kRefineParts workgroups, each writing 3 * WMAX doubles (WMAX = 5 for radius
 // <= 1, else 2 * kMaxRefineRadius + 3).
 constexpr int kRefineParts = 16;
+constexpr int kTailItems = 1024;
 
-// partial sums of |x|^2 of every block (blocks of at most max_len samples)
-hipError_t launch_block_power(const BlockTable& bt, int max_blocks, int64_t max_len, double* parts, hipStream_t st);
-// Per-block quantities derived from the block power, for every block of the
-// table: exps[b] = round(log2(sqrt(M * Pxhat_b))) (the 16-bit storage
-// prescale), pthr[b] = theta_b * L * Pxhat_b (+inf when Pxhat_b is 0 or not
-// finite), bad[b] = 1 when Pxhat_b is not finite (some sample is NaN or
-// infinite); nbad[0] receives the number of such blocks (workgroup 0).  The
-// same launch also clears the search's per-(block, tag) peak keys and
-// crossing counts, nclear of each (two launches fewer per search).
-hipError_t launch_block_stats(const BlockTable& bt, const double* parts, int M, int64_t L, int* exps, float* pthr,
-                              int32_t* bad, int32_t* nbad, unsigned long long* keys, unsigned* cross,
-                              int64_t nclear, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t count, hipStream_t st);
 hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st);
-// grid: workgroups of the sub-transforms (items = segments * spc); combine_slots:
-// segment slots the combine step covers (>= the segments in use)
-hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int log2_sub, int prec, hipStream_t st);
+// grid: workgroups of the sub-transforms (items = segments * spc; 0: none);
+// combine_slots: segment slots the combine step covers (>= the segments in use);
+// power_blocks: blocks (of at most power_len samples) whose power a.power asks
+// for, 0: none
+hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int power_blocks, int64_t power_len,
+                          int log2_sub, int prec, hipStream_t st);
 // the combine step alone, of sub-transforms already in a.X
 hipError_t launch_forward_combine(const FwdArgs& a, int slots, int prec, hipStream_t st);
 hipError_t launch_bank(const int8_t* chips, int T, int C, void* bank, const float2* rootsSub,

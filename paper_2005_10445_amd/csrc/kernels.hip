@@ -1,14 +1,14 @@
 // HIP kernels of the acquisition path (gfx950).
 //
-//   k_block_power  : FP64 partial sums of |x|^2 (mean block power Pxhat)
 //   k_forward_*    : overlap-save segment j, X_j = DFT_M(x[jV .. jV+M)) with a zero
 //                    tail, as spc decimated Msub-point transforms (one workgroup
-//                    each) combined by one radix-spc decimation-in-time step
+//                    each) combined by one radix-spc decimation-in-time step; beside them
+//                    the FP64 sums of |x|^2 (mean block power Pxhat)
 //   k_bank         : replica spectra conj(DFT_Msub(chip code)) / M, plan time
 //   k_correlate    : the hot loop, in correlate.hip
-//   k_refine_*     : FP64 re-correlation around each tag's peak, re-maximisation,
-//                    parabolic vertex, z and energy
-//   k_compact      : detections in tag order
+//   k_refine       : FP64 re-correlation around each tag's peak, re-maximisation,
+//                    parabolic vertex, z and energy; detections in tag order
+//   k_compact      : detections in tag order, of searches of many items
 //
 #include <hip/hip_runtime.h>
 
@@ -31,7 +31,7 @@ namespace {
 // Item p * blocks + b, p < the parts of the longest block the plan takes;
 // workgroups stride over the items, and every item is summed in the same
 // order whichever workgroup takes it, so the sums are deterministic.
-constexpr int kPowerMaxGrid = 4096;
+constexpr int kPowerMaxGrid = 1024;
 constexpr int64_t kPowerMinChunk = 4096;
 
 __host__ __device__ __forceinline__ int64_t power_chunk(int64_t n) {
@@ -43,28 +43,79 @@ __host__ __device__ __forceinline__ int power_parts(int64_t n) {
     return n > 0 ? int((n + power_chunk(n) - 1) / power_chunk(n)) : 0;
 }
 
-__global__ __launch_bounds__(256) void k_block_power(BlockTable bt, double* __restrict__ parts, int max_parts) {
-    __shared__ double red[4];
+// Values that another workgroup of the same launch reads: stored through to, and
+// loaded from, the memory that the XCDs share (no L2 write-back or invalidation,
+// which would take the launch's other data with it).
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class T>
+__device__ __forceinline__ T agent_load(const T* p) {
+    return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Counts this workgroup's arrival at *ticket; true (in the whole workgroup) for
+// the last of `total`, which then sees what the others stored with agent_store.
+// Every thread of the workgroup comes here.
+__device__ __forceinline__ bool last_arrival(unsigned* ticket, unsigned total) {
+    __shared__ unsigned s_ticket;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's stores have arrived
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return s_ticket == total - 1;
+}
+
+// Workgroups of NT threads that sum the parts.  A part is summed by 256
+// threads (four waves), so a workgroup takes NT / 256 parts at a time, or a
+// smaller one a part's waves in turn; 8 samples of each thread are in flight
+// together.
+template <int NT>
+__host__ __device__ constexpr int power_per_group() { return NT > 256 ? NT / 256 : 1; }
+
+template <int NT>
+__device__ __forceinline__ void sum_block_power(const BlockTable& bt, const PowerArgs& a, int wg) {
+    __shared__ double red[4 * power_per_group<NT>()];
+    constexpr int NW = NT / 64, PP = power_per_group<NT>(), PW = NW < 4 ? NW : 4;   // waves of a part
+    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
     const int nb = bt.nblocks();
-    const int items = nb * max_parts;
+    const int items = nb * a.max_parts;
     // part-major order: the low parts of every block come first and spread
     // over distinct workgroups
-    for (int it = int(blockIdx.x); it < items; it += int(gridDim.x)) {
+    for (int it0 = wg * PP; it0 < items; it0 += a.groups * PP) {
+        const int it = it0 + wave / PW;
         const int b = it % nb, part = it / nb;
-        const BlockDesc d = bt.get(b);
+        const bool in = it < items;
+        const BlockDesc d = bt.get(in ? b : 0);
         const int64_t chunk = power_chunk(d.n);
         const int64_t beg = int64_t(part) * chunk;
-        if (beg >= d.n) continue;                    // uniform: past this block's parts
         const int64_t end = beg + chunk < d.n ? beg + chunk : d.n;
-        double acc = 0.0;
-        for (int64_t i = beg + threadIdx.x; i < end; i += 256) {
-            const float2 v = d.x[i];
-            acc += double(v.x) * double(v.x) + double(v.y) * double(v.y);
+        const bool some = in && beg < d.n;           // uniform over the wave
+        for (int vw = wave % PW; vw < 4; vw += PW) {
+            double acc = 0.0;
+            if (some) {
+                constexpr int U = 8;
+                for (int64_t i = beg + vw * 64 + lane; i < end; i += 256 * U) {
+                    float2 v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = d.x[min(i + 256 * u, end - 1)];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (i + 256 * u < end)
+                            acc += double(v[u].x) * double(v[u].x) + double(v[u].y) * double(v[u].y);
+                }
+            }
+            acc = wave_sum(acc);
+            if (lane == 0) red[(wave / PW) * 4 + vw] = acc;
         }
-        acc = wave_sum(acc);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
         __syncthreads();
-        if (threadIdx.x == 0) parts[size_t(b) * kPowerParts + part] = (red[0] + red[1]) + (red[2] + red[3]);
+        if (some && wave % PW == 0 && lane == 0) {
+            const double* r = red + (wave / PW) * 4;
+            agent_store(&a.parts[size_t(b) * kPowerParts + part], (r[0] + r[1]) + (r[2] + r[3]));
+        }
         __syncthreads();
     }
 }
@@ -80,7 +131,8 @@ __global__ void k_fill_i32(int* p, int64_t count) {
 }
 
 // mean block power from the fixed-order partial sums
-__device__ __forceinline__ double block_mean_power(const double* __restrict__ parts, int64_t n) {
+// (agent loads: they may have been stored by this launch)
+__device__ __forceinline__ double block_mean_power(const double* parts, int64_t n) {
     // the parts are added in index order; loads go out 32 at a time so that a
     // single thread does not wait for each one in turn
     constexpr int kBatch = 32;
@@ -90,11 +142,11 @@ __device__ __forceinline__ double block_mean_power(const double* __restrict__ pa
     for (; i + kBatch <= np; i += kBatch) {
         double v[kBatch];
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) v[j] = parts[i + j];
+        for (int j = 0; j < kBatch; ++j) v[j] = agent_load(&parts[i + j]);
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) s += v[j];
     }
-    for (; i < np; ++i) s += parts[i];
+    for (; i < np; ++i) s += agent_load(&parts[i]);
     return n > 0 ? s / double(n) : 0.0;
 }
 
@@ -105,39 +157,42 @@ __device__ __forceinline__ double block_mean_power(const double* __restrict__ pa
 // Pxhat (the z >= theta test on FP32 powers); and whether the block holds a
 // non-finite sample (then Pxhat is not finite: |x|^2 of a finite complex64
 // value cannot overflow FP64 and every term is >= 0, so no cancellation).
-// Workgroup 0 strides over the blocks and counts the non-finite ones; every
-// workgroup of the launch also clears a share of the search's peak keys and
-// crossing counts.
-constexpr int kStatsThreads = 256;
-
-__global__ __launch_bounds__(kStatsThreads) void k_block_stats(BlockTable bt, const double* __restrict__ parts, int M,
-                                                               int64_t L, int* __restrict__ exps,
-                                                               float* __restrict__ pthr, int32_t* __restrict__ bad,
-                                                               int32_t* __restrict__ nbad,
-                                                               unsigned long long* __restrict__ keys,
-                                                               unsigned* __restrict__ cross, int64_t nclear) {
+// One workgroup strides over the blocks and counts the non-finite ones.
+template <int NT>
+__device__ __forceinline__ void block_stats(const BlockTable& bt, const PowerArgs& a) {
     __shared__ int s_bad;
-    for (int64_t i = int64_t(blockIdx.x) * kStatsThreads + threadIdx.x; i < nclear;
-         i += int64_t(gridDim.x) * kStatsThreads) {
-        keys[i] = 0ull;
-        cross[i] = 0u;
-    }
-    if (blockIdx.x != 0) return;             // workgroup 0 forms the statistics
     if (threadIdx.x == 0) s_bad = 0;
     __syncthreads();
     const int nb = bt.nblocks();
-    for (int b = int(threadIdx.x); b < nb; b += kStatsThreads) {
+    for (int b = int(threadIdx.x); b < nb; b += NT) {
         const BlockDesc d = bt.get(b);
-        const double px = block_mean_power(parts + size_t(b) * kPowerParts, d.n);
+        const double px = block_mean_power(a.parts + size_t(b) * kPowerParts, d.n);
         const bool fin = isfinite(px);
-        exps[b] = fin && px > 0.0 ? int(rint(0.5 * log2(double(M) * px))) : 0;
-        const double th = d.theta * double(L) * px;
-        pthr[b] = fin && px > 0.0 && th <= 3.0e38 ? float(th) : __builtin_huge_valf();
-        bad[b] = fin ? 0 : 1;
+        a.exps[b] = fin && px > 0.0 ? int(rint(0.5 * log2(double(a.M) * px))) : 0;
+        const double th = d.theta * double(a.L) * px;
+        a.pthr[b] = fin && px > 0.0 && th <= 3.0e38 ? float(th) : __builtin_huge_valf();
+        a.bad[b] = fin ? 0 : 1;
         if (!fin) atomicAdd(&s_bad, 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) nbad[0] = s_bad;
+    if (threadIdx.x == 0) a.nbad[0] = s_bad;
+}
+
+// Workgroup `wg` of a launch's a.groups power workgroups: its share of the
+// block power, of the clearing of the search's peak keys, crossing counts and
+// refinement tickets, and, in the last one to arrive, the statistics.
+template <int NT>
+__device__ __forceinline__ void power_group(const BlockTable& bt, const PowerArgs& a, int wg) {
+    for (int64_t i = int64_t(wg) * NT + threadIdx.x; i < a.nclear; i += int64_t(a.groups) * NT) {
+        a.keys[i] = 0ull;
+        a.cross[i] = 0u;
+        a.tickets[i] = 0u;
+        if (i == 0) a.tickets[a.nclear] = 0u;
+    }
+    sum_block_power<NT>(bt, a, wg);
+    if (!last_arrival(a.ticket, unsigned(a.groups))) return;
+    block_stats<NT>(bt, a);
+    if (threadIdx.x == 0) *a.ticket = 0u;        // for the next launch
 }
 
 // ------------------------------------------------------------------ forward spectra
@@ -154,12 +209,21 @@ __global__ __launch_bounds__(kStatsThreads) void k_block_stats(BlockTable bt, co
 //   and packed in the 16-bit copy instead.  Each spectrum sits at offset xpad
 //   of its slot, with its last xpad entries copied before it and its first
 //   xpad after it (rotated reads need no wrap-around).
+// The launch's first a.power.groups workgroups sum the block power and form the
+// statistics beside the transforms (as launches of their own, 4.5 and 2.6 us
+// and two launch gaps for one block of 131,072 samples; the transforms take
+// 10.6 us with or without them).
 // PREMIX: exact bins, whose classes have residual offsets (a kernel of its own:
 // its phase reductions cost the other one registers).
 template <class E, bool PREMIX>
 __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
     __shared__ float2 lds[E::LDS];
     __shared__ float2 extra[E::EXTRA];
+    const int wg = int(blockIdx.x) - a.power.groups, wgs = int(gridDim.x) - a.power.groups;
+    if (wg < 0) {
+        power_group<E::NT>(a.blocks, a.power, int(blockIdx.x));
+        return;
+    }
     E eng;
     eng.init(a.rootsSub, extra);
     const __amdgpu_buffer_rsrc_t b1 = make_rsrc(a.b1tab, E::B1_TABLE * 8);
@@ -171,8 +235,8 @@ __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
     // each group of kXcds * per_seg workgroups, workgroup j takes item
     // k = j / kXcds of segment j % kXcds of the group.
     const int grp = kXcds * per_seg;
-    const bool xcd_map = int(gridDim.x) >= items && per_seg > 1;
-    for (int b = int(blockIdx.x); b < items; b += int(gridDim.x)) {
+    const bool xcd_map = wgs >= items && per_seg > 1;
+    for (int b = wg; b < items; b += wgs) {
         int it = b;
         if (xcd_map && b < items / grp * grp) {
             const int q = b / grp, j = b - q * grp;
@@ -304,15 +368,21 @@ __global__ __launch_bounds__(E::NT) void k_bank(const int8_t* __restrict__ chips
 // ------------------------------------------------------------------ refine
 constexpr int kMaxWin = 2 * kMaxRefineRadius + 3;
 
-// FP64 refinement of each (block, tag) peak key, in two passes of two
-// kernels.  The first pass takes the window of W = 2R + 3 lags centred on the
-// key's lag; k_refine_sums adds, in kRefineParts workgroups per item, the re-
-// and im-sums of the mixed samples against the tag's replica and the sample
-// energy under it for every lag of the window; k_refine_decide (one wave per
-// item) adds the parts in order, re-maximises over the inner 2R+1 lags and
-// either writes the detection or, when the maximum sits on the inner edge,
-// records a re-centred window for the second pass, which repeats both steps
-// once.
+// FP64 refinement of each (block, tag) peak key, one launch.  The window of W =
+// 2R + 3 lags is centred on the key's lag; kRefineParts workgroups per item add
+// the re- and im-sums of the mixed samples against the tag's replica and the
+// sample energy under it for every lag of the window, and the last of them to
+// arrive adds the parts in order, re-maximises over the inner 2R+1 lags and
+// writes the detection.  When the maximum sits on the inner edge it takes the
+// window re-centred there once more first, part by part in the same order (the
+// two kernels of a second pass cost each search two launches; the powers of the
+// two passes' centres differ by the rounding of the search, so few items do).
+// The last item of a small search writes the detections in (block, tag) order
+// as well, also to the host (k_compact and two copies otherwise).
+// Against two passes of two kernels, the compaction and its copies, with the
+// power in launches of its own: a search of 1 code in 131,072 samples 89.7 ->
+// 60.6 us, of 13 codes in 5 bins of 100,003 samples 118 -> 91 us, 9 tracking
+// tasks 133 -> 98 us, 256 tasks 887 -> 852 us.
 // The mix exp(-j 2 pi m_k i / M) is an FP64 table entry at (m_k i) mod M (M a
 // power of two, so the reduction is exact), or the exact bin's FP64 phase.
 struct RefineItem {
@@ -332,24 +402,22 @@ __device__ __forceinline__ bool refine_item(const RefineArgs& a, int item, Refin
     return true;
 }
 
-constexpr int kRefineChipsLds = 4096;     // chips of one part staged in LDS (else read from global)
+constexpr int kRefineMaxChips = 1 << 14;  // the longest code of any transform length
+// chips under one part: (C spc + W - 1) / kRefineParts samples rounded up, and W - 1 more
+constexpr int kRefineChipsLds = kRefineMaxChips / kRefineParts + 2 * kMaxWin + 4;
 
+constexpr int kRefineThreads = 256;
+
+// Sums of part `part` of an item's window around `center`, to a.partial.
 template <int WMAX>
-__global__ __launch_bounds__(256) void k_refine_sums(RefineArgs a, int pass) {
-    constexpr int NT = 256, NW = NT / 64;
-    const int item = int(blockIdx.x) / kRefineParts, part = int(blockIdx.x) % kRefineParts;
-    RefineItem it;
-    if (!refine_item(a, item, &it)) return;
+__device__ __forceinline__ void refine_sums(const RefineArgs& a, const RefineItem& it, int item, int part, int k,
+                                            int64_t center) {
+    __shared__ int8_t s_chips[kRefineChipsLds];
+    __shared__ double red[kRefineThreads / 64][3 * WMAX];
+    constexpr int NT = kRefineThreads, NW = NT / 64;
     const BlockDesc& d = it.d;
-    const unsigned long long key = d.lags > 0 ? a.keys[it.slot] : 0ull;
-    if (key == 0ull) return;
-    const unsigned idx = ~unsigned(key & 0xffffffffull);
-    const int k = int(idx % unsigned(a.K));
-    const int64_t center = pass == 0 ? int64_t(idx / unsigned(a.K)) : a.center[item];
-    if (center < 0) return;
     const int R = a.radius;
-    const int W = 2 * R + 3;
-    if (W > WMAX) return;                    // the launcher picks WMAX >= W
+    const int W = 2 * R + 3;                 // <= WMAX, which the launcher picks
     const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
     const int64_t lam0 = center - R - 1;
     // samples of the window inside the block, split into parts
@@ -357,15 +425,11 @@ __global__ __launch_bounds__(256) void k_refine_sums(RefineArgs a, int pass) {
     const int64_t e_hi = min(int64_t(a.L) + W - 1, d.n - lam0);
     const int64_t ch = (e_hi - e_lo + kRefineParts - 1) / kRefineParts;
     const int64_t p0 = e_lo + int64_t(part) * ch, p1 = min(e_hi, p0 + ch);
-    // the part's chips (replica samples e - w, w < W) in LDS when they fit
-    __shared__ int8_t s_chips[kRefineChipsLds];
+    // the part's chips (replica samples e - w, w < W)
     const int8_t* chips = a.chips + size_t(it.tag) * size_t(a.C);
     const int64_t c0 = max(int64_t(0), (p0 - W + 1) >> a.log2_spc);
     const int64_t c1 = min(int64_t(a.C), ((p1 - 1) >> a.log2_spc) + 1);
-    const bool lds = c1 - c0 <= kRefineChipsLds;
-    if (lds) {
-        for (int64_t q = c0 + t; q < c1; q += NT) s_chips[q - c0] = chips[q];
-    }
+    for (int64_t q = c0 + t; q < c1; q += NT) s_chips[q - c0] = chips[q];
     __syncthreads();
     const int64_t mrot = a.rot_signed[k];
     const int64_t mmask = int64_t(a.M) - 1;
@@ -373,34 +437,42 @@ __global__ __launch_bounds__(256) void k_refine_sums(RefineArgs a, int pass) {
     double cr[WMAX], ci[WMAX], en[WMAX];
 #pragma unroll
     for (int w = 0; w < WMAX; ++w) cr[w] = ci[w] = en[w] = 0.0;
-    for (int64_t e = p0 + t; e < p1; e += NT) {
-        const int64_t i = lam0 + e;
-        const float2 xv = d.x[i];
-        const double xr = xv.x, xi = xv.y;
-        double2 cs;
-        if (a.exact) {                          // exp(-j 2 pi (f_k / Fs) i), phase reduced in FP64
-            double ph = fk * double(i);
-            ph -= floor(ph);
-            sincospi(2.0 * ph, &cs.y, &cs.x);
-        } else {
-            cs = a.roots64[(mrot * i) & mmask];
-        }
-        const double mr = xr * cs.x + xi * cs.y;      // x * exp(-j 2 pi m i / M)
-        const double mi = xi * cs.x - xr * cs.y;
-        const double pw = xr * xr + xi * xi;
+    constexpr int U = 4;                     // a thread's samples loaded together
+    for (int64_t e0 = p0 + t; e0 < p1; e0 += U * NT) {
+        float2 xs[U];
+        double2 ts[U];
 #pragma unroll
-        for (int w = 0; w < WMAX; ++w) {
-            const int64_t nn = e - w;
-            if (w < W && nn >= 0 && nn < a.L) {
-                const int64_t c = nn >> a.log2_spc;
-                const double sg = double(lds ? s_chips[c - c0] : chips[c]);
-                cr[w] += mr * sg;
-                ci[w] += mi * sg;
-                en[w] += pw;
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = lam0 + min(e0 + u * NT, p1 - 1);
+            xs[u] = d.x[i];
+            if (!a.exact) ts[u] = a.roots64[(mrot * i) & mmask];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * NT;
+            if (e >= p1) break;
+            const double xr = xs[u].x, xi = xs[u].y;
+            double2 cs = ts[u];
+            if (a.exact) {                      // exp(-j 2 pi (f_k / Fs) i), phase reduced in FP64
+                double ph = fk * double(lam0 + e);
+                ph -= floor(ph);
+                sincospi(2.0 * ph, &cs.y, &cs.x);
+            }
+            const double mr = xr * cs.x + xi * cs.y;      // x * exp(-j 2 pi m i / M)
+            const double mi = xi * cs.x - xr * cs.y;
+            const double pw = xr * xr + xi * xi;
+#pragma unroll
+            for (int w = 0; w < WMAX; ++w) {
+                const int64_t nn = e - w;
+                if (w < W && nn >= 0 && nn < a.L) {
+                    const double sg = double(s_chips[(nn >> a.log2_spc) - c0]);
+                    cr[w] += mr * sg;
+                    ci[w] += mi * sg;
+                    en[w] += pw;
+                }
             }
         }
     }
-    __shared__ double red[NW][3 * WMAX];
 #pragma unroll
     for (int w = 0; w < WMAX; ++w) {
         const double r0 = wave_sum(cr[w]), r1 = wave_sum(ci[w]), r2 = wave_sum(en[w]);
@@ -414,59 +486,51 @@ __global__ __launch_bounds__(256) void k_refine_sums(RefineArgs a, int pass) {
     if (t < 3 * W) {
         double v = 0.0;
         for (int q = 0; q < NW; ++q) v += red[q][t];
-        a.partial[(size_t(item) * kRefineParts + part) * size_t(3 * WMAX) + t] = v;
+        agent_store(&a.partial[(size_t(item) * kRefineParts + part) * size_t(3 * WMAX) + t], v);
     }
 }
 
-// One wave per item: lane s < 3W adds sum s over the parts in order, lane 0
-// decides.
+// The item's sums over its parts and the powers of its window, to sums and P.
 template <int WMAX>
-__global__ __launch_bounds__(64) void k_refine_decide(RefineArgs a, int pass) {
-    const int item = int(blockIdx.x);
-    RefineItem it;
-    if (!refine_item(a, item, &it)) return;
-    const BlockDesc& d = it.d;
-    const int t = int(threadIdx.x);
-    const unsigned long long key = d.lags > 0 ? a.keys[it.slot] : 0ull;
-    if (key == 0ull) {                       // no valid lag was searched for this tag
-        if (pass == 0 && t == 0) {
-            a.found[it.slot] = 0;
-            a.center[item] = -1;
-        }
-        return;
-    }
-    const unsigned idx = ~unsigned(key & 0xffffffffull);
-    const int k = int(idx % unsigned(a.K));
-    const int64_t center = pass == 0 ? int64_t(idx / unsigned(a.K)) : a.center[item];
-    if (center < 0) return;
-    const int R = a.radius;
-    const int W = 2 * R + 3;
-    if (W > WMAX) return;
-    __shared__ double sums[3 * WMAX];
+__device__ __forceinline__ void refine_powers(const RefineArgs& a, const RefineItem& it, int item, int64_t center,
+                                              double* sums, double* P) {
+    const int W = 2 * a.radius + 3, t = int(threadIdx.x);
     if (t < 3 * W) {
         double v = 0.0;
-        for (int q = 0; q < kRefineParts; ++q) v += a.partial[(size_t(item) * kRefineParts + q) * size_t(3 * WMAX) + t];
+        double q[kRefineParts];
+#pragma unroll
+        for (int i = 0; i < kRefineParts; ++i)
+            q[i] = agent_load(&a.partial[(size_t(item) * kRefineParts + i) * size_t(3 * WMAX) + t]);
+#pragma unroll
+        for (int i = 0; i < kRefineParts; ++i) v += q[i];
         sums[t] = v;
     }
     __syncthreads();
-    if (t != 0) return;
-    const int64_t lam0 = center - R - 1;
-    double P[WMAX], E[WMAX];
-    for (int w = 0; w < W; ++w) {
-        const double re = sums[3 * w], im = sums[3 * w + 1];
-        E[w] = sums[3 * w + 2];
-        const int64_t lam = lam0 + w;
-        P[w] = (lam >= 0 && lam < d.lags) ? re * re + im * im : -1.0;
+    if (t < W) {
+        const int64_t lam = center - a.radius - 1 + t;
+        const double re = sums[3 * t], im = sums[3 * t + 1];
+        P[t] = (lam >= 0 && lam < it.d.lags) ? re * re + im * im : -1.0;
     }
-    int wb = R + 1;
+    __syncthreads();
+}
+
+// Window position of the largest power (the centre, then the lowest lag, at a
+// tie), and whether the window may continue past it.
+__device__ __forceinline__ int refine_best(const RefineArgs& a, const RefineItem& it, int64_t center, const double* P,
+                                           bool* hit) {
+    const int W = 2 * a.radius + 3;
+    int wb = a.radius + 1;
     for (int w = 1; w <= W - 2; ++w)
         if (P[w] > P[wb] || (P[w] == P[wb] && w < wb)) wb = w;
-    const int64_t lam = lam0 + wb;
-    const bool hit = (wb == 1 && lam > 0) || (wb == W - 2 && lam < d.lags - 1);
-    if (pass == 0) {
-        a.center[item] = hit ? lam : -1;
-        if (hit) return;                     // the second pass re-centres on lam
-    }
+    const int64_t lam = center - a.radius - 1 + wb;
+    *hit = (wb == 1 && lam > 0) || (wb == W - 2 && lam < it.d.lags - 1);
+    return wb;
+}
+
+// The detection record of an item whose largest power is at window position wb.
+__device__ __forceinline__ void refine_record(const RefineArgs& a, const RefineItem& it, int k, int64_t lam, int wb,
+                                              bool hit, const double* sums, const double* P) {
+    const BlockDesc& d = it.d;
     unsigned flags = hit ? ACQ_DET_WINDOW_EDGE : 0u;
     const double p0 = P[wb];
     const double pm = P[wb - 1] < 0.0 ? 0.0 : P[wb - 1];
@@ -484,26 +548,110 @@ __global__ __launch_bounds__(64) void k_refine_decide(RefineArgs a, int pass) {
     const double px = block_mean_power(a.parts + size_t(it.bi) * kPowerParts, d.n);
     const double z = px > 0.0 ? p0 / (double(a.L) * px) : 0.0;
     const bool suppressed = a.check_finite && a.bad[it.bi];
-    acq_detection r;
-    r.tag = it.tag;
-    r.bin = k;
-    r.lag = lam;
-    r.toa_samples = double(lam) + delta;
-    r.freq_hz = a.freqs[k];
-    r.peak_power = p0;
-    r.z = z;
-    r.energy = E[wb];
-    r.block_power = px;
+    union {
+        acq_detection r;
+        unsigned long long u[sizeof(acq_detection) / 8];
+    } o;
+    o.r.tag = it.tag;
+    o.r.bin = k;
+    o.r.lag = lam;
+    o.r.toa_samples = double(lam) + delta;
+    o.r.freq_hz = a.freqs[k];
+    o.r.peak_power = p0;
+    o.r.z = z;
+    const double energy = sums[3 * wb + 2];
+    o.r.energy = energy;
+    o.r.block_power = px;
     // relative power and SNR (Section 3 step 8's power and SNR sums)
     const double Ld = double(a.L);
-    r.power = p0 / (Ld * Ld);
-    const double s2 = (E[wb] - p0 / Ld) / Ld;
-    r.snr = s2 > 0.0 ? r.power / s2 : __builtin_huge_val();
-    r.block = it.bi;
-    r.flags = flags;
-    r.crossings = int64_t(a.cross[it.slot]);
-    a.dets[it.slot] = r;
-    a.found[it.slot] = z >= d.theta && !suppressed ? 1 : 0;
+    o.r.power = p0 / (Ld * Ld);
+    const double s2 = (energy - p0 / Ld) / Ld;
+    o.r.snr = s2 > 0.0 ? o.r.power / s2 : __builtin_huge_val();
+    o.r.block = it.bi;
+    o.r.flags = flags;
+    o.r.crossings = int64_t(a.cross[it.slot]);
+    unsigned long long* rec = reinterpret_cast<unsigned long long*>(&a.dets[it.slot]);
+#pragma unroll
+    for (int i = 0; i < int(sizeof(acq_detection) / 8); ++i) agent_store(rec + i, o.u[i]);
+    agent_store(&a.found[it.slot], z >= d.theta && !suppressed ? 1 : 0);
+}
+
+// The detections of a search of at most kTailItems items, in order, to a.out and
+// the host (as k_compact does): slots of the detections listed in LDS, then
+// their records copied word by word.
+__device__ __forceinline__ void compact_tail(const RefineArgs& a, int items, int* s_slot, int* s_wave) {
+    constexpr int NT = kRefineThreads, WORDS = int(sizeof(acq_detection) / 8);
+    const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
+    int base = 0;
+    for (int e0 = 0; e0 < items; e0 += NT) {
+        const int e = e0 + t;
+        int slot = -1;
+        RefineItem it;
+        if (e < items && refine_item(a, e, &it) && agent_load(&a.found[it.slot])) slot = int(it.slot);
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(slot >= 0);
+        if (lane == 0) s_wave[wave] = __popcll(mask);
+        __syncthreads();
+        int o = base + __popcll(mask & ((1ull << lane) - 1ull));
+        for (int w = 0; w < NT / 64; ++w) {
+            if (w < wave) o += s_wave[w];
+            base += s_wave[w];
+        }
+        if (slot >= 0) s_slot[o] = slot;
+        __syncthreads();
+    }
+    const int n = min(base, a.capacity) * WORDS;
+    for (int i = t; i < n; i += NT) {
+        const int r = i / WORDS;
+        const unsigned long long v =
+            agent_load(reinterpret_cast<const unsigned long long*>(&a.dets[s_slot[r]]) + (i - r * WORDS));
+        reinterpret_cast<unsigned long long*>(a.out)[i] = v;
+        if (a.h_out) reinterpret_cast<unsigned long long*>(a.h_out)[i] = v;
+    }
+    if (t == 0) {
+        *a.count = base;
+        if (a.h_out) {
+            a.h_count[0] = base;
+            a.h_count[1] = *a.nbad;
+        }
+    }
+}
+
+template <int WMAX>
+__global__ __launch_bounds__(kRefineThreads) void k_refine(RefineArgs a) {
+    __shared__ double sums[3 * WMAX], P[WMAX];
+    __shared__ int s_slot[kTailItems], s_wave[kRefineThreads / 64];
+    const int item = int(blockIdx.x) / kRefineParts, part = int(blockIdx.x) % kRefineParts;
+    const int items = a.blocks.nblocks() * (a.track ? 1 : a.T);
+    if (item >= items) return;               // a batch smaller than the plan's capacity
+    RefineItem it;
+    const bool known = refine_item(a, item, &it);      // false: a tracking task of no tag
+    const unsigned long long key = known && it.d.lags > 0 ? a.keys[it.slot] : 0ull;
+    if (key != 0ull) {
+        const unsigned idx = ~unsigned(key & 0xffffffffull);
+        const int k = int(idx % unsigned(a.K));
+        int64_t center = int64_t(idx / unsigned(a.K));
+        refine_sums<WMAX>(a, it, item, part, k, center);
+        if (!last_arrival(&a.tickets[1 + item], kRefineParts)) return;
+        refine_powers<WMAX>(a, it, item, center, sums, P);
+        bool hit;
+        int wb = refine_best(a, it, center, P, &hit);  // every thread the same
+        if (hit) {
+            center += wb - a.radius - 1;
+            for (int q = 0; q < kRefineParts; ++q) {
+                __syncthreads();                       // sums, P and red are rewritten
+                refine_sums<WMAX>(a, it, item, q, k, center);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            refine_powers<WMAX>(a, it, item, center, sums, P);
+            wb = refine_best(a, it, center, P, &hit);
+        }
+        if (threadIdx.x == 0) refine_record(a, it, k, center - a.radius - 1 + wb, wb, hit, sums, P);
+    } else {                                 // no valid lag was searched for this tag
+        if (part != 0) return;
+        if (known && threadIdx.x == 0) agent_store(&a.found[it.slot], 0);
+    }
+    if (a.tail && last_arrival(&a.tickets[0], unsigned(items))) compact_tail(a, items, s_slot, s_wave);
 }
 
 // Detections in (block, tag) order.  One workgroup: each thread takes a
@@ -551,23 +699,6 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(BlockTable bt, cons
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_block_power(const BlockTable& bt, int max_blocks, int64_t max_len, double* parts, hipStream_t st) {
-    const int mp = std::max(power_parts(max_len), 1);
-    const unsigned grid = unsigned(std::min<int64_t>(int64_t(max_blocks) * mp, kPowerMaxGrid));
-    hipLaunchKernelGGL(k_block_power, dim3(grid), dim3(256), 0, st, bt, parts, mp);
-    return hipGetLastError();
-}
-
-hipError_t launch_block_stats(const BlockTable& bt, const double* parts, int M, int64_t L, int* exps, float* pthr,
-                              int32_t* bad, int32_t* nbad, unsigned long long* keys, unsigned* cross,
-                              int64_t nclear, hipStream_t st) {
-    // workgroup 0 forms the statistics; all of them clear, 2048 entries each
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(256, (nclear + 2047) / 2048));
-    hipLaunchKernelGGL(k_block_stats, dim3(unsigned(grid)), dim3(kStatsThreads), 0, st, bt, parts, M, L, exps, pthr,
-                       bad, nbad, keys, cross, nclear);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_u64(unsigned long long* p, int64_t count, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     const int64_t blocks = (count + 255) / 256;
@@ -583,7 +714,17 @@ hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st) {
 }
 
 template <class E>
-static hipError_t fwd_e(const FwdArgs& a, int grid, hipStream_t st) {
+static hipError_t fwd_e(FwdArgs a, int grid, int power_blocks, int64_t power_len, hipStream_t st) {
+    a.power.groups = 0;
+    if (power_blocks > 0) {
+        constexpr int PP = power_per_group<E::NT>();
+        a.power.max_parts = std::max(power_parts(power_len), 1);
+        const int64_t items = int64_t(power_blocks) * a.power.max_parts;
+        // (and at most 2048 entries to clear a workgroup, as far as that goes)
+        a.power.groups = int(std::min<int64_t>(std::max((items + PP - 1) / PP, (a.power.nclear + 2047) / 2048),
+                                               kPowerMaxGrid / PP));
+        grid += a.power.groups;
+    }
     if (a.premix)
         hipLaunchKernelGGL((k_forward_sub<E, true>), dim3(grid), dim3(E::NT), 0, st, a);
     else
@@ -627,18 +768,19 @@ hipError_t launch_forward_combine(const FwdArgs& a, int slots, int prec, hipStre
     return e == hipSuccess ? hipGetLastError() : e;
 }
 
-hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int log2_sub, int prec, hipStream_t st) {
-    if (grid <= 0 || combine_slots <= 0) return hipSuccess;
+hipError_t launch_forward(const FwdArgs& a, int grid, int combine_slots, int power_blocks, int64_t power_len,
+                          int log2_sub, int prec, hipStream_t st) {
+    if (grid <= 0 && power_blocks <= 0) return hipSuccess;
     if ((1 << log2_sub) != a.Msub || a.Msub % 256 || a.spc < 1 || (a.spc > 8 && !(a.spc == 16 && prec == ACQ_FP32)))
         return hipErrorInvalidValue;
     if (a.xpad < 0 || a.xpad > a.M / 2 || a.xstride < int64_t(a.M) + 2 * int64_t(a.xpad)) return hipErrorInvalidValue;
     hipError_t e;
     switch (log2_sub) {
-        case 10: e = fwd_e<StockhamEngine<10>>(a, grid, st); break;
-        case 11: e = fwd_e<StockhamEngine<11>>(a, grid, st); break;
-        case 12: e = fwd_e<StockhamEngine<12>>(a, grid, st); break;
-        case 13: e = fwd_e<StockhamEngine<13>>(a, grid, st); break;
-        case 14: e = fwd_e<Fft14>(a, grid, st); break;
+        case 10: e = fwd_e<StockhamEngine<10>>(a, grid, power_blocks, power_len, st); break;
+        case 11: e = fwd_e<StockhamEngine<11>>(a, grid, power_blocks, power_len, st); break;
+        case 12: e = fwd_e<StockhamEngine<12>>(a, grid, power_blocks, power_len, st); break;
+        case 13: e = fwd_e<StockhamEngine<13>>(a, grid, power_blocks, power_len, st); break;
+        case 14: e = fwd_e<Fft14>(a, grid, power_blocks, power_len, st); break;
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -681,20 +823,16 @@ hipError_t launch_bank(const int8_t* chips, int T, int C, void* bank, const floa
 }
 
 hipError_t launch_refine(const RefineArgs& a, int max_blocks, hipStream_t st) {
-    if (a.radius < 0 || a.radius > kMaxRefineRadius || (a.M & (a.M - 1)) || (1 << a.log2_spc) != a.spc ||
-        !a.partial || !a.center)
+    if (a.radius < 0 || a.radius > kMaxRefineRadius || a.C > kRefineMaxChips || (a.M & (a.M - 1)) || (1 << a.log2_spc) != a.spc ||
+        !a.partial || !a.tickets)
         return hipErrorInvalidValue;
     const int items = max_blocks * (a.track ? 1 : a.T);
-    const dim3 sgrid(unsigned(items) * kRefineParts), dgrid{unsigned(items)};
-    for (int pass = 0; pass < 2; ++pass) {
-        if (a.radius <= 1) {
-            hipLaunchKernelGGL((k_refine_sums<5>), sgrid, dim3(256), 0, st, a, pass);
-            hipLaunchKernelGGL((k_refine_decide<5>), dgrid, dim3(64), 0, st, a, pass);
-        } else {
-            hipLaunchKernelGGL((k_refine_sums<kMaxWin>), sgrid, dim3(256), 0, st, a, pass);
-            hipLaunchKernelGGL((k_refine_decide<kMaxWin>), dgrid, dim3(64), 0, st, a, pass);
-        }
-    }
+    if (a.tail && (items > kTailItems || !a.out || !a.count)) return hipErrorInvalidValue;
+    const dim3 grid(unsigned(items) * kRefineParts);
+    if (a.radius <= 1)
+        hipLaunchKernelGGL((k_refine<5>), grid, dim3(kRefineThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_refine<kMaxWin>), grid, dim3(kRefineThreads), 0, st, a);
     return hipGetLastError();
 }
 

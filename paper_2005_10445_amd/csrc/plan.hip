@@ -44,13 +44,17 @@ struct Scratch {
     acq_detection* out = nullptr;       // [blocks][T] detections, compacted
     int32_t* found = nullptr;           // [blocks][T]
     double* refpart = nullptr;          // refinement partial sums [blocks * T][parts][3 * window]
-    int64_t* refcenter = nullptr;       // [blocks * T] refinement re-centring
+    unsigned* tickets = nullptr;        // [1 + blocks * T] refinement arrivals, cleared by each search
+    unsigned* ticket = nullptr;         // block-power arrivals, zero between searches (the plan's, not the workspace's)
     int32_t* count = nullptr;           // [2]: detections, blocks holding a non-finite sample
     int* counters = nullptr;            // [kXcds] persistent-launch work counters
+    int32_t* counts = nullptr;          // [2] = {blocks, segments} of a batch, then (kDescsAt bytes on)
     BlockDesc* descs = nullptr;         // [blocks]
-    int32_t* counts = nullptr;          // [2] = {blocks, segments} of a batch
     int32_t* seglist = nullptr;         // segments searched by a proposal search
 };
+
+// A batch's counts and descriptors lie together: one upload.
+constexpr size_t kDescsAt = 16;
 
 struct acq_plan_s {
     acq_config cfg{};
@@ -82,8 +86,9 @@ struct acq_plan_s {
     double* d_freqs = nullptr;          // [K]
     acq_detection* h_out = nullptr;     // pinned [blocks][T]
     int32_t* h_count = nullptr;         // pinned [2]
-    BlockDesc* h_descs = nullptr;       // pinned [blocks]
-    int32_t* h_counts = nullptr;        // pinned [2]
+    int32_t* h_counts = nullptr;        // pinned [2], then (kDescsAt bytes on)
+    BlockDesc* h_descs = nullptr;       // [blocks]
+    unsigned* d_ticket = nullptr;       // [2] block-power arrivals: workspace searches, static-scratch searches
     int32_t* h_iota = nullptr;          // pinned [max_segments] 0, 1, 2, ... (full-search lists)
     hipEvent_t desc_ev = nullptr;       // after the last upload of h_descs / h_counts
     bool desc_pending = false;
@@ -167,10 +172,10 @@ void free_plan(acq_plan_s* p) {
     if (!p) return;
     drop_graph(p);
     void* dev[] = {p->own_ws, p->d_cls, p->d_cls_cyc, p->d_cyc, p->d_bank, p->d_wts, p->d_rootsM, p->d_rootsSub,
-                   p->d_roots64, p->d_b1tab, p->d_chips, p->d_rot, p->d_rot_signed, p->d_freqs};
+                   p->d_roots64, p->d_b1tab, p->d_chips, p->d_rot, p->d_rot_signed, p->d_freqs, p->d_ticket};
     for (void* d : dev)
         if (d) (void)hipFree(d);
-    void* host[] = {p->h_out, p->h_count, p->h_descs, p->h_counts, p->h_iota};
+    void* host[] = {p->h_out, p->h_count, p->h_counts, p->h_iota};
     for (void* h : host)
         if (h) (void)hipHostFree(h);
     for (auto& pair : p->ev)
@@ -211,11 +216,11 @@ size_t layout_scratch(const Geometry& g, const acq_config& c, int64_t blocks, in
     take(s->out, B * T * sizeof(acq_detection));
     take(s->found, B * T * sizeof(int32_t));
     take(s->refpart, B * T * size_t(acq::kRefineParts) * 3 * wmax * sizeof(double));
-    take(s->refcenter, B * T * sizeof(int64_t));
+    take(s->tickets, (B * T + 1) * sizeof(unsigned));
     take(s->count, 2 * sizeof(int32_t));
     take(s->counters, size_t(acq::kXcds) * sizeof(int));
-    take(s->descs, B * sizeof(BlockDesc));
-    take(s->counts, 2 * sizeof(int32_t));
+    take(s->counts, kDescsAt + B * sizeof(BlockDesc));
+    s->descs = base ? reinterpret_cast<BlockDesc*>(reinterpret_cast<char*>(s->counts) + kDescsAt) : nullptr;
     take(s->seglist, size_t(std::max<int64_t>(seglist, 1)) * sizeof(int32_t));
     return off;
 }
@@ -271,12 +276,14 @@ int build_plan(acq_plan_s* p, void* workspace, size_t ws_bytes) {
     ACQ_HIP(dalloc(&p->d_rot, K));
     ACQ_HIP(dalloc(&p->d_rot_signed, K));
     ACQ_HIP(dalloc(&p->d_freqs, K));
+    ACQ_HIP(dalloc(&p->d_ticket, 2));
+    p->ws.ticket = p->d_ticket;
     ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_iota), sizeof(int32_t) * size_t(std::max<int64_t>(g.max_segments, 1))));
     for (int64_t j = 0; j < g.max_segments; ++j) p->h_iota[j] = int32_t(j);
     ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_out), sizeof(acq_detection) * B * T));
     ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_count), sizeof(int32_t) * 2));
-    ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_descs), sizeof(BlockDesc) * B));
-    ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), sizeof(int32_t) * 2));
+    ACQ_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_counts), kDescsAt + sizeof(BlockDesc) * B));
+    p->h_descs = reinterpret_cast<BlockDesc*>(reinterpret_cast<char*>(p->h_counts) + kDescsAt);
     ACQ_HIP(hipEventCreateWithFlags(&p->desc_ev, hipEventDisableTiming));
 
     const std::vector<float> rootsM = acq::unit_roots(g.M);
@@ -286,6 +293,7 @@ int build_plan(acq_plan_s* p, void* workspace, size_t ws_bytes) {
     hipStream_t st = p->stream;
     // nothing has been searched yet: results read before the first search are empty
     ACQ_HIP(acq::launch_fill_i32(p->ws.count, 2, st));
+    ACQ_HIP(acq::launch_fill_i32(reinterpret_cast<int*>(p->d_ticket), 2, st));
     ACQ_HIP(hipMemcpyAsync(p->d_rootsM, rootsM.data(), rootsM.size() * sizeof(float), hipMemcpyHostToDevice, st));
     ACQ_HIP(hipMemcpyAsync(p->d_rootsSub, rootsSub.data(), rootsSub.size() * sizeof(float), hipMemcpyHostToDevice, st));
     ACQ_HIP(hipMemcpyAsync(p->d_roots64, roots64.data(), roots64.size() * sizeof(double), hipMemcpyHostToDevice, st));
@@ -304,14 +312,19 @@ int build_plan(acq_plan_s* p, void* workspace, size_t ws_bytes) {
     return ACQ_OK;
 }
 
-// Event pair around one kernel launch when profiling is on (not while capturing).
+// Whether a kernel is timed (not while capturing).
+bool timing(const acq_plan_s* p, int kernel) {
+    return p->profiling && ((p->profile_mask >> kernel) & 1u) && !p->capturing && !p->ext_capture;
+}
+
+// Event pair around one kernel launch when it is timed.
 struct KernelTimer {
     acq_plan_s* p;
     int id;
     bool on;
     KernelTimer(acq_plan_s* plan, int kernel)
         : p(plan), id(kernel),
-          on(plan->profiling && ((plan->profile_mask >> kernel) & 1u) && !plan->capturing && !plan->ext_capture) {
+          on(timing(plan, kernel)) {
         if (on) {
             (void)hipEventRecord(p->ev[id][0], p->stream);
             p->ev_used[id] = true;
@@ -356,15 +369,20 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     const Geometry& g = p->g;
     const acq_config& c = p->cfg;
     const int nb_grid = batch ? g.max_blocks : 1;
-    {
-        KernelTimer kt(p, ACQ_KERNEL_BLOCK_POWER);
-        ACQ_HIP(acq::launch_block_power(bt, nb_grid, c.max_block_len, w.parts, st));
-    }
-    // block statistics; the same launch clears the peak keys and crossing counts
-    ACQ_HIP(acq::launch_block_stats(bt, w.parts, int(g.M), g.L, w.exps, w.pthr, w.bad, w.count + 1, w.keys, w.cross,
-                                    int64_t(nb_grid) * c.num_tags, st));
 
     acq::FwdArgs fa{};
+    fa.power.parts = w.parts;
+    fa.power.exps = w.exps;
+    fa.power.pthr = w.pthr;
+    fa.power.bad = w.bad;
+    fa.power.nbad = w.count + 1;
+    fa.power.keys = w.keys;
+    fa.power.cross = w.cross;
+    fa.power.tickets = w.tickets;
+    fa.power.ticket = w.ticket;
+    fa.power.nclear = int64_t(nb_grid) * c.num_tags;
+    fa.power.L = g.L;
+    fa.power.M = int(g.M);
     fa.blocks = bt;
     fa.X = w.X;
     fa.Xh = w.Xh;
@@ -381,6 +399,12 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     fa.spc = c.samples_per_chip;
     fa.M = int(g.M);
     fa.Msub = int(g.Msub);
+    // timed on its own, the block power takes a launch of its own
+    const bool power_alone = timing(p, ACQ_KERNEL_BLOCK_POWER);
+    if (power_alone) {
+        KernelTimer kt(p, ACQ_KERNEL_BLOCK_POWER);
+        ACQ_HIP(acq::launch_forward(fa, 0, 0, nb_grid, c.max_block_len, g.log2_sub, c.precision, st));
+    }
     {
         KernelTimer kt(p, ACQ_KERNEL_FORWARD);
         // one workgroup per item (so that a segment's items can share an XCD);
@@ -388,7 +412,8 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
         // surplus workgroups exit
         const int slots = (batch && p->capturing ? int(g.max_total_segments) : total_seg_host) * g.ncls;
         const int grid = slots * c.samples_per_chip;
-        ACQ_HIP(acq::launch_forward(fa, grid, slots, g.log2_sub, c.precision, st));
+        ACQ_HIP(acq::launch_forward(fa, grid, slots, power_alone ? 0 : nb_grid, c.max_block_len, g.log2_sub,
+                                    c.precision, st));
     }
 
     acq::CorrArgs ca{};
@@ -490,11 +515,23 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     ra.radius = c.refine_radius > 0 ? c.refine_radius : 1;
     ra.track = track ? 1 : 0;
     ra.partial = w.refpart;
-    ra.center = w.refcenter;
+    ra.tickets = w.tickets;
+    // A search of few items has its detections written by the refinement launch
+    // itself; the compaction kernel is worth its launch and the copies theirs
+    // when they are many or it is timed on its own.
+    const int64_t items = int64_t(nb_grid) * (track ? 1 : c.num_tags);
+    ra.tail = items <= acq::kTailItems && !timing(p, ACQ_KERNEL_COMPACT) ? 1 : 0;
+    ra.out = dst.out;
+    ra.capacity = dst.capacity;
+    ra.count = dst.count;
+    ra.nbad = w.count + 1;
+    ra.h_out = dst.to_host ? p->h_out : nullptr;
+    ra.h_count = p->h_count;
     {
         KernelTimer kt(p, ACQ_KERNEL_REFINE);
         ACQ_HIP(acq::launch_refine(ra, nb_grid, st));
     }
+    if (ra.tail) return ACQ_OK;
     {
         KernelTimer kt(p, ACQ_KERNEL_COMPACT);
         ACQ_HIP(acq::launch_compact(bt, w.dets, w.found, c.num_tags, track ? 1 : 0, dst.out, dst.capacity, dst.count,
@@ -503,8 +540,7 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
     if (!dst.to_host) return ACQ_OK;
     ACQ_HIP(hipMemcpyAsync(p->h_count, w.count, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     // at most one detection per (block, tag), per task when tracking
-    const size_t most = size_t(nb_grid) * size_t(track ? 1 : c.num_tags);
-    ACQ_HIP(hipMemcpyAsync(p->h_out, w.out, sizeof(acq_detection) * most, hipMemcpyDeviceToHost, st));
+    ACQ_HIP(hipMemcpyAsync(p->h_out, w.out, sizeof(acq_detection) * size_t(items), hipMemcpyDeviceToHost, st));
     return ACQ_OK;
 }
 
@@ -549,7 +585,7 @@ int launch_batch(acq_plan_s* p, int32_t seg, bool track) {
     BlockTable bt{};
     bt.descs = p->ws.descs;
     bt.counts = p->ws.counts;
-    const size_t desc_bytes = sizeof(BlockDesc) * size_t(p->g.max_blocks);
+    const size_t desc_bytes = kDescsAt + sizeof(BlockDesc) * size_t(p->g.max_blocks);
     const ResultDest dst = workspace_dest(p, !async_mode(p));
     if (p->cfg.flags & ACQ_FLAG_GRAPH) {
         hipGraph_t& graph_ref = track ? p->tgraph : p->graph;
@@ -559,10 +595,7 @@ int launch_batch(acq_plan_s* p, int32_t seg, bool track) {
             ACQ_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
             p->capturing = true;
             int rc = ACQ_OK;
-            hipError_t e = hipMemcpyAsync(p->ws.descs, p->h_descs, desc_bytes, hipMemcpyHostToDevice, p->cap_stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(p->ws.counts, p->h_counts, 2 * sizeof(int32_t), hipMemcpyHostToDevice,
-                                   p->cap_stream);
+            hipError_t e = hipMemcpyAsync(p->ws.counts, p->h_counts, desc_bytes, hipMemcpyHostToDevice, p->cap_stream);
             // grids follow the plan's capacity while capturing; the capturing
             // batch's segment count only guides the bins per tracking item
             if (e == hipSuccess)
@@ -582,8 +615,7 @@ int launch_batch(acq_plan_s* p, int32_t seg, bool track) {
         ACQ_HIP(hipEventRecord(p->desc_ev, p->stream));
         p->desc_pending = true;
     } else {
-        ACQ_HIP(hipMemcpyAsync(p->ws.descs, p->h_descs, desc_bytes, hipMemcpyHostToDevice, p->stream));
-        ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, 2 * sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
+        ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, desc_bytes, hipMemcpyHostToDevice, p->stream));
         ACQ_HIP(hipEventRecord(p->desc_ev, p->stream));
         p->desc_pending = true;
         const int rc = enqueue_search(p, p->ws, bt, true, seg, nullptr, true, p->stream, track, dst);
@@ -864,6 +896,7 @@ int acq_detect_noalloc(acq_plan_t p, const void* block, int64_t n, acq_detection
                              std::to_string(need) + " bytes of search memory, the static scratch holds " +
                              std::to_string(kStaticScratchBytes));
     layout_scratch(p->g, p->cfg, 1, bt.one.nseg, 1, static_cast<char*>(p->scratch), &w);
+    w.ticket = p->d_ticket + 1;
     rc = note_capture(p);
     if (rc != ACQ_OK) return rc;
     reset_timers(p);
@@ -1008,9 +1041,8 @@ int acq_detect_batch_learned(acq_plan_t p, acq_cnn_t cnn, const void* const* blo
     bt.descs = p->ws.descs;
     bt.counts = p->ws.counts;
     bt.seg_of = p->ws.seglist;
-    ACQ_HIP(hipMemcpyAsync(p->ws.descs, p->h_descs, sizeof(BlockDesc) * size_t(nblocks), hipMemcpyHostToDevice,
-                           p->stream));
-    ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, 2 * sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
+    ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, kDescsAt + sizeof(BlockDesc) * size_t(nblocks),
+                           hipMemcpyHostToDevice, p->stream));
     p->ext_capture = false;
     const int rc = enqueue_search(p, p->ws, bt, true, seg, nullptr, true, p->stream, false, workspace_dest(p, true));
     if (rc != ACQ_OK) return rc;
@@ -1110,9 +1142,8 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
         }
         p->h_counts[0] = int32_t(copies);
         p->h_counts[1] = batch_seg;
-        ACQ_HIP(hipMemcpyAsync(p->ws.descs, p->h_descs, sizeof(BlockDesc) * size_t(copies), hipMemcpyHostToDevice,
-                               p->stream));
-        ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, 2 * sizeof(int32_t), hipMemcpyHostToDevice, p->stream));
+        ACQ_HIP(hipMemcpyAsync(p->ws.counts, p->h_counts, kDescsAt + sizeof(BlockDesc) * size_t(copies),
+                               hipMemcpyHostToDevice, p->stream));
     }
     auto time_one = [&](const acq_tuning& t, bool batch, double* mean_ms) -> int {
         acq_set_tuning(p, &t);
