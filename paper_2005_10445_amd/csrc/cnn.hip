@@ -64,16 +64,14 @@ struct acq_cnn_s {
     float* y = nullptr;             // [rows] logits
     float* labels = nullptr;        // [rows]
     float* P = nullptr;             // [rows][256] STFT powers
-    uint32_t* hist = nullptr;       // [kMaxBatch][2048]
-    MedianState* mstate = nullptr;  // [kMaxBatch]
+    MedianScratch ms{};             // of kMaxBatch blocks
     float* med = nullptr;           // [kMaxBatch]
     float* hann = nullptr;          // [256]
     float2* tw = nullptr;           // [256] exp(-j 2 pi m / 256)
     float* loss = nullptr;          // [1]
     SynthTx* d_tx = nullptr;        // [kMaxBatch][kMaxTx]
     int32_t* d_ntx = nullptr;       // [kMaxBatch]
-    float* wscore = nullptr;        // [max frames of one block]
-    int32_t* d_info = nullptr;      // [2]
+    uint32_t* segmask = nullptr;    // [kProposeWords]
 
     SynthTx* h_tx = nullptr;        // pinned staging
     int32_t* h_ntx = nullptr;
@@ -89,8 +87,8 @@ namespace {
 void free_cnn(acq_cnn_s* c) {
     if (!c) return;
     void* dev[] = {c->theta, c->grad, c->m, c->v, c->w_bf, c->wt_bf, c->act[0], c->act[1], c->act[2], c->act[3],
-                   c->act[4], c->dH[0], c->dH[1], c->dw_part, c->y, c->labels, c->P, c->hist, c->mstate, c->med,
-                   c->hann, c->tw, c->loss, c->d_tx, c->d_ntx, c->wscore, c->d_info};
+                   c->act[4], c->dH[0], c->dH[1], c->dw_part, c->y, c->labels, c->P, c->ms.hist, c->ms.tickets,
+                   c->ms.state, c->med, c->hann, c->tw, c->loss, c->d_tx, c->d_ntx, c->segmask};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     void* host[] = {c->h_tx, c->h_ntx, c->h_info, c->h_scalar};
@@ -102,7 +100,6 @@ void free_cnn(acq_cnn_s* c) {
 int build_cnn(acq_cnn_s* c) {
     const size_t rows = size_t(c->cfg.max_rows), np = size_t(c->lay.total);
     const size_t es = c->bf ? 2 : 4;
-    const size_t fmax = size_t(std::max<int64_t>(num_frames(c->cfg.max_block_len), 1));
     CNN_HIP(dalloc(&c->theta, np));
     CNN_HIP(dalloc(&c->grad, np));
     CNN_HIP(dalloc(&c->m, np));
@@ -122,16 +119,16 @@ int build_cnn(acq_cnn_s* c) {
     CNN_HIP(dalloc(&c->y, rows));
     CNN_HIP(dalloc(&c->labels, rows));
     CNN_HIP(dalloc(&c->P, rows * kWin));
-    CNN_HIP(dalloc(&c->hist, size_t(kMaxBatch) * 2048));
-    CNN_HIP(dalloc(&c->mstate, size_t(kMaxBatch)));
+    CNN_HIP(dalloc(&c->ms.hist, size_t(kMaxBatch * kMedianHist)));
+    CNN_HIP(dalloc(&c->ms.tickets, size_t(kMaxBatch)));
+    CNN_HIP(dalloc(&c->ms.state, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->med, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->hann, size_t(kWin)));
     CNN_HIP(dalloc(&c->tw, size_t(kWin)));
     CNN_HIP(dalloc(&c->loss, 1));
     CNN_HIP(dalloc(&c->d_tx, size_t(kMaxBatch) * kMaxTx));
     CNN_HIP(dalloc(&c->d_ntx, size_t(kMaxBatch)));
-    CNN_HIP(dalloc(&c->wscore, fmax));
-    CNN_HIP(dalloc(&c->d_info, 2));
+    CNN_HIP(dalloc(&c->segmask, size_t(kProposeWords)));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_tx), sizeof(SynthTx) * kMaxBatch * kMaxTx));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_ntx), sizeof(int32_t) * kMaxBatch));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_info), sizeof(int32_t) * 2));
@@ -149,6 +146,9 @@ int build_cnn(acq_cnn_s* c) {
     hipStream_t st = c->stream;
     CNN_HIP(hipMemcpyAsync(c->hann, hann.data(), sizeof(float) * kWin, hipMemcpyHostToDevice, st));
     CNN_HIP(hipMemcpyAsync(c->tw, tw.data(), sizeof(float) * 2 * kWin, hipMemcpyHostToDevice, st));
+    CNN_HIP(launch_fill_u32(c->ms.hist, kMaxBatch * kMedianHist, st));
+    CNN_HIP(launch_fill_u32(c->ms.tickets, kMaxBatch, st));
+    CNN_HIP(launch_fill_u32(c->segmask, kProposeWords, st));
     CNN_HIP(launch_fill_f32(c->theta, int64_t(np), st));
     CNN_HIP(launch_fill_f32(c->grad, int64_t(np), st));
     CNN_HIP(launch_fill_f32(c->m, int64_t(np), st));
@@ -204,10 +204,11 @@ int run_backward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, const
     return ACQ_OK;
 }
 
+// block 0's median is left in h_scalar[1]
 int run_map(acq_cnn_s* c, const BlockSource& src, int32_t nblocks, int64_t F, void* map, hipStream_t st) {
-    CNN_HIP(launch_stft(src, nblocks, F, c->hann, c->tw, c->P, st));
-    CNN_HIP(launch_median(c->P, nblocks, F * kWin, c->hist, c->mstate, c->med, st));
-    CNN_HIP(launch_map(c->P, nblocks, F, c->med, map, c->bf, st));
+    CNN_HIP(launch_stft(src, nblocks, F, c->hann, c->tw, c->P, c->ms, st));
+    CNN_HIP(launch_median(c->P, nblocks, F * kWin, c->ms, c->med, st));
+    CNN_HIP(launch_map(c->P, nblocks, F, c->med, map, c->bf, c->h_scalar + 1, st));
     return ACQ_OK;
 }
 
@@ -254,10 +255,7 @@ int cnn_propose(acq_cnn_t c, const void* block, int64_t n, int64_t L, int64_t V,
     if (rc != ACQ_OK) return rc;
     rc = run_forward(c, c->act[0], 1, F, st);
     if (rc != ACQ_OK) return rc;
-    CNN_HIP(launch_window(c->y, F, c->wscore, st));
-    CNN_HIP(launch_propose(c->wscore, F, kappa, n, L, V, max_segments, d_segs, c->d_info, st));
-    CNN_HIP(hipMemcpyAsync(c->h_info, c->d_info, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, st));
-    CNN_HIP(hipMemcpyAsync(c->h_scalar + 1, c->med, sizeof(float), hipMemcpyDeviceToHost, st));
+    CNN_HIP(launch_propose(c->y, F, kappa, n, L, V, max_segments, c->segmask, d_segs, c->h_info, st));
     CNN_HIP(hipStreamSynchronize(st));
     out->proposals = c->h_info[0];
     out->segments = c->h_info[1];
@@ -397,7 +395,6 @@ int acq_power_map(acq_cnn_t c, const void* block, int64_t n, void* map, float* m
     src.stride = n;
     const int rc = run_map(c, src, 1, F, map, c->stream);
     if (rc != ACQ_OK) return rc;
-    CNN_HIP(hipMemcpyAsync(c->h_scalar + 1, c->med, sizeof(float), hipMemcpyDeviceToHost, c->stream));
     CNN_HIP(hipStreamSynchronize(c->stream));
     *median = c->h_scalar[1];
     acq::clear_error();

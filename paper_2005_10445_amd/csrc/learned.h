@@ -66,12 +66,24 @@ struct MedianState {
     uint32_t rank;
 };
 
+// Scratch of the median: zero before the first launch, left so by every
+// launch_median.
+constexpr int64_t kMedianHist = 8 * 2048;   // histogram words of one block
+struct MedianScratch {
+    uint32_t* hist;             // [block][kMedianHist]
+    unsigned* tickets;          // [block]
+    MedianState* state;         // [block]
+};
+
+// Powers P[block][F][256] and the median's first digit; launch_median (on the
+// same blocks and scratch) selects the rest.
 hipError_t launch_stft(const BlockSource& src, int nblocks, int64_t F, const float* hann, const float2* tw,
-                       float* P, hipStream_t st);
-hipError_t launch_median(const float* P, int nblocks, int64_t per_block, uint32_t* hist, MedianState* state,
-                         float* med, hipStream_t st);
+                       float* P, const MedianScratch& ms, hipStream_t st);
+hipError_t launch_median(const float* P, int nblocks, int64_t per_block, const MedianScratch& ms, float* med,
+                         hipStream_t st);
+// h_med: block 0's median, to host memory (nullptr: no)
 hipError_t launch_map(const float* P, int nblocks, int64_t F, const float* med, void* map, bool bf16,
-                      hipStream_t st);
+                      float* h_med, hipStream_t st);
 // Samples of synthetic block 0 of `src` (src.x == nullptr) into out[n].
 hipError_t launch_synth(const BlockSource& src, int64_t n, float2* out, hipStream_t st);
 hipError_t launch_labels(const SynthTx* tx, const int32_t* ntx, int nblocks, int64_t F, int L, float* labels,
@@ -102,12 +114,14 @@ hipError_t launch_adam(float* theta, float* grad, float* m, float* v, int64_t n,
 hipError_t launch_fill_f32(float* p, int64_t n, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t st);
 
-// Window scores c[f] = sum_{i=-63}^{64} y[f+i] of one block.
-hipError_t launch_window(const float* y, int64_t F, float* c, hipStream_t st);
-// Frames at or above kappa, their lag ranges and the segment list of one block.
-// out_info = {proposed frames, segments}.
-hipError_t launch_propose(const float* c, int64_t F, float kappa, int64_t n, int64_t L, int64_t V,
-                          int32_t max_segments, int32_t* segs, int32_t* out_info, hipStream_t st);
+// Frames of one block whose window score c[f] = sum_{i=-63}^{64} y[f+i] is at or
+// above kappa, their lag ranges and the segment list.  h_info (host memory) =
+// {proposed frames, segments}.  mask: kProposeWords words, zero before the first
+// launch and left so.
+constexpr int kMaxSegList = 4096;
+constexpr int kProposeWords = kMaxSegList / 32 + 2;
+hipError_t launch_propose(const float* y, int64_t F, float kappa, int64_t n, int64_t L, int64_t V,
+                          int32_t max_segments, uint32_t* mask, int32_t* segs, int32_t* h_info, hipStream_t st);
 
 }  // namespace learned
 }  // namespace acq
