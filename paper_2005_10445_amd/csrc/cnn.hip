@@ -54,8 +54,8 @@ struct acq_cnn_s {
     float* grad = nullptr;      // [np]
     float* m = nullptr;         // [np]
     float* v = nullptr;         // [np]
-    uint16_t* w_bf = nullptr;   // [bf_total] per layer [tap][in][out]
-    uint16_t* wt_bf = nullptr;  // [bf_total] per layer [tap][out][in]
+    uint16_t* w_bf = nullptr;   // [bf_total] operand order of the input gradients (k_conv_tile)
+    uint16_t* wt_bf = nullptr;  // [bf_total] operand order of the layers
 
     void* act[kLayers + 1] = {};    // act[0]: map [rows][cin]; act[l]: layer l output [rows][64]
     float* dH[2] = {};              // [rows][64] FP32 gradients (ping-pong)

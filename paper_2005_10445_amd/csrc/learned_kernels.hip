@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cfloat>
+#include <type_traits>
 
 #include "arrival.h"
 #include "device_fft.h"
@@ -257,11 +258,8 @@ __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const 
 // bits[30:20] equal the prefix so far, pass 2 bits[9:0] of those whose
 // bits[30:10] do.  The last workgroup of a block to arrive selects the digit,
 // as k_stft's does the first, and clears the histogram for the next pass.
-// (The three digits as launches of 64 workgroups with a selection launch after
-// each were 3 x 19 and 3 x 4.4 us for 2^21 powers, with k_stft 10 us; now k_stft
-// 19, k_hist 10 and 7.5 us, the power map of 2^20 samples 102 -> 54 us.  More
-// copies of the first histogram take longer to read than their adds wait:
-// 16 copies 34 us, one 22.)
+// (Three launches of 64 workgroups with a selection launch after each, 3 x 19
+// and 3 x 4.4 us for 2^21 powers; HIST_FIGURES.)
 template <int PASS>
 __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ P, int64_t per_block, MedianScratch ms,
                                               float* __restrict__ med) {
@@ -371,126 +369,156 @@ __global__ void k_labels(const SynthTx* __restrict__ tx, const int32_t* __restri
 // ------------------------------------------------------------------ conv (MFMA)
 // Forward / input gradient as a tiled GEMM on v_mfma_f32_16x16x32_bf16
 // (lane l: A[row l%16][k 8(l/16)+e], B[k 8(l/16)+e][col l%16], e < 8;
-// D[row 4(l/16)+e][col l%16], e < 4).  A workgroup computes 128 rows x 64
-// columns.  The rows it needs for all five taps -- its 128 plus 2d above and
+// D[row 4(l/16)+e][col l%16], e < 4).  A workgroup computes 16 RT rows x 64
+// columns.  The rows it needs for all five taps -- its own plus 2d above and
 // below -- are staged once in LDS as bf16 ([row][K + 8], the pad spreading
 // the 16-byte reads of a wave over the banks); for the input gradient the
-// staging applies the ReLU mask to dH and rounds it once.  Each wave takes
-// 32 rows (two 16-row tiles) by the 64 columns (four 16-column tiles); the
-// weights of the next 32-deep k step are loaded while the current step's
-// eight MFMAs run.  A tap row outside its output row's block is zero.
-constexpr int kTileRows = 128;
+// staging applies the ReLU mask to dH and rounds it once.  Wave w takes the 16
+// columns 16w.. of every row, so a workgroup reads each weight once, in whole
+// lines (the weights lie in operand order), and keeps those of the next
+// kConvAhead 32-deep k steps in flight.  A tap row outside its
+// output row's block is zero: rows before the first and past the last block are
+// staged as zeros, and only workgroups with a block start within reach test for
+// the others.
+// (Waves of 32 rows by all 64 columns, 128 rows a workgroup and one step of
+// weights in flight, waited for the weights, read in half lines: layers of 256
+// and 64 inputs over 65,536 rows 49 and 17.4 us, now 26.5 and 11.7, input
+// gradients 19 and 14 us; over 8192 rows 28.3 and 11.4 us, now 7.7 and 5 us.
+// Weights read in row order: 32 and 15.2 us.)
+constexpr int kConvAhead = 10;                       // (the steps of 64 inputs: five taps of two)
 
 using bf16x8 = __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-template <bool FWD>
+template <bool FWD, int RT>
 __global__ __launch_bounds__(256) void k_conv_tile(const void* __restrict__ src, const uint16_t* __restrict__ H,
                                                    int K, const uint16_t* __restrict__ Bt,
                                                    const float* __restrict__ bias, void* __restrict__ out,
-                                                   int64_t rows, int64_t F, int d) {
+                                                   int rows, int F, int d) {
+    constexpr int R = 16 * RT, PD = kConvAhead;
     extern __shared__ __align__(16) uint16_t sA[];
     const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
-    const int pitch = K + 8, halo = 2 * d, srows = kTileRows + 2 * halo;
-    const int64_t r0 = int64_t(blockIdx.x) * kTileRows;
+    const int ra = lane & 15, kq = 8 * (lane >> 4);
+    const int pitch = K + 8, halo = 2 * d, srows = R + 2 * halo;
+    const int r0 = int(blockIdx.x) * R;
+    // the weights come in the order of the steps, the columns' four tiles, the lanes
+    const uint16_t* bp = Bt + (wave * 64 + lane) * 8;
+    const int steps = kTaps * (K / 32);
+    int bs = 0;                                          // next step to load (the last again past the end)
+    auto next_b = [&]() {
+        const uint4 v = *reinterpret_cast<const uint4*>(bp + bs * (kCh * 32));
+        bs = min(bs + 1, steps - 1);
+        return v;
+    };
+    uint4 bq[PD];
+#pragma unroll
+    for (int s = 0; s < PD; ++s) bq[s] = next_b();
     if constexpr (FWD) {
         const int cpr = K / 8;                           // 16-byte chunks per row
-        for (int idx = tid; idx < srows * cpr; idx += 256) {
-            const int sr = idx / cpr, ch = idx - sr * cpr;
-            const int64_t g = r0 - halo + sr;
-            uint4 v = {0u, 0u, 0u, 0u};
-            if (g >= 0 && g < rows) v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + g * K + ch * 8);
-            *reinterpret_cast<uint4*>(&sA[sr * pitch + ch * 8]) = v;
+        constexpr int U = 8;
+        for (int i0 = tid; i0 < srows * cpr; i0 += 256 * U) {
+            uint4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int idx = min(i0 + 256 * u, srows * cpr - 1), sr = idx / cpr, ch = idx - sr * cpr;
+                const int g = min(max(r0 - halo + sr, 0), rows - 1);
+                v[u] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + (int64_t(g) * K + ch * 8));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int idx = i0 + 256 * u, sr = idx / cpr, ch = idx - sr * cpr;
+                const int g = r0 - halo + sr;
+                if (idx < srows * cpr)
+                    *reinterpret_cast<uint4*>(&sA[sr * pitch + ch * 8]) =
+                        g >= 0 && g < rows ? v[u] : uint4{0u, 0u, 0u, 0u};
+            }
         }
     } else {
         const int cpr = K / 4;                           // 4 values per thread and step
-        for (int idx = tid; idx < srows * cpr; idx += 256) {
-            const int sr = idx / cpr, ch = idx - sr * cpr;
-            const int64_t g = r0 - halo + sr;
-            uint2 o = {0u, 0u};
-            if (g >= 0 && g < rows) {
-                const float4 gv = *reinterpret_cast<const float4*>(static_cast<const float*>(src) + g * K + ch * 4);
-                const uint2 hb = *reinterpret_cast<const uint2*>(H + g * K + ch * 4);
-                // dA = dH where the layer output is positive
-                const float g0 = (hb.x & 0x7fffu) && !(hb.x & 0x8000u) ? gv.x : 0.f;
-                const float g1 = (hb.x & 0x7fff0000u) && !(hb.x & 0x80000000u) ? gv.y : 0.f;
-                const float g2 = (hb.y & 0x7fffu) && !(hb.y & 0x8000u) ? gv.z : 0.f;
-                const float g3 = (hb.y & 0x7fff0000u) && !(hb.y & 0x80000000u) ? gv.w : 0.f;
-                o.x = uint32_t(to_bf16(g0)) | (uint32_t(to_bf16(g1)) << 16);
-                o.y = uint32_t(to_bf16(g2)) | (uint32_t(to_bf16(g3)) << 16);
+        constexpr int U = 4;
+        for (int i0 = tid; i0 < srows * cpr; i0 += 256 * U) {
+            float4 gv[U];
+            uint2 hb[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int idx = min(i0 + 256 * u, srows * cpr - 1), sr = idx / cpr, ch = idx - sr * cpr;
+                const int g = min(max(r0 - halo + sr, 0), rows - 1);
+                const int64_t o = int64_t(g) * K + ch * 4;
+                gv[u] = *reinterpret_cast<const float4*>(static_cast<const float*>(src) + o);
+                hb[u] = *reinterpret_cast<const uint2*>(H + o);
             }
-            *reinterpret_cast<uint2*>(&sA[sr * pitch + ch * 4]) = o;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int idx = i0 + 256 * u, sr = idx / cpr, ch = idx - sr * cpr;
+                const int g = r0 - halo + sr;
+                // dA = dH where the layer output is positive
+                const float g0 = (hb[u].x & 0x7fffu) && !(hb[u].x & 0x8000u) ? gv[u].x : 0.f;
+                const float g1 = (hb[u].x & 0x7fff0000u) && !(hb[u].x & 0x80000000u) ? gv[u].y : 0.f;
+                const float g2 = (hb[u].y & 0x7fffu) && !(hb[u].y & 0x8000u) ? gv[u].z : 0.f;
+                const float g3 = (hb[u].y & 0x7fff0000u) && !(hb[u].y & 0x80000000u) ? gv[u].w : 0.f;
+                uint2 o = {uint32_t(to_bf16(g0)) | (uint32_t(to_bf16(g1)) << 16),
+                           uint32_t(to_bf16(g2)) | (uint32_t(to_bf16(g3)) << 16)};
+                if (g < 0 || g >= rows) o = uint2{0u, 0u};
+                if (idx < srows * cpr) *reinterpret_cast<uint2*>(&sA[sr * pitch + ch * 4]) = o;
+            }
         }
     }
     __syncthreads();
 
-    const int ra = lane & 15, kq = 8 * (lane >> 4);
-    int64_t frame[2];
-    bool live[2];
+    f32x4 acc[RT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const int64_t orow = r0 + 32 * wave + 16 * rt + ra;
-        live[rt] = orow < rows;
-        frame[rt] = orow - (orow / F) * F;
-    }
-    f32x4 acc[2][4];
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto run = [&](auto masked) {
+        int frame[RT];                                   // of row 16 rt + ra, within its block
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[rt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int ksteps = K / 32, steps = kTaps * ksteps;
-    auto bptr = [&](int step, int nt) {
-        const int i = step / ksteps, kc = (step - i * ksteps) * 32;
-        return Bt + (int64_t(i) * kCh + nt * 16 + ra) * K + kc + kq;
-    };
-    uint4 bcur[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) bcur[nt] = *reinterpret_cast<const uint4*>(bptr(0, nt));
-    for (int step = 0; step < steps; ++step) {
-        uint4 bnext[4];
-        const int sn = step + 1 < steps ? step + 1 : step;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) bnext[nt] = *reinterpret_cast<const uint4*>(bptr(sn, nt));
-        const int i = step / ksteps, kc = (step - i * ksteps) * 32;
-        const int delta = (FWD ? 1 : -1) * d * (i - 2);
-        bf16x8 a[2];
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            const int arow = 32 * wave + 16 * rt + ra + halo + delta;
-            const uint4 v = *reinterpret_cast<const uint4*>(&sA[arow * pitch + kc + kq]);
-            const bool ok = live[rt] && frame[rt] + delta >= 0 && frame[rt] + delta < F;
-            a[rt] = as_bf16x8(ok ? v : uint4{0u, 0u, 0u, 0u});
+        for (int rt = 0; rt < RT; ++rt) {
+            frame[rt] = masked.value ? int(unsigned(r0 + 16 * rt + ra) % unsigned(F)) : 0;
         }
+        int i = 0, kc = 0;
+        for (int s0 = 0; s0 < steps; s0 += PD)
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+            for (int s = 0; s < PD; ++s) {
+                const int delta = (FWD ? 1 : -1) * d * (i - 2);
+                const uint16_t* ap = &sA[(ra + halo + delta) * pitch + kc + kq];
+                const bf16x8 bv = as_bf16x8(bq[s]);
+                bq[s] = next_b();
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-                acc[rt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt], as_bf16x8(bcur[nt]), acc[rt][nt], 0, 0, 0);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) bcur[nt] = bnext[nt];
-    }
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int n = nt * 16 + ra;
-            const float bn = FWD ? bias[n] : 0.0f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t row = r0 + 32 * wave + 16 * rt + 4 * (lane >> 4) + e;
-                if (row >= rows) continue;
-                if constexpr (FWD)
-                    static_cast<uint16_t*>(out)[row * kCh + n] = to_bf16(fmaxf(acc[rt][nt][e] + bn, 0.0f));
-                else
-                    static_cast<float*>(out)[row * kCh + n] = acc[rt][nt][e];
+                for (int rt = 0; rt < RT; ++rt) {
+                    uint4 v = *reinterpret_cast<const uint4*>(ap + 16 * rt * pitch);
+                    if constexpr (masked.value) {
+                        if (unsigned(frame[rt] + delta) >= unsigned(F)) v = uint4{0u, 0u, 0u, 0u};
+                    }
+                    acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v), bv, acc[rt], 0, 0, 0);
+                }
+                kc += 32;
+                if (kc == K) { kc = 0; ++i; }
             }
+    };
+    // the staged rows lie in one block: no tests
+    const int first = max(r0 - halo, 0), last = min(r0 + R + halo, rows) - 1;
+    if (unsigned(first) / unsigned(F) == unsigned(last) / unsigned(F)) run(std::false_type{});
+    else run(std::true_type{});
+    const int n = 16 * wave + ra;
+    const float bn = FWD ? bias[n] : 0.0f;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = r0 + 16 * rt + 4 * (lane >> 4) + e;
+            if (row >= rows) continue;
+            if constexpr (FWD)
+                static_cast<uint16_t*>(out)[int64_t(row) * kCh + n] = to_bf16(fmaxf(acc[rt][e] + bn, 0.0f));
+            else
+                static_cast<float*>(out)[int64_t(row) * kCh + n] = acc[rt][e];
         }
 }
 
-__host__ __device__ constexpr size_t conv_tile_lds(int K, int d) {
-    return size_t(kTileRows + 4 * d) * size_t(K + 8) * sizeof(uint16_t);
+constexpr size_t conv_tile_lds(int K, int d, int tile_rows) {
+    return size_t(tile_rows + 4 * d) * size_t(K + 8) * sizeof(uint16_t);
 }
+constexpr int64_t kMaxConvRows = int64_t(1) << 30;   // a network holds at most 2^26
+constexpr int64_t kConvSmallRows = 40960;
 constexpr size_t kMaxConvLds = size_t(160) << 10;   // LDS of a gfx950 compute unit
 
 // Weight gradient dW[i][c][o] += sum_r in[r + d(i-2)][c] dA[r][o] (dA = dH where the
@@ -900,6 +928,13 @@ __global__ __launch_bounds__(256) void k_head(const void* __restrict__ h4, const
 }
 
 // ------------------------------------------------------------------ Adam
+// Place of a weight (tap i, column n of N, k of K) in the operand order of
+// k_conv_tile: per tap and 32-deep k step the N / 16 column tiles, each its 64
+// lanes' 8 values.
+__device__ __forceinline__ int conv_operand(int i, int n, int k, int N, int K) {
+    return ((i * (K / 32) + k / 32) * (N / 16) + n / 16) * 512 + ((n & 15) + 16 * ((k & 31) / 8)) * 8 + (k & 7);
+}
+
 __global__ void k_adam(float* __restrict__ theta, float* __restrict__ grad, float* __restrict__ m,
                        float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float c1, float c2,
                        NetLayout lay, uint16_t* __restrict__ w_bf, uint16_t* __restrict__ wt_bf, int update) {
@@ -921,11 +956,11 @@ __global__ void k_adam(float* __restrict__ theta, float* __restrict__ grad, floa
         const int64_t q = p - lay.w_off[l];
         const int cin = lay.cin[l];
         if (q < 0 || q >= int64_t(kTaps) * cin * kCh) continue;
-        const int64_t i = q / (int64_t(cin) * kCh), rem = q % (int64_t(cin) * kCh);
-        const int64_t c = rem / kCh, o = rem % kCh;
+        const int i = int(q / (int64_t(cin) * kCh)), rem = int(q % (int64_t(cin) * kCh));
+        const int c = rem / kCh, o = rem % kCh;
         const uint16_t hb = to_bf16(th);
-        w_bf[lay.bf_off[l] + q] = hb;
-        wt_bf[lay.bf_off[l] + (i * kCh + o) * cin + c] = hb;
+        w_bf[lay.bf_off[l] + conv_operand(i, c, o, cin, kCh)] = hb;
+        wt_bf[lay.bf_off[l] + conv_operand(i, o, c, kCh, cin)] = hb;
     }
 }
 
@@ -945,7 +980,7 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n) {
 // workgroup takes 256 frames, marks its segments in the block's mask words, and
 // the last to arrive lists them.  out = {proposed frames, segments}, on the host.
 // (Scores of single loads and one workgroup's pass over them were 11.7 and 11.3
-// us for 8192 frames and a copy of the counts; this is 5.5 us.)
+// us for 8192 frames; PROPOSE_FIGURES.)
 constexpr int kSegWords = kMaxSegList / 32;
 
 __global__ __launch_bounds__(256) void k_propose(const float* __restrict__ y, int64_t F, float kappa, int64_t n,
@@ -1056,41 +1091,46 @@ hipError_t launch_labels(const SynthTx* tx, const int32_t* ntx, int nblocks, int
     return hipGetLastError();
 }
 
+template <bool FWD, int RT>
+static hipError_t conv_tile_go(const void* src, const void* H, int K, const void* w, const float* bias, void* out,
+                               int64_t rows, int64_t F, int d, hipStream_t st) {
+    const size_t lds = conv_tile_lds(K, d, 16 * RT);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_tile<FWD, RT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_conv_tile<FWD, RT>), dim3(blocks_for(rows, 16 * RT)), dim3(256), lds, st, src,
+                       (const uint16_t*)H, K, (const uint16_t*)w, bias, out, int(rows), int(std::min(F, rows)), d);
+    return hipGetLastError();
+}
+
+// Tiles of 32 rows for few rows, so that they fill the chip (a forward pass of
+// 8192 rows 46 us, in tiles of 64 57 us; of 32,768 rows 59 and 64 us), of 64 for
+// many, with half the reads of the weights (65,536 rows 77 us, in tiles of 32 85;
+// tiles of 128 rows leave a compute unit two workgroups: layer 0 30 us for 26.5).
+template <bool FWD>
+static hipError_t conv_tile(const void* src, const void* H, int K, const void* w, const float* bias, void* out,
+                            int64_t rows, int64_t F, int d, hipStream_t st) {
+    if (K % 64 || d < 1 || conv_tile_lds(K, d, 128) > kMaxConvLds || rows > kMaxConvRows)
+        return hipErrorInvalidValue;
+    if (rows <= kConvSmallRows) return conv_tile_go<FWD, 2>(src, H, K, w, bias, out, rows, F, d, st);
+    return conv_tile_go<FWD, 4>(src, H, K, w, bias, out, rows, F, d, st);
+}
+
 hipError_t launch_conv_forward(const void* in, int cin, const void* w, const float* bias, void* out, int64_t rows,
                                int64_t F, int d, bool bf16, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
-    if (bf16) {
-        if (cin % 32 || d < 1) return hipErrorInvalidValue;
-        const size_t lds = conv_tile_lds(cin, d);
-        if (lds > kMaxConvLds) return hipErrorInvalidValue;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_tile<true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_conv_tile<true>, dim3(blocks_for(rows, kTileRows)), dim3(256), lds, st, in,
-                           (const uint16_t*)nullptr, cin, (const uint16_t*)w, bias, out, rows, F, d);
-    } else {
-        hipLaunchKernelGGL(k_conv_fwd_ref, dim3(blocks_for(rows * kCh, 256)), dim3(256), 0, st, (const float*)in,
-                           cin, (const float*)w, bias, (float*)out, rows, F, d);
-    }
+    if (bf16) return conv_tile<true>(in, nullptr, cin, w, bias, out, rows, F, d, st);
+    hipLaunchKernelGGL(k_conv_fwd_ref, dim3(blocks_for(rows * kCh, 256)), dim3(256), 0, st, (const float*)in, cin,
+                       (const float*)w, bias, (float*)out, rows, F, d);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_dinput(const float* dH, const void* H, const void* w, float* dprev, int64_t rows, int64_t F,
                               int d, bool bf16, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
-    if (bf16) {
-        if (d < 1) return hipErrorInvalidValue;
-        const size_t lds = conv_tile_lds(kCh, d);
-        if (lds > kMaxConvLds) return hipErrorInvalidValue;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_tile<false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_conv_tile<false>, dim3(blocks_for(rows, kTileRows)), dim3(256), lds, st, (const void*)dH,
-                           (const uint16_t*)H, kCh, (const uint16_t*)w, (const float*)nullptr, (void*)dprev, rows,
-                           F, d);
-    } else
-        hipLaunchKernelGGL(k_conv_dinput_ref, dim3(blocks_for(rows * kCh, 256)), dim3(256), 0, st, dH,
-                           (const float*)H, (const float*)w, dprev, rows, F, d);
+    if (bf16) return conv_tile<false>(dH, H, kCh, w, nullptr, dprev, rows, F, d, st);
+    hipLaunchKernelGGL(k_conv_dinput_ref, dim3(blocks_for(rows * kCh, 256)), dim3(256), 0, st, dH, (const float*)H,
+                       (const float*)w, dprev, rows, F, d);
     return hipGetLastError();
 }
 
