@@ -59,8 +59,8 @@ struct acq_cnn_s {
 
     void* act[kLayers + 1] = {};    // act[0]: map [rows][cin]; act[l]: layer l output [rows][64]
     float* dH[2] = {};              // [rows][64] FP32 gradients (ping-pong)
-    float* dw_part = nullptr;       // [dw_part_elems] weight-gradient chunk sums
-    int64_t dw_part_elems = 0;
+    float* dw_part[kLayers] = {};   // weight-gradient chunk sums of each layer
+    float* head_part = nullptr;     // head sums of each workgroup
     float* y = nullptr;             // [rows] logits
     float* labels = nullptr;        // [rows]
     float* P = nullptr;             // [rows][256] STFT powers
@@ -68,7 +68,6 @@ struct acq_cnn_s {
     float* med = nullptr;           // [kMaxBatch]
     float* hann = nullptr;          // [256]
     float2* tw = nullptr;           // [256] exp(-j 2 pi m / 256)
-    float* loss = nullptr;          // [1]
     SynthTx* d_tx = nullptr;        // [kMaxBatch][kMaxTx]
     int32_t* d_ntx = nullptr;       // [kMaxBatch]
     uint32_t* segmask = nullptr;    // [kProposeWords]
@@ -87,8 +86,9 @@ namespace {
 void free_cnn(acq_cnn_s* c) {
     if (!c) return;
     void* dev[] = {c->theta, c->grad, c->m, c->v, c->w_bf, c->wt_bf, c->act[0], c->act[1], c->act[2], c->act[3],
-                   c->act[4], c->dH[0], c->dH[1], c->dw_part, c->y, c->labels, c->P, c->ms.hist, c->ms.tickets,
-                   c->ms.state, c->med, c->hann, c->tw, c->loss, c->d_tx, c->d_ntx, c->segmask};
+                   c->act[4], c->dH[0], c->dH[1], c->dw_part[0], c->dw_part[1], c->dw_part[2], c->dw_part[3],
+                   c->head_part, c->y, c->labels, c->P, c->ms.hist, c->ms.tickets,
+                   c->ms.state, c->med, c->hann, c->tw, c->d_tx, c->d_ntx, c->segmask};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     void* host[] = {c->h_tx, c->h_ntx, c->h_info, c->h_scalar};
@@ -112,10 +112,9 @@ int build_cnn(acq_cnn_s* c) {
     for (int l = 1; l <= kLayers; ++l) CNN_HIP(hipMalloc(&c->act[l], rows * kCh * es));
     CNN_HIP(dalloc(&c->dH[0], rows * kCh));
     CNN_HIP(dalloc(&c->dH[1], rows * kCh));
-    if (c->bf) {
-        c->dw_part_elems = std::max(dweight_part_elems(c->cfg.in_channels), dweight_part_elems(kCh));
-        CNN_HIP(dalloc(&c->dw_part, size_t(c->dw_part_elems)));
-    }
+    if (c->bf)
+        for (int l = 0; l < kLayers; ++l) CNN_HIP(dalloc(&c->dw_part[l], size_t(dweight_part_elems(c->lay.cin[l]))));
+    CNN_HIP(dalloc(&c->head_part, size_t(head_groups(c->cfg.max_rows) * kHeadSums)));
     CNN_HIP(dalloc(&c->y, rows));
     CNN_HIP(dalloc(&c->labels, rows));
     CNN_HIP(dalloc(&c->P, rows * kWin));
@@ -125,7 +124,6 @@ int build_cnn(acq_cnn_s* c) {
     CNN_HIP(dalloc(&c->med, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->hann, size_t(kWin)));
     CNN_HIP(dalloc(&c->tw, size_t(kWin)));
-    CNN_HIP(dalloc(&c->loss, 1));
     CNN_HIP(dalloc(&c->d_tx, size_t(kMaxBatch) * kMaxTx));
     CNN_HIP(dalloc(&c->d_ntx, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->segmask, size_t(kProposeWords)));
@@ -165,8 +163,8 @@ int check_rows(const acq_cnn_s* c, int32_t nblocks, int64_t frames) {
     return ACQ_OK;
 }
 
-// layer-0 input `in`; logits to c->y
-int run_forward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, hipStream_t st) {
+// the layers on input `in`, to c->act
+int run_layers(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, hipStream_t st) {
     const int64_t rows = int64_t(nblocks) * F;
     const void* x = in;
     for (int l = 0; l < kLayers; ++l) {
@@ -176,23 +174,46 @@ int run_forward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, hipStr
                                     kDilation[l], c->bf, st));
         x = c->act[l + 1];
     }
-    CNN_HIP(launch_head(c->act[kLayers], c->theta, c->lay.wh_off, c->y, nullptr, 0.f, 0.f, nullptr, nullptr, nullptr,
-                        rows, c->bf, st));
     return ACQ_OK;
 }
 
-// loss terms into c->loss and gradients added to c->grad (after run_forward on `in`)
-int run_backward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, const float* labels, float pw,
-                 hipStream_t st) {
+// layer-0 input `in`; logits to c->y
+int run_forward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, hipStream_t st) {
+    const int rc = run_layers(c, in, nblocks, F, st);
+    if (rc != ACQ_OK) return rc;
+    CNN_HIP(launch_head(c->act[kLayers], c->theta, c->lay.wh_off, c->y, nullptr, 0.f, 0.f, nullptr, nullptr,
+                        int64_t(nblocks) * F, c->bf, st));
+    return ACQ_OK;
+}
+
+// forward and backward on `in`: logits to c->y, the sum of losses to h_scalar[0],
+// gradients to c->grad and, if not null, `out`
+int run_gradients(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, const float* labels, float pw, float* out,
+                  hipStream_t st) {
     const int64_t rows = int64_t(nblocks) * F;
+    const int rc = run_layers(c, in, nblocks, F, st);
+    if (rc != ACQ_OK) return rc;
     CNN_HIP(launch_head(c->act[kLayers], c->theta, c->lay.wh_off, c->y, labels, pw, float(1.0 / double(rows)),
-                        c->dH[0], c->grad, c->loss, rows, c->bf, st));
+                        c->dH[0], c->head_part, rows, c->bf, st));
+    GradSums dw{};
+    dw.head = c->head_part;
+    dw.head_groups = head_groups(rows);
+    dw.wh_off = c->lay.wh_off;
     int cur = 0;
     for (int l = kLayers - 1; l >= 0; --l) {
         const void* x = l == 0 ? in : c->act[l];
-        CNN_HIP(launch_conv_dweight(x, c->lay.cin[l], c->dH[cur], c->act[l + 1], c->grad + c->lay.w_off[l],
-                                    c->grad + c->lay.b_off[l], c->dw_part, c->dw_part_elems, rows, F,
-                                    kDilation[l], c->bf, st));
+        if (c->bf) {
+            dw.part[l] = c->dw_part[l];
+            dw.w_off[l] = c->lay.w_off[l];
+            dw.cin[l] = c->lay.cin[l];
+            CNN_HIP(launch_conv_dweight(x, c->lay.cin[l], c->dH[cur], c->act[l + 1], c->dw_part[l],
+                                        dweight_part_elems(c->lay.cin[l]), &dw.nchunks[l], rows, F, kDilation[l],
+                                        st));
+        } else {
+            CNN_HIP(launch_conv_dweight_ref(static_cast<const float*>(x), c->lay.cin[l], c->dH[cur],
+                                            static_cast<const float*>(c->act[l + 1]), c->grad + c->lay.w_off[l],
+                                            c->grad + c->lay.b_off[l], rows, F, kDilation[l], st));
+        }
         if (l > 0) {
             const void* w = c->bf ? static_cast<const void*>(c->w_bf + c->lay.bf_off[l])
                                   : static_cast<const void*>(c->theta + c->lay.w_off[l]);
@@ -201,6 +222,9 @@ int run_backward(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, const
             cur = 1 - cur;
         }
     }
+    CNN_HIP(launch_grad_reduce(dw, c->grad, c->bf ? out : nullptr, c->h_scalar, st));
+    if (!c->bf && out)
+        CNN_HIP(hipMemcpyAsync(out, c->grad, sizeof(float) * size_t(c->lay.total), hipMemcpyDeviceToDevice, st));
     return ACQ_OK;
 }
 
@@ -360,14 +384,8 @@ int acq_cnn_gradients(acq_cnn_t c, const void* input, int32_t nblocks, int64_t f
     int rc = check_rows(c, nblocks, frames);
     if (rc != ACQ_OK) return rc;
     hipStream_t st = c->stream;
-    CNN_HIP(launch_fill_f32(c->grad, c->lay.total, st));
-    CNN_HIP(launch_fill_f32(c->loss, 1, st));
-    rc = run_forward(c, input, nblocks, frames, st);
-    if (rc == ACQ_OK) rc = run_backward(c, input, nblocks, frames, labels, pos_weight, st);
+    rc = run_gradients(c, input, nblocks, frames, labels, pos_weight, grad, st);
     if (rc != ACQ_OK) return rc;
-    if (grad)
-        CNN_HIP(hipMemcpyAsync(grad, c->grad, sizeof(float) * size_t(c->lay.total), hipMemcpyDeviceToDevice, st));
-    CNN_HIP(hipMemcpyAsync(c->h_scalar, c->loss, sizeof(float), hipMemcpyDeviceToHost, st));
     CNN_HIP(hipStreamSynchronize(st));
     *loss = float(double(c->h_scalar[0]) / (double(nblocks) * double(frames)));
     acq::clear_error();
@@ -438,15 +456,11 @@ int acq_cnn_train_synthetic(acq_cnn_t c, const acq_synth_batch* batch, float pos
     rc = run_map(c, src, nb, F, c->act[0], st);
     if (rc != ACQ_OK) return rc;
     CNN_HIP(launch_labels(c->d_tx, c->d_ntx, nb, F, src.chip_len, c->labels, st));
-    CNN_HIP(launch_fill_f32(c->grad, c->lay.total, st));
-    CNN_HIP(launch_fill_f32(c->loss, 1, st));
-    rc = run_forward(c, c->act[0], nb, F, st);
-    if (rc == ACQ_OK) rc = run_backward(c, c->act[0], nb, F, c->labels, pos_weight, st);
+    rc = run_gradients(c, c->act[0], nb, F, c->labels, pos_weight, nullptr, st);
     if (rc != ACQ_OK) return rc;
     c->step += 1;
     CNN_HIP(launch_adam(c->theta, c->grad, c->m, c->v, c->lay.total, lr, 0.9f, 0.999f, 1e-8f, c->step, c->lay,
                         c->bf ? c->w_bf : nullptr, c->bf ? c->wt_bf : nullptr, st));
-    CNN_HIP(hipMemcpyAsync(c->h_scalar, c->loss, sizeof(float), hipMemcpyDeviceToHost, st));
     CNN_HIP(hipStreamSynchronize(st));
     *loss = float(double(c->h_scalar[0]) / (double(nb) * double(F)));
     acq::clear_error();

@@ -96,19 +96,32 @@ hipError_t launch_conv_forward(const void* in, int cin, const void* wt, const fl
 // dA = dH * (H > 0).
 hipError_t launch_conv_dinput(const float* dH, const void* H, const void* w, float* dprev, int64_t rows,
                               int64_t F, int d, bool bf16, hipStream_t st);
-// Weight and bias gradients (accumulated): dW[i][c][o] += sum_r in[r + d(i-2)][c] dA[r][o],
-// db[o] += sum_r dA[r][o].  The bf16 form sums row chunks into `part` (FP32, at least
-// dweight_part_elems(cin) values; unused by the FP32 form) and adds the chunk sums
-// to dW and db in a fixed order.
+// Weight and bias gradients of one layer, dW[i][c][o] = sum_r in[r + d(i-2)][c] dA[r][o],
+// db[o] = sum_r dA[r][o]: the bf16 form leaves the sums of *chunks row chunks in
+// `part` (FP32, at least dweight_part_elems(cin) values).
 int64_t dweight_part_elems(int cin);
-hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* dW, float* db,
-                               float* part, int64_t part_elems, int64_t rows, int64_t F, int d, bool bf16,
-                               hipStream_t st);
-// Head logits y[r] = bh + h4[r] . wh; with labels also the loss terms and
-// dH4 = dy wh^T, dwh += h4^T dy, dbh += sum dy, loss_sum += sum of losses.
+hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* part,
+                               int64_t part_elems, int32_t* chunks, int64_t rows, int64_t F, int d, hipStream_t st);
+hipError_t launch_conv_dweight_ref(const float* in, int cin, const float* dH, const float* H, float* dW, float* db,
+                                   int64_t rows, int64_t F, int d, hipStream_t st);
+// Head logits y[r] = bh + h4[r] . wh; with labels also dH4 = dy wh^T and, of each
+// of head_groups(rows) row groups, the sums dwh = h4^T dy, dbh = sum dy and of the
+// loss terms: part[kHeadSums][groups].
+constexpr int kHeadSums = kCh + 2;
+int64_t head_groups(int64_t rows);
 hipError_t launch_head(const void* h4, const float* theta, int64_t wh_off, float* y, const float* labels,
-                       float pos_weight, float inv_rows, float* dH4, float* grad, float* loss_sum, int64_t rows,
-                       bool bf16, hipStream_t st);
+                       float pos_weight, float inv_rows, float* dH4, float* part, int64_t rows, bool bf16,
+                       hipStream_t st);
+// Partial sums added up in a fixed order: the head's and, where part is not null,
+// the layers', to grad and, if not null, out; the loss to host memory.
+struct GradSums {
+    const float* head;
+    int64_t head_groups, wh_off;
+    const float* part[kLayers];
+    int64_t w_off[kLayers];     // of the layer's weights, the bias after them
+    int32_t cin[kLayers], nchunks[kLayers];
+};
+hipError_t launch_grad_reduce(const GradSums& a, float* grad, float* out, float* h_loss, hipStream_t st);
 hipError_t launch_adam(float* theta, float* grad, float* m, float* v, int64_t n, float lr, float b1, float b2,
                        float eps, int t, const NetLayout& lay, uint16_t* w_bf, uint16_t* wt_bf, hipStream_t st);
 hipError_t launch_fill_f32(float* p, int64_t n, hipStream_t st);

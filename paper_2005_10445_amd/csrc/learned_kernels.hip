@@ -12,7 +12,7 @@
 //                     (v_mfma_f32_16x16x32_bf16, FP32 accumulation): forward and
 //                     input gradient
 //   k_conv_dw_taps    weight gradient, all taps of a channel group per workgroup,
-//                     on the same MFMA; k_dw_reduce adds the row-chunk sums
+//                     on the same MFMA; k_grad_reduce adds the row-chunk sums
 //   k_conv_*_ref      the same products in FP32 FMA, one output per thread
 //                     (reference arithmetic for tests)
 //   k_head            1x1 head, weighted BCE with logits and its gradient
@@ -530,7 +530,7 @@ constexpr size_t kMaxConvLds = size_t(160) << 10;   // LDS of a gfx950 compute u
 // consecutive rows are one read, and every tap reads the input tile at its own
 // row shift D*i.  Wave w holds the 16 channels 16w.. of every tap and output
 // channel (20 accumulator tiles); the sums stay in registers over the chunk and
-// are stored once as the chunk's sums, which k_dw_reduce adds up in a fixed
+// are stored once as the chunk's sums, which k_grad_reduce adds up in a fixed
 // order (atomic adds of every chunk's sums cost more than the products).  A pair (r, r + D(i-2)) whose rows lie in different
 // blocks contributes nothing: pieces with no block start near them need no
 // test, the others clear those operand rows tap by tap.
@@ -734,25 +734,50 @@ __global__ __launch_bounds__(256, 2) void k_conv_dw_taps(const uint16_t* __restr
     }
 }
 
-// dW[i][c][o] += sum over chunks of their sums, and db[o] likewise (the last
-// workgroup): workgroup (i, c) takes the 64 outputs of one row, thread (s, o4) the
-// chunks s, s + 16, ... of 4 outputs, then the 16 partial sums are added in order.
-__global__ __launch_bounds__(256) void k_dw_reduce(const float* __restrict__ part, const float* __restrict__ pdb,
-                                                   float* __restrict__ dW, float* __restrict__ db, int cin,
-                                                   int nchunks) {
+// Gradients from their partial sums, to grad and, if not null, to `out`, one launch
+// for all (a launch for each layer was 4 x 6.5 us over 65,536 rows, this one 14).
+// The first kHeadSums workgroups take a sum of the head each: thread t the groups
+// t, t + 256, ..., then the threads' in a tree (the loss goes to host memory).
+// Then workgroup (layer, i, c) takes the 64 outputs of one row (a layer's last one
+// its bias), thread (s, o4) the chunks s, s + 16, ... of 4 outputs, then the 16
+// partial sums are added in order.
+__global__ __launch_bounds__(256) void k_grad_reduce(GradSums a, float* __restrict__ grad, float* __restrict__ out,
+                                                     float* __restrict__ h_loss) {
     __shared__ float4 red[16][16];
     const int tid = int(threadIdx.x), s = tid >> 4, o4 = tid & 15;
-    const int row = int(blockIdx.x);             // i * cin + c, or the bias row after them
+    if (blockIdx.x < kHeadSums) {                // uniform
+        __shared__ float wsum[4];
+        const int q = int(blockIdx.x);
+        float v = 0.0f;
+        for (int64_t g = tid; g < a.head_groups; g += 256) v += a.head[q * a.head_groups + g];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if ((tid & 63) == 0) wsum[tid >> 6] = v;
+        __syncthreads();
+        if (tid == 0) {
+            v = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+            if (q <= kCh) {
+                grad[a.wh_off + q] = v;
+                if (out) out[a.wh_off + q] = v;
+            } else {
+                *h_loss = v;
+            }
+        }
+        return;
+    }
+    int row = int(blockIdx.x) - kHeadSums, l = 0;      // i * cin + c, or the bias row after them
+    while (l < kLayers - 1 && row > kTaps * a.cin[l]) row -= kTaps * a.cin[l++] + 1;
+    const int cin = a.cin[l], nchunks = a.nchunks[l];
     const int ngroups = cin / 64;
     const bool brow = row == kTaps * cin;
     const float* src;
     int64_t stride;
     if (brow) {
-        src = pdb + 4 * o4;
+        src = a.part[l] + int64_t(nchunks) * ngroups * kDwBlock + 4 * o4;
         stride = kCh;
     } else {
         const int i = row / cin, c = row - i * cin;
-        src = part + int64_t(c / 64) * kDwBlock + (i * 64 + c % 64) * kCh + 4 * o4;
+        src = a.part[l] + int64_t(c / 64) * kDwBlock + (i * 64 + c % 64) * kCh + 4 * o4;
         stride = int64_t(ngroups) * kDwBlock;
     }
     float4 t = {0.f, 0.f, 0.f, 0.f};
@@ -773,11 +798,17 @@ __global__ __launch_bounds__(256) void k_dw_reduce(const float* __restrict__ par
             u.z += red[k][tid].z;
             u.w += red[k][tid].w;
         }
-        float* dst = brow ? db + 4 * tid : dW + int64_t(row) * kCh + 4 * tid;
-        dst[0] += u.x;
-        dst[1] += u.y;
-        dst[2] += u.z;
-        dst[3] += u.w;
+        const int64_t o = a.w_off[l] + int64_t(row) * kCh + 4 * tid;      // the bias follows the weights
+        grad[o] = u.x;
+        grad[o + 1] = u.y;
+        grad[o + 2] = u.z;
+        grad[o + 3] = u.w;
+        if (out) {
+            out[o] = u.x;
+            out[o + 1] = u.y;
+            out[o + 2] = u.z;
+            out[o + 3] = u.w;
+        }
     }
 }
 
@@ -839,11 +870,9 @@ __global__ void k_conv_dw_ref(const float* __restrict__ in, int cin, const float
         if (fs < 0 || fs >= F) continue;
         acc = fmaf(in[(blk * F + fs) * cin + c], g, acc);
     }
-    dW[t] += acc;
-    if (i == 0 && c == 0) db[o] += bacc;
+    dW[t] = acc;
+    if (i == 0 && c == 0) db[o] = bacc;
 }
-
-// db[o] += sum_r dA[r][o] (bf16 activations)
 
 // ------------------------------------------------------------------ head and loss
 __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.0f) + log1pf(expf(-fabsf(x))); }
@@ -851,14 +880,16 @@ __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.0f) + log
 // Head and loss.  Sixteen lanes share a row, each holding four of its 64
 // channels (coalesced reads of the layer output and writes of dH4): the
 // logit is a 16-lane sum; the head-weight gradient is kept per lane over the
-// workgroup's rows and added over its 16 row slots in LDS at the end.
+// workgroup's rows and added over its 16 row slots in LDS at the end.  The
+// workgroups' sums go to `part`, which k_grad_reduce adds up.  (Rows one at a time
+// and an atomic add of each sum: 20 us over 65,536 rows, now 13.5.)
 constexpr int kHeadRows = 256;          // rows per workgroup
 
 template <bool BF>
 __global__ __launch_bounds__(256) void k_head(const void* __restrict__ h4, const float* __restrict__ theta,
                                               int64_t wh_off, float* __restrict__ y, const float* __restrict__ labels,
                                               float pw, float inv_rows, float* __restrict__ dH4,
-                                              float* __restrict__ grad, float* __restrict__ loss_sum, int64_t rows) {
+                                              float* __restrict__ part, int64_t rows) {
     __shared__ float sdw[16][kCh + 1];
     __shared__ float sred[2][16];
     const int t = int(threadIdx.x), j = t & 15, slot = t >> 4;
@@ -869,38 +900,45 @@ __global__ __launch_bounds__(256) void k_head(const void* __restrict__ h4, const
     float dw[4] = {0.f, 0.f, 0.f, 0.f};
     float dzs = 0.0f, ls = 0.0f;
     const int64_t rbase = int64_t(blockIdx.x) * kHeadRows;
-    for (int rr = 0; rr < kHeadRows; rr += 16) {
-        const int64_t r = rbase + rr + slot;
-        const bool ok = r < rows;
-        float h[4] = {0.f, 0.f, 0.f, 0.f};
-        if (ok) {
+    constexpr int U = 8;                 // a slot's rows loaded together
+    for (int rr = 0; rr < kHeadRows; rr += 16 * U) {
+        float h[U][4], lab[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = min(rbase + rr + 16 * u + slot, rows - 1);
             if constexpr (BF) {
                 const uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(h4) + r * kCh + 4 * j);
-                h[0] = __uint_as_float(v.x << 16);
-                h[1] = __uint_as_float(v.x & 0xffff0000u);
-                h[2] = __uint_as_float(v.y << 16);
-                h[3] = __uint_as_float(v.y & 0xffff0000u);
+                h[u][0] = __uint_as_float(v.x << 16);
+                h[u][1] = __uint_as_float(v.x & 0xffff0000u);
+                h[u][2] = __uint_as_float(v.y << 16);
+                h[u][3] = __uint_as_float(v.y & 0xffff0000u);
             } else {
                 const float4 v = *reinterpret_cast<const float4*>(static_cast<const float*>(h4) + r * kCh + 4 * j);
-                h[0] = v.x; h[1] = v.y; h[2] = v.z; h[3] = v.w;
+                h[u][0] = v.x; h[u][1] = v.y; h[u][2] = v.z; h[u][3] = v.w;
             }
+            lab[u] = labels ? labels[r] : 0.0f;
         }
-        float z = fmaf(h[3], w[3], fmaf(h[2], w[2], fmaf(h[1], w[1], h[0] * w[0])));
 #pragma unroll
-        for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
-        z += bias;
-        if (ok && j == 0) y[r] = z;
-        if (!labels) continue;     // uniform: inference
-        if (ok) {
-            const float lab = labels[r];
-            const float sg = 1.0f / (1.0f + expf(-z));
-            const float dz = (pw * lab * (sg - 1.0f) + (1.0f - lab) * sg) * inv_rows;
-            *reinterpret_cast<float4*>(dH4 + r * kCh + 4 * j) = make_float4(dz * w[0], dz * w[1], dz * w[2], dz * w[3]);
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = rbase + rr + 16 * u + slot;
+            const bool ok = r < rows;
+            float z = fmaf(h[u][3], w[3], fmaf(h[u][2], w[2], fmaf(h[u][1], w[1], h[u][0] * w[0])));
 #pragma unroll
-            for (int c = 0; c < 4; ++c) dw[c] = fmaf(dz, h[c], dw[c]);
-            if (j == 0) {
-                dzs += dz;
-                ls += pw * lab * softplus(-z) + (1.0f - lab) * softplus(z);
+            for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
+            z += bias;
+            if (ok && j == 0) y[r] = z;
+            if (!labels) continue;     // uniform: inference
+            if (ok) {
+                const float sg = 1.0f / (1.0f + expf(-z));
+                const float dz = (pw * lab[u] * (sg - 1.0f) + (1.0f - lab[u]) * sg) * inv_rows;
+                *reinterpret_cast<float4*>(dH4 + r * kCh + 4 * j) =
+                    make_float4(dz * w[0], dz * w[1], dz * w[2], dz * w[3]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dw[c] = fmaf(dz, h[u][c], dw[c]);
+                if (j == 0) {
+                    dzs += dz;
+                    ls += pw * lab[u] * softplus(-z) + (1.0f - lab[u]) * softplus(z);
+                }
             }
         }
     }
@@ -912,18 +950,10 @@ __global__ __launch_bounds__(256) void k_head(const void* __restrict__ h4, const
         sred[1][slot] = ls;
     }
     __syncthreads();
-    if (t < kCh) {
+    if (t < kHeadSums) {                 // 64 weights, the bias, the loss
         float a = 0.0f;
-        for (int q = 0; q < 16; ++q) a += sdw[q][t];
-        atomicAdd(&grad[wh_off + t], a);
-    } else if (t == kCh) {
-        float a = 0.0f, b = 0.0f;
-        for (int q = 0; q < 16; ++q) {
-            a += sred[0][q];
-            b += sred[1][q];
-        }
-        atomicAdd(&grad[wh_off + kCh], a);
-        atomicAdd(loss_sum, b);
+        for (int q = 0; q < 16; ++q) a += t < kCh ? sdw[q][t] : sred[t - kCh][q];
+        part[int64_t(t) * gridDim.x + blockIdx.x] = a;
     }
 }
 
@@ -1140,48 +1170,59 @@ int64_t dweight_part_elems(int cin) {
     return (kDwWgs + ngroups) * (kDwBlock + kCh);
 }
 
-hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* dW, float* db,
-                               float* part, int64_t part_elems, int64_t rows, int64_t F, int d, bool bf16,
-                               hipStream_t st) {
+hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* part,
+                               int64_t part_elems, int32_t* chunks, int64_t rows, int64_t F, int d, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
-    if (bf16) {
-        if (cin % 64 || cin <= 0 || rows >= (int64_t(1) << 31) || !part) return hipErrorInvalidValue;
-        const int64_t ngroups = cin / 64, pieces = (rows + kDwRows - 1) / kDwRows;
-        const int64_t chunk = kDwRows * std::max<int64_t>(1, (pieces * ngroups + kDwWgs - 1) / kDwWgs);
-        const int nchunks = int((rows + chunk - 1) / chunk);
-        if ((nchunks * ngroups) * (kDwBlock + kCh) > part_elems) return hipErrorInvalidValue;
-        float* pdb = db ? part + nchunks * ngroups * kDwBlock : nullptr;
-        const unsigned grid = unsigned((nchunks + kDwXcds - 1) / kDwXcds * kDwXcds * ngroups);
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const uint16_t*)in, cin, dH,
-                               (const uint16_t*)H, part, pdb, rows, F, int(chunk), nchunks);
-        };
-        switch (d) {
-        case 1: go(k_conv_dw_taps<1>); break;
-        case 2: go(k_conv_dw_taps<2>); break;
-        case 4: go(k_conv_dw_taps<4>); break;
-        case 8: go(k_conv_dw_taps<8>); break;
-        default: return hipErrorInvalidValue;    // the network's dilations only
-        }
-        hipLaunchKernelGGL(k_dw_reduce, dim3(unsigned(kTaps * cin + (db ? 1 : 0))), dim3(256), 0, st,
-                           (const float*)part, (const float*)pdb, dW, db, cin, nchunks);
-    } else {
-        hipLaunchKernelGGL(k_conv_dw_ref, dim3(blocks_for(int64_t(kTaps) * cin * kCh, 256)), dim3(256), 0, st,
-                           (const float*)in, cin, dH, (const float*)H, dW, db, rows, F, d);
+    if (cin % 64 || cin <= 0 || rows >= (int64_t(1) << 31) || !part) return hipErrorInvalidValue;
+    const int64_t ngroups = cin / 64, pieces = (rows + kDwRows - 1) / kDwRows;
+    const int64_t chunk = kDwRows * std::max<int64_t>(1, (pieces * ngroups + kDwWgs - 1) / kDwWgs);
+    const int nchunks = int((rows + chunk - 1) / chunk);
+    if ((nchunks * ngroups) * (kDwBlock + kCh) > part_elems) return hipErrorInvalidValue;
+    float* pdb = part + nchunks * ngroups * kDwBlock;
+    const unsigned grid = unsigned((nchunks + kDwXcds - 1) / kDwXcds * kDwXcds * ngroups);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const uint16_t*)in, cin, dH, (const uint16_t*)H,
+                           part, pdb, rows, F, int(chunk), nchunks);
+    };
+    switch (d) {
+    case 1: go(k_conv_dw_taps<1>); break;
+    case 2: go(k_conv_dw_taps<2>); break;
+    case 4: go(k_conv_dw_taps<4>); break;
+    case 8: go(k_conv_dw_taps<8>); break;
+    default: return hipErrorInvalidValue;    // the network's dilations only
     }
+    *chunks = nchunks;
     return hipGetLastError();
 }
 
+hipError_t launch_grad_reduce(const GradSums& a, float* grad, float* out, float* h_loss, hipStream_t st) {
+    int grid = kHeadSums;
+    for (int l = 0; l < kLayers; ++l)
+        if (a.part[l]) grid += kTaps * a.cin[l] + 1;
+    hipLaunchKernelGGL(k_grad_reduce, dim3(unsigned(grid)), dim3(256), 0, st, a, grad, out, h_loss);
+    return hipGetLastError();
+}
+
+hipError_t launch_conv_dweight_ref(const float* in, int cin, const float* dH, const float* H, float* dW, float* db,
+                                   int64_t rows, int64_t F, int d, hipStream_t st) {
+    if (rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_conv_dw_ref, dim3(blocks_for(int64_t(kTaps) * cin * kCh, 256)), dim3(256), 0, st, in, cin,
+                       dH, H, dW, db, rows, F, d);
+    return hipGetLastError();
+}
+
+int64_t head_groups(int64_t rows) { return (rows + kHeadRows - 1) / kHeadRows; }
+
 hipError_t launch_head(const void* h4, const float* theta, int64_t wh_off, float* y, const float* labels,
-                       float pos_weight, float inv_rows, float* dH4, float* grad, float* loss_sum, int64_t rows,
-                       bool bf16, hipStream_t st) {
+                       float pos_weight, float inv_rows, float* dH4, float* part, int64_t rows, bool bf16,
+                       hipStream_t st) {
     if (rows <= 0) return hipSuccess;
     if (bf16)
         hipLaunchKernelGGL(k_head<true>, dim3(blocks_for(rows, kHeadRows)), dim3(256), 0, st, h4, theta, wh_off, y,
-                           labels, pos_weight, inv_rows, dH4, grad, loss_sum, rows);
+                           labels, pos_weight, inv_rows, dH4, part, rows);
     else
         hipLaunchKernelGGL(k_head<false>, dim3(blocks_for(rows, kHeadRows)), dim3(256), 0, st, h4, theta, wh_off, y,
-                           labels, pos_weight, inv_rows, dH4, grad, loss_sum, rows);
+                           labels, pos_weight, inv_rows, dH4, part, rows);
     return hipGetLastError();
 }
 
