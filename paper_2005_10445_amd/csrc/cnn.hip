@@ -113,7 +113,7 @@ int build_cnn(acq_cnn_s* c) {
     CNN_HIP(dalloc(&c->dH[0], rows * kCh));
     CNN_HIP(dalloc(&c->dH[1], rows * kCh));
     if (c->bf)
-        for (int l = 0; l < kLayers; ++l) CNN_HIP(dalloc(&c->dw_part[l], size_t(dweight_part_elems(c->lay.cin[l]))));
+        for (int l = 0; l < kLayers; ++l) CNN_HIP(dalloc(&c->dw_part[l], size_t(dweight_part_elems(c->lay.cin[l], c->cfg.max_rows))));
     CNN_HIP(dalloc(&c->head_part, size_t(head_groups(c->cfg.max_rows) * kHeadSums)));
     CNN_HIP(dalloc(&c->y, rows));
     CNN_HIP(dalloc(&c->labels, rows));
@@ -207,7 +207,7 @@ int run_gradients(acq_cnn_s* c, const void* in, int32_t nblocks, int64_t F, cons
             dw.w_off[l] = c->lay.w_off[l];
             dw.cin[l] = c->lay.cin[l];
             CNN_HIP(launch_conv_dweight(x, c->lay.cin[l], c->dH[cur], c->act[l + 1], c->dw_part[l],
-                                        dweight_part_elems(c->lay.cin[l]), &dw.nchunks[l], rows, F, kDilation[l],
+                                        dweight_part_elems(c->lay.cin[l], c->cfg.max_rows), &dw.nchunks[l], rows, F, kDilation[l],
                                         st));
         } else {
             CNN_HIP(launch_conv_dweight_ref(static_cast<const float*>(x), c->lay.cin[l], c->dH[cur],

@@ -98,8 +98,8 @@ hipError_t launch_conv_dinput(const float* dH, const void* H, const void* w, flo
                               int64_t F, int d, bool bf16, hipStream_t st);
 // Weight and bias gradients of one layer, dW[i][c][o] = sum_r in[r + d(i-2)][c] dA[r][o],
 // db[o] = sum_r dA[r][o]: the bf16 form leaves the sums of *chunks row chunks in
-// `part` (FP32, at least dweight_part_elems(cin) values).
-int64_t dweight_part_elems(int cin);
+// `part` (FP32, at least dweight_part_elems(cin, rows) values, which grow with the rows).
+int64_t dweight_part_elems(int cin, int64_t max_rows);
 hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* part,
                                int64_t part_elems, int32_t* chunks, int64_t rows, int64_t F, int d, hipStream_t st);
 hipError_t launch_conv_dweight_ref(const float* in, int cin, const float* dH, const float* H, float* dW, float* db,

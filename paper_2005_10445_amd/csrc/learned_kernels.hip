@@ -539,7 +539,11 @@ constexpr int kDwPitchD = 72;    // dA tile row: 64 rows + 8 pad (bf16), 36 dwor
 constexpr int kDwPitchI = 104;   // input tile row: 64 + 4 * 8 rows + 8 pad, 52 dwords = 4 x odd, so
                                  // the 16 channels of an operand read fall on distinct banks
 constexpr int kDwXcds = 8;       // workgroups go to the XCDs in turn
-constexpr int kDwWgs = 256;      // workgroups per call (one per CU): sets the rows per workgroup
+// Workgroups of a call, which set the rows of each: one per compute unit, two where
+// that leaves each more than 8 pieces (256 inputs over 65,536 rows: 16 pieces,
+// 37.8 us; 8 pieces of twice the workgroups 27.9, and 3.4 us more to add up twice
+// the sums; four per unit 34.6 and 10.5 us more).
+constexpr int dw_wgs(int64_t pieces) { return pieces > 8 * 256 ? 512 : 256; }
 constexpr int kDwBlock = kTaps * 64 * kCh;   // sums of one chunk and 64-channel group
 
 // 8 bf16 of LDS row `p` starting SHIFT elements past a 16-byte boundary
@@ -1164,10 +1168,10 @@ hipError_t launch_conv_dinput(const float* dH, const void* H, const void* w, flo
     return hipGetLastError();
 }
 
-// chunks x groups <= (pieces / k + 1) * groups <= kDwWgs + groups for k = ceil(pieces * groups / kDwWgs)
-int64_t dweight_part_elems(int cin) {
-    const int64_t ngroups = std::max(cin / 64, 1);
-    return (kDwWgs + ngroups) * (kDwBlock + kCh);
+// chunks x groups <= (pieces / k + 1) * groups <= wgs + groups for k = ceil(pieces * groups / wgs)
+int64_t dweight_part_elems(int cin, int64_t max_rows) {
+    const int64_t ngroups = std::max(cin / 64, 1), pieces = (max_rows + kDwRows - 1) / kDwRows;
+    return (dw_wgs(pieces * ngroups) + ngroups) * (kDwBlock + kCh);
 }
 
 hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* part,
@@ -1175,7 +1179,8 @@ hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const v
     if (rows <= 0) return hipSuccess;
     if (cin % 64 || cin <= 0 || rows >= (int64_t(1) << 31) || !part) return hipErrorInvalidValue;
     const int64_t ngroups = cin / 64, pieces = (rows + kDwRows - 1) / kDwRows;
-    const int64_t chunk = kDwRows * std::max<int64_t>(1, (pieces * ngroups + kDwWgs - 1) / kDwWgs);
+    const int wgs = dw_wgs(pieces * ngroups);
+    const int64_t chunk = kDwRows * std::max<int64_t>(1, (pieces * ngroups + wgs - 1) / wgs);
     const int nchunks = int((rows + chunk - 1) / chunk);
     if ((nchunks * ngroups) * (kDwBlock + kCh) > part_elems) return hipErrorInvalidValue;
     float* pdb = part + nchunks * ngroups * kDwBlock;
