@@ -31,4 +31,54 @@ __device__ __forceinline__ bool last_arrival(unsigned* ticket, unsigned total) {
     return s_ticket == total - 1;
 }
 
+// The last workgroup's compaction of a small search: the records of the found
+// ones of at most MAX items, in item order, to out and h_out (either may be null),
+// at most `capacity` of them; returns how many were found.  slot(e) is item e's
+// record in dets, or -1.  NT threads; the slots are listed in LDS and the records
+// copied word by word.
+template <int NT, int MAX, class Rec, class Slot>
+__device__ __forceinline__ int compact_records(int items, const Rec* dets, Slot slot, int capacity, Rec* out,
+                                               Rec* h_out) {
+    constexpr int WORDS = int(sizeof(Rec) / 8);
+    static_assert(sizeof(Rec) % 8 == 0 && NT % 64 == 0, "records of whole words, whole waves");
+    __shared__ int s_slot[MAX], s_wave[NT / 64];
+    const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
+    int base = 0;
+    for (int e0 = 0; e0 < items; e0 += NT) {
+        const int e = e0 + t;
+        const int s = e < items ? slot(e) : -1;
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(s >= 0);
+        if (lane == 0) s_wave[wave] = __popcll(mask);
+        __syncthreads();
+        int o = base + __popcll(mask & ((1ull << lane) - 1ull));
+        for (int w = 0; w < NT / 64; ++w) {
+            if (w < wave) o += s_wave[w];
+            base += s_wave[w];
+        }
+        if (s >= 0) s_slot[o] = s;
+        __syncthreads();
+    }
+    const int n = (base < capacity ? base : capacity) * WORDS;
+    for (int i = t; i < n; i += NT) {
+        const int r = i / WORDS;
+        const unsigned long long v =
+            agent_load(reinterpret_cast<const unsigned long long*>(&dets[s_slot[r]]) + (i - r * WORDS));
+        if (out) reinterpret_cast<unsigned long long*>(out)[i] = v;
+        if (h_out) reinterpret_cast<unsigned long long*>(h_out)[i] = v;
+    }
+    return base;
+}
+
+// A record that another workgroup's compact_records reads.
+template <class Rec>
+__device__ __forceinline__ void agent_store_record(Rec* p, const Rec& r) {
+    union {
+        Rec rec;
+        unsigned long long u[sizeof(Rec) / 8];
+    } o;
+    o.rec = r;
+#pragma unroll
+    for (int i = 0; i < int(sizeof(Rec) / 8); ++i) agent_store(reinterpret_cast<unsigned long long*>(p) + i, o.u[i]);
+}
+
 }  // namespace acq

@@ -46,6 +46,7 @@
 #include <vector>
 
 #include "acq.h"
+#include "arrival.h"
 #include "device_common.h"
 #include "host_logic.h"
 #include "kernels.h"
@@ -119,6 +120,8 @@ struct FrontArgs {
     float2* out;                // replica: [T][out_stride] (d, 0)
     float* out_d;               // block: d at the block's zoff
     float* out_u;               // block: u at the block's zoff
+    unsigned long long* keys;   // block: [nkeys] peak keys to clear
+    int32_t nkeys;
     int64_t n_in, n_out, out_stride;     // replica mode
     double lo_cyc;              // f_LO / Fs
     float2 lo_step[16];         // exp(-j 2 pi (f_LO / Fs) (NT m)), m < 16 (FP64, rounded once)
@@ -143,6 +146,7 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
         s = int(blockIdx.x) % a.nseg;
         tag = int(blockIdx.x) / a.nseg;
     } else {
+        for (int i = int(blockIdx.x) * 256 + int(threadIdx.x); i < a.nkeys; i += int(gridDim.x) * 256) a.keys[i] = 0ull;
         const int b = fsk_task_of(a.tasks, int(blockIdx.x));
         const FskTask tk = a.tasks.t[b];
         s = int(blockIdx.x) - tk.fseg0;
@@ -268,6 +272,13 @@ __global__ void k_fsk_conj_scale(float2* bank, int64_t count, float scale) {
         const float2 v = bank[i];
         bank[i] = make_float2(v.x * scale, -v.y * scale);
     }
+}
+
+// rows of real parts: out[t][i] = in[t][i].x, i < stride, of count values in all
+__global__ void k_fsk_real(const float2* __restrict__ in, int64_t in_stride, float* __restrict__ out, int64_t stride,
+                           int64_t count) {
+    const int64_t o = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (o < count) out[o] = in[o / stride * in_stride + o % stride].x;
 }
 
 __global__ void k_fsk_fill(float2* p, int64_t count) {
@@ -546,11 +557,14 @@ __global__ __launch_bounds__(E::NT, 4) void k_fsk_phase(FskCorrArgs a) {
 struct FskRefineArgs {
     const float* d;             // the blocks' d (each at its zoff)
     const float* u;
-    const float2* tmpl;         // [T][tstride] (d^(c), 0)
+    const float* tmpl;          // [T][tstride] d^(c), zero beyond n_t
     const unsigned long long* keys;     // [items]
     double* partial;            // [items][kFskParts][kFskSums]
     acq_fsk_detection* dets;    // [items]
     int32_t* found;             // [items]
+    unsigned* tickets;          // [1 + items] arrivals, zero before and after each call
+    acq_fsk_detection* h_out;   // host results of a call of at most kTailItems items, else nullptr
+    int32_t* h_count;
     FskTasks tasks;
     int64_t nt, tstride;
     double theta;
@@ -571,116 +585,24 @@ __device__ __forceinline__ FskItem fsk_item(const FskRefineArgs& a, int item) {
 
 // FP64 sums over lags tau*-3 .. tau*+3 around the peak key: w_c, p_c and q at
 // each lag and E_c, enough for the re-maximisation over +/-1 and one
-// re-centring.  Each (tag, part) workgroup sums a fixed chunk of the template
-// in a fixed order and the parts are added in order: deterministic.
+// re-centring.  Each (item, part) workgroup sums a fixed chunk of the template
+// in a fixed order and the last of an item's to arrive adds the parts in order:
+// deterministic.  It writes the item's result, and the last item of a call of at
+// most kTailItems the results to the host.
+// A thread takes 4 template samples at a time, whose 7 lags use 10 block samples
+// (from LDS, in three 16-byte reads of d and of u), and a chunk's loads are all
+// in flight before the first is waited for.  (One sample at a time, its loads
+// waited for in turn, 47 us for 128 templates of 65,736 samples, with launches for
+// the results, their order and two copies after it; 33 us now, the search 444 ->
+// 409 us, 64 tracking tasks 263 -> 230 us.)
 constexpr int kFskWin = 7;
 constexpr int kFskParts = 16;
 constexpr int kFskSums = 3 * kFskWin + 1;
-constexpr int kFskStage = 4608;     // d and u samples of one part staged in LDS (longer parts read global)
+constexpr int kFskChunk = 3072;     // template samples of a part staged in LDS at a time, at most
 
-__global__ __launch_bounds__(256) void k_fsk_refine_sums(FskRefineArgs a) {
-    constexpr int NT = 256, NW = NT / 64;
-    const int item = int(blockIdx.x) / kFskParts, part = int(blockIdx.x) % kFskParts;
-    const FskItem fi = fsk_item(a, item);
-    const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
-    __shared__ double red[NW][kFskSums];
-    double* out = a.partial + (size_t(item) * kFskParts + part) * kFskSums;
-    const unsigned long long key = fi.tk.lags > 0 ? a.keys[item] : 0ull;
-    if (key == 0ull) {
-        if (t < kFskSums) out[t] = 0.0;
-        return;
-    }
-    const int64_t lam0 = int64_t(~unsigned(key & 0xffffffffull)) - kFskWin / 2;
-    const float2* dc = a.tmpl + size_t(fi.tag) * size_t(a.tstride);
-    const float* db = a.d + fi.tk.zoff;
-    const float* ub = a.u + fi.tk.zoff;
-    const int64_t ch = (a.nt + kFskParts - 1) / kFskParts;
-    const int64_t i0 = int64_t(part) * ch, i1 = min(a.nt, i0 + ch);
-    // the part reads block samples k0 .. k0 + span - 1 (zero outside the block),
-    // each kFskWin times: stage them in LDS when they fit
-    __shared__ float s_d[kFskStage], s_u[kFskStage];
-    const int64_t k0 = lam0 + i0;
-    const int64_t span = i1 > i0 ? i1 - i0 + kFskWin - 1 : 0;
-    const bool staged = span <= kFskStage;
-    if (staged) {
-        for (int64_t q = t; q < span; q += NT) {
-            const int64_t k = k0 + q;
-            const bool in = k >= 0 && k < fi.tk.n;
-            s_d[q] = in ? db[k] : 0.f;
-            s_u[q] = in ? ub[k] : 0.f;
-        }
-    }
-    __syncthreads();
-    double wv[kFskWin], pv[kFskWin], qv[kFskWin], ec = 0.0;
-#pragma unroll
-    for (int w = 0; w < kFskWin; ++w) wv[w] = pv[w] = qv[w] = 0.0;
-    for (int64_t i = i0 + t; i < i1; i += NT) {
-        const double c = dc[i].x;
-        ec += c * c;
-#pragma unroll
-        for (int w = 0; w < kFskWin; ++w) {
-            double zd = 0.0, zu = 0.0;
-            if (staged) {                           // zero outside the block, as staged
-                zd = s_d[i - i0 + w];
-                zu = s_u[i - i0 + w];
-            } else {
-                const int64_t k = lam0 + w + i;
-                if (k >= 0 && k < fi.tk.n) {
-                    zd = db[k];
-                    zu = ub[k];
-                }
-            }
-            wv[w] += c * zd;
-            pv[w] += c * zu;
-            qv[w] += zd * zd;
-        }
-    }
-#pragma unroll
-    for (int w = 0; w < kFskWin; ++w) {
-        const double r0 = wave_sum(wv[w]), r1 = wave_sum(pv[w]), r2 = wave_sum(qv[w]);
-        if (lane == 0) {
-            red[wave][3 * w] = r0;
-            red[wave][3 * w + 1] = r1;
-            red[wave][3 * w + 2] = r2;
-        }
-    }
-    const double es = wave_sum(ec);
-    if (lane == 0) red[wave][3 * kFskWin] = es;
-    __syncthreads();
-    if (t < kFskSums) {
-        double v = 0.0;
-        for (int q = 0; q < NW; ++q) v += red[q][t];
-        out[t] = v;
-    }
-}
-
-// One wave per item: lane k < kFskSums adds sum k over the parts in order;
-// lane 0 re-maximises |w_c| over +/-1 lag (one re-centring when it lands on
-// the edge), fits the parabola and writes the result.
-__global__ __launch_bounds__(64) void k_fsk_refine_final(FskRefineArgs a) {
-    const int item = int(blockIdx.x);
-    const FskItem fi = fsk_item(a, item);
+__device__ __forceinline__ void fsk_result(const FskRefineArgs& a, const FskItem& fi, int item, int64_t lam0,
+                                           const double* S, const double* A) {
     const int64_t lags = fi.tk.lags;
-    const unsigned long long key = lags > 0 ? a.keys[item] : 0ull;
-    const int t = int(threadIdx.x);
-    if (key == 0ull) {
-        if (t == 0) a.found[item] = 0;
-        return;
-    }
-    __shared__ double S[kFskSums];
-    if (t < kFskSums) {
-        double v = 0.0;
-        for (int p = 0; p < kFskParts; ++p) v += a.partial[(size_t(item) * kFskParts + p) * kFskSums + t];
-        S[t] = v;
-    }
-    __syncthreads();
-    if (t != 0) return;
-    const int64_t lam0 = int64_t(~unsigned(key & 0xffffffffull)) - kFskWin / 2;
-    double A[kFskWin];
-    for (int w = 0; w < kFskWin; ++w) {
-        const int64_t lam = lam0 + w;
-        A[w] = (lam >= 0 && lam < lags) ? fabs(S[3 * w]) : -1.0;
-    }
     const double Ec = S[3 * kFskWin];
     int c = kFskWin / 2;
     bool hit = false;
@@ -719,8 +641,131 @@ __global__ __launch_bounds__(64) void k_fsk_refine_final(FskRefineArgs a) {
     r.p = S[3 * c + 1];
     r.q = S[3 * c + 2];
     r.z = (r.q > 0.0 && Ec > 0.0) ? r.xcorr * r.xcorr / (r.q * Ec) : 0.0;
-    a.dets[item] = r;
-    a.found[item] = (a.theta <= 0.0 || r.z >= a.theta) ? 1 : 0;
+    agent_store_record(&a.dets[item], r);
+    agent_store(&a.found[item], (a.theta <= 0.0 || r.z >= a.theta) ? 1 : 0);
+}
+
+__global__ __launch_bounds__(256, 4) void k_fsk_refine(FskRefineArgs a) {
+    constexpr int NT = 256, NW = NT / 64;
+    constexpr int G = kFskChunk / (4 * NT);          // groups of 4 samples per thread and chunk
+    constexpr int S = (kFskChunk + 8 + NT - 1) / NT; // staged samples per thread
+    __shared__ __align__(16) float s_d[S * NT], s_u[S * NT];
+    __shared__ double red[NW][kFskSums];
+    __shared__ double sums[kFskSums], amp[kFskWin];
+    const int item = int(blockIdx.x) / kFskParts, part = int(blockIdx.x) % kFskParts;
+    const int items = int(gridDim.x) / kFskParts;
+    const FskItem fi = fsk_item(a, item);
+    const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
+    const unsigned long long key = fi.tk.lags > 0 ? a.keys[item] : 0ull;
+    if (key != 0ull) {
+        const int64_t lam0 = int64_t(~unsigned(key & 0xffffffffull)) - kFskWin / 2;
+        const float* dc = a.tmpl + size_t(fi.tag) * size_t(a.tstride);
+        const int64_t ch = ((a.nt + kFskParts - 1) / kFskParts + 3) / 4 * 4;     // whole groups
+        const int64_t i0 = min(a.nt, int64_t(part) * ch), i1 = min(a.nt, i0 + ch);
+        double wv[kFskWin], pv[kFskWin], qv[kFskWin], ec = 0.0;
+#pragma unroll
+        for (int w = 0; w < kFskWin; ++w) wv[w] = pv[w] = qv[w] = 0.0;
+        const int64_t nch = (ch + kFskChunk - 1) / kFskChunk, cl = (ch + 4 * nch - 1) / (4 * nch) * 4;  // even chunks
+        for (int64_t c0 = i0; c0 < i1; c0 += cl) {
+            const int len = int(min(i1 - c0, cl));
+            float4 cs[G];                            // (the template's rows end in whole groups)
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+                cs[g] = *reinterpret_cast<const float4*>(dc + c0 + min(4 * (t + NT * g), (len - 1) / 4 * 4));
+            // block samples from k0 on, by buffer loads bounded by the block: zero
+            // outside it (a position before its start is a large unsigned offset)
+            const int64_t k0 = lam0 + c0, first = k0 > 0 ? k0 : 0;
+            const int64_t left = min(fi.tk.n - first, int64_t(S * NT));
+            const uint32_t bytes = left > 0 ? uint32_t(left) * 4u : 0u;
+            const __amdgpu_buffer_rsrc_t dr = make_rsrc(a.d + fi.tk.zoff + first, bytes);
+            const __amdgpu_buffer_rsrc_t ur = make_rsrc(a.u + fi.tk.zoff + first, bytes);
+            const int q0 = int(k0 - first) + t;
+            float sd[S], su[S];
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                sd[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, (q0 + NT * q) * 4, 0, 0));
+                su[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ur, (q0 + NT * q) * 4, 0, 0));
+            }
+            if (c0 != i0) __syncthreads();           // the chunk before has been read
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                s_d[t + NT * q] = sd[q];
+                s_u[t + NT * q] = su[q];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int o = 4 * (t + NT * g);
+                if (o >= len) break;
+                double zd[12], zu[12];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const float4 vd = *reinterpret_cast<const float4*>(&s_d[o + 4 * q]);
+                    const float4 vu = *reinterpret_cast<const float4*>(&s_u[o + 4 * q]);
+                    zd[4 * q] = vd.x; zd[4 * q + 1] = vd.y; zd[4 * q + 2] = vd.z; zd[4 * q + 3] = vd.w;
+                    zu[4 * q] = vu.x; zu[4 * q + 1] = vu.y; zu[4 * q + 2] = vu.z; zu[4 * q + 3] = vu.w;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (o + e >= len) break;
+                    const double c = e == 0 ? cs[g].x : e == 1 ? cs[g].y : e == 2 ? cs[g].z : cs[g].w;
+                    ec += c * c;
+#pragma unroll
+                    for (int w = 0; w < kFskWin; ++w) {
+                        wv[w] += c * zd[e + w];
+                        pv[w] += c * zu[e + w];
+                        qv[w] += zd[e + w] * zd[e + w];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < kFskWin; ++w) {
+            const double r0 = wave_sum(wv[w]), r1 = wave_sum(pv[w]), r2 = wave_sum(qv[w]);
+            if (lane == 0) {
+                red[wave][3 * w] = r0;
+                red[wave][3 * w + 1] = r1;
+                red[wave][3 * w + 2] = r2;
+            }
+        }
+        const double es = wave_sum(ec);
+        if (lane == 0) red[wave][3 * kFskWin] = es;
+        __syncthreads();
+        if (t < kFskSums) {
+            double v = 0.0;
+            for (int q = 0; q < NW; ++q) v += red[q][t];
+            agent_store(&a.partial[(size_t(item) * kFskParts + part) * kFskSums + t], v);
+        }
+        if (!last_arrival(&a.tickets[1 + item], kFskParts)) return;
+        if (t < kFskSums) {
+            double q[kFskParts], v = 0.0;
+#pragma unroll
+            for (int p = 0; p < kFskParts; ++p) q[p] = agent_load(&a.partial[(size_t(item) * kFskParts + p) * kFskSums + t]);
+#pragma unroll
+            for (int p = 0; p < kFskParts; ++p) v += q[p];
+            sums[t] = v;
+        }
+        __syncthreads();
+        if (t < kFskWin) {
+            const int64_t lam = lam0 + t;
+            amp[t] = (lam >= 0 && lam < fi.tk.lags) ? fabs(sums[3 * t]) : -1.0;
+        }
+        __syncthreads();
+        if (t == 0) {
+            fsk_result(a, fi, item, lam0, sums, amp);
+            a.tickets[1 + item] = 0u;                // for the next call
+        }
+    } else {
+        if (part != 0) return;
+        if (t == 0) agent_store(&a.found[item], 0);
+    }
+    if (!a.h_out || !last_arrival(&a.tickets[0], unsigned(items))) return;
+    auto slot = [&](int e) { return agent_load(&a.found[e]) ? e : -1; };
+    const int n = compact_records<NT, kTailItems, acq_fsk_detection>(items, a.dets, slot, items, nullptr, a.h_out);
+    if (t == 0) {
+        *a.h_count = n;
+        a.tickets[0] = 0u;
+    }
 }
 
 // Results in tag order: one workgroup of 1024 threads, runs of tags per
@@ -885,7 +930,7 @@ int fsk_geometry(const acq_fsk_config* c, FskGeometry* g) {
     g->group = g->P > 1 ? std::min<int64_t>(std::max<int64_t>(T * ((g->max_seg + 1) / 2), slots),
                                             std::max<int64_t>(1, kFskGroup / M)) * M : 0;
     g->bytes = c->max_block_len * 8 + slots * M * 8 + g->group * 8 + slots * 2 * int64_t(sizeof(FskUnit)) +
-               2 * T * M * 8 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
+               T * M * 8 + T * (g->nt + 4) * 4 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
                kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
     return ACQ_OK;
 }
@@ -943,7 +988,8 @@ struct acq_fsk_plan_s {
     float2* d_rootsF = nullptr;         // unit roots and pass twiddles of the front end's transform
     uint8_t* d_bits = nullptr;          // [T][nbits]
     double* d_bitcyc = nullptr;         // [T][nbits]
-    float2* d_tmpl = nullptr;           // [T][M] (d^(c), 0), zero beyond n_t
+    float* d_tmpl = nullptr;            // [T][tstride] d^(c), zero beyond n_t
+    int64_t tstride = 0;                // n_t in whole groups of 4
     float2* d_bank = nullptr;           // [T][M] conj(DFT_M(d^(c))) / M
     float* d_d = nullptr;               // [max_block_len] demodulated d
     float* d_u = nullptr;               // [max_block_len] u
@@ -960,6 +1006,7 @@ struct acq_fsk_plan_s {
     acq_fsk_detection* d_out = nullptr;
     int32_t* d_found = nullptr;
     int32_t* d_count = nullptr;
+    unsigned* d_tickets = nullptr;      // [1 + items] refinement arrivals
     acq::FskTask* d_tasks = nullptr;        // [max_tasks] blocks of a call, then (right after the call's
                                             // blocks) [2 slots] its correlation segments
     acq::FskTask* h_tasks = nullptr;        // pinned, the same
@@ -1003,7 +1050,7 @@ void free_fsk(acq_fsk_plan_s* p) {
             if (e) (void)hipEventDestroy(e);
     void* dev[] = {p->d_G1, p->d_G0, p->d_rootsF, p->d_bits, p->d_bitcyc, p->d_tmpl, p->d_bank, p->d_d, p->d_u, p->d_X, p->d_G, p->d_partial,
                    p->d_rootsM, p->d_rootsSub, p->d_b1tab, p->d_tdescs, p->d_tcounts, p->d_keys,
-                   p->d_dets, p->d_out, p->d_found, p->d_count};
+                   p->d_dets, p->d_out, p->d_found, p->d_count, p->d_tickets};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (p->h_out) (void)hipHostFree(p->h_out);
@@ -1015,7 +1062,8 @@ void free_fsk(acq_fsk_plan_s* p) {
 
 // Replica mode writes `out` ([T][M]); block mode processes the call's blocks
 // (device task table, fsegs front-end segments in all) into the plan's d, u.
-hipError_t launch_front(acq_fsk_plan_s* p, const acq::FskTasks& tasks, int fsegs, bool replica, float2* out) {
+hipError_t launch_front(acq_fsk_plan_s* p, const acq::FskTasks& tasks, int fsegs, bool replica, float2* out,
+                        int nkeys) {
     const acq_fsk_config& c = p->cfg;
     acq::FrontArgs a{};
     a.tasks = tasks;
@@ -1027,6 +1075,8 @@ hipError_t launch_front(acq_fsk_plan_s* p, const acq::FskTasks& tasks, int fsegs
     a.out = out;
     a.out_d = p->d_d;
     a.out_u = p->d_u;
+    a.keys = p->d_keys;
+    a.nkeys = nkeys;
     a.n_in = int64_t(c.num_bits) * c.mf_len;
     a.n_out = p->g.nt;
     a.out_stride = p->g.M;
@@ -1083,7 +1133,14 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(dalloc(&p->d_rootsF, size_t(acq::transform_roots_len(acq::kFrontN))));
     FSK_HIP(dalloc(&p->d_bits, T * NB));
     FSK_HIP(dalloc(&p->d_bitcyc, T * NB));
-    FSK_HIP(dalloc(&p->d_tmpl, T * M));
+    p->tstride = (g.nt + 3) / 4 * 4;
+    FSK_HIP(dalloc(&p->d_tmpl, T * size_t(p->tstride)));
+    float2* wave = nullptr;                         // [T][M] (d^(c), 0), zero beyond n_t, while the plan is made
+    FSK_HIP(dalloc(&wave, T * M));
+    struct WaveFree {
+        float2* p;
+        ~WaveFree() { (void)hipFree(p); }
+    } wave_free{wave};
     FSK_HIP(dalloc(&p->d_bank, T * M));
     const size_t slots = size_t(g.slots);
     const size_t items = size_t(g.items);
@@ -1106,6 +1163,8 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(dalloc(&p->d_out, items));
     FSK_HIP(dalloc(&p->d_found, items));
     FSK_HIP(dalloc(&p->d_count, 1));
+    FSK_HIP(dalloc(&p->d_tickets, items + 1));
+    FSK_HIP(acq::launch_fill_i32(reinterpret_cast<int*>(p->d_tickets), int64_t(items) + 1, p->stream));
     FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_out), sizeof(acq_fsk_detection) * items));
     FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_count), sizeof(int32_t)));
 
@@ -1139,13 +1198,13 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
 
     // replica templates d^(c) (zero beyond n_t), then their spectra
     const int64_t tcount = int64_t(T * M);
-    hipLaunchKernelGGL(acq::k_fsk_fill, dim3(unsigned((tcount + 255) / 256)), dim3(256), 0, st, p->d_tmpl, tcount);
+    hipLaunchKernelGGL(acq::k_fsk_fill, dim3(unsigned((tcount + 255) / 256)), dim3(256), 0, st, wave, tcount);
     FSK_HIP(hipGetLastError());
-    FSK_HIP(launch_front(p, acq::FskTasks{}, 0, true, p->d_tmpl));
+    FSK_HIP(launch_front(p, acq::FskTasks{}, 0, true, wave, 0));
     std::vector<BlockDesc> descs(T);
     for (size_t t = 0; t < T; ++t) {
         BlockDesc d{};
-        d.x = p->d_tmpl + t * M;
+        d.x = wave + t * M;
         d.n = g.nt;
         d.lags = 1;
         d.seg0 = int32_t(t);
@@ -1163,6 +1222,10 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(acq::launch_forward(fa, int(T) * g.P, int(T), 0, 0, g.log2_sub, ACQ_FP32, st));
     hipLaunchKernelGGL(acq::k_fsk_conj_scale, dim3(unsigned((tcount + 255) / 256)), dim3(256), 0, st, p->d_bank, tcount,
                        float(1.0 / double(g.M)));
+    FSK_HIP(hipGetLastError());
+    // the refinement reads d^(c) alone: half the bytes, 16 at a time
+    hipLaunchKernelGGL(acq::k_fsk_real, dim3(unsigned((int64_t(T) * p->tstride + 255) / 256)), dim3(256), 0, st, wave,
+                       int64_t(M), p->d_tmpl, p->tstride, int64_t(T) * p->tstride);
     FSK_HIP(hipGetLastError());
     FSK_HIP(hipStreamSynchronize(st));
     return ACQ_OK;
@@ -1239,7 +1302,7 @@ int acq_fsk_demod(acq_fsk_plan_t p, const int16_t* iq, int64_t n, float* d, floa
     tk.tag = -1;
     tk.nfseg = int((n + p->g.vf - 1) / p->g.vf);
     FSK_HIP(hipMemcpyAsync(p->d_tasks, p->h_tasks, sizeof(acq::FskTask), hipMemcpyHostToDevice, p->stream));
-    FSK_HIP(launch_front(p, acq::FskTasks{p->d_tasks, 1, 0}, tk.nfseg, false, nullptr));
+    FSK_HIP(launch_front(p, acq::FskTasks{p->d_tasks, 1, 0}, tk.nfseg, false, nullptr, 0));
     FSK_HIP(hipMemcpyAsync(d, p->d_d, sizeof(float) * size_t(n), hipMemcpyDeviceToDevice, p->stream));
     FSK_HIP(hipMemcpyAsync(u, p->d_u, sizeof(float) * size_t(n), hipMemcpyDeviceToDevice, p->stream));
     FSK_HIP(hipStreamSynchronize(p->stream));
@@ -1250,8 +1313,8 @@ int acq_fsk_demod(acq_fsk_plan_t p, const int16_t* iq, int64_t n, float* d, floa
 int acq_fsk_template(acq_fsk_plan_t p, int32_t tag, float* out) {
     if (!p || !out) return acq::fail(ACQ_ERR_INVALID_ARG, "null argument");
     if (tag < 0 || tag >= p->cfg.num_tags) return acq::fail(ACQ_ERR_INVALID_ARG, "tag outside [0, num_tags)");
-    FSK_HIP(hipMemcpy2DAsync(out, sizeof(float), p->d_tmpl + size_t(tag) * size_t(p->g.M), sizeof(float2),
-                             sizeof(float), size_t(p->g.nt), hipMemcpyDeviceToDevice, p->stream));
+    FSK_HIP(hipMemcpyAsync(out, p->d_tmpl + size_t(tag) * size_t(p->tstride), sizeof(float) * size_t(p->g.nt),
+                           hipMemcpyDeviceToDevice, p->stream));
     FSK_HIP(hipStreamSynchronize(p->stream));
     acq::clear_error();
     return ACQ_OK;
@@ -1312,11 +1375,10 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
                            hipMemcpyHostToDevice, st));
     const acq::FskUnit* du = reinterpret_cast<const acq::FskUnit*>(p->d_tasks + nblocks);
     acq::FskTasks tt{p->d_tasks, nblocks, track ? 1 : 0};
-    FSK_HIP(acq::launch_fill_u64(p->d_keys, *items, st));
-    if (slots == 0) return ACQ_OK;
+    if (slots == 0) return ACQ_OK;                  // no lags: no key is read
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_FRONT);
-        FSK_HIP(launch_front(p, tt, fsegs, false, nullptr));
+        FSK_HIP(launch_front(p, tt, fsegs, false, nullptr, *items));
     }
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_FORWARD);
@@ -1378,20 +1440,26 @@ int finish_fsk(acq_fsk_plan_s* p, int nblocks, bool track, int items, acq_fsk_de
     ra.found = p->d_found;
     ra.tasks = acq::FskTasks{p->d_tasks, nblocks, track ? 1 : 0};
     ra.nt = g.nt;
-    ra.tstride = g.M;
+    ra.tstride = p->tstride;
     ra.theta = p->cfg.threshold;
+    ra.tickets = p->d_tickets;
+    // few results are ordered and sent to the host by the refinement launch itself
+    const bool tail = items <= acq::kTailItems;
+    ra.h_out = tail ? p->h_out : nullptr;
+    ra.h_count = p->h_count;
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_REFINE);
-        hipLaunchKernelGGL(acq::k_fsk_refine_sums, dim3(unsigned(items) * acq::kFskParts), dim3(256), 0, st, ra);
-        FSK_HIP(hipGetLastError());
-        hipLaunchKernelGGL(acq::k_fsk_refine_final, dim3(unsigned(items)), dim3(64), 0, st, ra);
+        hipLaunchKernelGGL(acq::k_fsk_refine, dim3(unsigned(items) * acq::kFskParts), dim3(256), 0, st, ra);
         FSK_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(acq::k_fsk_compact, dim3(1), dim3(1024), 0, st, p->d_dets, p->d_found, items, p->d_out,
-                       p->d_count);
-    FSK_HIP(hipGetLastError());
-    FSK_HIP(hipMemcpyAsync(p->h_count, p->d_count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    FSK_HIP(hipMemcpyAsync(p->h_out, p->d_out, sizeof(acq_fsk_detection) * size_t(items), hipMemcpyDeviceToHost, st));
+    if (!tail) {
+        hipLaunchKernelGGL(acq::k_fsk_compact, dim3(1), dim3(1024), 0, st, p->d_dets, p->d_found, items, p->d_out,
+                           p->d_count);
+        FSK_HIP(hipGetLastError());
+        FSK_HIP(hipMemcpyAsync(p->h_count, p->d_count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        FSK_HIP(hipMemcpyAsync(p->h_out, p->d_out, sizeof(acq_fsk_detection) * size_t(items), hipMemcpyDeviceToHost,
+                               st));
+    }
     FSK_HIP(hipStreamSynchronize(st));
     const int32_t found = *p->h_count;
     *n_found = found;

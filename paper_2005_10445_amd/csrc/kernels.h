@@ -156,7 +156,6 @@ struct RefineArgs {
 constexpr int kRefineParts = 16;
 constexpr int kTailItems = 1024;
 
-hipError_t launch_fill_u64(unsigned long long* p, int64_t count, hipStream_t st);
 hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st);
 // grid: workgroups of the sub-transforms (items = segments * spc; 0: none);
 // combine_slots: segment slots the combine step covers (>= the segments in use);

@@ -95,11 +95,6 @@ __device__ __forceinline__ void sum_block_power(const BlockTable& bt, const Powe
     }
 }
 
-__global__ void k_fill_u64(unsigned long long* p, int64_t count) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0ull;
-}
-
 __global__ void k_fill_i32(int* p, int64_t count) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < count) p[i] = 0;
@@ -523,69 +518,41 @@ __device__ __forceinline__ void refine_record(const RefineArgs& a, const RefineI
     const double px = block_mean_power(a.parts + size_t(it.bi) * kPowerParts, d.n);
     const double z = px > 0.0 ? p0 / (double(a.L) * px) : 0.0;
     const bool suppressed = a.check_finite && a.bad[it.bi];
-    union {
-        acq_detection r;
-        unsigned long long u[sizeof(acq_detection) / 8];
-    } o;
-    o.r.tag = it.tag;
-    o.r.bin = k;
-    o.r.lag = lam;
-    o.r.toa_samples = double(lam) + delta;
-    o.r.freq_hz = a.freqs[k];
-    o.r.peak_power = p0;
-    o.r.z = z;
+    acq_detection r;
+    r.tag = it.tag;
+    r.bin = k;
+    r.lag = lam;
+    r.toa_samples = double(lam) + delta;
+    r.freq_hz = a.freqs[k];
+    r.peak_power = p0;
+    r.z = z;
     const double energy = sums[3 * wb + 2];
-    o.r.energy = energy;
-    o.r.block_power = px;
+    r.energy = energy;
+    r.block_power = px;
     // relative power and SNR (Section 3 step 8's power and SNR sums)
     const double Ld = double(a.L);
-    o.r.power = p0 / (Ld * Ld);
+    r.power = p0 / (Ld * Ld);
     const double s2 = (energy - p0 / Ld) / Ld;
-    o.r.snr = s2 > 0.0 ? o.r.power / s2 : __builtin_huge_val();
-    o.r.block = it.bi;
-    o.r.flags = flags;
-    o.r.crossings = int64_t(a.cross[it.slot]);
-    unsigned long long* rec = reinterpret_cast<unsigned long long*>(&a.dets[it.slot]);
-#pragma unroll
-    for (int i = 0; i < int(sizeof(acq_detection) / 8); ++i) agent_store(rec + i, o.u[i]);
+    r.snr = s2 > 0.0 ? r.power / s2 : __builtin_huge_val();
+    r.block = it.bi;
+    r.flags = flags;
+    r.crossings = int64_t(a.cross[it.slot]);
+    agent_store_record(&a.dets[it.slot], r);
     agent_store(&a.found[it.slot], z >= d.theta && !suppressed ? 1 : 0);
 }
 
 // The detections of a search of at most kTailItems items, in order, to a.out and
-// the host (as k_compact does): slots of the detections listed in LDS, then
-// their records copied word by word.
-__device__ __forceinline__ void compact_tail(const RefineArgs& a, int items, int* s_slot, int* s_wave) {
-    constexpr int NT = kRefineThreads, WORDS = int(sizeof(acq_detection) / 8);
-    const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
-    int base = 0;
-    for (int e0 = 0; e0 < items; e0 += NT) {
-        const int e = e0 + t;
-        int slot = -1;
+// the host (as k_compact does).
+__device__ __forceinline__ void compact_tail(const RefineArgs& a, int items) {
+    auto slot = [&](int e) {
         RefineItem it;
-        if (e < items && refine_item(a, e, &it) && agent_load(&a.found[it.slot])) slot = int(it.slot);
-        const unsigned long long mask = __builtin_amdgcn_ballot_w64(slot >= 0);
-        if (lane == 0) s_wave[wave] = __popcll(mask);
-        __syncthreads();
-        int o = base + __popcll(mask & ((1ull << lane) - 1ull));
-        for (int w = 0; w < NT / 64; ++w) {
-            if (w < wave) o += s_wave[w];
-            base += s_wave[w];
-        }
-        if (slot >= 0) s_slot[o] = slot;
-        __syncthreads();
-    }
-    const int n = min(base, a.capacity) * WORDS;
-    for (int i = t; i < n; i += NT) {
-        const int r = i / WORDS;
-        const unsigned long long v =
-            agent_load(reinterpret_cast<const unsigned long long*>(&a.dets[s_slot[r]]) + (i - r * WORDS));
-        reinterpret_cast<unsigned long long*>(a.out)[i] = v;
-        if (a.h_out) reinterpret_cast<unsigned long long*>(a.h_out)[i] = v;
-    }
-    if (t == 0) {
-        *a.count = base;
+        return refine_item(a, e, &it) && agent_load(&a.found[it.slot]) ? int(it.slot) : -1;
+    };
+    const int n = compact_records<kRefineThreads, kTailItems>(items, a.dets, slot, a.capacity, a.out, a.h_out);
+    if (threadIdx.x == 0) {
+        *a.count = n;
         if (a.h_out) {
-            a.h_count[0] = base;
+            a.h_count[0] = n;
             a.h_count[1] = *a.nbad;
         }
     }
@@ -594,7 +561,6 @@ __device__ __forceinline__ void compact_tail(const RefineArgs& a, int items, int
 template <int WMAX>
 __global__ __launch_bounds__(kRefineThreads) void k_refine(RefineArgs a) {
     __shared__ double sums[3 * WMAX], P[WMAX];
-    __shared__ int s_slot[kTailItems], s_wave[kRefineThreads / 64];
     const int item = int(blockIdx.x) / kRefineParts, part = int(blockIdx.x) % kRefineParts;
     const int items = a.blocks.nblocks() * (a.track ? 1 : a.T);
     if (item >= items) return;               // a batch smaller than the plan's capacity
@@ -626,7 +592,7 @@ __global__ __launch_bounds__(kRefineThreads) void k_refine(RefineArgs a) {
         if (part != 0) return;
         if (known && threadIdx.x == 0) agent_store(&a.found[it.slot], 0);
     }
-    if (a.tail && last_arrival(&a.tickets[0], unsigned(items))) compact_tail(a, items, s_slot, s_wave);
+    if (a.tail && last_arrival(&a.tickets[0], unsigned(items))) compact_tail(a, items);
 }
 
 // Detections in (block, tag) order.  One workgroup: each thread takes a
@@ -674,13 +640,6 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(BlockTable bt, cons
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_fill_u64(unsigned long long* p, int64_t count, hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    const int64_t blocks = (count + 255) / 256;
-    hipLaunchKernelGGL(k_fill_u64, dim3(unsigned(blocks)), dim3(256), 0, st, p, count);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_i32(int* p, int64_t count, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     const int64_t blocks = (count + 255) / 256;
