@@ -126,15 +126,22 @@ struct FrontArgs {
     double lo_cyc;              // f_LO / Fs
     float2 lo_step[16];         // exp(-j 2 pi (f_LO / Fs) (NT m)), m < 16 (FP64, rounded once)
     double f1_cyc, f0_cyc;      // tones, cycles per sample
-    int32_t nbits, sps, lg, vf, nseg, replica;   // nseg: segments per replica
+    int32_t nbits, sps, lg, vf, nseg;   // nseg: segments per replica
 };
 
 // One workgroup per (template, segment) of the replicas or per global segment
 // of the blocks: outputs s*vf .. s*vf + vf - 1 of the causal convolution with
-// the composed filters, from inputs s*vf - (lg-1) ..  Three workgroups per CU
-// (at most 168 VGPRs: the forward spectrum stays in registers through the
-// first inverse transform; at 128 it spills and runs slower).
-__global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
+// the composed filters, from inputs s*vf - (lg-1) ..  Four workgroups per CU (128
+// VGPRs; the forward spectrum stays in registers through the first inverse
+// transform), three when the templates and the blocks shared one kernel: 64 blocks
+// of 96,000 samples, 1600 workgroups, 56 us in three rounds, 50.5 us in two.  The
+// last butterflies of the second tone's transform and the roots and quotients lie
+// within the branch around each output.  Formed without branches they overlap
+// (46.8 us), but their products then fuse with the sums: other roundings of d and u
+// than before, 5e-10 of the FP64 results.
+// REPLICA: the templates, at plan time.
+template <bool REPLICA>
+__global__ __launch_bounds__(256, 4) void k_fsk_front(FrontArgs a) {
     using E = StockhamEngine<kFrontLog, false>;
     __shared__ float2 lds[E::LDS];
     E eng;
@@ -142,7 +149,7 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
     int s, tag = 0;
     const int16_t* iq = nullptr;
     int64_t n_in = a.n_in, n_out = a.n_out, zoff = 0;
-    if (a.replica) {
+    if constexpr (REPLICA) {
         s = int(blockIdx.x) % a.nseg;
         tag = int(blockIdx.x) / a.nseg;
     } else {
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
     }
     const int64_t base = int64_t(s) * a.vf - (a.lg - 1);
     float2 x[16];
-    if (a.replica) {
+    if constexpr (REPLICA) {
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int64_t p = base + eng.in_index(m);
@@ -200,15 +207,17 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
     }
     const __amdgpu_buffer_rsrc_t dummy = make_rsrc(a.roots, 8);   // unused by the Stockham engine
     eng.template transform<-1>(x, lds, dummy, nullptr);
+    const __amdgpu_buffer_rsrc_t g1 = make_rsrc(a.G1, kFrontN * 8), g0 = make_rsrc(a.G0, kFrontN * 8);
+    const int in0 = eng.in_index(0);                         // in_index(m) = in0 + NT m
     float a1[16];
     float2 w[16];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) w[m] = cmul(x[m], a.G1[eng.in_index(m)]);
+    for (int m = 0; m < 16; ++m) w[m] = cmul(x[m], bload(g1, in0 * 8, E::NT * m * 8));
     eng.template transform<+1>(w, lds, dummy, nullptr);
 #pragma unroll
     for (int m = 0; m < 16; ++m) a1[m] = sqrtf(fmaf(w[m].x, w[m].x, w[m].y * w[m].y));
 #pragma unroll
-    for (int m = 0; m < 16; ++m) w[m] = cmul(x[m], a.G0[eng.in_index(m)]);
+    for (int m = 0; m < 16; ++m) w[m] = cmul(x[m], bload(g0, in0 * 8, E::NT * m * 8));
     eng.template transform<+1>(w, lds, dummy, nullptr);
 #pragma unroll
     for (int m = 0; m < 16; ++m) {
@@ -218,7 +227,7 @@ __global__ __launch_bounds__(256, 3) void k_fsk_front(FrontArgs a) {
             const float a0 = sqrtf(fmaf(w[m].x, w[m].x, w[m].y * w[m].y));
             const float sum = a1[m] + a0, dif = a1[m] - a0;
             const float d = sum > 0.f ? dif / sum : 0.f;
-            if (a.replica) {
+            if constexpr (REPLICA) {
                 a.out[size_t(tag) * size_t(a.out_stride) + size_t(o)] = make_float2(d, 0.f);
             } else {
                 a.out_d[zoff + o] = d;
@@ -1096,10 +1105,12 @@ hipError_t launch_front(acq_fsk_plan_s* p, const acq::FskTasks& tasks, int fsegs
     a.lg = int(p->g.lg);
     a.vf = int(p->g.vf);
     a.nseg = int((a.n_out + p->g.vf - 1) / p->g.vf);
-    a.replica = replica ? 1 : 0;
     const unsigned grid = replica ? unsigned(a.nseg) * unsigned(c.num_tags) : unsigned(fsegs);
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL(acq::k_fsk_front, dim3(grid), dim3(256), 0, p->stream, a);
+    if (replica)
+        hipLaunchKernelGGL(acq::k_fsk_front<true>, dim3(grid), dim3(256), 0, p->stream, a);
+    else
+        hipLaunchKernelGGL(acq::k_fsk_front<false>, dim3(grid), dim3(256), 0, p->stream, a);
     return hipGetLastError();
 }
 
