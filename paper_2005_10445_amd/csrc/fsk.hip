@@ -190,15 +190,17 @@ __global__ __launch_bounds__(256, 4) void k_fsk_front(FrontArgs a) {
         sincospif(2.0f * float(cyc), &sn0, &cs0);
         const float2 e0 = make_float2(cs0, sn0);
         // samples outside the block are zero: buffer loads bounded by the
-        // block's samples (a position before its start is a large unsigned
-        // offset), so that all 16 are in flight together
+        // block's samples (those before its start at offset -1, past every
+        // bound), so that all 16 are in flight together.  Offsets must not wrap:
+        // where a negative one plus the load's immediate offset crosses zero
+        // within four lanes, the lanes past it read zero too.
         const int64_t first = base > 0 ? base : 0;
         const int64_t left = n_in - first < kFrontN ? n_in - first : kFrontN;
         const __amdgpu_buffer_rsrc_t ir = make_rsrc(iq + 2 * first, left > 0 ? uint32_t(left) * 4u : 0u);
         uint32_t raw[16];
 #pragma unroll
         for (int m = 0; m < 16; ++m)
-            raw[m] = __builtin_amdgcn_raw_buffer_load_b32(ir, int(base - first + eng.in_index(m)) * 4, 0, 0);
+            raw[m] = __builtin_amdgcn_raw_buffer_load_b32(ir, max(int(base - first) + eng.in_index(m), -1) * 4, 0, 0);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const float2 e = m ? cmul(e0, a.lo_step[m]) : e0;
@@ -682,7 +684,7 @@ __global__ __launch_bounds__(256, 4) void k_fsk_refine(FskRefineArgs a) {
             for (int g = 0; g < G; ++g)
                 cs[g] = *reinterpret_cast<const float4*>(dc + c0 + min(4 * (t + NT * g), (len - 1) / 4 * 4));
             // block samples from k0 on, by buffer loads bounded by the block: zero
-            // outside it (a position before its start is a large unsigned offset)
+            // outside it (positions before its start at offset -1, as in k_fsk_front)
             const int64_t k0 = lam0 + c0, first = k0 > 0 ? k0 : 0;
             const int64_t left = min(fi.tk.n - first, int64_t(S * NT));
             const uint32_t bytes = left > 0 ? uint32_t(left) * 4u : 0u;
@@ -692,8 +694,9 @@ __global__ __launch_bounds__(256, 4) void k_fsk_refine(FskRefineArgs a) {
             float sd[S], su[S];
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                sd[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, (q0 + NT * q) * 4, 0, 0));
-                su[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ur, (q0 + NT * q) * 4, 0, 0));
+                const int at = max(q0 + NT * q, -1) * 4;
+                sd[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, at, 0, 0));
+                su[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ur, at, 0, 0));
             }
             if (c0 != i0) __syncthreads();           // the chunk before has been read
 #pragma unroll
