@@ -657,7 +657,7 @@ def bench_fsk(args, w):
                    "tasks": len(tasks) if tracking else None,
                    "codes_realtime_half_duty": None if tracking else codes_rt, "parallelism": "single GPU"},
         "roofline": dict(roofline(achieved, corr_avg, flops, traffic_per_launch(args.workload)),
-                         kernel="k_fsk_correlate"),
+                         kernel="k_fsk_first + k_fsk_phase"),
         "device": device_info(),
     }
     if args.cpu_budget > 0 and not tracking:

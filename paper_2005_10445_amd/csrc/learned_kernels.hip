@@ -129,25 +129,25 @@ constexpr int kDigit0 = 2048;
 constexpr int kHistCopies = 8;       // of a block's first-digit counts (workgroups go to them in turn)
 
 // The digit of 2^LOG buckets that holds rank s.rank, from a block's histogram of
-// COPIES copies, which are cleared; and the state it leaves.  256 threads.
+// COPIES copies, which are cleared; and the state it leaves.  256 threads; bucket is
+// LDS for the 2^LOG counts.
 template <int COPIES, int LOG>
-__device__ __forceinline__ MedianState select_digit(uint32_t* h, MedianState s, MedianState* s_out) {
+__device__ __forceinline__ MedianState select_digit(uint32_t* h, MedianState s, MedianState* s_out, uint32_t* bucket) {
     constexpr int PER = (1 << LOG) / 256;
     __shared__ uint32_t part[256];
-    __shared__ uint32_t bucket[1 << LOG];
     const int t = int(threadIdx.x);
-    uint32_t c[COPIES * PER];
+    uint32_t v[PER];
 #pragma unroll
-    for (int k = 0; k < COPIES * PER; ++k) c[k] = agent_load(&h[(k / PER) * kDigit0 + (k % PER) * 256 + t]);
+    for (int q = 0; q < PER; ++q) v[q] = 0u;
+#pragma unroll 4
+    for (int k = 0; k < COPIES; ++k)
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        uint32_t v = 0;
+        for (int q = 0; q < PER; ++q) v[q] += agent_load(&h[k * kDigit0 + q * 256 + t]);
 #pragma unroll
-        for (int k = 0; k < COPIES; ++k) v += c[k * PER + q];
-        bucket[q * 256 + t] = v;
-    }
+    for (int q = 0; q < PER; ++q) bucket[q * 256 + t] = v[q];
+    for (int k = 0; k < COPIES; ++k)
 #pragma unroll
-    for (int k = 0; k < COPIES * PER; ++k) h[(k / PER) * kDigit0 + (k % PER) * 256 + t] = 0u;
+        for (int q = 0; q < PER; ++q) h[k * kDigit0 + q * 256 + t] = 0u;
     __syncthreads();
     uint32_t local[PER];
     uint32_t sum = 0;
@@ -245,7 +245,8 @@ __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const 
     for (int i = tid; i < kDigit0; i += 256)
         if (hist[i]) atomicAdd(&hc[i], hist[i]);
     if (!last_arrival(&ms.tickets[b], gridDim.x)) return;
-    const MedianState s = select_digit<kHistCopies, 11>(h, MedianState{0u, uint32_t((F * kWin - 1) / 2)}, &state);
+    const MedianState s = select_digit<kHistCopies, 11>(h, MedianState{0u, uint32_t((F * kWin - 1) / 2)}, &state,
+                                                           hist);
     if (tid == 0) {
         ms.state[b] = s;
         ms.tickets[b] = 0u;                        // for the next launch
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ P, int64
     for (int i = tid; i < 1024; i += 256)
         if (hist[i]) atomicAdd(&h[i], hist[i]);
     if (!last_arrival(&ms.tickets[b], gridDim.x)) return;
-    const MedianState r = select_digit<1, 10>(h, s, &state);
+    const MedianState r = select_digit<1, 10>(h, s, &state, hist);
     if (tid == 0) {
         ms.state[b] = r;
         if (PASS == 2) med[b] = __uint_as_float(r.prefix);
@@ -1077,12 +1078,13 @@ __global__ __launch_bounds__(256) void k_propose(const float* __restrict__ y, in
 // ------------------------------------------------------------------ launchers
 static unsigned blocks_for(int64_t n, int per) { return unsigned((n + per - 1) / per); }
 
-// workgroups per block: enough of them to fill the chip (two a compute unit),
-// and no more, as each adds its nonzero first-digit buckets to the block's counts
+// Workgroups in all: two a compute unit for device blocks, whose loads set the pace
+// (each workgroup adds its nonzero first-digit buckets to the block's counts), six,
+// as many as fit, for generated ones, whose arithmetic does.
 hipError_t launch_stft(const BlockSource& src, int nblocks, int64_t F, const float* hann, const float2* tw, float* P,
                        const MedianScratch& ms, hipStream_t st) {
     if (nblocks <= 0 || F <= 0) return hipSuccess;
-    const unsigned groups = unsigned(std::min<int64_t>((F + 3) / 4, std::max(1, 512 / nblocks)));
+    const unsigned groups = unsigned(std::min<int64_t>((F + 3) / 4, std::max(1, (src.x ? 512 : 1536) / nblocks)));
     hipLaunchKernelGGL(k_stft, dim3(groups, unsigned(nblocks)), dim3(256), 0, st, src, F, hann, tw, P, ms);
     return hipGetLastError();
 }

@@ -30,7 +30,7 @@ CSRC = os.path.join(ROOT, "paper_2005_10445_amd", "csrc")
 # the correlation kernel and everything it includes from the library
 KERNEL_SOURCES = ("correlate.hip", "device_common.h", "device_fft.h", "fft14.h", "storage.h", "kernels.h")
 # the FSK pipeline's kernels
-FSK_SOURCES = ("fsk.hip", "device_common.h", "device_fft.h", "fft14.h", "storage.h", "kernels.h")
+FSK_SOURCES = ("fsk.hip", "arrival.h", "device_common.h", "device_fft.h", "fft14.h", "storage.h", "kernels.h")
 
 
 def kernel_source_hash(sources=KERNEL_SOURCES) -> str:
