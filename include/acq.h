@@ -381,7 +381,9 @@ int acq_correlate_power(acq_plan_t plan, const void* block, int64_t n, float* po
  * HIP events on the plan's stream around each kernel they launch; after the
  * call, acq_last_kernel_times writes the durations (milliseconds) in the order
  * ACQ_KERNEL_* below to host `ms[0..n)` and the number of kernels to *count.
- * Kernels a call did not launch, or did not time, report 0.  `on` is
+ * Kernels a call did not launch, or did not time, report 0.  Timed (every kernel), the
+ * block power and the compaction of a small search run as launches of their own;
+ * untimed they are part of the forward and the refinement launch.  `on` is
  * ACQ_PROFILE_OFF (the default), ACQ_PROFILE_ALL (every kernel) or
  * ACQ_PROFILE_CORRELATE (the correlation kernel only: two events per call,
  * so the timed calls run closest to unprofiled ones); other values return
