@@ -480,8 +480,11 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
         grid = p->cus;
     } else {
         // the kernel reads a batch's real item count from the block table
-        const int64_t nwork = int64_t(ca.ntiles) * segs * c.num_bins * c.samples_per_chip;
-        if (nwork >= (int64_t(1) << 31) - 8) return acq::fail(ACQ_ERR_UNSUPPORTED, "too many work items");
+        const int64_t per_tile = segs * c.num_bins * c.samples_per_chip;
+        const int64_t nwork = int64_t(ca.ntiles) * per_tile;
+        // (the limit on work items is that of the reported tile)
+        const int64_t named = int64_t((c.num_tags + p->tile - 1) / p->tile) * per_tile;
+        if (std::max(nwork, named) >= (int64_t(1) << 31) - 8) return acq::fail(ACQ_ERR_UNSUPPORTED, "too many work items");
         grid = int((nwork + acq::kXcds - 1) / acq::kXcds) * acq::kXcds;
     }
     {
