@@ -307,7 +307,8 @@ std::vector<float> phase_weights(int64_t M, int spc) {
 // x 8 segments of 2^12 points 57.7 -> 37.3; 30 tags x 7 x 2 x 11 of 2^14
 // points 200.8 -> 141.3; 7 tags x 3 x 2 x 6 of 2^14 points 53.8 -> 20.1; 64
 // tags x 11 x 2 x 63 of 2^14 points 2065 -> 2019; 256 tags x 21 x 2 over 6
-// blocks, the whole search: 16 tags 95.2 ms, 32 92.2, the rule's 64 90.8).
+// blocks, the whole search: 16 tags 95.2 ms, 32 92.2, the rule's 64 90.8, and on
+// cards that run it at lower clocks 97.0, 95.5 and 95.5).
 int choose_tag_tile(int64_t T, int64_t per_tile, int log2_sub, int cus) {
     const int64_t r = int64_t(1) << (14 - log2_sub);
     const int top = int(std::min<int64_t>(T, kMaxTagTile));

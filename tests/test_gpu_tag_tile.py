@@ -18,7 +18,7 @@ FS = 8e6
     (33, 1500, 1, 3, 40001, "fp32"),        # 2^13 points
     (64, 260, 2, 5, 70000, "fp32"),         # 2^11 points
     (40, 260, 1, 3, 20000, "fp32"),         # 2^10 points
-    (70, 300, 8, 3, 20000, "fp32"),         # eight phases, tiles of up to 64 tags
+    (70, 300, 8, 3, 20000, "fp32"),         # eight phases, more tags than a tile takes
     (20, 1000, 4, 3, 30000, "fp16"),        # 16-bit storage
     (20, 8192, 2, 3, 60000, "bf16"),
 ])
