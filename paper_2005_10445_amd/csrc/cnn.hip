@@ -7,6 +7,7 @@
 // max_rows frames, the STFT/median scratch and the transform tables.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -50,7 +51,7 @@ struct acq_cnn_s {
     NetLayout lay{};
     int step = 0;
 
-    float* theta = nullptr;     // [np] FP32 master parameters
+    float* theta = nullptr;     // [np] FP32 master parameters (grad, m and v after them, one allocation)
     float* grad = nullptr;      // [np]
     float* m = nullptr;         // [np]
     float* v = nullptr;         // [np]
@@ -59,18 +60,18 @@ struct acq_cnn_s {
 
     void* act[kLayers + 1] = {};    // act[0]: map [rows][cin]; act[l]: layer l output [rows][64]
     float* dH[2] = {};              // [rows][64] FP32 gradients (ping-pong)
-    float* dw_part[kLayers] = {};   // weight-gradient chunk sums of each layer
-    float* head_part = nullptr;     // head sums of each workgroup
+    float* P = nullptr;             // [rows][256] STFT powers; in their place while gradients are formed,
+    float* dw_part[kLayers] = {};   // the weight-gradient chunk sums of each layer and
+    float* head_part = nullptr;     // the head sums of each workgroup
     float* y = nullptr;             // [rows] logits
     float* labels = nullptr;        // [rows]
-    float* P = nullptr;             // [rows][256] STFT powers
     MedianScratch ms{};             // of kMaxBatch blocks
     float* med = nullptr;           // [kMaxBatch]
     float* hann = nullptr;          // [256]
     float2* tw = nullptr;           // [256] exp(-j 2 pi m / 256)
     SynthTx* d_tx = nullptr;        // [kMaxBatch][kMaxTx]
     int32_t* d_ntx = nullptr;       // [kMaxBatch]
-    uint32_t* segmask = nullptr;    // [kProposeWords]
+    uint32_t* segmask = nullptr;    // [kProposeWords] (after ms.hist and ms.tickets, one allocation)
 
     SynthTx* h_tx = nullptr;        // pinned staging
     int32_t* h_ntx = nullptr;
@@ -85,10 +86,9 @@ namespace {
 
 void free_cnn(acq_cnn_s* c) {
     if (!c) return;
-    void* dev[] = {c->theta, c->grad, c->m, c->v, c->w_bf, c->wt_bf, c->act[0], c->act[1], c->act[2], c->act[3],
-                   c->act[4], c->dH[0], c->dH[1], c->dw_part[0], c->dw_part[1], c->dw_part[2], c->dw_part[3],
-                   c->head_part, c->y, c->labels, c->P, c->ms.hist, c->ms.tickets,
-                   c->ms.state, c->med, c->hann, c->tw, c->d_tx, c->d_ntx, c->segmask};
+    void* dev[] = {c->theta, c->w_bf, c->wt_bf, c->act[0], c->act[1], c->act[2], c->act[3],
+                   c->act[4], c->dH[0], c->dH[1], c->y, c->labels, c->P, c->ms.hist, c->ms.state, c->med, c->hann, c->tw,
+                   c->d_tx, c->d_ntx};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     void* host[] = {c->h_tx, c->h_ntx, c->h_info, c->h_scalar};
@@ -100,10 +100,11 @@ void free_cnn(acq_cnn_s* c) {
 int build_cnn(acq_cnn_s* c) {
     const size_t rows = size_t(c->cfg.max_rows), np = size_t(c->lay.total);
     const size_t es = c->bf ? 2 : 4;
-    CNN_HIP(dalloc(&c->theta, np));
-    CNN_HIP(dalloc(&c->grad, np));
-    CNN_HIP(dalloc(&c->m, np));
-    CNN_HIP(dalloc(&c->v, np));
+    const size_t np_stride = (np + 63) / 64 * 64;
+    CNN_HIP(dalloc(&c->theta, 4 * np_stride));
+    c->grad = c->theta + np_stride;
+    c->m = c->grad + np_stride;
+    c->v = c->m + np_stride;
     if (c->bf) {
         CNN_HIP(dalloc(&c->w_bf, size_t(c->lay.bf_total)));
         CNN_HIP(dalloc(&c->wt_bf, size_t(c->lay.bf_total)));
@@ -112,21 +113,28 @@ int build_cnn(acq_cnn_s* c) {
     for (int l = 1; l <= kLayers; ++l) CNN_HIP(hipMalloc(&c->act[l], rows * kCh * es));
     CNN_HIP(dalloc(&c->dH[0], rows * kCh));
     CNN_HIP(dalloc(&c->dH[1], rows * kCh));
-    if (c->bf)
-        for (int l = 0; l < kLayers; ++l) CNN_HIP(dalloc(&c->dw_part[l], size_t(dweight_part_elems(c->lay.cin[l], c->cfg.max_rows))));
-    CNN_HIP(dalloc(&c->head_part, size_t(head_groups(c->cfg.max_rows) * kHeadSums)));
+    // the powers' rows or the partial sums that max_rows can fill, which no call
+    // needs at once (a buffer for each layer, sized for any number of rows, took 84
+    // of a network's 100 MiB at 300 rows, and creating and releasing it 0.9 ms for 0.2)
+    int64_t part_at[kLayers + 1] = {};
+    for (int l = 0; l < kLayers; ++l)
+        part_at[l + 1] = part_at[l] + (c->bf ? dweight_part_elems(c->lay.cin[l], c->cfg.max_rows) : 0);
+    CNN_HIP(dalloc(&c->P, std::max(rows * kWin, size_t(part_at[kLayers] + head_groups(c->cfg.max_rows) * kHeadSums))));
+    for (int l = 0; l < kLayers; ++l) c->dw_part[l] = c->P + part_at[l];
+    c->head_part = c->P + part_at[kLayers];
     CNN_HIP(dalloc(&c->y, rows));
     CNN_HIP(dalloc(&c->labels, rows));
-    CNN_HIP(dalloc(&c->P, rows * kWin));
-    CNN_HIP(dalloc(&c->ms.hist, size_t(kMaxBatch * kMedianHist)));
-    CNN_HIP(dalloc(&c->ms.tickets, size_t(kMaxBatch)));
+    constexpr int64_t zeros = kMaxBatch * kMedianDigit + kMaxBatch + kProposeWords;      // left zero by every call
+    CNN_HIP(dalloc(&c->ms.hist, size_t(zeros)));
+    c->ms.blocks = kMaxBatch;
+    c->ms.tickets = c->ms.hist + kMaxBatch * kMedianDigit;
+    c->segmask = c->ms.tickets + kMaxBatch;
     CNN_HIP(dalloc(&c->ms.state, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->med, size_t(kMaxBatch)));
     CNN_HIP(dalloc(&c->hann, size_t(kWin)));
     CNN_HIP(dalloc(&c->tw, size_t(kWin)));
     CNN_HIP(dalloc(&c->d_tx, size_t(kMaxBatch) * kMaxTx));
     CNN_HIP(dalloc(&c->d_ntx, size_t(kMaxBatch)));
-    CNN_HIP(dalloc(&c->segmask, size_t(kProposeWords)));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_tx), sizeof(SynthTx) * kMaxBatch * kMaxTx));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_ntx), sizeof(int32_t) * kMaxBatch));
     CNN_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_info), sizeof(int32_t) * 2));
@@ -144,13 +152,8 @@ int build_cnn(acq_cnn_s* c) {
     hipStream_t st = c->stream;
     CNN_HIP(hipMemcpyAsync(c->hann, hann.data(), sizeof(float) * kWin, hipMemcpyHostToDevice, st));
     CNN_HIP(hipMemcpyAsync(c->tw, tw.data(), sizeof(float) * 2 * kWin, hipMemcpyHostToDevice, st));
-    CNN_HIP(launch_fill_u32(c->ms.hist, kMaxBatch * kMedianHist, st));
-    CNN_HIP(launch_fill_u32(c->ms.tickets, kMaxBatch, st));
-    CNN_HIP(launch_fill_u32(c->segmask, kProposeWords, st));
-    CNN_HIP(launch_fill_f32(c->theta, int64_t(np), st));
-    CNN_HIP(launch_fill_f32(c->grad, int64_t(np), st));
-    CNN_HIP(launch_fill_f32(c->m, int64_t(np), st));
-    CNN_HIP(launch_fill_f32(c->v, int64_t(np), st));
+    CNN_HIP(launch_fill_u32(c->ms.hist, zeros, st));
+    CNN_HIP(launch_fill_f32(c->theta, int64_t(4 * np_stride), st));
     if (c->bf) CNN_HIP(launch_adam(c->theta, c->grad, c->m, c->v, int64_t(np), 0.f, 0.f, 0.f, 0.f, 0, c->lay,
                                    c->w_bf, c->wt_bf, st));
     CNN_HIP(hipStreamSynchronize(st));

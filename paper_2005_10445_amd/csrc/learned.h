@@ -68,9 +68,10 @@ struct MedianState {
 
 // Scratch of the median: zero before the first launch, left so by every
 // launch_median.
-constexpr int64_t kMedianHist = 8 * 2048;   // histogram words of one block
+constexpr int64_t kMedianDigit = 2048;      // histogram words of one digit
 struct MedianScratch {
-    uint32_t* hist;             // [block][kMedianHist]
+    uint32_t* hist;             // [blocks][kMedianDigit]
+    int32_t blocks;             // histograms held: a call of fewer blocks gives each several copies
     unsigned* tickets;          // [block]
     MedianState* state;         // [block]
 };

@@ -125,14 +125,15 @@ __device__ float2 synth_sample(const BlockSource& s, int b, int64_t n) {
 //
 // Workgroup (g, b) takes every gridDim.x-th group of 4 frames of block b, and
 // counts the first digit (11 bits) of its powers for the median.
-constexpr int kDigit0 = 2048;
-constexpr int kHistCopies = 8;       // of a block's first-digit counts (workgroups go to them in turn)
+constexpr int kDigit0 = int(kMedianDigit);
+constexpr int kHistCopies = 8;       // of a block's first-digit counts, at most (workgroups go to them in turn)
 
 // The digit of 2^LOG buckets that holds rank s.rank, from a block's histogram of
-// COPIES copies, which are cleared; and the state it leaves.  256 threads; bucket is
+// `copies` copies, which are cleared; and the state it leaves.  256 threads; bucket is
 // LDS for the 2^LOG counts.
-template <int COPIES, int LOG>
-__device__ __forceinline__ MedianState select_digit(uint32_t* h, MedianState s, MedianState* s_out, uint32_t* bucket) {
+template <int LOG>
+__device__ __forceinline__ MedianState select_digit(uint32_t* h, int copies, MedianState s, MedianState* s_out,
+                                                    uint32_t* bucket) {
     constexpr int PER = (1 << LOG) / 256;
     __shared__ uint32_t part[256];
     const int t = int(threadIdx.x);
@@ -140,12 +141,12 @@ __device__ __forceinline__ MedianState select_digit(uint32_t* h, MedianState s, 
 #pragma unroll
     for (int q = 0; q < PER; ++q) v[q] = 0u;
 #pragma unroll 4
-    for (int k = 0; k < COPIES; ++k)
+    for (int k = 0; k < copies; ++k)
 #pragma unroll
         for (int q = 0; q < PER; ++q) v[q] += agent_load(&h[k * kDigit0 + q * 256 + t]);
 #pragma unroll
     for (int q = 0; q < PER; ++q) bucket[q * 256 + t] = v[q];
-    for (int k = 0; k < COPIES; ++k)
+    for (int k = 0; k < copies; ++k)
 #pragma unroll
         for (int q = 0; q < PER; ++q) h[k * kDigit0 + q * 256 + t] = 0u;
     __syncthreads();
@@ -180,7 +181,7 @@ __device__ __forceinline__ MedianState select_digit(uint32_t* h, MedianState s, 
 
 __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const float* __restrict__ hann,
                                               const float2* __restrict__ tw, float* __restrict__ P,
-                                              MedianScratch ms) {
+                                              MedianScratch ms, int copies) {
     constexpr int kShared = 3 * kHop + kWin;   // samples of the workgroup's 4 frames
     __shared__ float2 buf[4][kWin];
     __shared__ float2 stw[kWin];
@@ -240,13 +241,12 @@ __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const 
         }
     }
     __syncthreads();
-    uint32_t* h = ms.hist + int64_t(b) * kHistCopies * kDigit0;
-    uint32_t* hc = h + (blockIdx.x % kHistCopies) * kDigit0;
+    uint32_t* h = ms.hist + int64_t(b) * copies * kDigit0;
+    uint32_t* hc = h + (blockIdx.x % unsigned(copies)) * kDigit0;
     for (int i = tid; i < kDigit0; i += 256)
         if (hist[i]) atomicAdd(&hc[i], hist[i]);
     if (!last_arrival(&ms.tickets[b], gridDim.x)) return;
-    const MedianState s = select_digit<kHistCopies, 11>(h, MedianState{0u, uint32_t((F * kWin - 1) / 2)}, &state,
-                                                           hist);
+    const MedianState s = select_digit<11>(h, copies, MedianState{0u, uint32_t((F * kWin - 1) / 2)}, &state, hist);
     if (tid == 0) {
         ms.state[b] = s;
         ms.tickets[b] = 0u;                        // for the next launch
@@ -290,11 +290,11 @@ __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ P, int64
         }
     }
     __syncthreads();
-    uint32_t* h = ms.hist + int64_t(b) * kHistCopies * kDigit0;
+    uint32_t* h = ms.hist + int64_t(b) * kDigit0;
     for (int i = tid; i < 1024; i += 256)
         if (hist[i]) atomicAdd(&h[i], hist[i]);
     if (!last_arrival(&ms.tickets[b], gridDim.x)) return;
-    const MedianState r = select_digit<1, 10>(h, s, &state, hist);
+    const MedianState r = select_digit<10>(h, 1, s, &state, hist);
     if (tid == 0) {
         ms.state[b] = r;
         if (PASS == 2) med[b] = __uint_as_float(r.prefix);
@@ -1084,15 +1084,18 @@ static unsigned blocks_for(int64_t n, int per) { return unsigned((n + per - 1) /
 hipError_t launch_stft(const BlockSource& src, int nblocks, int64_t F, const float* hann, const float2* tw, float* P,
                        const MedianScratch& ms, hipStream_t st) {
     if (nblocks <= 0 || F <= 0) return hipSuccess;
+    if (nblocks > ms.blocks) return hipErrorInvalidValue;
+    // (64 blocks share 4 copies each between 24 workgroups, 256 blocks one between 6)
+    const int copies = std::min(kHistCopies, ms.blocks / nblocks);
     const unsigned groups = unsigned(std::min<int64_t>((F + 3) / 4, std::max(1, (src.x ? 512 : 1536) / nblocks)));
-    hipLaunchKernelGGL(k_stft, dim3(groups, unsigned(nblocks)), dim3(256), 0, st, src, F, hann, tw, P, ms);
+    hipLaunchKernelGGL(k_stft, dim3(groups, unsigned(nblocks)), dim3(256), 0, st, src, F, hann, tw, P, ms, copies);
     return hipGetLastError();
 }
 
 hipError_t launch_median(const float* P, int nblocks, int64_t per_block, const MedianScratch& ms, float* med,
                          hipStream_t st) {
     if (nblocks <= 0 || per_block <= 0) return hipSuccess;
-    if (per_block % 4) return hipErrorInvalidValue;
+    if (per_block % 4 || nblocks > ms.blocks) return hipErrorInvalidValue;
     const unsigned groups = unsigned(std::min<int64_t>((per_block + 8191) / 8192, std::max(1, 512 / nblocks)));
     const dim3 grid(groups, unsigned(nblocks));
     hipLaunchKernelGGL(k_hist<1>, grid, dim3(256), 0, st, P, per_block, ms, med);
@@ -1170,10 +1173,11 @@ hipError_t launch_conv_dinput(const float* dH, const void* H, const void* w, flo
     return hipGetLastError();
 }
 
-// chunks x groups <= (pieces / k + 1) * groups <= wgs + groups for k = ceil(pieces * groups / wgs)
+// chunks x groups <= (pieces / k + 1) * groups <= wgs + groups for k = ceil(pieces * groups / wgs),
+// and a chunk is at least one piece
 int64_t dweight_part_elems(int cin, int64_t max_rows) {
     const int64_t ngroups = std::max(cin / 64, 1), pieces = (max_rows + kDwRows - 1) / kDwRows;
-    return (dw_wgs(pieces * ngroups) + ngroups) * (kDwBlock + kCh);
+    return std::min<int64_t>(dw_wgs(pieces * ngroups) + ngroups, pieces * ngroups) * (kDwBlock + kCh);
 }
 
 hipError_t launch_conv_dweight(const void* in, int cin, const float* dH, const void* H, float* part,
