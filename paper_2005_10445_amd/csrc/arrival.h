@@ -59,12 +59,21 @@ __device__ __forceinline__ int compact_records(int items, const Rec* dets, Slot 
         __syncthreads();
     }
     const int n = (base < capacity ? base : capacity) * WORDS;
-    for (int i = t; i < n; i += NT) {
-        const int r = i / WORDS;
-        const unsigned long long v =
-            agent_load(reinterpret_cast<const unsigned long long*>(&dets[s_slot[r]]) + (i - r * WORDS));
-        if (out) reinterpret_cast<unsigned long long*>(out)[i] = v;
-        if (h_out) reinterpret_cast<unsigned long long*>(h_out)[i] = v;
+    constexpr int U = 8;                     // words of a thread in flight together
+    for (int i0 = t; i0 < n; i0 += U * NT) {
+        unsigned long long v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * NT, n - 1), r = i / WORDS;
+            v[u] = agent_load(reinterpret_cast<const unsigned long long*>(&dets[s_slot[r]]) + (i - r * WORDS));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * NT;
+            if (i >= n) break;
+            if (out) reinterpret_cast<unsigned long long*>(out)[i] = v[u];
+            if (h_out) reinterpret_cast<unsigned long long*>(h_out)[i] = v[u];
+        }
     }
     return base;
 }

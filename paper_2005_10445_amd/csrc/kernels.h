@@ -91,7 +91,7 @@ struct CorrArgs {
 // search's peak keys, crossing counts and refinement tickets, nclear of each
 // (one ticket more).
 struct PowerArgs {
-    double* parts;              // [block][kPowerParts] partial sums of |x|^2
+    double* parts;              // [block][kPowerParts] partial sums of |x|^2; the first becomes their mean
     int* exps;
     float* pthr;
     int32_t* bad;
@@ -139,6 +139,7 @@ struct RefineArgs {
     int32_t T, C, K, spc, log2_spc, M, radius, exact;
     int32_t track;              // 1: one candidate per block, the block's own tag
     int32_t check_finite;       // 1: no detection in a block with a non-finite sample
+    int32_t parts_each;         // parts a workgroup sums (set by launch_refine)
     double* partial;            // [items][kRefineParts][3 * window] FP64 partial sums
     unsigned* tickets;          // [1 + items] arrivals, zero at the launch: of the items, of each item's parts
     // tail = 1 (at most kTailItems items): the launch writes the detections too
@@ -170,7 +171,7 @@ hipError_t launch_bank(const int8_t* chips, int T, int C, void* bank, const floa
                        hipStream_t st);
 // engine: 0 = the library's choice for the size, 1 = Stockham passes (any size)
 hipError_t launch_correlate(const CorrArgs& a, int grid, int log2_sub, int prec, int engine, hipStream_t st);
-hipError_t launch_refine(const RefineArgs& a, int max_blocks, hipStream_t st);
+hipError_t launch_refine(RefineArgs a, int max_blocks, hipStream_t st);
 // track: one candidate per block (its tag), else T per block
 // capacity: records written to out (the rest are counted only)
 hipError_t launch_compact(const BlockTable& bt, const acq_detection* dets, const int32_t* found, int T, int track,

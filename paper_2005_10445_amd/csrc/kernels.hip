@@ -137,6 +137,7 @@ __device__ __forceinline__ void block_stats(const BlockTable& bt, const PowerArg
     for (int b = int(threadIdx.x); b < nb; b += NT) {
         const BlockDesc d = bt.get(b);
         const double px = block_mean_power(a.parts + size_t(b) * kPowerParts, d.n);
+        a.parts[size_t(b) * kPowerParts] = px;
         const bool fin = isfinite(px);
         a.exps[b] = fin && px > 0.0 ? int(rint(0.5 * log2(double(a.M) * px))) : 0;
         const double th = d.theta * double(a.L) * px;
@@ -339,7 +340,8 @@ __global__ __launch_bounds__(E::NT) void k_bank(const int8_t* __restrict__ chips
 constexpr int kMaxWin = 2 * kMaxRefineRadius + 3;
 
 // FP64 refinement of each (block, tag) peak key, one launch.  The window of W =
-// 2R + 3 lags is centred on the key's lag; kRefineParts workgroups per item add
+// 2R + 3 lags is centred on the key's lag and its samples are split into
+// kRefineParts parts; an item's workgroups take a.parts_each of them each and add
 // the re- and im-sums of the mixed samples against the tag's replica and the
 // sample energy under it for every lag of the window, and the last of them to
 // arrive adds the parts in order, re-maximises over the inner 2R+1 lags and
@@ -352,7 +354,14 @@ constexpr int kMaxWin = 2 * kMaxRefineRadius + 3;
 // Against two passes of two kernels, the compaction and its copies, with the
 // power in launches of its own: a search of 1 code in 131,072 samples 89.7 ->
 // 60.6 us, of 13 codes in 5 bins of 100,003 samples 118 -> 91 us, 9 tracking
-// tasks 133 -> 98 us, 256 tasks 887 -> 852 us.
+// tasks 133 -> 98 us.  The kernel against the two passes', 16,384 samples each: 64
+// items 22 -> 18 us, 256 42 -> 36, 4096 418 -> 356, 16,384 1.49 -> 1.21 ms (with 16
+// workgroups of one part for every item 18, 51, 656 and 2.59 ms: an item's share
+// is then smaller than what a workgroup pays besides).
+// Registers decide how many workgroups hide each other's loads and sums: 32-bit
+// indices (a window has fewer than 2^18 samples), the exact bins' phases in a
+// kernel of their own, and one copy of the sums for both passes leave 95 of them
+// at radius 1 (121 with two copies and 64-bit indices).
 // The mix exp(-j 2 pi m_k i / M) is an FP64 table entry at (m_k i) mod M (M a
 // power of two, so the reduction is exact), or the exact bin's FP64 phase.
 struct RefineItem {
@@ -378,63 +387,67 @@ constexpr int kRefineChipsLds = kRefineMaxChips / kRefineParts + 2 * kMaxWin + 4
 
 constexpr int kRefineThreads = 256;
 
-// Sums of part `part` of an item's window around `center`, to a.partial.
-template <int WMAX>
-__device__ __forceinline__ void refine_sums(const RefineArgs& a, const RefineItem& it, int item, int part, int k,
-                                            int64_t center) {
+// Sums of part `part` of an item's window around `center`: sum t in thread t < 3W.
+// (One after the other is safe: a barrier lies between any two uses of the LDS.)
+template <int WMAX, bool EXACT>
+__device__ __forceinline__ double refine_sums(const RefineArgs& a, const RefineItem& it, int part, int k,
+                                              int64_t center) {
     __shared__ int8_t s_chips[kRefineChipsLds];
     __shared__ double red[kRefineThreads / 64][3 * WMAX];
     constexpr int NT = kRefineThreads, NW = NT / 64;
     const BlockDesc& d = it.d;
-    const int R = a.radius;
+    const int R = a.radius, L = int(a.L);
     const int W = 2 * R + 3;                 // <= WMAX, which the launcher picks
     const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
     const int64_t lam0 = center - R - 1;
-    // samples of the window inside the block, split into parts
-    const int64_t e_lo = lam0 < 0 ? -lam0 : 0;
-    const int64_t e_hi = min(int64_t(a.L) + W - 1, d.n - lam0);
-    const int64_t ch = (e_hi - e_lo + kRefineParts - 1) / kRefineParts;
-    const int64_t p0 = e_lo + int64_t(part) * ch, p1 = min(e_hi, p0 + ch);
+    // samples e of the window (lag lam0's first is e = 0) inside the block, split into parts
+    const int e_lo = lam0 < 0 ? int(-lam0) : 0;
+    const int e_hi = int(min(int64_t(L) + W - 1, d.n - lam0));
+    const int ch = (e_hi - e_lo + kRefineParts - 1) / kRefineParts;
+    const int p0 = e_lo + part * ch, p1 = min(e_hi, p0 + ch);
     // the part's chips (replica samples e - w, w < W)
     const int8_t* chips = a.chips + size_t(it.tag) * size_t(a.C);
-    const int64_t c0 = max(int64_t(0), (p0 - W + 1) >> a.log2_spc);
-    const int64_t c1 = min(int64_t(a.C), ((p1 - 1) >> a.log2_spc) + 1);
-    for (int64_t q = c0 + t; q < c1; q += NT) s_chips[q - c0] = chips[q];
+    const int c0 = max(0, (p0 - W + 1) >> a.log2_spc);
+    const int c1 = min(a.C, ((p1 - 1) >> a.log2_spc) + 1);
+    for (int q = c0 + t; q < c1; q += NT) s_chips[q - c0] = chips[q];
     __syncthreads();
-    const int64_t mrot = a.rot_signed[k];
-    const int64_t mmask = int64_t(a.M) - 1;
+    // table index (m_k i) mod M in 32 bits (M a power of two)
+    const unsigned mrot = unsigned(a.rot_signed[k]), mmask = unsigned(a.M) - 1u, i0 = unsigned(lam0);
     const double fk = a.cyc[k];
+    const float2* x = d.x + lam0;
     double cr[WMAX], ci[WMAX], en[WMAX];
 #pragma unroll
     for (int w = 0; w < WMAX; ++w) cr[w] = ci[w] = en[w] = 0.0;
-    constexpr int U = 4;                     // a thread's samples loaded together
-    for (int64_t e0 = p0 + t; e0 < p1; e0 += U * NT) {
+    constexpr int U = WMAX > 5 ? 1 : 4;      // a thread's samples loaded together
+    for (int e0 = p0 + t; e0 < p1; e0 += U * NT) {
         float2 xs[U];
         double2 ts[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t i = lam0 + min(e0 + u * NT, p1 - 1);
-            xs[u] = d.x[i];
-            if (!a.exact) ts[u] = a.roots64[(mrot * i) & mmask];
+            const int e = min(e0 + u * NT, p1 - 1);
+            xs[u] = x[unsigned(e)];
+            if constexpr (!EXACT) ts[u] = a.roots64[(mrot * (i0 + unsigned(e))) & mmask];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t e = e0 + u * NT;
+            const int e = e0 + u * NT;
             if (e >= p1) break;
             const double xr = xs[u].x, xi = xs[u].y;
-            double2 cs = ts[u];
-            if (a.exact) {                      // exp(-j 2 pi (f_k / Fs) i), phase reduced in FP64
+            double2 cs;
+            if constexpr (EXACT) {              // exp(-j 2 pi (f_k / Fs) i), phase reduced in FP64
                 double ph = fk * double(lam0 + e);
                 ph -= floor(ph);
                 sincospi(2.0 * ph, &cs.y, &cs.x);
+            } else {
+                cs = ts[u];
             }
             const double mr = xr * cs.x + xi * cs.y;      // x * exp(-j 2 pi m i / M)
             const double mi = xi * cs.x - xr * cs.y;
             const double pw = xr * xr + xi * xi;
 #pragma unroll
             for (int w = 0; w < WMAX; ++w) {
-                const int64_t nn = e - w;
-                if (w < W && nn >= 0 && nn < a.L) {
+                const int nn = e - w;
+                if (w < W && nn >= 0 && nn < L) {
                     const double sg = double(s_chips[(nn >> a.log2_spc) - c0]);
                     cr[w] += mr * sg;
                     ci[w] += mi * sg;
@@ -453,35 +466,10 @@ __device__ __forceinline__ void refine_sums(const RefineArgs& a, const RefineIte
         }
     }
     __syncthreads();
-    if (t < 3 * W) {
-        double v = 0.0;
+    double v = 0.0;
+    if (t < 3 * W)
         for (int q = 0; q < NW; ++q) v += red[q][t];
-        agent_store(&a.partial[(size_t(item) * kRefineParts + part) * size_t(3 * WMAX) + t], v);
-    }
-}
-
-// The item's sums over its parts and the powers of its window, to sums and P.
-template <int WMAX>
-__device__ __forceinline__ void refine_powers(const RefineArgs& a, const RefineItem& it, int item, int64_t center,
-                                              double* sums, double* P) {
-    const int W = 2 * a.radius + 3, t = int(threadIdx.x);
-    if (t < 3 * W) {
-        double v = 0.0;
-        double q[kRefineParts];
-#pragma unroll
-        for (int i = 0; i < kRefineParts; ++i)
-            q[i] = agent_load(&a.partial[(size_t(item) * kRefineParts + i) * size_t(3 * WMAX) + t]);
-#pragma unroll
-        for (int i = 0; i < kRefineParts; ++i) v += q[i];
-        sums[t] = v;
-    }
-    __syncthreads();
-    if (t < W) {
-        const int64_t lam = center - a.radius - 1 + t;
-        const double re = sums[3 * t], im = sums[3 * t + 1];
-        P[t] = (lam >= 0 && lam < it.d.lags) ? re * re + im * im : -1.0;
-    }
-    __syncthreads();
+    return v;
 }
 
 // Window position of the largest power (the centre, then the lowest lag, at a
@@ -515,7 +503,7 @@ __device__ __forceinline__ void refine_record(const RefineArgs& a, const RefineI
             delta = delta > 0.5 ? 0.5 : (delta < -0.5 ? -0.5 : delta);
         }
     }
-    const double px = block_mean_power(a.parts + size_t(it.bi) * kPowerParts, d.n);
+    const double px = a.parts[size_t(it.bi) * kPowerParts];      // the mean power (block_stats)
     const double z = px > 0.0 ? p0 / (double(a.L) * px) : 0.0;
     const bool suppressed = a.check_finite && a.bad[it.bi];
     acq_detection r;
@@ -558,10 +546,11 @@ __device__ __forceinline__ void compact_tail(const RefineArgs& a, int items) {
     }
 }
 
-template <int WMAX>
-__global__ __launch_bounds__(kRefineThreads) void k_refine(RefineArgs a) {
+template <int WMAX, bool EXACT>
+__global__ __launch_bounds__(kRefineThreads, WMAX > 5 ? (EXACT ? 2 : 3) : EXACT ? 4 : 5) void k_refine(RefineArgs a) {
     __shared__ double sums[3 * WMAX], P[WMAX];
-    const int item = int(blockIdx.x) / kRefineParts, part = int(blockIdx.x) % kRefineParts;
+    const int groups = kRefineParts / a.parts_each;    // workgroups of an item
+    const int item = int(blockIdx.x) / groups, first = int(blockIdx.x) % groups * a.parts_each;
     const int items = a.blocks.nblocks() * (a.track ? 1 : a.T);
     if (item >= items) return;               // a batch smaller than the plan's capacity
     RefineItem it;
@@ -569,27 +558,47 @@ __global__ __launch_bounds__(kRefineThreads) void k_refine(RefineArgs a) {
     const unsigned long long key = known && it.d.lags > 0 ? a.keys[it.slot] : 0ull;
     if (key != 0ull) {
         const unsigned idx = ~unsigned(key & 0xffffffffull);
-        const int k = int(idx % unsigned(a.K));
+        const int k = int(idx % unsigned(a.K)), t = int(threadIdx.x), W = 2 * a.radius + 3;
         int64_t center = int64_t(idx / unsigned(a.K));
-        refine_sums<WMAX>(a, it, item, part, k, center);
-        if (!last_arrival(&a.tickets[1 + item], kRefineParts)) return;
-        refine_powers<WMAX>(a, it, item, center, sums, P);
-        bool hit;
-        int wb = refine_best(a, it, center, P, &hit);  // every thread the same
-        if (hit) {
-            center += wb - a.radius - 1;
-            for (int q = 0; q < kRefineParts; ++q) {
-                __syncthreads();                       // sums, P and red are rewritten
-                refine_sums<WMAX>(a, it, item, q, k, center);
+        int q0 = first, q1 = first + a.parts_each, wb = 0;
+        bool hit = false;
+        for (int pass = 0; pass < 2; ++pass) {
+            const bool split = q1 - q0 < kRefineParts;
+            double* partial = a.partial + size_t(item) * kRefineParts * size_t(3 * WMAX) + t;
+            double tot = 0.0;                          // sum t over the parts, in their order
+            for (int q = q0; q < q1; ++q) {
+                const double v = refine_sums<WMAX, EXACT>(a, it, q, k, center);
+                if (split && t < 3 * W) agent_store(&partial[q * (3 * WMAX)], v);
+                tot += v;
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (split) {
+                if (!last_arrival(&a.tickets[1 + item], unsigned(groups))) return;
+                tot = 0.0;
+                if (t < 3 * W) {
+                    double v[kRefineParts];
+#pragma unroll
+                    for (int q = 0; q < kRefineParts; ++q) v[q] = agent_load(&partial[q * (3 * WMAX)]);
+#pragma unroll
+                    for (int q = 0; q < kRefineParts; ++q) tot += v[q];
+                }
+            }
+            if (t < 3 * W) sums[t] = tot;
             __syncthreads();
-            refine_powers<WMAX>(a, it, item, center, sums, P);
-            wb = refine_best(a, it, center, P, &hit);
+            if (t < W) {
+                const int64_t lam = center - a.radius - 1 + t;
+                const double re = sums[3 * t], im = sums[3 * t + 1];
+                P[t] = (lam >= 0 && lam < it.d.lags) ? re * re + im * im : -1.0;
+            }
+            __syncthreads();
+            wb = refine_best(a, it, center, P, &hit);  // every thread the same
+            if (!hit || pass) break;
+            center += wb - a.radius - 1;
+            q0 = 0;
+            q1 = kRefineParts;
         }
         if (threadIdx.x == 0) refine_record(a, it, k, center - a.radius - 1 + wb, wb, hit, sums, P);
     } else {                                 // no valid lag was searched for this tag
-        if (part != 0) return;
+        if (first != 0) return;
         if (known && threadIdx.x == 0) agent_store(&a.found[it.slot], 0);
     }
     if (a.tail && last_arrival(&a.tickets[0], unsigned(items))) compact_tail(a, items);
@@ -756,17 +765,30 @@ hipError_t launch_bank(const int8_t* chips, int T, int C, void* bank, const floa
     }
 }
 
-hipError_t launch_refine(const RefineArgs& a, int max_blocks, hipStream_t st) {
+// Parts that a workgroup of k_refine takes, one after the other.  Few items need
+// all 16 workgroups each to fill the chip (64 items of 16,384 samples 18 us; with 4
+// parts a workgroup 26, with all 16, 71); of many, each workgroup pays its start,
+// its stores to the item's last one and the arrival again (4096 items 510 us; with
+// 4 parts 382, 8 364, 16 356).  The lines lie about where the times cross: over 16
+// to 16,384 items of 1024 and 16,384 samples the rule is 3 % off the best of 1, 2, 4,
+// 8 and 16 on average, 18 % at the worst (80 items), at radius 8 3 and 15 %.
+static int refine_parts_each(int items) {
+    return items < 96 ? 1 : items < 192 ? 2 : items < 1024 ? 4 : items < 4096 ? 8 : 16;
+}
+
+hipError_t launch_refine(RefineArgs a, int max_blocks, hipStream_t st) {
     if (a.radius < 0 || a.radius > kMaxRefineRadius || a.C > kRefineMaxChips || (a.M & (a.M - 1)) || (1 << a.log2_spc) != a.spc ||
         !a.partial || !a.tickets)
         return hipErrorInvalidValue;
     const int items = max_blocks * (a.track ? 1 : a.T);
     if (a.tail && (items > kTailItems || !a.out || !a.count)) return hipErrorInvalidValue;
-    const dim3 grid(unsigned(items) * kRefineParts);
+    a.parts_each = refine_parts_each(items);
+    const dim3 grid(unsigned(items) * unsigned(kRefineParts / a.parts_each));
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(kRefineThreads), 0, st, a); };
     if (a.radius <= 1)
-        hipLaunchKernelGGL((k_refine<5>), grid, dim3(kRefineThreads), 0, st, a);
+        a.exact ? go(k_refine<5, true>) : go(k_refine<5, false>);
     else
-        hipLaunchKernelGGL((k_refine<kMaxWin>), grid, dim3(kRefineThreads), 0, st, a);
+        a.exact ? go(k_refine<kMaxWin, true>) : go(k_refine<kMaxWin, false>);
     return hipGetLastError();
 }
 
