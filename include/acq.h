@@ -306,9 +306,10 @@ int acq_detect_noalloc(acq_plan_t plan, const void* block, int64_t n, acq_detect
  * Launch configuration of the correlation kernel.  engine: 0 = the default
  * transform engine for the plan's inverse-transform length, 1 = Stockham
  * passes through padded LDS (available for every length).  tag_tile: tags per
- * work item, 1..64; a plan made with tag_tile 0 and not tuned since reports 16
- * and chooses the tile of each launch from its work items (batches captured
- * into the plan's graph keep 16).  Results do not depend on the tuning.
+ * work item, 1..64; a plan made with tag_tile 0 reports 16 (or its tags, if
+ * fewer) and chooses the tile of each launch from its work items (batches captured
+ * into the plan's graph keep 16) until acq_set_tuning names another tile or acq_tune
+ * finds one faster than its choice.  Results do not depend on the tuning.
  */
 typedef struct acq_tuning {
     int32_t engine;
@@ -339,7 +340,8 @@ int acq_set_tuning(acq_plan_t plan, const acq_tuning* tuning);
 
 /*
  * Autotune: time every candidate tuning (engines x tag tiles 4..64 that divide
- * the work sensibly) on the device block `block` of n samples, `reps` runs
+ * the work sensibly, and the tile that a plan made with tag_tile 0 chooses for the
+ * block, which it goes on choosing if that is the fastest) on the device block `block` of n samples, `reps` runs
  * each (HIP events around the correlation kernel), then both batch launch
  * forms with the fastest engine and tile on a batch of copies of the same
  * block (as many as the batch capacity holds, at most 16; the last two

@@ -1082,6 +1082,26 @@ int acq_get_tuning(acq_plan_t p, acq_tuning* out) {
     return ACQ_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// auto_tile: searches choose their tile per launch, t.tag_tile is what is reported.
+void apply_tuning(acq_plan_s* p, const acq_tuning& t, bool auto_tile) {
+    if (t.engine != p->engine || t.tag_tile != p->tile || auto_tile != p->auto_tile ||
+        t.batch_launch != p->batch_launch || t.track_bins != p->track_bins)
+        drop_graph(p);   // the captured kernels change
+    p->engine = t.engine;
+    p->tile = t.tag_tile;
+    p->auto_tile = auto_tile;
+    p->batch_launch = t.batch_launch;
+    p->track_bins = t.track_bins;
+}
+
+}  // namespace
+
+extern "C" {
+
 int acq_set_tuning(acq_plan_t p, const acq_tuning* t) {
     if (!p || !t) return acq::fail(ACQ_ERR_INVALID_ARG, "null argument");
     if (t->engine < 0 || t->engine > 1 || t->tag_tile < 1 || t->tag_tile > acq::kMaxTagTile ||
@@ -1089,15 +1109,10 @@ int acq_set_tuning(acq_plan_t p, const acq_tuning* t) {
         t->track_bins > acq::kMaxTagTile)
         return acq::fail(ACQ_ERR_INVALID_ARG,
                          "engine must be 0 or 1, tag_tile in [1, 64], batch_launch 0 or 1, track_bins in [0, 64]");
-    const int tile = t->tag_tile < p->cfg.num_tags ? t->tag_tile : p->cfg.num_tags;
-    if (t->engine != p->engine || tile != p->tile || p->auto_tile || t->batch_launch != p->batch_launch ||
-        t->track_bins != p->track_bins)
-        drop_graph(p);   // the captured kernels change
-    p->engine = t->engine;
-    p->tile = tile;
-    p->auto_tile = false;
-    p->batch_launch = t->batch_launch;
-    p->track_bins = t->track_bins;
+    acq_tuning clamped = *t;
+    clamped.tag_tile = std::min(t->tag_tile, p->cfg.num_tags);
+    // the tile reported while the plan chooses its own leaves it that choice
+    apply_tuning(p, clamped, p->auto_tile && clamped.tag_tile == p->tile);
     return ACQ_OK;
 }
 
@@ -1111,21 +1126,37 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
     const int was_profiling = p->profile_mode;
     rc = acq_set_profiling(p, ACQ_PROFILE_CORRELATE);          // the tuner times the correlation kernel
     if (rc != ACQ_OK) return rc;
-    std::vector<acq_tune_entry> cand;
-    const int engines = p->g.log2_sub == 14 ? 2 : 1;
-    for (int e = 0; e < engines; ++e)
-        for (int tile : {4, 8, 16, 32, 64}) {
-            if (tile > p->cfg.num_tags && tile != 4) continue;
-            acq_tune_entry c{};
-            c.tuning.engine = e;
-            c.tuning.tag_tile = tile;
-            c.fft_len = int32_t(p->g.M);
-            cand.push_back(c);
-        }
     const bool was_auto = p->auto_tile;
     const acq_tuning before{p->engine, p->tile, p->batch_launch, p->track_bins};
     BlockTable bt{};
     bt.one = single_desc(p, block, n);
+    std::vector<acq_tune_entry> cand;
+    const int engines = p->g.log2_sub == 14 ? 2 : 1;
+    // a plan that chooses its tiles is timed with the choice for this block as
+    // well, and keeps choosing where that is the fastest (8192 chips at 2 samples in
+    // one block: 7 tags in 3 bins 69 us, and 85 with the best of the others, 4; 30
+    // tags in 7 bins 198 and 211)
+    const int own = was_auto ? acq::choose_tag_tile(p->cfg.num_tags,
+                                                    int64_t(bt.one.nseg) * p->cfg.num_bins * p->cfg.samples_per_chip,
+                                                    p->g.log2_sub, p->cus)
+                             : 0;
+    for (int e = 0; e < engines; ++e)
+        for (int tile : {4, 8, 16, 32, 64, own}) {
+            if (tile == 0 || (tile > p->cfg.num_tags && tile != 4)) continue;
+            acq_tune_entry c{};
+            c.tuning.engine = e;
+            c.tuning.tag_tile = tile;
+            c.fft_len = int32_t(p->g.M);
+            if (std::none_of(cand.begin(), cand.end(), [&](const acq_tune_entry& o) {
+                    return o.tuning.engine == e && o.tuning.tag_tile == tile;
+                }))
+                cand.push_back(c);
+        }
+    auto apply = [&](acq_tuning t) {
+        const bool keeps = was_auto && t.tag_tile == own;
+        t.tag_tile = keeps ? before.tag_tile : std::min(t.tag_tile, p->cfg.num_tags);
+        apply_tuning(p, t, keeps);
+    };
     // the same block repeated as a batch (device descriptor table): as many
     // copies as the plan's batch capacity holds, at most 16
     BlockTable bbt{};
@@ -1149,7 +1180,7 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
                                hipMemcpyHostToDevice, p->stream));
     }
     auto time_one = [&](const acq_tuning& t, bool batch, double* mean_ms) -> int {
-        acq_set_tuning(p, &t);
+        apply(t);
         double total = 0.0;
         for (int r = 0; r <= reps; ++r) {           // one warm-up run
             reset_timers(p);
@@ -1190,12 +1221,11 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
         }
     }
     if (rc != ACQ_OK) {
-        acq_set_tuning(p, &before);
-        p->auto_tile = was_auto;
+        apply_tuning(p, before, was_auto);
         acq_set_profiling(p, was_profiling);
         return rc;
     }
-    acq_set_tuning(p, &chosen);
+    apply(chosen);
     acq_set_profiling(p, was_profiling);
     *n_out = int32_t(cand.size());
     for (size_t i = 0; i < cand.size() && int32_t(i) < capacity; ++i) out[i] = cand[i];

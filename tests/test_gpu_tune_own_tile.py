@@ -1,0 +1,56 @@
+"""Tuning a plan that chooses its own tag tiles: its choice is among the candidates, and
+neither tuning nor handing back the reported tuning makes the search slower."""
+import pytest
+
+import siggen
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+FS = 8e6
+
+
+def _correlate_ms(p, x, runs=40):
+    p.set_profiling(True)
+    times = []
+    for _ in range(runs):
+        p.detect(x)
+        times.append(p.last_kernel_times()["correlate"])
+    p.set_profiling(False)
+    return sorted(times)[len(times) // 2]
+
+
+@pytest.mark.parametrize("tags,bins,n", [(1, 1, 50000), (7, 3, 100000), (13, 5, 60000), (30, 7, 190000)])
+def test_tuned_plan_is_no_slower(tags, bins, n):
+    """7 and 30 tags have choices (1 and 10 or 15 tags) outside the tuner's list, 1.7 and 1.1 times as fast as the
+    best on it; 10 % covers what two measurements of one tile differ by."""
+    from paper_2005_10445_amd import Plan
+    codes = siggen.make_codes(9100 + tags, tags, 8192)
+    x = torch.randn(n, dtype=torch.complex64, generator=torch.Generator().manual_seed(9101)).to("cuda:0")
+    kw = dict(num_bins=bins, bin_step_hz=1000.0 if bins > 1 else 0.0, max_block_len=n, fft_len=1 << 15)
+    with Plan(codes, 2, FS, **kw) as own, Plan(codes, 2, FS, **kw) as tuned:
+        table = tuned.tune(x, 5)
+        assert len({(e["engine"], e["tag_tile"], e["batch_launch"]) for e in table[:-2]}) == len(table) - 2
+        t = tuned.tuning
+        own.set_tuning(t["engine"], own.tuning["tag_tile"], t["batch_launch"])     # as quick an engine
+        a, b = _correlate_ms(own, x), _correlate_ms(tuned, x)
+        assert b <= 1.10 * a, (a, b, t, table)
+        assert tuned.detect(x) == own.detect(x)
+
+
+def test_reported_tuning_handed_back():
+    """The plan goes on choosing (1 tag a work item here: 20 us, the 7 that it reports 54)."""
+    from paper_2005_10445_amd import Plan
+    codes = siggen.make_codes(9110, 7, 8192)
+    x = torch.randn(100000, dtype=torch.complex64, generator=torch.Generator().manual_seed(9111)).to("cuda:0")
+    kw = dict(num_bins=3, bin_step_hz=1000.0, max_block_len=100000, fft_len=1 << 15)
+    with Plan(codes, 2, FS, **kw) as p, Plan(codes, 2, FS, tag_tile=16, **kw) as named:
+        before = _correlate_ms(p, x)
+        t = p.tuning
+        assert t == named.tuning
+        p.set_tuning(t["engine"], t["tag_tile"], t["batch_launch"], t["track_bins"])
+        assert p.tuning == t
+        after, seven = _correlate_ms(p, x), _correlate_ms(named, x)
+        assert after <= 1.25 * before and seven >= 1.5 * before, (before, after, seven)
+        p.set_tuning(t["engine"], 4)                      # another tile is kept
+        assert p.tuning["tag_tile"] == 4
