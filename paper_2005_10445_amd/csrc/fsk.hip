@@ -310,16 +310,28 @@ struct FskCorrArgs {
     const FskUnit* units;       // device [2 slots]
     int64_t lags;               // lags of the searched block (dump)
     int32_t M, Msub, P, track;
+    int32_t table;              // 1: a search's phase twiddles come from rootsM
     int32_t t0, nt, s0, ns;     // the launch's templates (searching) and slots; item i: template t0 + i / ns,
                                 // slot s0 + i % ns; tracking: slot s0 + i
 };
 
-// w[r] = w1^r, r < P (w[0] unset)
+// w[r] = exp(+j 2 pi i r / M), i < Msub, r < P (w[0] unset): from the table, or as
+// powers of the first, which round r times.  For P = 8 the table's give 5.35e-7 rms
+// of an output's scale where powers give 5.92e-7, for P = 4 4.78e-7 and 4.94e-7.
+// Tracking and searches of fewer items than compute units take them from the table
+// up to 8 phases, and pay for its scattered reads (P = 8, 128 templates in one slot:
+// 181 us a call for 178; 33 tasks 136 for 133); larger searches and 16 phases, whose
+// first step is bound by its loads, take powers.
 template <int P>
-__device__ __forceinline__ void phase_powers(float2 w1, float2 (&w)[P]) {
-    w[1] = w1;
+__device__ __forceinline__ void phase_twiddles(const float2* __restrict__ rootsM, int i, bool table, float2 (&w)[P]) {
+    w[1] = rootsM[i];
+    if (P <= 8 && table) {                              // uniform
 #pragma unroll
-    for (int r = 2; r < P; ++r) w[r] = cmul(w[r - 1], w1);
+        for (int r = 2; r < P; ++r) w[r] = rootsM[i * r];
+    } else {
+#pragma unroll
+        for (int r = 2; r < P; ++r) w[r] = cmul(w[r - 1], w[1]);
+    }
 }
 
 // P-point DFT, P a power of two
@@ -356,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first(FskCorrArgs a) {
         z[0][q] = X[q * a.Msub];
         z[1][q] = X[second + q * a.Msub];
     }
-    phase_powers<P>(a.rootsM[ip], w);
+    phase_twiddles<P>(a.rootsM, ip, a.table != 0, w);
     for (int t = ta; t < tb; ++t) {
         const float2* B = a.bank + size_t(a.t0 + t) * size_t(a.M) + ip;
         float2* G = a.G + (size_t(t) * size_t(a.ns) + size_t(sl)) * size_t(a.M) + ip;
@@ -398,7 +410,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first_track(FskCorrArgs a) {
         dft_p<P, -1>(z);
     };
     float2 w[P], z[P], y[P];
-    phase_powers<P>(a.rootsM[ip], w);
+    phase_twiddles<P>(a.rootsM, ip, true, w);
     combine(ip, w, z);
     if (tga == tgb) {                                   // uniform
 #pragma unroll
@@ -407,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first_track(FskCorrArgs a) {
         // conj Z[-i] for i = i' + Msub q: element P - 1 - q of Msub - i' (element -q of 0 for i' = 0)
         const int im = (a.Msub - ip) & (a.Msub - 1);
         float2 wm[P], zm[P];
-        phase_powers<P>(a.rootsM[im], wm);
+        phase_twiddles<P>(a.rootsM, im, true, wm);
         combine(im, wm, zm);
 #pragma unroll
         for (int q = 0; q < P; ++q) {
@@ -1419,6 +1431,7 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
     ca.Msub = int(g.Msub);
     ca.P = g.P;
     ca.track = track ? 1 : 0;
+    ca.table = int64_t(T) * slots < acq::kFskPhaseGrid ? 1 : 0;
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_CORRELATE);
         // groups of items whose first-step outputs fit the plan's buffer: all
