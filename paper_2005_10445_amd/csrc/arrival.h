@@ -20,13 +20,16 @@ __device__ __forceinline__ T agent_load(const T* p) {
 
 // Counts this workgroup's arrival at *ticket; true (in the whole workgroup) for
 // the last of `total`, which then sees what the others stored with agent_store.
-// Every thread of the workgroup comes here.
+// Every thread of the workgroup comes here.  The count wraps to zero with the last
+// arrival, for the next launch, and does so as well when launches that their caller
+// failed to order share a ticket: a reset by the last workgroup's store would lose
+// the arrivals of the other launch and leave every later search a wrong count.
 __device__ __forceinline__ bool last_arrival(unsigned* ticket, unsigned total) {
     __shared__ unsigned s_ticket;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the wave's stores have arrived
     __syncthreads();
     if (threadIdx.x == 0)
-        s_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_ticket = atomicInc(ticket, total - 1u);          // relaxed, device scope
     __syncthreads();
     return s_ticket == total - 1;
 }

@@ -775,10 +775,7 @@ __global__ __launch_bounds__(256, 4) void k_fsk_refine(FskRefineArgs a) {
             amp[t] = (lam >= 0 && lam < fi.tk.lags) ? fabs(sums[3 * t]) : -1.0;
         }
         __syncthreads();
-        if (t == 0) {
-            fsk_result(a, fi, item, lam0, sums, amp);
-            a.tickets[1 + item] = 0u;                // for the next call
-        }
+        if (t == 0) fsk_result(a, fi, item, lam0, sums, amp);
     } else {
         if (part != 0) return;
         if (t == 0) agent_store(&a.found[item], 0);
@@ -786,10 +783,7 @@ __global__ __launch_bounds__(256, 4) void k_fsk_refine(FskRefineArgs a) {
     if (!a.h_out || !last_arrival(&a.tickets[0], unsigned(items))) return;
     auto slot = [&](int e) { return agent_load(&a.found[e]) ? e : -1; };
     const int n = compact_records<NT, kTailItems, acq_fsk_detection>(items, a.dets, slot, items, nullptr, a.h_out);
-    if (t == 0) {
-        *a.h_count = n;
-        a.tickets[0] = 0u;
-    }
+    if (t == 0) *a.h_count = n;
 }
 
 // Results in tag order: one workgroup of 1024 threads, runs of tags per

@@ -163,7 +163,6 @@ __device__ __forceinline__ void power_group(const BlockTable& bt, const PowerArg
     sum_block_power<NT>(bt, a, wg);
     if (!last_arrival(a.ticket, unsigned(a.groups))) return;
     block_stats<NT>(bt, a);
-    if (threadIdx.x == 0) *a.ticket = 0u;        // for the next launch
 }
 
 // ------------------------------------------------------------------ forward spectra

@@ -247,10 +247,7 @@ __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const 
         if (hist[i]) atomicAdd(&hc[i], hist[i]);
     if (!last_arrival(&ms.tickets[b], gridDim.x)) return;
     const MedianState s = select_digit<11>(h, copies, MedianState{0u, uint32_t((F * kWin - 1) / 2)}, &state, hist);
-    if (tid == 0) {
-        ms.state[b] = s;
-        ms.tickets[b] = 0u;                        // for the next launch
-    }
+    if (tid == 0) ms.state[b] = s;
 }
 
 // ------------------------------------------------------------------ median
@@ -298,7 +295,6 @@ __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ P, int64
     if (tid == 0) {
         ms.state[b] = r;
         if (PASS == 2) med[b] = __uint_as_float(r.prefix);
-        ms.tickets[b] = 0u;
     }
 }
 
@@ -1068,8 +1064,7 @@ __global__ __launch_bounds__(256) void k_propose(const float* __restrict__ y, in
     if (t == 0) {
         out[0] = int32_t(agent_load(&total[0]));
         out[1] = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
-        total[0] = 0u;
-        total[1] = 0u;
+        total[0] = 0u;                             // (the arrivals are zero again)
     }
 }
 
