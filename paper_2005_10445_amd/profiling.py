@@ -250,8 +250,8 @@ def learned_summary(trace_dir: str, cmd: str, batch: int, block_len: int, steps_
     rows = batch * frames
     conv_macs = rows * 64 * 5 * (256 + 3 * 64)          # all layers, forward
     flops = {
-        "k_conv_tile<true>": (2.0 * conv_macs, PEAK_BF16_MFMA_TFLOPS, "forward, 4 layers"),
-        "k_conv_tile<false>": (2.0 * rows * 64 * 5 * 64 * 3, PEAK_BF16_MFMA_TFLOPS, "input gradient, layers 1-3"),
+        "k_conv_tile<true": (2.0 * conv_macs, PEAK_BF16_MFMA_TFLOPS, "forward, 4 layers"),
+        "k_conv_tile<false": (2.0 * rows * 64 * 5 * 64 * 3, PEAK_BF16_MFMA_TFLOPS, "input gradient, layers 1-3"),
         "k_conv_dw_taps<1>": (2.0 * rows * 64 * 5 * 256, PEAK_BF16_MFMA_TFLOPS, "weight gradient, layer 0 (d = 1)"),
         "k_conv_dw_taps<2>": (2.0 * rows * 64 * 5 * 64, PEAK_BF16_MFMA_TFLOPS, "weight gradient, layer 1 (d = 2)"),
         "k_conv_dw_taps<4>": (2.0 * rows * 64 * 5 * 64, PEAK_BF16_MFMA_TFLOPS, "weight gradient, layer 2 (d = 4)"),
@@ -271,8 +271,14 @@ def learned_summary(trace_dir: str, cmd: str, batch: int, block_len: int, steps_
              f"{steps} timed steps after {warmup} warm-up",
              "", f"{'kernel':44s} {'calls/step':>10s} {'us/step':>9s} {'share':>6s} {'GFLOP':>8s} {'TFLOP/s':>8s} "
              f"{'of peak':>8s}  work"]
+    shorts = {name: name.replace("void ", "").replace("(anonymous namespace)::", "").split("(")[0].split("::")[-1]
+              for name in per_step}
+    for k in flops:                                     # each is the work of one kernel of the step
+        found = [s for s in shorts.values() if s.startswith(k)]
+        if len(found) != 1:
+            raise ValueError(f"the work of {k} belongs to one kernel, the trace has {found or 'none'}")
     for name, us in sorted(per_step.items(), key=lambda kv: -kv[1]):
-        short = name.replace("void ", "").replace("(anonymous namespace)::", "").split("(")[0].split("::")[-1]
+        short = shorts[name]
         calls = len(timed[name]) / steps
         f = next((v for k, v in flops.items() if short.startswith(k)), None)
         if f:
