@@ -63,6 +63,16 @@ __device__ __forceinline__ float wave_fmax(float v) {
     return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(__float_as_uint(v)), 63)));
 }
 
+// A pointer that is the same in every lane, in scalar registers: a buffer resource made
+// of it takes no loop over the lanes' values.
+template <class T>
+__device__ __forceinline__ const T* wave_uniform(const T* p) {
+    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(v))));
+    const unsigned hi = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(v >> 32))));
+    return reinterpret_cast<const T*>((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
 // Smallest value over the wave (uniform, no LDS): the same steps.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ unsigned dpp_umin_step(unsigned v) {

@@ -221,14 +221,17 @@ __global__ __launch_bounds__(E::NT) void k_forward_sub(FwdArgs a) {
         // by the samples left, so that all 16 are in flight together (a branch
         // around each load waits for them one by one)
         const int64_t left = d.n - base < a.M ? d.n - base : a.M;
-        const __amdgpu_buffer_rsrc_t xr = make_rsrc(d.x + base, uint32_t(left) * 8u);
+        const __amdgpu_buffer_rsrc_t xr =
+            make_rsrc(wave_uniform(d.x + base), uint32_t(__builtin_amdgcn_readfirstlane(int(left))) * 8u);
         float2 v[16];
 #pragma unroll
         for (int m = 0; m < 16; ++m) v[m] = bload(xr, (a.spc * eng.in_index(m) + r) * 8, 0);
         if (PREMIX && cyc != 0.0) {                // x * exp(-j 2 pi cyc idx), phase reduced in FP64
+            int n0 = eng.in_index(0);              // (opaque: 16 indices held over the loop spilled)
+            asm volatile("" : "+v"(n0));
 #pragma unroll
             for (int m = 0; m < 16; ++m) {
-                const int64_t idx = base + int64_t(a.spc) * eng.in_index(m) + r;
+                const int64_t idx = base + a.spc * (n0 + m * (E::N / 16)) + r;
                 double ph = cyc * double(idx);
                 ph -= floor(ph);
                 float sn, cs;
