@@ -285,6 +285,12 @@ __global__ void k_fsk_conj_scale(float2* bank, int64_t count, float scale) {
     }
 }
 
+// phases[r][i] = exp(+j 2 pi i r / M), i < Msub, r < P
+__global__ void k_fsk_phase_roots(const float2* __restrict__ rootsM, int Msub, float2* __restrict__ phases) {
+    const int o = int(blockIdx.x) * 256 + int(threadIdx.x);
+    phases[o] = rootsM[(o / Msub) * (o % Msub)];
+}
+
 // rows of real parts: out[t][i] = in[t][i].x, i < stride, of count values in all
 __global__ void k_fsk_real(const float2* __restrict__ in, int64_t in_stride, float* __restrict__ out, int64_t stride,
                            int64_t count) {
@@ -302,6 +308,7 @@ struct FskCorrArgs {
                                 // decimated transforms, not yet combined)
     const float2* bank;         // [T][M] conj(DFT_M(d^(c))) / M
     const float2* rootsM;       // [M]
+    const float2* phases;       // [P][Msub] exp(+j 2 pi i r / M) (P <= 8)
     const float2* rootsSub;     // [Msub], then the pass twiddles
     const float2* b1tab;
     float2* G;                  // [items of the launch][P][Msub] first-step outputs (P > 1)
@@ -310,28 +317,20 @@ struct FskCorrArgs {
     const FskUnit* units;       // device [2 slots]
     int64_t lags;               // lags of the searched block (dump)
     int32_t M, Msub, P, track;
-    int32_t table;              // 1: a search's phase twiddles come from rootsM
     int32_t t0, nt, s0, ns;     // the launch's templates (searching) and slots; item i: template t0 + i / ns,
                                 // slot s0 + i % ns; tracking: slot s0 + i
 };
 
-// w[r] = exp(+j 2 pi i r / M), i < Msub, r < P (w[0] unset): from the table, or as
-// powers of the first, which round r times.  For P = 8 the table's give 5.35e-7 rms
-// of an output's scale where powers give 5.92e-7, for P = 4 4.78e-7 and 4.94e-7.
-// Tracking and searches of fewer items than compute units take them from the table
-// up to 8 phases, and pay for its scattered reads (P = 8, 128 templates in one slot:
-// 181 us a call for 178; 33 tasks 136 for 133); larger searches and 16 phases, whose
-// first step is bound by its loads, take powers.
+// w[r] = exp(+j 2 pi i r / M), i < Msub, r < P (w[0] unset): from a table [r][i], or for
+// P = 16, whose first step is bound by its loads, as powers of the first.  Powers round
+// r times: for P = 8 they give 5.92e-7 rms of an output's scale where the table's give
+// 5.35e-7, for P = 4 4.94e-7 and 4.78e-7.  (Gathered from rootsM, at i r, they take
+// 33 tasks over eight phases 136 us a call; 134 so, 133 with powers.)
 template <int P>
-__device__ __forceinline__ void phase_twiddles(const float2* __restrict__ rootsM, int i, bool table, float2 (&w)[P]) {
-    w[1] = rootsM[i];
-    if (P <= 8 && table) {                              // uniform
+__device__ __forceinline__ void phase_twiddles(const FskCorrArgs& a, int i, float2 (&w)[P]) {
+    w[1] = a.rootsM[i];
 #pragma unroll
-        for (int r = 2; r < P; ++r) w[r] = rootsM[i * r];
-    } else {
-#pragma unroll
-        for (int r = 2; r < P; ++r) w[r] = cmul(w[r - 1], w[1]);
-    }
+    for (int r = 2; r < P; ++r) w[r] = P > 8 ? cmul(w[r - 1], w[1]) : a.phases[r * a.Msub + i];
 }
 
 // P-point DFT, P a power of two
@@ -368,7 +367,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first(FskCorrArgs a) {
         z[0][q] = X[q * a.Msub];
         z[1][q] = X[second + q * a.Msub];
     }
-    phase_twiddles<P>(a.rootsM, ip, a.table != 0, w);
+    phase_twiddles<P>(a, ip, w);
     for (int t = ta; t < tb; ++t) {
         const float2* B = a.bank + size_t(a.t0 + t) * size_t(a.M) + ip;
         float2* G = a.G + (size_t(t) * size_t(a.ns) + size_t(sl)) * size_t(a.M) + ip;
@@ -410,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first_track(FskCorrArgs a) {
         dft_p<P, -1>(z);
     };
     float2 w[P], z[P], y[P];
-    phase_twiddles<P>(a.rootsM, ip, true, w);
+    phase_twiddles<P>(a, ip, w);
     combine(ip, w, z);
     if (tga == tgb) {                                   // uniform
 #pragma unroll
@@ -419,7 +418,7 @@ __global__ __launch_bounds__(256, 2) void k_fsk_first_track(FskCorrArgs a) {
         // conj Z[-i] for i = i' + Msub q: element P - 1 - q of Msub - i' (element -q of 0 for i' = 0)
         const int im = (a.Msub - ip) & (a.Msub - 1);
         float2 wm[P], zm[P];
-        phase_twiddles<P>(a.rootsM, im, true, wm);
+        phase_twiddles<P>(a, im, wm);
         combine(im, wm, zm);
 #pragma unroll
         for (int q = 0; q < P; ++q) {
@@ -949,7 +948,7 @@ int fsk_geometry(const acq_fsk_config* c, FskGeometry* g) {
                                             std::max<int64_t>(1, kFskGroup / M)) * M : 0;
     g->bytes = c->max_block_len * 8 + slots * M * 8 + g->group * 8 + slots * 2 * int64_t(sizeof(FskUnit)) +
                T * M * 8 + T * (g->nt + 4) * 4 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
-               kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
+               kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 * (g->P > 1 && g->P <= 8 ? 2 : 1) + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
     return ACQ_OK;
 }
 
@@ -1015,6 +1014,7 @@ struct acq_fsk_plan_s {
     float2* d_G = nullptr;              // [group] first-step outputs of the correlation
     double* d_partial = nullptr;        // [T][parts][sums] refinement partial sums
     float2* d_rootsM = nullptr;
+    float2* d_phases = nullptr;         // [P][Msub] phase twiddles (P <= 8)
     float2* d_rootsSub = nullptr;
     float2* d_b1tab = nullptr;
     BlockDesc* d_tdescs = nullptr;      // [T] templates as blocks of the forward transform
@@ -1067,7 +1067,7 @@ void free_fsk(acq_fsk_plan_s* p) {
         for (hipEvent_t e : pair)
             if (e) (void)hipEventDestroy(e);
     void* dev[] = {p->d_G1, p->d_G0, p->d_rootsF, p->d_bits, p->d_bitcyc, p->d_tmpl, p->d_bank, p->d_d, p->d_u, p->d_X, p->d_G, p->d_partial,
-                   p->d_rootsM, p->d_rootsSub, p->d_b1tab, p->d_tdescs, p->d_tcounts, p->d_keys,
+                   p->d_rootsM, p->d_phases, p->d_rootsSub, p->d_b1tab, p->d_tdescs, p->d_tcounts, p->d_keys,
                    p->d_dets, p->d_out, p->d_found, p->d_count, p->d_tickets};
     for (void* d : dev)
         if (d) (void)hipFree(d);
@@ -1172,6 +1172,8 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_tasks), table_bytes));
     FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_tasks), table_bytes));
     FSK_HIP(dalloc(&p->d_rootsM, M));
+    const bool phases = g.P > 1 && g.P <= 8;
+    if (phases) FSK_HIP(dalloc(&p->d_phases, M));
     FSK_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
     FSK_HIP(dalloc(&p->d_b1tab, b1.size() / 2));
@@ -1210,6 +1212,11 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(hipMemcpyAsync(p->d_G0, G0.data(), G0.size() * sizeof(float), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_rootsF, rootsF.data(), rootsF.size() * sizeof(float), hipMemcpyHostToDevice, st));
     FSK_HIP(hipMemcpyAsync(p->d_rootsM, rootsM.data(), rootsM.size() * sizeof(float), hipMemcpyHostToDevice, st));
+    if (phases) {
+        hipLaunchKernelGGL(acq::k_fsk_phase_roots, dim3(unsigned(M / 256)), dim3(256), 0, st, p->d_rootsM, int(g.Msub),
+                           p->d_phases);
+        FSK_HIP(hipGetLastError());
+    }
     FSK_HIP(hipMemcpyAsync(p->d_rootsSub, rootsSub.data(), rootsSub.size() * sizeof(float), hipMemcpyHostToDevice,
                            st));
     FSK_HIP(hipMemcpyAsync(p->d_b1tab, b1.data(), b1.size() * sizeof(float), hipMemcpyHostToDevice, st));
@@ -1425,7 +1432,7 @@ int enqueue_fsk(acq_fsk_plan_s* p, int nblocks, bool track, float* dump, int* it
     ca.Msub = int(g.Msub);
     ca.P = g.P;
     ca.track = track ? 1 : 0;
-    ca.table = int64_t(T) * slots < acq::kFskPhaseGrid ? 1 : 0;
+    ca.phases = p->d_phases;
     {
         FskTimer kt(p, ACQ_FSK_KERNEL_CORRELATE);
         // groups of items whose first-step outputs fit the plan's buffer: all
