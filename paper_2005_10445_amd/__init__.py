@@ -75,7 +75,11 @@ def _task_array(struct, dtype, field, tasks, device_ptrs):
     rec = np.zeros(n, dtype=dtype)               # a column at a time
     rec[field] = np.array([p for p, _ in ptrs], dtype=np.uint64)
     rec["n"] = [m for _, m in ptrs]
-    rec["tag"] = np.array([int(tag) for _, tag in tasks], dtype=np.int64)
+    tags = [int(tag) for _, tag in tasks]
+    try:
+        rec["tag"] = np.array(tags, dtype=np.int64)
+    except OverflowError:                        # the low 32 bits, as of every other tag
+        rec["tag"] = np.array([t & 0xffffffff for t in tags], dtype=np.int64)
     return (struct * n).from_buffer(rec)
 
 
