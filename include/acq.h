@@ -614,7 +614,8 @@ typedef struct acq_fsk_geometry {
     int64_t valid_per_segment; /* M - n_t + 1                                          */
     int64_t filter_len;      /* composed filter length bp_len + mf_len - 1             */
     int64_t front_fft_len;   /* overlap-save length of the composed filters (4096)     */
-    int64_t device_bytes;
+    int64_t device_bytes;    /* device memory that a plan holds; making it takes another
+                                num_tags * fft_len * 8 bytes for its duration            */
 } acq_fsk_geometry;
 
 int acq_fsk_plan_geometry(const acq_fsk_config* cfg, acq_fsk_geometry* out);

@@ -308,7 +308,7 @@ struct FskCorrArgs {
                                 // decimated transforms, not yet combined)
     const float2* bank;         // [T][M] conj(DFT_M(d^(c))) / M
     const float2* rootsM;       // [M]
-    const float2* phases;       // [P][Msub] exp(+j 2 pi i r / M) (P <= 8)
+    const float2* phases;       // [P][Msub] exp(+j 2 pi i r / M) (2 < P <= 8)
     const float2* rootsSub;     // [Msub], then the pass twiddles
     const float2* b1tab;
     float2* G;                  // [items of the launch][P][Msub] first-step outputs (P > 1)
@@ -948,7 +948,7 @@ int fsk_geometry(const acq_fsk_config* c, FskGeometry* g) {
                                             std::max<int64_t>(1, kFskGroup / M)) * M : 0;
     g->bytes = c->max_block_len * 8 + slots * M * 8 + g->group * 8 + slots * 2 * int64_t(sizeof(FskUnit)) +
                T * M * 8 + T * (g->nt + 4) * 4 + T * c->num_bits * 9 + int64_t(g->items) * (kFskParts * kFskSums * 8 + 64) +
-               kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 * (g->P > 1 && g->P <= 8 ? 2 : 1) + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
+               kFrontN * 8 * 2 + transform_roots_len(kFrontN) * 8 + M * 8 * (g->P > 2 && g->P <= 8 ? 2 : 1) + transform_roots_len(g->Msub) * 8 + T * (8 + 4 + 2 * int64_t(sizeof(acq_fsk_detection)));
     return ACQ_OK;
 }
 
@@ -1014,7 +1014,7 @@ struct acq_fsk_plan_s {
     float2* d_G = nullptr;              // [group] first-step outputs of the correlation
     double* d_partial = nullptr;        // [T][parts][sums] refinement partial sums
     float2* d_rootsM = nullptr;
-    float2* d_phases = nullptr;         // [P][Msub] phase twiddles (P <= 8)
+    float2* d_phases = nullptr;         // [P][Msub] phase twiddles (2 < P <= 8)
     float2* d_rootsSub = nullptr;
     float2* d_b1tab = nullptr;
     BlockDesc* d_tdescs = nullptr;      // [T] templates as blocks of the forward transform
@@ -1172,7 +1172,7 @@ int build_fsk(acq_fsk_plan_s* p, const acq_fsk_config* cfg) {
     FSK_HIP(hipMalloc(reinterpret_cast<void**>(&p->d_tasks), table_bytes));
     FSK_HIP(hipHostMalloc(reinterpret_cast<void**>(&p->h_tasks), table_bytes));
     FSK_HIP(dalloc(&p->d_rootsM, M));
-    const bool phases = g.P > 1 && g.P <= 8;
+    const bool phases = g.P > 2 && g.P <= 8;
     if (phases) FSK_HIP(dalloc(&p->d_phases, M));
     FSK_HIP(dalloc(&p->d_rootsSub, size_t(acq::transform_roots_len(g.Msub))));
     const std::vector<float> b1 = g.log2_sub == 14 ? acq::fft14_b1_table() : std::vector<float>(2, 0.f);
