@@ -245,7 +245,7 @@ __device__ __forceinline__ void dft16_rest(float2 (&u)[16]) {
     for (int i = 0; i < 16; ++i) u[i] = r[i];
 }
 
-// the first butterflies of dft16_rest without and with twiddles w[0..15] on the inputs
+// the first butterflies that dft16_rest leaves out
 __device__ __forceinline__ void dft16_first(float2 (&u)[16]) {
 #pragma unroll
     for (int n = 0; n < 8; ++n) {

@@ -33,7 +33,7 @@
 //                     Y the spectrum product (first step, k_fsk_first*), then an
 //                     Msub-point inverse transform of G_rho (k_fsk_phase).
 //                     Keys: bits(|Re c|) << 32 | ~tau.
-//   k_fsk_refine_*  : FP64 sums over +/-3 lags of the peak from the stored d,
+//   k_fsk_refine    : FP64 sums over +/-3 lags of the peak from the stored d,
 //                     u and template (in parts, added in order), re-maximisation,
 //                     parabola, w_c, q, p_c, z.
 #include <hip/hip_runtime.h>

@@ -151,9 +151,9 @@ struct RefineArgs {
     int32_t* h_count;           // [2] {detections, blocks with a non-finite sample}
 };
 
-// Refinement work: items = blocks * (tracking ? 1 : T); each item's sums run in
-// kRefineParts workgroups, each writing 3 * WMAX doubles (WMAX = 5 for radius
-// <= 1, else 2 * kMaxRefineRadius + 3).
+// Refinement work: items = blocks * (tracking ? 1 : T); each item's sums come in
+// kRefineParts parts of 3 * WMAX doubles (WMAX = 5 for radius <= 1, else
+// 2 * kMaxRefineRadius + 3).
 constexpr int kRefineParts = 16;
 constexpr int kTailItems = 1024;
 
