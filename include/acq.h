@@ -307,9 +307,10 @@ int acq_detect_noalloc(acq_plan_t plan, const void* block, int64_t n, acq_detect
  * transform engine for the plan's inverse-transform length, 1 = Stockham
  * passes through padded LDS (available for every length).  tag_tile: tags per
  * work item, 1..64; a plan made with tag_tile 0 reports 16 (or its tags, if
- * fewer) and chooses the tile of each launch from its work items (batches captured
- * into the plan's graph keep 16) until acq_set_tuning names another tile or acq_tune
- * finds one faster than its choice.  Results do not depend on the tuning.
+ * fewer), or what it chose for the block that acq_tune was given, and chooses the
+ * tile of each launch from its work items (batches captured into the plan's graph
+ * keep the reported one) until acq_set_tuning names another tile or acq_tune finds
+ * one faster than its choice.  Results do not depend on the tuning.
  */
 typedef struct acq_tuning {
     int32_t engine;

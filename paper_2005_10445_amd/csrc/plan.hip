@@ -482,8 +482,9 @@ int enqueue_search(acq_plan_s* p, const Scratch& w, const BlockTable& bt, bool b
         // the kernel reads a batch's real item count from the block table
         const int64_t per_tile = segs * c.num_bins * c.samples_per_chip;
         const int64_t nwork = int64_t(ca.ntiles) * per_tile;
-        // (the limit on work items is that of the reported tile)
-        const int64_t named = int64_t((c.num_tags + p->tile - 1) / p->tile) * per_tile;
+        // (the limit on work items is that of the configured tile, or the one set)
+        const int limit_tile = p->auto_tile ? g.tag_tile : p->tile;
+        const int64_t named = int64_t((c.num_tags + limit_tile - 1) / limit_tile) * per_tile;
         if (std::max(nwork, named) >= (int64_t(1) << 31) - 8) return acq::fail(ACQ_ERR_UNSUPPORTED, "too many work items");
         grid = int((nwork + acq::kXcds - 1) / acq::kXcds) * acq::kXcds;
     }
@@ -1153,9 +1154,10 @@ int acq_tune(acq_plan_t p, const void* block, int64_t n, int32_t reps, acq_tune_
                 cand.push_back(c);
         }
     auto apply = [&](acq_tuning t) {
-        const bool keeps = was_auto && t.tag_tile == own;
-        t.tag_tile = keeps ? before.tag_tile : std::min(t.tag_tile, p->cfg.num_tags);
-        apply_tuning(p, t, keeps);
+        // the choice is reported too: other plans, and this one's captured batches,
+        // run with it
+        t.tag_tile = std::min(t.tag_tile, p->cfg.num_tags);
+        apply_tuning(p, t, was_auto && t.tag_tile == own);
     };
     // the same block repeated as a batch (device descriptor table): as many
     // copies as the plan's batch capacity holds, at most 16

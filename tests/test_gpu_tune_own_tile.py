@@ -54,3 +54,19 @@ def test_reported_tuning_handed_back():
         assert after <= 1.25 * before and seven >= 1.5 * before, (before, after, seven)
         p.set_tuning(t["engine"], 4)                      # another tile is kept
         assert p.tuning["tag_tile"] == 4
+
+
+def test_tuning_handed_to_another_plan():
+    """A tuned plan reports the tile that it chose for the block, so that a plan of captured batches, which keep
+    the tile they are given, runs with it (1 tag a work item, and not the 7 of a plan that was not tuned)."""
+    from paper_2005_10445_amd import Plan
+    codes = siggen.make_codes(9110, 7, 8192)
+    x = torch.randn(100000, dtype=torch.complex64, generator=torch.Generator().manual_seed(9111)).to("cuda:0")
+    kw = dict(num_bins=3, bin_step_hz=1000.0, max_block_len=100000, fft_len=1 << 15)
+    with Plan(codes, 2, FS, **kw) as p, Plan(codes, 2, FS, graph=True, **kw) as g:
+        p.tune(x, 5)
+        t = p.tuning
+        assert t["tag_tile"] == 1
+        g.set_tuning(t["engine"], t["tag_tile"], t["batch_launch"], t["track_bins"])
+        assert g.tuning == t
+        assert g.detect_batch([x]) == p.detect_batch([x])
